@@ -5,7 +5,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <functional>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -46,41 +45,42 @@ struct Rng {
     }
 };
 
-// Orthonormalise the columns of the dim x dim Gaussian matrix g (column-major) in place:
-// classical Gram-Schmidt with one re-orthogonalisation pass, both inner loops split over threads.
-void orthonormalise(std::vector<double>& g, uint32_t dim, unsigned threads) {
-    std::vector<double> proj(dim);
-    auto parallel = [&](uint32_t count, const std::function<void(uint32_t, uint32_t)>& fn) {
-        if (threads <= 1 || count < 256) { fn(0, count); return; }
-        std::vector<std::thread> th;
-        for (unsigned t = 0; t < threads; ++t)
-            th.emplace_back(fn, (uint32_t)((uint64_t)count * t / threads), (uint32_t)((uint64_t)count * (t + 1) / threads));
-        for (auto& x : th) x.join();
+// Fills g with normals, two draws each, in order.  The generator's state advances by a constant per draw, so several
+// threads can start where their part of g begins.
+void draw_normals(const Rng& first, std::vector<double>& g) {
+    const size_t threads = g.size() < (1u << 16) ? 1 : std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
+    auto part = [&](size_t lo, size_t hi) {
+        Rng rng = first;
+        rng.state += 2ull * lo * 0x9E3779B97F4A7C15ull;
+        for (size_t i = lo; i < hi; ++i) g[i] = rng.normal();
     };
+    struct Threads {
+        std::vector<std::thread> all;
+        ~Threads() { for (auto& t : all) t.join(); }
+    } started;
+    started.all.reserve(threads);
+    for (size_t t = 1; t < threads; ++t) started.all.emplace_back(part, g.size() * t / threads, g.size() * (t + 1) / threads);
+    part(0, g.size() / threads);
+}
+
+// Orthonormalise the columns of the dim x dim Gaussian matrix g (column-major) in place:
+// classical Gram-Schmidt with one re-orthogonalisation pass.
+void orthonormalise(std::vector<double>& g, uint32_t dim) {
+    std::vector<double> proj(dim);
     for (uint32_t j = 0; j < dim; ++j) {
         double* aj = &g[(size_t)j * dim];
         for (int pass = 0; pass < 2 && j > 0; ++pass) {
-            parallel(j, [&](uint32_t lo, uint32_t hi) {
-                for (uint32_t i = lo; i < hi; ++i) {
-                    const double* qi = &g[(size_t)i * dim];
-                    double s = 0.0;
-                    for (uint32_t k = 0; k < dim; ++k) s += qi[k] * aj[k];
-                    proj[i] = s;
-                }
-            });
-            parallel(j >= 256 ? dim : 0, [&](uint32_t lo, uint32_t hi) {
-                for (uint32_t i = 0; i < j; ++i) {
-                    const double* qi = &g[(size_t)i * dim];
-                    const double p = proj[i];
-                    for (uint32_t k = lo; k < hi; ++k) aj[k] -= p * qi[k];
-                }
-            });
-            if (j < 256)
-                for (uint32_t i = 0; i < j; ++i) {
-                    const double* qi = &g[(size_t)i * dim];
-                    const double p = proj[i];
-                    for (uint32_t k = 0; k < dim; ++k) aj[k] -= p * qi[k];
-                }
+            for (uint32_t i = 0; i < j; ++i) {
+                const double* qi = &g[(size_t)i * dim];
+                double s = 0.0;
+                for (uint32_t k = 0; k < dim; ++k) s += qi[k] * aj[k];
+                proj[i] = s;
+            }
+            for (uint32_t i = 0; i < j; ++i) {
+                const double* qi = &g[(size_t)i * dim];
+                const double p = proj[i];
+                for (uint32_t k = 0; k < dim; ++k) aj[k] -= p * qi[k];
+            }
         }
         double nrm = 0.0;
         for (uint32_t k = 0; k < dim; ++k) nrm += aj[k] * aj[k];
@@ -89,7 +89,9 @@ void orthonormalise(std::vector<double>& g, uint32_t dim, unsigned threads) {
     }
 }
 
-void make_transform(uint32_t d, uint64_t seed, bool permutation, std::vector<float>& rot) {
+// Q into `out` (dev).  Small transforms are orthogonalised on the host: below d = 192 that takes less than the GPU's
+// 5 d launches.  `rot` keeps the host's copy alive until the stream has been synchronised.
+int make_transform(hipStream_t stream, uint32_t d, uint64_t seed, bool permutation, float* out, std::vector<float>& rot) {
     Rng rng(seed, 1);
     if (permutation) {
         // a signed permutation: row j has one entry +-1, in a column drawn by a Fisher-Yates shuffle
@@ -98,15 +100,17 @@ void make_transform(uint32_t d, uint64_t seed, bool permutation, std::vector<flo
         for (uint32_t j = d - 1; j > 0; --j) std::swap(col[j], col[rng.next() % (j + 1)]);
         rot.assign((size_t)d * d, 0.f);
         for (uint32_t j = 0; j < d; ++j) rot[(size_t)j * d + col[j]] = (rng.next() & 1) ? 1.f : -1.f;
-        return;
+    } else {
+        std::vector<double> g((size_t)d * d);
+        draw_normals(rng, g);
+        if (d >= 192) return pag_orthonormalise(stream, g.data(), d, out);
+        orthonormalise(g, d);
+        rot.resize((size_t)d * d);
+        // orthonormal columns are as good as rows: rot[j][k] = column j, element k
+        for (size_t i = 0; i < rot.size(); ++i) rot[i] = (float)g[i];
     }
-    std::vector<double> g((size_t)d * d);
-    for (auto& x : g) x = rng.normal();
-    unsigned threads = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
-    orthonormalise(g, d, threads);
-    rot.resize((size_t)d * d);
-    // orthonormal columns are as good as rows: rot[j][k] = column j, element k
-    for (size_t i = 0; i < rot.size(); ++i) rot[i] = (float)g[i];
+    PAG_HIP(hipMemcpyAsync(out, rot.data(), rot.size() * 4, hipMemcpyHostToDevice, stream));
+    return PAG_OK;
 }
 
 // cb[l][j][k]: per subspace, cross-polytopes rotated independently; from each polytope its axes in
@@ -121,7 +125,7 @@ void make_codebooks(uint32_t d, uint32_t P, uint64_t seed, std::vector<float>& c
         uint32_t j = 0;
         while (j < PAG_NCODE) {
             for (auto& x : g) x = rng.normal();
-            orthonormalise(g, ds, 1);
+            orthonormalise(g, ds);
             const uint32_t k = std::min<uint32_t>(ds, (PAG_NCODE - j) / 2);
             for (uint32_t a = 0; a < k; ++a)
                 for (uint32_t e = 0; e < ds; ++e) {
@@ -331,10 +335,9 @@ extern "C" int pag_build(const float* D, uint64_t n, uint32_t d, const pag_param
         const auto t0 = std::chrono::steady_clock::now();
         if ((rc = alloc_index(ix))) return rc;
         std::vector<float> rot, cb;
-        make_transform(d, params->seed, (params->flags & PAG_FLAG_PERMUTATION_TRANSFORM) != 0, rot);
+        if ((rc = make_transform(ix->stream, d, params->seed, (params->flags & PAG_FLAG_PERMUTATION_TRANSFORM) != 0, ix->rot, rot))) return rc;
         make_codebooks(d, L.P, params->seed, cb);
-        hipError_t e = hipMemcpyAsync(ix->rot, rot.data(), rot.size() * 4, hipMemcpyHostToDevice, ix->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(ix->cb, cb.data(), cb.size() * 4, hipMemcpyHostToDevice, ix->stream);
+        hipError_t e = hipMemcpyAsync(ix->cb, cb.data(), cb.size() * 4, hipMemcpyHostToDevice, ix->stream);
         if (e == hipSuccess) e = hipMemsetAsync(ix->rec, 0xFF, ix->capacity * L.rec_bytes, ix->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ix->stream);
         if (e != hipSuccess) { pag_set_error(std::string("pag_build upload: ") + hipGetErrorString(e)); return PAG_EHIP; }

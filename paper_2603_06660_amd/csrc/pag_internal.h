@@ -143,6 +143,8 @@ int pag_launch_search(const pag_index* ix, const SearchArgs& a, u32 lds_bytes, i
 int pag_search_lds_bytes(const pag_layout& L, u32 b, u32 hlog, u32 blog, SearchArgs* a);
 int pag_search_max_grid(const pag_index* ix, u32 b, u32 lds_bytes, int* grid);
 
+// g (host): a dim x dim Gaussian matrix, column after column; rot (dev): the orthogonal transform made of it, by rows
+int pag_orthonormalise(hipStream_t s, const double* g, u32 dim, float* rot);
 int pag_launch_rotate(hipStream_t s, const float* X, u64 rows, u32 d, const float* rot, float* out);
 int pag_launch_tables(hipStream_t s, const float* qrot, u64 rows, const pag_layout& L, const float* cb, float* tables);
 int pag_launch_normalise(hipStream_t s, const float* X, u64 rows, u32 d, float* out);

@@ -1,0 +1,66 @@
+"""The orthogonal transform of an index is the same, bit for bit, whichever way the library orthogonalises it."""
+import math
+
+import numpy as np
+import pytest
+
+MASK = (1 << 64) - 1
+
+
+def _normals(seed, count):
+    """SplitMix64 (stream 1 of the seed) and Box-Muller, as the library draws Q's Gaussian matrix."""
+    state = (seed * 0x9E3779B97F4A7C15 + 0xD1B54A32D192ED03 + 0x2545F4914F6CDD1D) & MASK
+    out = np.empty(count)
+
+    def uniform():
+        nonlocal state
+        state = (state + 0x9E3779B97F4A7C15) & MASK
+        z = state
+        z = ((z ^ (z >> 30)) * 0xBF58476D1CE4E5B9) & MASK
+        z = ((z ^ (z >> 27)) * 0x94D049BB133111EB) & MASK
+        return (float((z ^ (z >> 31)) >> 11) + 0.5) * (1.0 / 9007199254740992.0)
+
+    for i in range(count):
+        u1, u2 = uniform(), uniform()
+        out[i] = math.sqrt(-2.0 * math.log(u1)) * math.cos(6.283185307179586476925 * u2)
+    return out
+
+
+def _orthonormalise(g):
+    """Classical Gram-Schmidt with one re-orthogonalisation pass; row j of g is column j of the Gaussian matrix.  Sums run
+    in index order (vectorised over the independent ones only)."""
+    d = g.shape[0]
+    for j in range(d):
+        for _ in range(2 if j else 0):
+            s = np.zeros(j)
+            for k in range(d):
+                s = s + g[:j, k] * g[j, k]
+            for i in range(j):
+                g[j] = g[j] - s[i] * g[i]
+        n = 0.0
+        for x in g[j].tolist():
+            n = n + x * x
+        g[j] = g[j] / math.sqrt(n)
+    return g.astype(np.float32)
+
+
+def test_reference_is_orthogonal():
+    q = _orthonormalise(_normals(9, 48 * 48).reshape(48, 48)).astype(np.float64)
+    assert np.abs(q @ q.T - np.eye(48)).max() < 1e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [128, 188, 192, 196, 256, 260])     # below and above the line, chunks of 64 with and without a rest
+def test_transform_bits(d):
+    import torch
+    from paper_2603_06660_amd import PagIndex
+    seed = 1234 + d
+    base = torch.from_numpy(np.random.default_rng(d).standard_normal((64, d), dtype=np.float32)).cuda()
+    ix = PagIndex.build(base, metric="l2", max_degree=8, num_subspaces=4, ef_construction=20, seed=seed)
+    got = ix.export()["rotation"]
+    ix.close()
+    want = _orthonormalise(_normals(seed, d * d).reshape(d, d))
+    # the two logarithms and cosines may come from different math libraries: a last bit of fp32 here and there
+    differ = got != want
+    assert differ.mean() <= 1e-4, differ.mean()
+    assert np.abs(got - want).max() <= 2.0 ** -23
