@@ -124,15 +124,16 @@ typedef struct {
     uint64_t queries;
     uint64_t hops;               /* expanded nodes (n' of Sec. 4.2) */
     uint64_t tests;              /* neighbours the projection test was evaluated for: the unseen ones; in long
-                                    searches also already-seen ones that only the second level of the seen
-                                    set would have recognised (it is consulted for passing neighbours only),
-                                    unless PAG_FLAG_EXACT_TEST_COUNT is set */
+                                    searches of large batches also already-seen ones that only the second
+                                    level of the seen set would have recognised (it is consulted for passing
+                                    neighbours only), unless PAG_FLAG_EXACT_TEST_COUNT is set */
     uint64_t passes;             /* of those, how many passed (gamma = passes / tests) */
     uint64_t exact;              /* exact distances computed, entry nodes included */
     uint64_t rounds;             /* TFB rounds */
     uint64_t rf_overflow;        /* entries overwritten in the ring R_F */
     uint64_t rt_overflow;        /* entries overwritten in the ring R_T */
-    uint64_t seen_spills;        /* seen-set insertions that went to the HBM bitmap (all of them in long searches) */
+    uint64_t seen_spills;        /* seen-set insertions that went to the HBM bitmap (in long searches all of them, unless
+                                    the batch is so small that the on-chip memory holds its seen sets) */
     double   last_search_kernel_ms; /* HIP-event time of the search kernel of the last pag_search */
     double   last_prepare_ms;       /* HIP-event time of rotation + projection tables of the last pag_search */
     double   last_build_ms;         /* wall time of the last pag_build / pag_insert */

@@ -267,8 +267,12 @@ pag_index* new_index(const pag_params* p, uint32_t d) {
     ix->vec_half = (p->flags & PAG_FLAG_FP16_VECTORS) ? 1u : 0u;
     ix->seed = p->seed;
     hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, ix->device) == hipSuccess) ix->num_cu = prop.multiProcessorCount;
+    if (hipGetDeviceProperties(&prop, ix->device) == hipSuccess) {
+        ix->num_cu = prop.multiProcessorCount;
+        ix->lds_per_cu = (u32)std::min<size_t>(prop.sharedMemPerBlock, prop.maxSharedMemoryPerMultiProcessor);
+    }
     if (ix->num_cu <= 0) ix->num_cu = 256;
+    if (ix->lds_per_cu < 65536) ix->lds_per_cu = 65536;
     (void)d;
     return ix;
 }
@@ -615,9 +619,61 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
     if (ix->seen_log2) *hlog = ix->seen_log2;
 }
 
+// Batches that leave the GPU mostly idle with one wave per query get several (a team); `share` queries then share a CU.
+// Fills a->waves, the seen-set sizes, the LDS carve-up and the grid; a->waves stays 1 where one wave is the better plan.
+// The lines, with kernel times of one wave -> a team (100,000 rows, efS 128, unless stated):
+//   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
+//     query 375 -> 242, 491 -> 271, 777 -> 414
+//   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
+//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455).  Working sets above 128
+//     nodes gain with the four waves that fit, too (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
+//   up to four per CU: 4 waves, if the rows come from HBM and not from the 256 MB cache: 1M x 768, efS 256, 1,000 queries
+//     1796 -> 1608 us, 200k x 1536, efS 768, 777 queries 5868 -> 5288.  Within the cache the instructions that a team
+//     adds cost more than the shorter wait saves (100k x 128, 800 queries: 534 -> 557)
+static int plan_team(const pag_index* ix, u64 nq, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
+    const u64 cus = (u64)ix->num_cu;
+    const bool large_set = b > PAG_LDS_RING_MAX_B;
+    u32 share, most, least;
+    if (nq <= cus) {
+        share = 1; most = 12; least = 4;
+    } else if (nq <= 2 * cus) {
+        share = 2; most = 8; least = large_set ? 4 : 8;
+    } else if (nq <= 4 * cus && !large_set && ix->capacity * ix->L.d * pag_vec_elem(ix) >= (512ull << 20)) {
+        share = 4; most = 4; least = 4;
+    } else {
+        return PAG_OK;
+    }
+    most = std::min<u32>(most, (u32)pag_team_max(b <= 512 ? 8 : 16));
+    const u32 room = ix->lds_per_cu / share - 512;
+    SearchArgs t = *a;
+    t.waves = most;
+    // The seen set: an exact hash of everything the search is expected to compute, if the LDS holds it half full;
+    // otherwise the bitmap behind a Bloom filter of 16 bits per node, as far as the LDS goes.
+    const u64 expected = b + 8ull * std::max(ef, b);
+    u32 lg = 9;
+    while ((1ull << lg) < 2 * expected && lg < 16) ++lg;
+    auto fits = [&](u32 hlog, u32 blog) { SearchArgs u = t; return (u32)pag_search_lds_bytes(ix->L, b, hlog, blog, &u) <= room; };
+    if (!ix->seen_log2 && (1ull << lg) >= 2 * expected && fits(lg, 0)) {
+        t.hlog = lg; t.blog = 0;
+    } else if (t.blog) {
+        while (t.blog < 20 && (1ull << t.blog) < 16 * expected && fits(t.hlog, t.blog + 1)) ++t.blog;
+    }
+    if (!fits(t.hlog, t.blog)) return PAG_OK;
+    const u32 need = (u32)pag_search_lds_bytes(ix->L, b, t.hlog, t.blog, &t);
+    // as many waves as leave every query resident
+    for (; t.waves >= least; --t.waves) {
+        int rc, g = 0;
+        if ((rc = pag_search_max_grid(ix, b, t.waves, need, &g))) return rc;
+        if ((u64)g < nq) continue;
+        *a = t; *lds = need; *grid = (int)nq;
+        return PAG_OK;
+    }
+    return PAG_OK;
+}
+
 // Plans a search: fills the part of SearchArgs that depends only on the index and (b, ef), the LDS carve-up and the
 // largest useful grid.  Allocates nothing.
-static int search_plan(const pag_index* ix, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+static int search_plan(const pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
     const pag_layout& L = ix->L;
     std::memset((void*)a, 0, sizeof(*a));
     a->vec = ix->vec; a->rec = ix->rec; a->entry = ix->entry;
@@ -629,10 +685,14 @@ static int search_plan(const pag_index* ix, u32 b, u32 ef, u64 n_limit, SearchAr
     seen_sizes_for(ix, ef, b, &a->hlog, &a->blog);
     a->flags = ix->flags;
     a->qcounter = ix->d_qcounter; a->counters = ix->d_counters;
+    // per-wave spill bitmaps of the seen set: one bit per node, rounded to 16 bytes
+    a->bitmap_words = ((u64)ix->capacity + 127) / 128 * 4;
+    a->waves = 1;
+    int rc = plan_team(ix, nq, b, ef, a, lds, grid);
+    if (rc || a->waves > 1) return rc;
     *lds = (u32)pag_search_lds_bytes(L, b, a->hlog, a->blog, a);
     if (*lds > 65536) { pag_set_error("search: working set, tables and seen set need more than 64 KB of LDS per wave"); return PAG_EUNSUPPORTED; }
-    int rc = pag_search_max_grid(ix, b, *lds, grid);
-    if (rc) return rc;
+    if ((rc = pag_search_max_grid(ix, b, 1, *lds, grid))) return rc;
     // Long searches use the LDS hash only for their first nodes.  Where the registers of the kernel
     // would allow more waves per CU than this LDS footprint does, a smaller hash buys them.  The
     // comparison is made with half a KB of slack: a footprint that only just fits the count the
@@ -640,28 +700,31 @@ static int search_plan(const pag_index* ix, u32 b, u32 ef, u64 n_limit, SearchAr
     if (a->blog && !ix->seen_log2) {
         const u32 slack = 512;
         int best = 0;
-        if ((rc = pag_search_max_grid(ix, b, *lds + slack, &best))) return rc;
+        if ((rc = pag_search_max_grid(ix, b, 1, *lds + slack, &best))) return rc;
         for (u32 lg = a->hlog - 1; lg >= 7; --lg) {
             SearchArgs t = *a;
             t.hlog = lg;
             const u32 l2 = (u32)pag_search_lds_bytes(L, b, lg, t.blog, &t);
             int g2 = 0;
-            if ((rc = pag_search_max_grid(ix, b, l2 + slack, &g2))) return rc;
+            if ((rc = pag_search_max_grid(ix, b, 1, l2 + slack, &g2))) return rc;
             if (g2 > best) {
                 best = g2;
                 *a = t; *lds = l2;
-                if ((rc = pag_search_max_grid(ix, b, l2, grid))) return rc;
+                if ((rc = pag_search_max_grid(ix, b, 1, l2, grid))) return rc;
             }
         }
     }
-    // per-wave spill bitmaps of the seen set: one bit per node, rounded to 16 bytes
-    a->bitmap_words = ((u64)ix->capacity + 127) / 128 * 4;
+    // With the GPU full from beginning to end, more rows in flight only make the waves evict each other's from the
+    // memory-side cache.  1M x 768, 10,000 queries, efS 1408: 51.5 -> 50.65 ms with paced requests; 200k x 1536, 8,000
+    // queries, efS 400: 19.3 -> 19.1.  Batches of one round of waves and short searches lose instead (1M x 768, 2,048
+    // queries: 13.0 -> 13.5 ms; 200k x 1024, 10,000 queries, efS 128: 4.92 -> 4.97).
+    if (nq > (u64)*grid && ef >= 256) a->flags |= PAG_SEARCH_PACED;
     return PAG_OK;
 }
 
 // The plan plus the workspaces it needs (grown on demand); shared with indexing.
-int pag_search_common(pag_index* ix, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
-    int rc = search_plan(ix, b, ef, n_limit, a, lds, grid);
+int pag_search_common(pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+    int rc = search_plan(ix, nq, b, ef, n_limit, a, lds, grid);
     if (rc) return rc;
     const u64 need = (u64)*grid * a->bitmap_words;
     if (ix->ws_bitmap_cap < need) {
@@ -697,7 +760,7 @@ static int search_impl(pag_index* ix, const float* Q, uint64_t nq, uint32_t K, u
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = pag_search_common(ix, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = pag_search_common(ix, nq, b, efS, ix->n, &a, &lds, &grid))) return rc;
     if (nq > (u64)grid) {
         // several rounds of waves: as many waves as make the rounds equally full (10,000 queries on 4,096 waves: 3,334),
         // instead of a last round that leaves most of the GPU idle
@@ -765,7 +828,7 @@ extern "C" int pag_search_static(const pag_index* cix, const float* Q, uint64_t 
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = search_plan(ix, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = search_plan(ix, nq, b, efS, ix->n, &a, &lds, &grid))) return rc;
     // bitmap part: as many per-wave bitmaps as fit behind the query part; fewer waves than the GPU could hold
     // make the search slower, not different
     const u64 room = (u64)PAG_STATIC_SCRATCH_BYTES - off_bitmap;

@@ -20,9 +20,14 @@ typedef uint32_t u32;
 #define PAG_LDS_RING_MAX_B 128  // larger working sets keep R_F / R_T in HBM (the kernel's NW > 2 instantiations)
 #define PAG_MAX_DEG 64      // one neighbour per lane
 #define PAG_MAX_CW 8        // code dwords per neighbour: up to 64 subspaces
+#define PAG_TEAM_WORDS 512  // LDS words that a team shares
 #define PAG_SEARCH_DISTINCT (1u << 30)  // SearchArgs.flags, internal: a hop drops an id that an earlier slot of the record also lists
+#define PAG_SEARCH_PACED (1u << 29)     // SearchArgs.flags, internal: a wave asks for rows only when those before have arrived
 #define PAG_STATIC_SCRATCH_BYTES (48u << 20)   // the device array behind pag_search_static, per GPU
 #define PAG_STATIC_QUERY_FLOATS (4ull << 20)    // of which at most 16 MB hold rotated queries, tables and normalised copies
+
+// waves per query at most: three per SIMD; W of 1024 nodes leaves registers for two
+constexpr int pag_team_max(int nw) { return nw <= 8 ? 12 : 8; }
 
 void pag_set_error(const std::string& msg);
 
@@ -105,6 +110,7 @@ struct pag_index {
     u64* d_counters;                      // CTR_COUNT
     hipEvent_t ev[4];
     int num_cu;
+    u32 lds_per_cu;                       // bytes
     double last_search_ms, last_prepare_ms, last_build_ms;
     double build_phase_ms[4];             // of the last pag_build / pag_insert: search kernel, sort + RobustPrune, pair sort + reverse edges, inference information
     u64 relinked_batches;                 // insertion batches that were linked a second time (crowded regions)
@@ -121,7 +127,8 @@ struct SearchArgs {
     u32 n_limit;             // only nodes < n_limit belong to the graph
     u32 d, deg, Ppad, cw, rec_bytes, off_a, off_c, off_codes;
     u32 nq, K, b, Rmax, hlog, blog, flags;   // hlog: log2 slots of the LDS hash; blog: log2 bits of the Bloom filter (0 = none)
-    u32 off_hash, off_bloom, off_sa, off_sb, off_rf, off_rt;   // LDS offsets (bytes)
+    u32 off_hash, off_bloom, off_sa, off_sb, off_rf, off_rt, off_team;   // LDS offsets (bytes)
+    u32 waves;               // waves per query; above 1 the kernel for teams runs
     u32 ring_mask;           // rings live in power-of-two buffers of >= b slots; only the last b pushes are valid
     u64* rings;              // [grid * 3 * (ring_mask + 1)] per-wave R_F, R_T and R_L when b > PAG_LDS_RING_MAX_B, else unused
     long long* out_ids;      // [nq * K]       (search mode)
@@ -140,8 +147,8 @@ struct SearchArgs {
 
 // kernels / launchers (defined in the .hip files)
 int pag_launch_search(const pag_index* ix, const SearchArgs& a, u32 lds_bytes, int* grid_out);
-int pag_search_lds_bytes(const pag_layout& L, u32 b, u32 hlog, u32 blog, SearchArgs* a);
-int pag_search_max_grid(const pag_index* ix, u32 b, u32 lds_bytes, int* grid);
+int pag_search_lds_bytes(const pag_layout& L, u32 b, u32 hlog, u32 blog, SearchArgs* a);   // a->waves is read
+int pag_search_max_grid(const pag_index* ix, u32 b, u32 waves, u32 lds_bytes, int* grid);
 
 // g (host): a dim x dim Gaussian matrix, column after column; rot (dev): the orthogonal transform made of it, by rows
 int pag_orthonormalise(hipStream_t s, const double* g, u32 dim, float* rot);
@@ -163,7 +170,7 @@ int pag_launch_hop_traffic(hipStream_t s, const pag_index* ix, u64 hops, u32* bi
 int pag_launch_edge_info_list(hipStream_t s, const pag_index* ix, const u32* edge_list, u64 n_edges);
 int pag_launch_edge_info_of(hipStream_t s, const pag_index* ix, const u32* nodes, u64 m);   // every slot of m listed nodes (device ids)
 
-int pag_search_common(pag_index* ix, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid);
+int pag_search_common(pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid);
 inline pag_vecs pag_vecs_of(const pag_index* ix) { return pag_vecs{ ix->vec, ix->L.d, ix->vec_half }; }
 inline size_t pag_vec_elem(const pag_index* ix) { return ix->vec_half ? 2 : 4; }
 int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end);   // batch-synchronous insertion of nodes [n_begin, n_end)

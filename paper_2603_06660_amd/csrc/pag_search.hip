@@ -3,32 +3,15 @@
 #include "pag_internal.h"
 
 typedef void (*pag_search_fn)(const SearchArgs);   // selectors: one per (row chunks per lane, code dwords)
-pag_search_fn pag_search_fn_nq1_cw2(int, int);
-pag_search_fn pag_search_fn_nq1_cw4(int, int);
-pag_search_fn pag_search_fn_nq1_cw8(int, int);
-pag_search_fn pag_search_fn_nq2_cw2(int, int);
-pag_search_fn pag_search_fn_nq2_cw4(int, int);
-pag_search_fn pag_search_fn_nq2_cw8(int, int);
-pag_search_fn pag_search_fn_nq3_cw2(int, int);
-pag_search_fn pag_search_fn_nq3_cw4(int, int);
-pag_search_fn pag_search_fn_nq3_cw8(int, int);
-pag_search_fn pag_search_fn_nq4_cw2(int, int);
-pag_search_fn pag_search_fn_nq4_cw4(int, int);
-pag_search_fn pag_search_fn_nq4_cw8(int, int);
-pag_search_fn pag_search_fn_nq6_cw2(int, int);
-pag_search_fn pag_search_fn_nq6_cw4(int, int);
-pag_search_fn pag_search_fn_nq6_cw8(int, int);
-pag_search_fn pag_search_fn_nq8_cw2(int, int);
-pag_search_fn pag_search_fn_nq8_cw4(int, int);
-pag_search_fn pag_search_fn_nq8_cw8(int, int);
-pag_search_fn pag_search_fn_nq10_cw2(int, int);
-pag_search_fn pag_search_fn_nq10_cw4(int, int);
-pag_search_fn pag_search_fn_nq10_cw8(int, int);
-pag_search_fn pag_search_fn_nq12_cw2(int, int);
-pag_search_fn pag_search_fn_nq12_cw4(int, int);
-pag_search_fn pag_search_fn_nq12_cw8(int, int);
+#define PAG_DECLARE(NQ)                                                                                  \
+    pag_search_fn pag_search_fn_nq##NQ##_cw2(int, int);                                                  \
+    pag_search_fn pag_search_fn_nq##NQ##_cw4(int, int);                                                  \
+    pag_search_fn pag_search_fn_nq##NQ##_cw8(int, int);                                                  \
+    pag_search_fn pag_search_team_fn_nq##NQ(int, int);
+PAG_DECLARE(1) PAG_DECLARE(2) PAG_DECLARE(3) PAG_DECLARE(4) PAG_DECLARE(6) PAG_DECLARE(8) PAG_DECLARE(10) PAG_DECLARE(12)
+#undef PAG_DECLARE
 
-static pag_search_fn pick(u32 d, u32 b, bool half, u32 cw) {
+static pag_search_fn pick(u32 d, u32 b, bool half, u32 cw, bool team) {
     int nw = 1;                                       // entries of W per lane: 64 * nw >= b
     while (64u * nw < b) nw *= 2;
     // how a row is cut into per-lane chunks: fp32 rows in 16-byte chunks (256 elements per chunk
@@ -45,6 +28,7 @@ static pag_search_fn pick(u32 d, u32 b, bool half, u32 cw) {
     // for one more (it masks its last two chunk rows): 1, 2, 3, 4, 6, 8, 10, 12
     const u32 chunks = (d + per_chunk_row - 1) / per_chunk_row;
 #define PAG_PICK_CW(NQ)                                              \
+    if (team) return pag_search_team_fn_nq##NQ(nw, vm);              \
     switch (cw) {                                                    \
         case 2: return pag_search_fn_nq##NQ##_cw2(nw, vm);         \
         case 4: return pag_search_fn_nq##NQ##_cw4(nw, vm);         \
@@ -82,28 +66,30 @@ int pag_search_lds_bytes(const pag_layout& L, u32 b, u32 hlog, u32 blog, SearchA
     const u32 ring_lds = b > PAG_LDS_RING_MAX_B ? 0 : ring * 8;   // above that the rings live in HBM
     a->off_rf = off;   off += ring_lds;
     a->off_rt = off;   off += ring_lds;
+    a->off_team = off;
+    if (a->waves > 1) off += PAG_TEAM_WORDS * 4;
     return (int)off;
 }
 
-int pag_search_max_grid(const pag_index* ix, u32 b, u32 lds_bytes, int* grid) {
-    pag_search_fn fn = pick(ix->L.d, b, ix->vec_half != 0, ix->L.cw);
+int pag_search_max_grid(const pag_index* ix, u32 b, u32 waves, u32 lds_bytes, int* grid) {
+    pag_search_fn fn = pick(ix->L.d, b, ix->vec_half != 0, ix->L.cw, waves > 1);
     if (!fn) { pag_set_error("search: dimension above 3072 is not built"); return PAG_EUNSUPPORTED; }
     int per_cu = 0;
-    PAG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)fn, 64, lds_bytes));
+    PAG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)fn, (int)(64 * waves), lds_bytes));
     if (per_cu < 1) per_cu = 1;
     *grid = per_cu * ix->num_cu;
     return PAG_OK;
 }
 
 int pag_launch_search(const pag_index* ix, const SearchArgs& a, u32 lds_bytes, int* grid_io) {
-    pag_search_fn fn = pick(a.d, a.b, ix->vec_half != 0, a.cw);
+    pag_search_fn fn = pick(a.d, a.b, ix->vec_half != 0, a.cw, a.waves > 1);
     if (!fn) { pag_set_error("search: dimension above 3072 is not built"); return PAG_EUNSUPPORTED; }
     int grid = *grid_io;
     if ((u64)grid > a.nq) grid = (int)a.nq;
     if (grid < 1) return PAG_OK;
     SearchArgs args = a;
     void* kargs[] = { (void*)&args };
-    PAG_HIP(hipLaunchKernel((const void*)fn, dim3(grid), dim3(64), kargs, lds_bytes, ix->stream));
+    PAG_HIP(hipLaunchKernel((const void*)fn, dim3(grid), dim3(64 * a.waves), kargs, lds_bytes, ix->stream));
     *grid_io = grid;
     return PAG_OK;
 }

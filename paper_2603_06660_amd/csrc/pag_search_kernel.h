@@ -83,7 +83,22 @@ __device__ __forceinline__ void bloom_set(u32* B, u32 blog, u32 id) {
 }
 
 // dst[rank] = src[i], rank = number of smaller keys; keys are distinct.  Quadratic: for short lists.
+// Up to 64 keys sit in one register and are broadcast from there, four at a time: their comparisons do not wait for each
+// other, nor for LDS.
 __device__ __forceinline__ void rank_sort(const u64* src, u64* dst, u32 n, int lane) {
+    if (n <= 64) {
+        const u64 k = (u32)lane < n ? src[lane] : PAG_KEY_INVALID;
+        u32 r = 0;
+        for (u32 j = 0; j < n; j += 4) {
+            u64 o[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) o[g] = rdlane64(k, (int)j + g);     // beyond n: the largest key, smaller than none
+#pragma unroll
+            for (int g = 0; g < 4; ++g) r += (o[g] < k) ? 1u : 0u;
+        }
+        if ((u32)lane < n) dst[r] = k;
+        return;
+    }
     for (u32 i = lane; i < n; i += 64) {
         const u64 k = src[i];
         u32 r = 0;
@@ -177,25 +192,25 @@ __device__ __forceinline__ const u64* sort_keys(u64* a, u64* b, u32 n, bool by_r
 #endif
 
 // S = sum_l T[l][code_l] over the CW * 8 subspaces of one neighbour, added in increasing l.
-// The LDS gathers of 16 subspaces are issued together, then consumed in order.  `t_base` is the
+// The LDS gathers of G subspaces are issued together, then consumed in order.  `t_base` is the
 // LDS byte address of T, a multiple of 64, so that "4 * code" can be OR-ed into it and the row
 // offset 64 * l rides in the instruction.
 typedef __attribute__((address_space(3))) const float* lds_cfloat_ptr;
-template <int CW>
-__device__ __forceinline__ float table_sum(u32 t_base, const u32 (&cwv)[CW]) {
+template <int CW, int N, int G = 16>
+__device__ __forceinline__ float table_sum(u32 t_base, const u32 (&cwv)[N]) {
     float S = 0.f;
 #pragma unroll
-    for (int k = 0; k < CW; k += 2) {
-        float t[16];
+    for (int k = 0; k < CW; k += G / 8) {
+        float t[G];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+        for (int j = 0; j < G; ++j) {
             const u32 wd = cwv[k + j / 8];
             const int sh = 4 * (j % 8) - 2;
             const u32 x = sh < 0 ? wd << 2 : wd >> sh;
             t[j] = ((lds_cfloat_ptr)(uintptr_t)((x & 60u) | t_base))[(k * 8 + j) * PAG_NCODE];
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) S = S + t[j];
+        for (int j = 0; j < G; ++j) S = S + t[j];
     }
     return S;
 }
@@ -206,7 +221,9 @@ __device__ __forceinline__ float table_sum(u32 t_base, const u32 (&cwv)[CW]) {
 // lengths that would leave half of the lanes idle in the last 16-byte chunk); 16-bit values are
 // widened to fp32 on use; CW: dwords of 4-bit codes per neighbour (2, 4 or 8 for up to 16, 32 or
 // 64 subspaces).
-template <int NQ, int NW, int VM, int CW>
+// TEAM: the workgroup has several waves that work on one query (see run_team()).  CW is then the most that is supported,
+// the index's own count is read at run time.
+template <int NQ, int NW, int VM, int CW, bool TEAM = false>
 struct Wave {
     static constexpr bool HALF = VM != 0;
     static constexpr int EPC = VM == 1 ? 8 : 4;     // elements per chunk
@@ -214,6 +231,7 @@ struct Wave {
     // constant for the kernel
     const SearchArgs A;
     const int lane;
+    const int wave, nwaves;         // TEAM: this wave's number in its workgroup, and how many there are
     float* T;
     u32 t_base;                     // LDS byte address of T
     u32* H;
@@ -223,7 +241,7 @@ struct Wave {
     // per query
     static constexpr int QV = NQ * EPC / 4;         // float4 registers holding the query
     static constexpr bool RINGS_IN_HBM = NW > 2;    // matches the host's LDS carve-up
-    static constexpr bool BIG = NW > 2;             // large working sets: W unsorted, see admit_unsorted
+    static constexpr bool BIG = NW > 2;             // large working sets: W unsorted, see merge_unsorted
     u64 wmax;                       // BIG: key of W's farthest member, valid while nW == b
     u64 nx_key;                     // BIG: key of the node to expand next (PAG_KEY_INVALID: W has no unvisited node)
     bool nx_known;                  // BIG: nx_key is up to date
@@ -235,6 +253,10 @@ struct Wave {
     u32 nW, nRL;
     u32 cntF, hdF, cntT, hdT;       // rings: valid entries (<= b) and total pushes; slot = push number & ring mask
     u32 n_hash, n_spill;
+    u32 n_cand;                     // indexing mode: entries of R_L written so far
+    u32 round;                      // TEAM, wave 0: rounds finished
+    u32 scr_id;                     // TEAM, wave 1: the neighbours last screened
+    float pf_sum; bool pf_summed;   // TEAM: the code sums of the record in pf_*, once they are computed
     // The last TAILS chunk rows of the NQ may lie partly or wholly beyond the end of a row (the host
     // picks NQ = the rows needed, or one more where that count is not instantiated): per such chunk the
     // index this lane reads (0 if past the end) and a mask (all ones if inside the row, else zero)
@@ -245,6 +267,8 @@ struct Wave {
     u32 nx_id;                      // whose record pf_* holds (PAG_EMPTY: none)
     u32 pf_id, pf_cw[CW];
     float pf_a, pf_c;
+    // TEAM: what the waves of a workgroup share (LDS), see run_team()
+    u32* team;                      // words TM_* below
     u64 Hk;                         // indexing: PES buffer H(v), lane i = i-th closest surviving node (Alg. 1)
     // statistics (wave-uniform)
     u32 s_hops, s_tests, s_passes, s_exact, s_rounds, s_rf, s_rt, s_spill, s_queries;
@@ -253,7 +277,8 @@ struct Wave {
     u64 t_last;
 #endif
 
-    __device__ Wave(const SearchArgs& a, unsigned char* smem, int ln) : A(a), lane(ln) {
+    __device__ Wave(const SearchArgs& a, unsigned char* smem, int ln, int wv = 0, int nw = 1)
+        : A(a), lane(ln), wave(wv), nwaves(nw) {
         T = (float*)smem;
         t_base = (u32)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
         H = (u32*)(smem + a.off_hash);
@@ -269,6 +294,7 @@ struct Wave {
             RF = (u64*)(smem + a.off_rf);
             RT = (u64*)(smem + a.off_rt);
         }
+        team = (u32*)(smem + a.off_team);
         bitmap = a.bitmap + (u64)blockIdx.x * a.bitmap_words;
 #pragma unroll
         for (int t = 0; t < TAILS; ++t) {
@@ -300,16 +326,30 @@ struct Wave {
     // lane s < deg reads neighbour slot s of node u: id, a, c and its chunk of 4-bit codes.  The
     // other lanes read slot 0 and get an empty id (their a, c and codes are never used), so the
     // loads sit in straight-line code and can stay in flight across whatever follows.
-    __device__ __forceinline__ void load_record(u32 u, u32& id, float& ea, float& ec, u32 (&cwv)[CW]) const {
-        const uint8_t* rec = A.rec + (u64)u * A.rec_bytes;
+    __device__ __forceinline__ u32 load_id(u32 u) const {
         const bool in = (u32)lane < A.deg;
-        const u32 sl = in ? (u32)lane : 0u;
-        const u32 raw = ((const u32*)rec)[sl];
-        id = in ? raw : PAG_EMPTY;
+        const u32 raw = ((const u32*)(A.rec + (u64)u * A.rec_bytes))[in ? (u32)lane : 0u];
+        return in ? raw : PAG_EMPTY;
+    }
+    __device__ __forceinline__ void load_edges(u32 u, float& ea, float& ec, u32 (&cwv)[CW]) const {
+        const uint8_t* rec = A.rec + (u64)u * A.rec_bytes;
+        const u32 sl = (u32)lane < A.deg ? (u32)lane : 0u;
         ea = ((const float*)(rec + A.off_a))[sl];
         ec = ((const float*)(rec + A.off_c))[sl];
-        const u32* cp = (const u32*)(rec + A.off_codes) + sl * CW;   // 16-byte aligned section
-        if constexpr (CW == 2) {
+        const u32* cp = (const u32*)(rec + A.off_codes) + sl * (TEAM ? A.cw : (u32)CW);   // 16-byte aligned section
+        if constexpr (TEAM) {
+            // every word is written on every path, else the arrays would not stay in registers
+            uint4 t = make_uint4(0, 0, 0, 0), v = t;
+            if (A.cw == 2) {
+                const uint2 w = *(const uint2*)cp;
+                t.x = w.x; t.y = w.y;
+            } else {
+                t = *(const uint4*)cp;
+                if (A.cw == 8) v = *(const uint4*)(cp + 4);
+            }
+            cwv[0] = t.x; cwv[1] = t.y; cwv[2] = t.z; cwv[3] = t.w;
+            cwv[4] = v.x; cwv[5] = v.y; cwv[6] = v.z; cwv[7] = v.w;
+        } else if constexpr (CW == 2) {
             const uint2 t = *(const uint2*)cp;
             cwv[0] = t.x; cwv[1] = t.y;
         } else {
@@ -319,6 +359,10 @@ struct Wave {
                 cwv[k] = t.x; cwv[k + 1] = t.y; cwv[k + 2] = t.z; cwv[k + 3] = t.w;
             }
         }
+    }
+    __device__ __forceinline__ void load_record(u32 u, u32& id, float& ea, float& ec, u32 (&cwv)[CW]) const {
+        id = load_id(u);
+        load_edges(u, ea, ec, cwv);
     }
 
     // The node expanded next is the unvisited entry with the smallest rank after the merge: either the
@@ -356,19 +400,26 @@ struct Wave {
     static constexpr int GB = NQ * (int)sizeof(Chunk) <= 64 ? 2 : 1;
 
     // Branch-free row load: only the last TAILS chunks can run past the row; there the lane re-reads
-    // chunk 0 (in bounds) and the value is replaced by zeros, so no load ever sits inside a branch and
-    // the loads of several rows stay in flight together.
+    // chunk 0 (in bounds), so no load ever sits inside a branch and the loads of several rows stay in
+    // flight together.  The values read past the end are replaced by zeros where they are used
+    // (lane_partial): doing it here would wait for the row right after asking for it.
     __device__ __forceinline__ void load_vec(Chunk (&v)[NQ], u32 id) const {
         const Chunk* p = (const Chunk*)((const char*)A.vec + (u64)id * A.d * (HALF ? 2 : 4));
 #pragma unroll
         for (int c = 0; c < NQ - TAILS; ++c) v[c] = p[c * 64 + lane];
 #pragma unroll
         for (int t = 0; t < TAILS; ++t) {
-            Chunk x = p[tail_idx[t]];
-            x.x &= tail_mask[t]; x.y &= tail_mask[t];
-            if constexpr (VM != 2) { x.z &= tail_mask[t]; x.w &= tail_mask[t]; }
-            v[NQ - TAILS + t] = x;
+            v[NQ - TAILS + t] = p[tail_idx[t]];
         }
+    }
+
+    __device__ __forceinline__ Chunk inside_row(Chunk x, int c) const {
+        if (c >= NQ - TAILS) {
+            const u32 m = tail_mask[c - (NQ - TAILS)];
+            x.x &= m; x.y &= m;
+            if constexpr (VM != 2) { x.z &= m; x.w &= m; }
+        }
+        return x;
     }
 
     // sum over this lane's elements of fl32(q - x)^2, accumulated in fp64
@@ -376,9 +427,10 @@ struct Wave {
         double a = 0.0;
 #pragma unroll
         for (int c = 0; c < NQ; ++c) {
+            const Chunk x = inside_row(v[c], c);
             if constexpr (VM == 1) {
-                const float2 x0 = __half22float2(*(const __half2*)&v[c].x), x1 = __half22float2(*(const __half2*)&v[c].y);
-                const float2 x2 = __half22float2(*(const __half2*)&v[c].z), x3 = __half22float2(*(const __half2*)&v[c].w);
+                const float2 x0 = __half22float2(*(const __half2*)&x.x), x1 = __half22float2(*(const __half2*)&x.y);
+                const float2 x2 = __half22float2(*(const __half2*)&x.z), x3 = __half22float2(*(const __half2*)&x.w);
                 const float d0 = q[2 * c].x - x0.x, d1 = q[2 * c].y - x0.y, d2 = q[2 * c].z - x1.x, d3 = q[2 * c].w - x1.y;
                 const float d4 = q[2 * c + 1].x - x2.x, d5 = q[2 * c + 1].y - x2.y;
                 const float d6 = q[2 * c + 1].z - x3.x, d7 = q[2 * c + 1].w - x3.y;
@@ -387,13 +439,13 @@ struct Wave {
                 a = __builtin_fma((double)d4, (double)d4, a); a = __builtin_fma((double)d5, (double)d5, a);
                 a = __builtin_fma((double)d6, (double)d6, a); a = __builtin_fma((double)d7, (double)d7, a);
             } else if constexpr (VM == 2) {
-                const float2 x0 = __half22float2(*(const __half2*)&v[c].x), x1 = __half22float2(*(const __half2*)&v[c].y);
+                const float2 x0 = __half22float2(*(const __half2*)&x.x), x1 = __half22float2(*(const __half2*)&x.y);
                 const float d0 = q[c].x - x0.x, d1 = q[c].y - x0.y, d2 = q[c].z - x1.x, d3 = q[c].w - x1.y;
                 a = __builtin_fma((double)d0, (double)d0, a); a = __builtin_fma((double)d1, (double)d1, a);
                 a = __builtin_fma((double)d2, (double)d2, a); a = __builtin_fma((double)d3, (double)d3, a);
             } else {
-                const float dx = q[c].x - __uint_as_float(v[c].x), dy = q[c].y - __uint_as_float(v[c].y);
-                const float dz = q[c].z - __uint_as_float(v[c].z), dw = q[c].w - __uint_as_float(v[c].w);
+                const float dx = q[c].x - __uint_as_float(x.x), dy = q[c].y - __uint_as_float(x.y);
+                const float dz = q[c].z - __uint_as_float(x.z), dw = q[c].w - __uint_as_float(x.w);
                 a = __builtin_fma((double)dx, (double)dx, a);
                 a = __builtin_fma((double)dy, (double)dy, a);
                 a = __builtin_fma((double)dz, (double)dz, a);
@@ -435,14 +487,17 @@ struct Wave {
         u64 m = mask;
         int last = __ffsll((long long)mask) - 1;
         int left = __popcll(mask);
+        const bool paced = (A.flags & PAG_SEARCH_PACED) != 0;
         issue(va, pa, m, last, id_lane);
         for (;;) {
             // the scheduling barriers keep the requests for one buffer ahead of the arithmetic on the other
+            if (paced) __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
             issue(vb, pb, m, last, id_lane);
             __builtin_amdgcn_sched_barrier(0);
             reduce(va, pa, mine);
             left -= GB;
             if (left <= 0) break;
+            if (paced) __builtin_amdgcn_s_waitcnt(0x0F70);
             issue(va, pa, m, last, id_lane);
             __builtin_amdgcn_sched_barrier(0);
             reduce(vb, pb, mine);
@@ -452,33 +507,8 @@ struct Wave {
         return mine;
     }
 
-    // Admission of the lanes in `mask` (ids in id_lane): exact keys, seen-set insertion, merge into W.
-    __device__ __forceinline__ void admit(u32 id_lane, u64 mask) {
-        const u32 np = (u32)__popcll(mask);
-        if (np == 0) {
-            set_priority(0);
-            if constexpr (BIG) {
-                look_ahead();
-            } else {
-                u32 zero[NW];
-#pragma unroll
-                for (int s = 0; s < NW; ++s) zero[s] = 0;
-                request_next(zero, false, 0, 0, id_lane);
-            }
-            return;
-        }
-        const u32 b = A.b;
-        const bool pass = (mask >> lane) & 1ull;
-        if constexpr (BIG) {
-            admit_unsorted(id_lane, mask, np, pass);
-            return;
-        }
-        PAG_MARK(2);
-        const float dist = exact_keys(id_lane, mask);
-        set_priority(0);
-        PAG_MARK(3);
-        s_exact += np;
-        // seen set
+    // the hop's passers enter the seen set
+    __device__ __forceinline__ void mark_seen(u32 id_lane, u32 np, bool pass) {
         if (A.blog != 0) {
             // long searches: every node goes to the bitmap and the Bloom filter; the LDS table keeps the
             // most recently admitted id per slot (a hit there is definite)
@@ -497,48 +527,99 @@ struct Wave {
             }
             if (spill) { n_spill += np; s_spill += np; } else n_hash += np;
         }
+    }
 
-        const u64 pk = pass ? (((u64)__float_as_uint(dist) << 32) | ((u64)id_lane << 1)) : PAG_KEY_INVALID;
-        u32 cntW[NW];
+    // Admission of the lanes in `mask` (ids in id_lane): exact keys, seen-set insertion, merge into W.
+    __device__ __forceinline__ void admit(u32 id_lane, u64 mask) {
+        const u32 np = (u32)__popcll(mask);
+        if (np == 0) {
+            set_priority(0);
+            if constexpr (BIG) {
+                look_ahead();
+            } else {
+                u32 zero[NW];
 #pragma unroll
-        for (int s = 0; s < NW; ++s) cntW[s] = 0;
-        u32 cP = 0, cPW = 0;
-        for (u64 m = mask; m;) {
-            const int p = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            const u64 k = rdlane64(pk, p);
-            u32 c = 0;
-#pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                // keys are distinct, so one comparison tells both sides (an empty slot counts as larger)
-                const bool lt = W[s] < k;
-                c += (u32)__popcll(__ballot(lt));
-                cntW[s] += lt ? 0u : 1u;
+                for (int s = 0; s < NW; ++s) zero[s] = 0;
+                request_next(zero, false, 0, 0, id_lane);
             }
-            cP += (k < pk) ? 1u : 0u;
-            if (lane == p) cPW = c;
+            return;
         }
+        const bool pass = (mask >> lane) & 1ull;
+        PAG_MARK(2);
+        const float dist = exact_keys(id_lane, mask);
+        set_priority(0);
+        PAG_MARK(3);
+        mark_seen(id_lane, np, pass);
+        merge(id_lane, mask, np, pass, dist);
+        PAG_MARK(4);
+    }
+
+    // What a merge of the hop's passers into a sorted W comes to, before anything is moved.
+    struct Ranks {
+        u64 pk;                         // my passer's key
+        u32 cntW[NW];                   // passers closer than my members of W
+        u32 cP, rP;                     // my passer's rank among the passers and in the merged list
+    };
+    __device__ __forceinline__ void rank(Ranks& R, u32 id_lane, u64 mask, bool pass, float dist) const {
+        R.pk = pass ? (((u64)__float_as_uint(dist) << 32) | ((u64)id_lane << 1)) : PAG_KEY_INVALID;
+#pragma unroll
+        for (int s = 0; s < NW; ++s) R.cntW[s] = 0;
+        u32 cP = 0, cPW = 0;
+        // MU passers at a time: their broadcasts and counts do not depend on each other (a missing one counts as larger
+        // than everything)
+        constexpr int MU = TEAM ? 4 : 1;    // one wave per query: others fill the gaps
+        for (u64 m = mask; m;) {
+            u64 k[MU];
+            int p[MU];
+#pragma unroll
+            for (int g = 0; g < MU; ++g) {
+                p[g] = m ? __ffsll((long long)m) - 1 : -1;
+                k[g] = m ? rdlane64(R.pk, p[g]) : PAG_KEY_INVALID;
+                m &= m - 1;
+            }
+            u32 c[MU];
+#pragma unroll
+            for (int g = 0; g < MU; ++g) {
+                c[g] = 0;
+#pragma unroll
+                for (int s = 0; s < NW; ++s) {
+                    // keys are distinct, so one comparison tells both sides (an empty slot counts as larger)
+                    const bool lt = W[s] < k[g];
+                    c[g] += (u32)__popcll(__ballot(lt));
+                    R.cntW[s] += lt ? 0u : 1u;
+                }
+                cP += (k[g] < R.pk) ? 1u : 0u;
+            }
+#pragma unroll
+            for (int g = 0; g < MU; ++g)
+                if (lane == p[g]) cPW = c[g];
+        }
+        R.cP = cP;
+        R.rP = cP + cPW;
+    }
+
+    // the passers into a sorted W, as ranked
+    __device__ __forceinline__ void settle(const Ranks& R, u32 np, bool pass) {
+        const u32 b = A.b;
         const u32 total = nW + np;
         const u32 nW2 = total < b ? total : b;
-        const u32 rP = cP + cPW;                                   // merged rank of my passer
-        const u32 n_ins = (u32)__popcll(__ballot(pass && rP < b)); // passers that enter W
+        const u32 n_ins = (u32)__popcll(__ballot(pass && R.rP < b)); // passers that enter W
         const u32 n_f = np - n_ins;                                // false positives -> R_F
         const u32 n_ej = nW + n_ins - nW2;                         // displaced members -> R_T
-        request_next(cntW, pass, cP, rP, id_lane);
 #pragma unroll
         for (int s = 0; s < NW; ++s) {
             const u32 idx = s * 64 + lane;
             if (idx < nW) {
-                const u32 r = idx + cntW[s];
+                const u32 r = idx + R.cntW[s];
                 if (r < b) SA[r] = W[s];
                 else RT[(hdT + (nW - 1 - idx)) & A.ring_mask] = W[s];   // largest first
             }
         }
         if (pass) {
-            if (rP < b) SA[rP] = pk;
+            if (R.rP < b) SA[R.rP] = R.pk;
             else {
-                const u32 oi = cP - n_ins;                          // smallest first
-                if (oi + b >= n_f) RF[(hdF + oi) & A.ring_mask] = pk;  // older ones would be overwritten anyway
+                const u32 oi = R.cP - n_ins;                        // smallest first
+                if (oi + b >= n_f) RF[(hdF + oi) & A.ring_mask] = R.pk;  // older ones would be overwritten anyway
             }
         }
         if (n_ej) {
@@ -559,7 +640,19 @@ struct Wave {
         }
         nW = nW2;
         lds_sync();
-        PAG_MARK(4);
+    }
+
+    // the hop's passers, with their exact distances, into W (see the head of this file)
+    __device__ __forceinline__ void merge(u32 id_lane, u64 mask, u32 np, bool pass, float dist) {
+        s_exact += np;
+        if constexpr (BIG) {
+            merge_unsorted(id_lane, mask, np, pass, dist);
+        } else {
+            Ranks R;
+            rank(R, id_lane, mask, pass, dist);
+            if constexpr (!TEAM) request_next(R.cntW, pass, R.cP, R.rP, id_lane);
+            settle(R, np, pass);
+        }
     }
 
     // ---- working sets above 128 nodes (NW >= 4): W is kept unsorted ----
@@ -604,12 +697,15 @@ struct Wave {
         return ((u64)mh << 32) | row0_extreme_u32<MAX>(lo);
     }
 
-    // runs f(slot) for the one slot g (uniform), with the slot number as a compile-time constant
-    template <int S = 0, class F>
+    // runs f(slot) for the one slot g (uniform), with the slot number as a compile-time constant; found by halving
+    template <int LO = 0, int HI = NW, class F>
     __device__ __forceinline__ void at_slot(int g, F&& f) {
-        if constexpr (S < NW) {
-            if (g == S) f(std::integral_constant<int, S>{});
-            else at_slot<S + 1>(g, f);
+        if constexpr (HI - LO == 1) {
+            f(std::integral_constant<int, LO>{});
+        } else {
+            constexpr int MID = (LO + HI) / 2;
+            if (g < MID) at_slot<LO, MID>(g, f);
+            else at_slot<MID, HI>(g, f);
         }
     }
 
@@ -629,28 +725,9 @@ struct Wave {
     // farthest member takes that member's place and the member goes to R_T; the first passer that is not closer
     // ends it -- the farthest member can only have come closer since, and the remaining passers are no smaller --,
     // and that passer and all after it go to R_F.
-    __device__ __forceinline__ void admit_unsorted(u32 id_lane, u64 mask, u32 np, bool pass) {
+    __device__ __forceinline__ void merge_unsorted(u32 id_lane, u64 mask, u32 np, bool pass, float dist) {
         const u32 b = A.b;
-        PAG_MARK(2);
-        const float dist = exact_keys(id_lane, mask);
-        set_priority(0);
-        PAG_MARK(3);
-        s_exact += np;
-        if (A.blog != 0) {
-            if (pass) {
-                H[hash_slot(id_lane, A.hlog)] = id_lane;
-                atomicOr(&bitmap[id_lane >> 5], 1u << (id_lane & 31));
-                bloom_set(BL, A.blog, id_lane);
-            }
-            n_spill += np; s_spill += np;
-        } else {
-            const bool spill = (n_hash + np) > (1u << (A.hlog - 1));
-            if (pass) {
-                if (!spill) hash_insert(H, A.hlog, id_lane);
-                else atomicOr(&bitmap[id_lane >> 5], 1u << (id_lane & 31));
-            }
-            if (spill) { n_spill += np; s_spill += np; } else n_hash += np;
-        }
+        if constexpr (TEAM) nx_known = false;
         const u64 pk = pass ? (((u64)__float_as_uint(dist) << 32) | ((u64)id_lane << 1)) : PAG_KEY_INVALID;
         // rank of my passer among the hop's passers (keys are distinct)
         u32 cP = 0;
@@ -702,310 +779,302 @@ struct Wave {
             cntF = cntF + n_f < b ? cntF + n_f : b;
             hdF += n_f;
         }
-        look_ahead();
-        PAG_MARK(4);
+        if constexpr (!TEAM) look_ahead();
     }
 
-    __device__ __forceinline__ void run_query(u32 qi) {
-        const u32 d = A.d, b = A.b, deg = A.deg;
-        // ---- load query, table, reset state ----
-        {
-            const float4* qp = (const float4*)(A.qrot + (u64)qi * d);
+    // The query into registers, its table into LDS, the LDS levels of the seen set empty; the waves of a team share the
+    // LDS part out.
+    __device__ __forceinline__ void begin_query(u32 qi) {
+        const u32 d = A.d, tid = (u32)(wave * 64 + lane), step = 64u * (u32)nwaves;
+        const float4* qp = (const float4*)(A.qrot + (u64)qi * d);
 #pragma unroll
-            for (int c = 0; c < NQ; ++c) {
-                const u32 idx = c * 64 + lane;
-                if constexpr (VM == 1) {
-                    const bool in = c < NQ - TAILS || idx * 8 < d;
-                    q[2 * c] = in ? qp[2 * idx] : make_float4(0.f, 0.f, 0.f, 0.f);
-                    q[2 * c + 1] = in ? qp[2 * idx + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
-                } else {
-                    q[c] = (c < NQ - TAILS || idx * 4 < d) ? qp[idx] : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
-            const float4* tp = (const float4*)(A.tables + (u64)qi * A.Ppad * PAG_NCODE);
-            for (u32 i = lane; i < A.Ppad * PAG_NCODE / 4; i += 64) ((float4*)T)[i] = tp[i];
-            const uint4 e4 = make_uint4(PAG_EMPTY, PAG_EMPTY, PAG_EMPTY, PAG_EMPTY);
-            for (u32 i = lane; i < (1u << A.hlog) / 4; i += 64) ((uint4*)H)[i] = e4;
-            if (A.blog) {
-                const uint4 z4 = make_uint4(0, 0, 0, 0);
-                for (u32 i = lane; i < (1u << A.blog) / 128; i += 64) ((uint4*)BL)[i] = z4;
-            }
-#pragma unroll
-            for (int s = 0; s < NW; ++s) W[s] = PAG_KEY_INVALID;
-#pragma unroll
-            for (int s = 0; s < (BIG ? 1 : NW); ++s) RL[s] = PAG_KEY_INVALID;
-            nW = nRL = 0;
-            cntF = hdF = cntT = hdT = 0;
-            n_hash = n_spill = 0;
-            Hk = PAG_KEY_INVALID;
-            nx_id = PAG_EMPTY;
-            wmax = 0; nx_key = PAG_KEY_INVALID; nx_known = false;
-            GM = 0ull; GU = PAG_KEY_INVALID;
-            __syncthreads();
-        }
-        s_queries++;
-        u32 n_cand = 0;   // indexing mode: entries of R_L written so far
-
-        // ---- b entry nodes (Alg. 2, entry step) ----
-        {
-            u32 ne = A.n_entry < b ? A.n_entry : b;
-            for (u32 base = 0; base < ne; base += 64) {
-                const u32 i = base + lane;
-                u32 id = PAG_EMPTY;
-                if (i < ne) id = A.entry[i];
-                const bool ok = id != PAG_EMPTY && id < A.n_limit;
-                admit(id, __ballot(ok));
-            }
-        }
-
-        // ---- rounds ----
-        for (u32 r = 0; r < A.Rmax; ++r) {
-            if (nW == 0) break;
-            s_rounds++;
-            for (;;) {
-                // closest unvisited member of W
-                u64 ukey = 0;
-                if constexpr (BIG) {
-                    if (!nx_known) nx_key = over_slots<false>(GU);
-                    nx_known = false;
-                    if (nx_key == PAG_KEY_INVALID) break;
-                    PAG_MARK(5);
-                    ukey = nx_key;
-                    const int g = __ffsll((long long)__ballot(GU == ukey)) - 1;        // its slot
-                    at_slot(g, [&](auto S_) {
-                        constexpr int S = decltype(S_)::value;
-                        if (W[S] == ukey) W[S] |= 1ull;
-                        const u64 m = slot_min_unvisited<S>();
-                        if (lane == S) GU = m;
-                    });
-                    if (GM == ukey) GM |= 1ull;                                         // it may be its slot's farthest too
-                    if (nW == b && (wmax | 1ull) == (ukey | 1ull)) wmax |= 1ull;
-                } else {
-                    int us = -1, ul = 0;
-#pragma unroll
-                    for (int s = 0; s < NW; ++s) {
-                        const u32 idx = s * 64 + lane;
-                        const u64 m = __ballot(idx < nW && !(W[s] & 1ull));
-                        if (us < 0 && m) { us = s; ul = __ffsll((long long)m) - 1; }
-                    }
-                    if (us < 0) break;
-                    PAG_MARK(5);
-#pragma unroll
-                    for (int s = 0; s < NW; ++s)
-                        if (s == us) {
-                            ukey = rdlane64(W[s], ul);
-                            if (lane == ul) W[s] |= 1ull;
-                        }
-                }
-                s_hops++;
-                set_priority(2);   // screening leads to the next loads: ahead of other waves' bookkeeping
-                const u32 u = (u32)(ukey & 0xFFFFFFFFull) >> 1;
-                const float Du = __uint_as_float((u32)(ukey >> 32));
-                // threshold ||z_max - q||^2, read once per hop (Eq. 4); +inf while W is not full
-                float Dmax = __builtin_inff();
-                if (nW == b) {
-                    if constexpr (BIG) {
-                        Dmax = __uint_as_float((u32)(wmax >> 32));
-                    } else {
-                        const u32 wr = b - 1;
-#pragma unroll
-                        for (int s = 0; s < NW; ++s)
-                            if ((int)(wr >> 6) == s) Dmax = __uint_as_float(rdlane((u32)(W[s] >> 32), wr & 63));
-                    }
-                }
-                PAG_MARK(0);
-                // adjacency record of u: normally already on its way (see request_next)
-                u32 id;
-                float ea, ec;
-                u32 cwv[CW];
-                if (u == nx_id) {
-                    id = pf_id; ea = pf_a; ec = pf_c;
-#pragma unroll
-                    for (int k = 0; k < CW; ++k) cwv[k] = pf_cw[k];
-                } else {
-                    load_record(u, id, ea, ec, cwv);
-                }
-                nx_id = PAG_EMPTY;
-                PAG_MARK(1);
-                const bool in_graph = id != PAG_EMPTY && id < A.n_limit;
-                // seen-set lookup.  Short searches: the exact LDS hash, then the bitmap word if the hash has
-                // overflowed, requested now and consumed after the table sums.  Long searches: the LDS cache of
-                // recent ids now; the Bloom filter and the bitmap only for the neighbours that pass the test
-                // (a bitmap read costs more than the table sums of the seen neighbours it would spare).
-                bool cand = in_graph;
-                if (cand) cand = A.blog != 0 ? H[hash_slot(id, A.hlog)] != id : !hash_contains(H, A.hlog, id);
-                u32 bm_word = 0;
-                if (A.blog == 0 && n_spill && cand)
-                    bm_word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                // counting mode of long searches: the second level is consulted for every neighbour, before the
-                // test, so that `tests` counts the unseen neighbours only (same results, more bitmap reads)
-                const bool resolve_first = A.blog != 0 && (A.flags & PAG_FLAG_EXACT_TEST_COUNT);
-                if (resolve_first) {
-                    u32 wd = 0;
-                    if (cand && bloom_maybe(BL, A.blog, id))
-                        wd = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    cand = cand && !((wd >> (id & 31)) & 1u);
-                }
-                // projection test: S = sum_l T[l][code_l] (increasing l), est = D_u + c - 2 a S
-                float est = 0.f;
-                const bool want_pes = A.pes != nullptr;   // indexing: every neighbour's estimate feeds Eq. 5
-                if (!(A.flags & PAG_FLAG_NO_PRT)) {
-                    float S = 0.f;
-                    if (cand || (want_pes && in_graph)) {
-                        S = table_sum<CW>(t_base, cwv);
-                    }
-                    est = __builtin_fmaf(-2.0f * ea, S, Du + ec);
-                }
-                if (A.blog != 0 && !resolve_first) {
-                    // long searches: only neighbours that pass the test are looked up in the Bloom filter and the bitmap
-                    const bool maybe = cand && ((A.flags & PAG_FLAG_NO_PRT) || est < Dmax) && bloom_maybe(BL, A.blog, id);
-                    if (maybe) bm_word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                const bool unseen = cand && !((bm_word >> (id & 31)) & 1u);
-                bool pass = unseen;
-                if (!(A.flags & PAG_FLAG_NO_PRT)) pass = unseen && (est < Dmax);
-                if (A.blog == 0) cand = unseen;
-                if (want_pes) {
-                    // PES screening (Eq. 5): max_i (cos theta_i / cos beta_i - delta_i) < 0 for all neighbours
-                    // <=> every estimate est_i exceeds D_u, i.e. no neighbour of u looks closer to v than
-                    // u itself.  Then u -> v is a candidate edge; H(v) keeps the closest `deg` such nodes.
-                    if (__ballot(in_graph && !(est > Du)) == 0ull) {
-                        const u64 key = (ukey & ~1ull);
-                        const u32 pos = (u32)__popcll(__ballot(Hk < key));
-                        const u64 up = __shfl_up(Hk, 1, 64);
-                        if ((u32)lane == pos) Hk = key;
-                        else if ((u32)lane > pos) Hk = up;
-                    }
-                }
-                if (A.flags & PAG_SEARCH_DISTINCT) {
-                    // searches that overlap an insertion: a record read between two states of a reverse-edge pass may
-                    // list one node in two slots; the first slot stands, the merge needs distinct keys
-                    for (u64 m = __ballot(pass); m;) {
-                        const int p = __ffsll((long long)m) - 1;
-                        m &= m - 1;
-                        if (lane > p && id == rdlane(id, p)) { pass = false; cand = false; }
-                    }
-                }
-                const u64 cmask = __ballot(cand);
-                const u64 pmask = __ballot(pass);
-                s_tests += (u32)__popcll(cmask);
-                s_passes += (u32)__popcll(pmask);
-                admit(id, pmask);
-            }
-
-            // ---- round end (Alg. 2): W -> R_L, clear W; merge + sort rings; refill W; rest -> R_T ----
-            nx_id = PAG_EMPTY;
-            if (A.cand) {
-                // indexing: R_L has room for every round's W (capacity efC >= Rmax * b is enforced by the host)
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const u32 idx = s * 64 + lane;
-                    if (idx < nW && n_cand + idx < A.cand_cap) A.cand[(u64)qi * A.cand_cap + n_cand + idx] = W[s];
-                }
-                n_cand = n_cand + nW < A.cand_cap ? n_cand + nW : A.cand_cap;
-            } else if constexpr (BIG) {
-                // R_L <- best K of R_L + W: R_L (sorted, SA[0, nRL) in HBM) and W are sorted together in registers
-                u64 x[2 * NW];
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const u32 idx = s * 64 + lane;
-                    x[s] = idx < nW ? W[s] : PAG_KEY_INVALID;
-                    x[NW + s] = idx < nRL ? SA[idx] : PAG_KEY_INVALID;
-                }
-                bitonic_registers<2 * NW>(x, lane);
-                const u32 n = nRL + nW;
-                nRL = n < A.K ? n : A.K;
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {                  // K <= b <= 64 NW
-                    const u32 idx = s * 64 + lane;
-                    if (idx < nRL) SA[idx] = x[s];
-                }
+        for (int c = 0; c < NQ; ++c) {
+            const u32 idx = c * 64 + lane;
+            if constexpr (VM == 1) {
+                const bool in = c < NQ - TAILS || idx * 8 < d;
+                q[2 * c] = in ? qp[2 * idx] : make_float4(0.f, 0.f, 0.f, 0.f);
+                q[2 * c + 1] = in ? qp[2 * idx + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
             } else {
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const u32 idx = s * 64 + lane;
-                    if (idx < nRL) SA[idx] = RL[s];
-                    if (idx < nW) SA[nRL + idx] = W[s];
-                }
-                lds_sync();
-                const u32 n = nRL + nW;
-                const u64* S = sort_keys(SA, SB, n, 2 * b <= PAG_RANK_SORT_MAX, lane);
-                nRL = n < A.K ? n : A.K;
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const u32 idx = s * 64 + lane;
-                    RL[s] = idx < nRL ? S[idx] : PAG_KEY_INVALID;
-                }
-                lds_sync();
-            }
-            if constexpr (BIG) {
-                // this wave's own stores (ring pushes, R_L) must have landed before other lanes read them
-                __threadfence();
-                const u32 n = cntF + cntT;                       // <= 2b <= 128 NW
-                u64 x[2 * NW];
-#pragma unroll
-                for (int s = 0; s < 2 * NW; ++s) {
-                    const u32 i = s * 64 + lane;
-                    u64 k = PAG_KEY_INVALID;
-                    if (i < cntF) k = RF[(hdF - cntF + i) & A.ring_mask];
-                    else if (i < n) k = RT[(hdT - cntT + (i - cntF)) & A.ring_mask];
-                    x[s] = k;
-                }
-                bitonic_registers<2 * NW>(x, lane);
-                nW = n < b ? n : b;
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const u32 idx = s * 64 + lane;
-                    W[s] = idx < nW ? x[s] : PAG_KEY_INVALID;
-                }
-                // W is sorted now: a slot's farthest member is its last, its closest unvisited one the first unvisited
-                GM = 0ull; GU = PAG_KEY_INVALID;
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const u32 first = s * 64;
-                    if (nW > first) {
-                        const u32 cnt = nW - first < 64u ? nW - first : 64u;
-                        const u64 far = rdlane64(W[s], (int)cnt - 1);
-                        const u64 open = __ballot((u32)lane < cnt && !(W[s] & 1ull));
-                        const u64 near = open ? rdlane64(W[s], __ffsll((long long)open) - 1) : PAG_KEY_INVALID;
-                        if (lane == s) { GM = far; GU = near; }
-                    }
-                }
-                wmax = nW == b ? over_slots<true>(GM) : 0ull;
-                nx_known = false;
-                const u32 rest = n - nW;                         // <= b; written worst first
-#pragma unroll
-                for (int s = 0; s < 2 * NW; ++s) {
-                    const u32 e = s * 64 + lane;
-                    if (e >= nW && e < n) RT[n - 1 - e] = x[s];
-                }
-                cntT = rest; hdT = rest;
-                cntF = 0; hdF = 0;
-            } else {
-                for (u32 i = lane; i < cntF; i += 64) SA[i] = RF[(hdF - cntF + i) & A.ring_mask];
-                for (u32 i = lane; i < cntT; i += 64) SA[cntF + i] = RT[(hdT - cntT + i) & A.ring_mask];
-                lds_sync();
-                const u32 n = cntF + cntT;
-                const u64* S = sort_keys(SA, SB, n, 2 * b <= PAG_RANK_SORT_MAX, lane);
-                nW = n < b ? n : b;
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const u32 idx = s * 64 + lane;
-                    W[s] = idx < nW ? S[idx] : PAG_KEY_INVALID;
-                }
-                const u32 rest = n - nW;                         // <= b; written worst first
-                for (u32 j = lane; j < rest; j += 64) RT[j] = S[n - 1 - j];
-                cntT = rest; hdT = rest;
-                cntF = 0; hdF = 0;
-                lds_sync();
+                q[c] = (c < NQ - TAILS || idx * 4 < d) ? qp[idx] : make_float4(0.f, 0.f, 0.f, 0.f);
             }
         }
+        const float4* tp = (const float4*)(A.tables + (u64)qi * A.Ppad * PAG_NCODE);
+        for (u32 i = tid; i < A.Ppad * PAG_NCODE / 4; i += step) ((float4*)T)[i] = tp[i];
+        const uint4 e4 = make_uint4(PAG_EMPTY, PAG_EMPTY, PAG_EMPTY, PAG_EMPTY);
+        for (u32 i = tid; i < (1u << A.hlog) / 4; i += step) ((uint4*)H)[i] = e4;
+        if (A.blog) {
+            const uint4 z4 = make_uint4(0, 0, 0, 0);
+            for (u32 i = tid; i < (1u << A.blog) / 128; i += step) ((uint4*)BL)[i] = z4;
+        }
+    }
 
-        // ---- output ----
-        if (A.cand) {
-            if (lane == 0) A.cand_cnt[qi] = n_cand;
-            if (A.pes && (u32)lane < deg) A.pes[(u64)qi * deg + lane] = Hk;
+    __device__ __forceinline__ void reset_lists() {
+#pragma unroll
+        for (int s = 0; s < NW; ++s) W[s] = PAG_KEY_INVALID;
+#pragma unroll
+        for (int s = 0; s < (BIG ? 1 : NW); ++s) RL[s] = PAG_KEY_INVALID;
+        nW = nRL = 0;
+        cntF = hdF = cntT = hdT = 0;
+        n_hash = n_spill = 0;
+        Hk = PAG_KEY_INVALID;
+        nx_id = PAG_EMPTY;
+        wmax = 0; nx_key = PAG_KEY_INVALID; nx_known = false;
+        GM = 0ull; GU = PAG_KEY_INVALID;
+        n_cand = 0;
+        round = 0;
+    }
+
+    // Marks the closest unvisited member of W visited and returns its key; PAG_KEY_INVALID: there is none.
+    __device__ __forceinline__ u64 pop() {
+        const u32 b = A.b;
+        u64 ukey = PAG_KEY_INVALID;
+        if constexpr (BIG) {
+            if (!nx_known) nx_key = over_slots<false>(GU);
+            nx_known = false;
+            if (nx_key == PAG_KEY_INVALID) return nx_key;
+            PAG_MARK(5);
+            ukey = nx_key;
+            const int g = __ffsll((long long)__ballot(GU == ukey)) - 1;        // its slot
+            at_slot(g, [&](auto S_) {
+                constexpr int S = decltype(S_)::value;
+                if (W[S] == ukey) W[S] |= 1ull;
+                const u64 m = slot_min_unvisited<S>();
+                if (lane == S) GU = m;
+            });
+            if (GM == ukey) GM |= 1ull;                                         // it may be its slot's farthest too
+            if (nW == b && (wmax | 1ull) == (ukey | 1ull)) wmax |= 1ull;
         } else {
+            int us = -1, ul = 0;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                const u64 m = __ballot(idx < nW && !(W[s] & 1ull));
+                if (us < 0 && m) { us = s; ul = __ffsll((long long)m) - 1; }
+            }
+            if (us < 0) return ukey;
+            PAG_MARK(5);
+#pragma unroll
+            for (int s = 0; s < NW; ++s)
+                if (s == us) {
+                    ukey = rdlane64(W[s], ul);
+                    if (lane == ul) W[s] |= 1ull;
+                }
+        }
+        s_hops++;
+        return ukey;
+    }
+
+    // key of W's farthest member; PAG_KEY_INVALID while W is not full
+    __device__ __forceinline__ u64 farthest() const {
+        if (nW != A.b) return PAG_KEY_INVALID;
+        if constexpr (BIG) {
+            return wmax;
+        } else {
+            const u32 wr = A.b - 1;
+            u64 k = 0;
+#pragma unroll
+            for (int s = 0; s < NW; ++s)
+                if ((int)(wr >> 6) == s) k = rdlane64(W[s], wr & 63);
+            return k;
+        }
+    }
+
+    // threshold ||z_max - q||^2 of a hop (Eq. 4); +inf while W is not full
+    __device__ __forceinline__ static float threshold(u64 far) {
+        return far == PAG_KEY_INVALID ? __builtin_inff() : __uint_as_float((u32)(far >> 32));
+    }
+
+    // The projection test's input for all neighbours of a node at distance Du: their estimates, and which of them are
+    // candidates (in the graph and not known to be seen) and unseen.  Dmax is the threshold or, where that is not known
+    // yet, a bound above it: it only decides which neighbours of a long search are looked up in the second level.
+    __device__ __forceinline__ void screen(u32 id, float ea, float ec, const u32 (&cwv)[CW], float Du, float Dmax, float& est, bool& cand,
+                                           bool& unseen) {
+        const bool in_graph = id != PAG_EMPTY && id < A.n_limit;
+        // seen-set lookup.  Short searches: the exact LDS hash, then the bitmap word if the hash has
+        // overflowed, requested now and consumed after the table sums.  Long searches: the LDS cache of
+        // recent ids now; the Bloom filter and the bitmap only for the neighbours that pass the test
+        // (a bitmap read costs more than the table sums of the seen neighbours it would spare).
+        cand = in_graph;
+        if (cand) cand = A.blog != 0 ? H[hash_slot(id, A.hlog)] != id : !hash_contains(H, A.hlog, id);
+        u32 bm_word = 0;
+        if (A.blog == 0 && n_spill && cand)
+            bm_word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // counting mode of long searches: the second level is consulted for every neighbour, before the
+        // test, so that `tests` counts the unseen neighbours only (same results, more bitmap reads)
+        const bool resolve_first = A.blog != 0 && (A.flags & PAG_FLAG_EXACT_TEST_COUNT);
+        if (resolve_first) {
+            u32 wd = 0;
+            if (cand && bloom_maybe(BL, A.blog, id))
+                wd = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            cand = cand && !((wd >> (id & 31)) & 1u);
+        }
+        // projection test: S = sum_l T[l][code_l] (increasing l), est = D_u + c - 2 a S
+        est = 0.f;
+        const bool want_pes = A.pes != nullptr;   // indexing: every neighbour's estimate feeds Eq. 5
+        if (!(A.flags & PAG_FLAG_NO_PRT)) {
+            float S = 0.f;
+            if (cand || (want_pes && in_graph)) {
+                S = table_sum<CW>(t_base, cwv);
+            }
+            est = __builtin_fmaf(-2.0f * ea, S, Du + ec);
+        }
+        if (A.blog != 0 && !resolve_first) {
+            // long searches: only neighbours that pass the test are looked up in the Bloom filter and the bitmap
+            const bool maybe = cand && ((A.flags & PAG_FLAG_NO_PRT) || est < Dmax) && bloom_maybe(BL, A.blog, id);
+            if (maybe) bm_word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        unseen = cand && !((bm_word >> (id & 31)) & 1u);
+        if (A.blog == 0) cand = unseen;
+    }
+
+    __device__ __forceinline__ bool passes(bool unseen, float est, float Dmax) const {
+        return unseen && ((A.flags & PAG_FLAG_NO_PRT) || est < Dmax);
+    }
+
+    // PES screening (Eq. 5): max_i (cos theta_i / cos beta_i - delta_i) < 0 for all neighbours
+    // <=> every estimate est_i exceeds D_u, i.e. no neighbour of u looks closer to v than
+    // u itself.  Then u -> v is a candidate edge; H(v) keeps the closest `deg` such nodes.
+    __device__ __forceinline__ void screen_pes(u32 id, float est, u64 ukey) {
+        const bool in_graph = id != PAG_EMPTY && id < A.n_limit;
+        const float Du = __uint_as_float((u32)(ukey >> 32));
+        if (__ballot(in_graph && !(est > Du)) == 0ull) {
+            const u64 key = (ukey & ~1ull);
+            const u32 pos = (u32)__popcll(__ballot(Hk < key));
+            const u64 up = __shfl_up(Hk, 1, 64);
+            if ((u32)lane == pos) Hk = key;
+            else if ((u32)lane > pos) Hk = up;
+        }
+    }
+
+    // searches that overlap an insertion: a record read between two states of a reverse-edge pass may
+    // list one node in two slots; the first slot stands, the merge needs distinct keys
+    __device__ __forceinline__ bool first_of_id(u32 id, bool pass) const {
+        bool first = true;
+        for (u64 m = __ballot(pass); m;) {
+            const int p = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            const u64 same = __ballot(lane > p && id == rdlane(id, p));
+            if (same) { m &= ~same; if ((same >> lane) & 1ull) first = false; }
+        }
+        return first;
+    }
+
+    // ---- round end (Alg. 2): W -> R_L, clear W; merge + sort rings; refill W; rest -> R_T ----
+    __device__ __forceinline__ void end_round(u32 qi) {
+        const u32 b = A.b;
+        nx_id = PAG_EMPTY;
+        if (A.cand) {
+            // indexing: R_L has room for every round's W (capacity efC >= Rmax * b is enforced by the host)
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                if (idx < nW && n_cand + idx < A.cand_cap) A.cand[(u64)qi * A.cand_cap + n_cand + idx] = W[s];
+            }
+            n_cand = n_cand + nW < A.cand_cap ? n_cand + nW : A.cand_cap;
+        } else if constexpr (BIG) {
+            // R_L <- best K of R_L + W: R_L (sorted, SA[0, nRL) in HBM) and W are sorted together in registers
+            u64 x[2 * NW];
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                x[s] = idx < nW ? W[s] : PAG_KEY_INVALID;
+                x[NW + s] = idx < nRL ? SA[idx] : PAG_KEY_INVALID;
+            }
+            bitonic_registers<2 * NW>(x, lane);
+            const u32 n = nRL + nW;
+            nRL = n < A.K ? n : A.K;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {                  // K <= b <= 64 NW
+                const u32 idx = s * 64 + lane;
+                if (idx < nRL) SA[idx] = x[s];
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                if (idx < nRL) SA[idx] = RL[s];
+                if (idx < nW) SA[nRL + idx] = W[s];
+            }
+            lds_sync();
+            const u32 n = nRL + nW;
+            const u64* S = sort_keys(SA, SB, n, 2 * b <= PAG_RANK_SORT_MAX, lane);
+            nRL = n < A.K ? n : A.K;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                RL[s] = idx < nRL ? S[idx] : PAG_KEY_INVALID;
+            }
+            lds_sync();
+        }
+        if constexpr (BIG) {
+            // this wave's own stores (ring pushes, R_L) must have landed before other lanes read them
+            __threadfence();
+            const u32 n = cntF + cntT;                       // <= 2b <= 128 NW
+            u64 x[2 * NW];
+#pragma unroll
+            for (int s = 0; s < 2 * NW; ++s) {
+                const u32 i = s * 64 + lane;
+                u64 k = PAG_KEY_INVALID;
+                if (i < cntF) k = RF[(hdF - cntF + i) & A.ring_mask];
+                else if (i < n) k = RT[(hdT - cntT + (i - cntF)) & A.ring_mask];
+                x[s] = k;
+            }
+            bitonic_registers<2 * NW>(x, lane);
+            nW = n < b ? n : b;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                W[s] = idx < nW ? x[s] : PAG_KEY_INVALID;
+            }
+            // W is sorted now: a slot's farthest member is its last, its closest unvisited one the first unvisited
+            GM = 0ull; GU = PAG_KEY_INVALID;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 first = s * 64;
+                if (nW > first) {
+                    const u32 cnt = nW - first < 64u ? nW - first : 64u;
+                    const u64 far = rdlane64(W[s], (int)cnt - 1);
+                    const u64 open = __ballot((u32)lane < cnt && !(W[s] & 1ull));
+                    const u64 near = open ? rdlane64(W[s], __ffsll((long long)open) - 1) : PAG_KEY_INVALID;
+                    if (lane == s) { GM = far; GU = near; }
+                }
+            }
+            wmax = nW == b ? over_slots<true>(GM) : 0ull;
+            nx_known = false;
+            const u32 rest = n - nW;                         // <= b; written worst first
+#pragma unroll
+            for (int s = 0; s < 2 * NW; ++s) {
+                const u32 e = s * 64 + lane;
+                if (e >= nW && e < n) RT[n - 1 - e] = x[s];
+            }
+            cntT = rest; hdT = rest;
+            cntF = 0; hdF = 0;
+        } else {
+            for (u32 i = lane; i < cntF; i += 64) SA[i] = RF[(hdF - cntF + i) & A.ring_mask];
+            for (u32 i = lane; i < cntT; i += 64) SA[cntF + i] = RT[(hdT - cntT + i) & A.ring_mask];
+            lds_sync();
+            const u32 n = cntF + cntT;
+            const u64* S = sort_keys(SA, SB, n, 2 * b <= PAG_RANK_SORT_MAX, lane);
+            nW = n < b ? n : b;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                W[s] = idx < nW ? S[idx] : PAG_KEY_INVALID;
+            }
+            const u32 rest = n - nW;                         // <= b; written worst first
+            for (u32 j = lane; j < rest; j += 64) RT[j] = S[n - 1 - j];
+            cntT = rest; hdT = rest;
+            cntF = 0; hdF = 0;
+            lds_sync();
+        }
+    }
+
+    __device__ __forceinline__ void write_results(u32 qi) const {
+        if (A.cand) {
+            if (wave == 0 && lane == 0) A.cand_cnt[qi] = n_cand;
+            // the buffer H(v) is kept where the screening is done
+            if (A.pes && wave == (TEAM ? 1 : 0) && (u32)lane < A.deg) A.pes[(u64)qi * A.deg + lane] = Hk;
+        } else if (wave == 0) {
 #pragma unroll
             for (int s = 0; s < NW; ++s) {
                 const u32 idx = s * 64 + lane;
@@ -1024,12 +1093,507 @@ struct Wave {
                 }
             }
         }
-        // a spilled query leaves its bitmap clean for the next one
-        if (n_spill) {
-            uint4* bm = (uint4*)bitmap;
-            const uint4 z = make_uint4(0, 0, 0, 0);
-            for (u64 i = lane; i < A.bitmap_words / 4; i += 64) bm[i] = z;
-            __threadfence();
+    }
+
+    // a spilled query leaves its bitmap clean for the next one
+    __device__ __forceinline__ void clear_bitmap() const {
+        uint4* bm = (uint4*)bitmap;
+        const uint4 z = make_uint4(0, 0, 0, 0);
+        for (u64 i = wave * 64 + lane; i < A.bitmap_words / 4; i += 64 * nwaves) bm[i] = z;
+        __threadfence();
+    }
+
+    // entry nodes base .. base + 63 (Alg. 2, entry step): this lane's id, or PAG_EMPTY
+    __device__ __forceinline__ u32 entry_node(u32 base, u32 ne) const {
+        const u32 i = base + lane;
+        u32 id = PAG_EMPTY;
+        if (i < ne) id = A.entry[i];
+        return id != PAG_EMPTY && id < A.n_limit ? id : PAG_EMPTY;
+    }
+
+    // one query, one wave
+    __device__ __forceinline__ void run_query(u32 qi) {
+        begin_query(qi);
+        reset_lists();
+        __syncthreads();
+        s_queries++;
+        // ---- b entry nodes (Alg. 2, entry step) ----
+        const u32 ne = A.n_entry < A.b ? A.n_entry : A.b;
+        for (u32 base = 0; base < ne; base += 64) {
+            const u32 id = entry_node(base, ne);
+            admit(id, __ballot(id != PAG_EMPTY));
+        }
+        // ---- rounds ----
+        for (u32 r = 0; r < A.Rmax; ++r) {
+            if (nW == 0) break;
+            s_rounds++;
+            for (;;) {
+                const u64 ukey = pop();
+                if (ukey == PAG_KEY_INVALID) break;
+                set_priority(2);   // screening leads to the next loads: ahead of other waves' bookkeeping
+                const u32 u = (u32)(ukey & 0xFFFFFFFFull) >> 1;
+                const float Dmax = threshold(farthest());      // read once per hop
+                PAG_MARK(0);
+                // adjacency record of u: normally already on its way (see request_next)
+                u32 id;
+                float ea, ec;
+                u32 cwv[CW];
+                if (u == nx_id) {
+                    id = pf_id; ea = pf_a; ec = pf_c;
+#pragma unroll
+                    for (int k = 0; k < CW; ++k) cwv[k] = pf_cw[k];
+                } else {
+                    load_record(u, id, ea, ec, cwv);
+                }
+                nx_id = PAG_EMPTY;
+                PAG_MARK(1);
+                float est;
+                bool cand, unseen;
+                screen(id, ea, ec, cwv, __uint_as_float((u32)(ukey >> 32)), Dmax, est, cand, unseen);
+                bool pass = passes(unseen, est, Dmax);
+                if (A.pes != nullptr) screen_pes(id, est, ukey);
+                if (A.flags & PAG_SEARCH_DISTINCT) {
+                    const bool first = first_of_id(id, pass);
+                    pass = pass && first;
+                    cand = cand && first;
+                }
+                const u64 pmask = __ballot(pass);
+                s_tests += (u32)__popcll(__ballot(cand));
+                s_passes += (u32)__popcll(pmask);
+                admit(id, pmask);
+            }
+            end_round(qi);
+        }
+        write_results(qi);
+        if (n_spill) clear_bitmap();
+    }
+
+    // ---- several waves on one query (TEAM) ----
+    // With few queries the GPU waits for one hop after the other, and a single wave adds up the hop's trips to memory
+    // (record, rows two at a time, next record) and all of its bookkeeping, at one instruction per 4 to 10 clocks.  Here
+    // wave 0 keeps W and the rings, wave 1 the seen set, wave 2 (wave 1 too, in teams of less than six) computes the
+    // estimates, and the other waves fetch the rows.  A hop has two phases between barriers:
+    //   rows    every wave reads the node's neighbours, their estimates and the threshold from LDS and derives the
+    //           passers, whose rows are fetched all at once.  Meanwhile wave 0 finishes the last merge, wave 1 enters the
+    //           passers into the seen set, and the neighbours of W's closest unvisited member are screened ahead.  A
+    //           barrier inside the phase, while the rows are on their way, makes W's keys available to all: each wave
+    //           ranks its passers' keys against them as they are computed;
+    //   lists   wave 0 rebuilds W from the ranks and pops the next node.  Which node that will be is known before: the
+    //           closest passer, if it enters W and is closer than W's closest unvisited member, else that member, whose
+    //           neighbours are screened already; a passer's are screened now.  Only the threshold has to wait.
+    // Where a round has ended in between the node is another one, and it is screened in a phase of its own.
+    enum : u32 {
+        TM_QUERY = 0,                                  // query number, PAG_EMPTY: no more
+        TM_NODE, TM_NODE_DIST, TM_FAR_LO, TM_FAR_HI,   // wave 0: the node to expand (PAG_EMPTY: the search is over), W's farthest
+        TM_SECOND, TM_SECOND_DIST,                     // wave 0: W's closest unvisited member after that (PAG_EMPTY: none)
+        TM_COUNT,                                      // wave 0: members of W, whose keys lie in SA
+        TM_SCREENED,                                   // wave 1: the node whose neighbours are screened
+        TM_SPILLED,                                    // wave 1: the search has used its bitmap
+        TM_MIN = 16,                                   // u64: the smallest key of the hop's passers
+        TM_ID = 64,                                    // wave 1, per neighbour slot: id (PAG_EMPTY: not an unseen node)
+        TM_EST = 128,                                  // wave 2, per neighbour slot: estimate
+        TM_KEY = 192,                                  // u64: keys of the hop's passers, in slot order
+        TM_BEFORE = 320,                               // per passer: members of W that are closer
+        TM_CLOSER = 384                                // per member of W (NW <= 2): passers that are closer
+    };
+    static_assert(TM_CLOSER + 128 <= PAG_TEAM_WORDS, "team words");
+
+    // raw barrier: unlike __syncthreads() it leaves global loads in flight
+    __device__ __forceinline__ void team_barrier() const {
+        lds_sync();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+
+    // whether the estimates have a wave of their own
+    __device__ __forceinline__ bool split() const { return nwaves >= 6; }
+
+    __device__ __forceinline__ u32 team_index(u64 mask) const { return (u32)__popcll(mask & ((1ull << lane) - 1)); }
+    __device__ __forceinline__ u64* team_keys() const { return (u64*)(team + TM_KEY); }
+    __device__ __forceinline__ u64* team_min() const { return (u64*)(team + TM_MIN); }
+
+    // This wave's share of the rows of the lanes in `mask`, TR of them in flight at a time, and the inner barrier of the
+    // rows phase.  The rows of a wave are reduced together: one row alone is a chain of dependent instructions.
+    static constexpr int TR = NQ * (int)sizeof(Chunk) <= 48 ? 4 : (NQ * (int)sizeof(Chunk) <= 96 ? 2 : 1);
+
+    // keys of G rows (those with i < r exist), and their ranks against W's keys w
+    template <int G>
+    __device__ __forceinline__ void team_reduce(const Chunk (&v)[TR][NQ], const u32 (&id)[TR], const u64 (&w)[NW > 2 ? 1 : NW], u32 at, u32 step, u32 r) const {
+        double acc[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g] = lane_partial(v[g]);
+        const double tot = fold_sum<G>(acc);                // lanes g * 64 / G ...: the total of row g
+        u32 my_id = id[0], before = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const u32 bits = __float_as_uint((float)fold_total<G>(tot, g));
+            if (g > 0 && lane >= g * (64 / G)) my_id = id[g];
+            if constexpr (!BIG) {
+                if ((u32)g < r) {
+                    const u64 key = ((u64)bits << 32) | ((u64)id[g] << 1);
+                    u32 c = 0;
+#pragma unroll
+                    for (int s = 0; s < NW; ++s) {
+                        const bool lt = w[s] < key;
+                        c += (u32)__popcll(__ballot(lt));
+                        if (!lt) atomicAdd(&team[TM_CLOSER + s * 64 + lane], 1u);
+                    }
+                    if (lane >= g * (64 / G)) before = c;
+                }
+            }
+        }
+        const u32 g = (u32)lane / (64 / G);
+        if ((u32)lane % (64 / G) == 0 && g < r) {
+            const u64 key = ((u64)__float_as_uint((float)tot) << 32) | ((u64)my_id << 1);
+            team_keys()[at + g * step] = key;
+            team[TM_BEFORE + at + g * step] = before;
+            atomicMin((unsigned long long*)team_min(), (unsigned long long)key);
+        }
+    }
+
+    __device__ __forceinline__ void team_rows(u32 id_lane, u64 mask) const {
+        const u32 first = split() ? 3u : 2u;                // the first wave that fetches rows
+        const u32 n = (u32)__popcll(mask), step = (u32)nwaves - first;
+        const u32 mine = ((mask >> lane) & 1ull) ? team_index(mask) : PAG_EMPTY;
+        u32 at = (u32)wave - first;
+        u64 w[NW > 2 ? 1 : NW];
+        bool joined = false;
+        do {
+            Chunk v[TR][NQ];
+            u32 id[TR], r = 0;
+#pragma unroll
+            for (int g = 0; g < TR; ++g) {
+                id[g] = 0;
+                if (at + (u32)g * step < n) {
+                    id[g] = rdlane(id_lane, __ffsll((long long)__ballot(mine == at + (u32)g * step)) - 1);
+                    load_vec(v[g], id[g]);
+                    ++r;
+                }
+            }
+            if (!joined) {
+                team_barrier();
+                joined = true;
+                if constexpr (!BIG) {
+                    const u32 count = uniform(team[TM_COUNT]);
+#pragma unroll
+                    for (int s = 0; s < NW; ++s) w[s] = (u32)(s * 64 + lane) < count ? SA[s * 64 + lane] : PAG_KEY_INVALID;
+                }
+            }
+            if (TR >= 4 && r > 2) { if constexpr (TR >= 4) team_reduce<4>(v, id, w, at, step, r); }
+            else if (TR >= 2 && r > 1) { if constexpr (TR >= 2) team_reduce<2>(v, id, w, at, step, r); }
+            else if (r) team_reduce<1>(v, id, w, at, step, r);
+            at += TR * step;
+        } while (at < n);
+    }
+
+    // key of W's closest unvisited member, which stays unvisited
+    __device__ __forceinline__ u64 peek() {
+        if constexpr (BIG) {
+            if (!nx_known) nx_key = over_slots<false>(GU);
+            nx_known = true;
+            return nx_key;
+        } else {
+            u64 k = PAG_KEY_INVALID;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u64 m = __ballot((u32)(s * 64 + lane) < nW && !(W[s] & 1ull));
+                if (m && k == PAG_KEY_INVALID) k = rdlane64(W[s], __ffsll((long long)m) - 1);
+            }
+            return k;
+        }
+    }
+
+    // wave 0: what the other waves need to know of W
+    __device__ __forceinline__ void post(u64 node, u64 far, u64 second) const {
+        if (lane == 0) {
+            team[TM_NODE] = node != PAG_KEY_INVALID ? (u32)node >> 1 : PAG_EMPTY;
+            team[TM_NODE_DIST] = (u32)(node >> 32);
+            team[TM_FAR_LO] = (u32)far; team[TM_FAR_HI] = (u32)(far >> 32);
+            team[TM_SECOND] = second != PAG_KEY_INVALID ? (u32)second >> 1 : PAG_EMPTY;
+            team[TM_SECOND_DIST] = (u32)(second >> 32);
+            team[TM_COUNT] = nW;
+        }
+    }
+
+    // wave 0: pops the next node, through as many round ends as that takes, and posts it
+    __device__ __forceinline__ void post_next(u32 qi) {
+        u64 ukey = PAG_KEY_INVALID;
+        while (round < A.Rmax && nW != 0) {
+            ukey = pop();
+            if (ukey != PAG_KEY_INVALID) break;
+            end_round(qi);
+            round++;
+            if (round < A.Rmax && nW != 0) s_rounds++;
+            if constexpr (!BIG) {
+#pragma unroll
+                for (int s = 0; s < NW; ++s)
+                    if ((u32)(s * 64 + lane) < nW) SA[s * 64 + lane] = W[s];
+            }
+        }
+        post(ukey, farthest(), ukey != PAG_KEY_INVALID ? peek() : PAG_KEY_INVALID);
+    }
+
+    // wave 0, sorted W: a merge whose ranks against W are known (see team_rows), in two parts: W itself, ...
+    struct Merge {
+        u64 oldW[NW], pk;
+        u32 closer[NW], cP, rP, nW, n_ins, np;
+        bool pass;
+    };
+    __device__ __forceinline__ void merge_w(Merge& M, u64 mask, u32 np, bool pass) {
+        const u32 b = A.b, mine = team_index(mask);
+        M.np = np; M.pass = pass; M.nW = nW;
+        // all of LDS that is needed, asked for at once (lanes without a passer read what is not theirs)
+        const u32 x = (u32)lane >> 3, y = (u32)lane & 7u, at = mine & 63u;
+        const u64 pk = team_keys()[at], kx = team_keys()[x], ky = team_keys()[y];
+        const u32 before = team[TM_BEFORE + at];
+#pragma unroll
+        for (int s = 0; s < NW; ++s) M.closer[s] = team[TM_CLOSER + s * 64 + lane];
+#pragma unroll
+        for (int s = 0; s < NW; ++s) M.oldW[s] = W[s];
+        M.pk = pk;
+        // ranks among the passers: lane 8 x + y compares passers x and y of two groups of eight
+        u32 cP = (u32)__popcll((__ballot(x < np && y < np && kx < ky) >> (mine & 7u)) & 0x0101010101010101ull);
+        if (np > 8) {
+            cP = 0;
+            for (u32 i = 0; i < np; i += 8) {
+                const u64 a = i + x < np ? team_keys()[i + x] : PAG_KEY_INVALID;
+                for (u32 j = 0; j < np; j += 8) {
+                    const u64 lt = __ballot(a < (j + y < np ? team_keys()[j + y] : PAG_KEY_INVALID));
+                    if ((mine & ~7u) == j) cP += (u32)__popcll((lt >> (mine & 7u)) & 0x0101010101010101ull);
+                }
+            }
+        }
+        M.cP = cP; M.rP = cP + before;
+        M.n_ins = (u32)__popcll(__ballot(pass && M.rP < b));
+#pragma unroll
+        for (int s = 0; s < NW; ++s) {
+            const u32 idx = s * 64 + lane, r = idx + M.closer[s];
+            if (idx < nW && r < b) SA[r] = W[s];
+        }
+        if (pass && M.rP < b) SA[M.rP] = M.pk;
+        nW = nW + np < b ? nW + np : b;
+        lds_sync();
+#pragma unroll
+        for (int s = 0; s < NW; ++s) W[s] = (u32)(s * 64 + lane) < nW ? SA[s * 64 + lane] : PAG_KEY_INVALID;
+    }
+    // ... and what it pushes to the rings
+    __device__ __forceinline__ void merge_rings(const Merge& M) {
+        const u32 b = A.b;
+        const u32 n_f = M.np - M.n_ins;                            // false positives -> R_F
+        const u32 n_ej = M.nW + M.n_ins - nW;                      // displaced members -> R_T
+        if (n_ej) {
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 idx = s * 64 + lane;
+                if (idx < M.nW && idx + M.closer[s] >= b) RT[(hdT + (M.nW - 1 - idx)) & A.ring_mask] = M.oldW[s];   // largest first
+            }
+            if (cntT + n_ej > b) s_rt += cntT + n_ej - b;
+            cntT = cntT + n_ej < b ? cntT + n_ej : b;
+            hdT += n_ej;
+        }
+        if (n_f) {
+            if (M.pass && M.rP >= b) {
+                const u32 oi = M.cP - M.n_ins;                      // smallest first
+                if (oi + b >= n_f) RF[(hdF + oi) & A.ring_mask] = M.pk;  // older ones would be overwritten anyway
+            }
+            if (cntF + n_f > b) s_rf += cntF + n_f - b;
+            cntF = cntF + n_f < b ? cntF + n_f : b;
+            hdF += n_f;
+        }
+    }
+
+    // wave 0: the words that a hop's keys are counted in
+    __device__ __forceinline__ void clear_counts() const {
+#pragma unroll
+        for (int s = 0; s < (BIG ? 0 : NW); ++s) team[TM_CLOSER + s * 64 + lane] = 0u;
+        if (lane == 0) *team_min() = PAG_KEY_INVALID;
+    }
+
+    // which of a node's neighbours (in pf_id) are unseen
+    __device__ __forceinline__ bool find_unseen() const {
+        const u32 id = pf_id;
+        bool cand = id != PAG_EMPTY && id < A.n_limit;
+        u32 word = 0;
+        if (A.blog != 0) {
+            // the second level is consulted for every neighbour that the first does not know: the estimates, which
+            // could spare some, are computed by another wave meanwhile
+            cand = cand && H[hash_slot(id, A.hlog)] != id;
+            if (cand && bloom_maybe(BL, A.blog, id))
+                word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            if (cand) cand = !hash_contains(H, A.hlog, id);
+            if (n_spill && cand) word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return cand && !((word >> (id & 31)) & 1u);
+    }
+
+    // sum_l T[l][code_l] of a node's neighbours (in pf_cw)
+    __device__ __forceinline__ float code_sum() const {
+        if (A.flags & PAG_FLAG_NO_PRT) return 0.f;
+        if (A.cw == 2) return table_sum<2>(t_base, pf_cw);
+        if (A.cw == 4) return table_sum<4, CW, 32>(t_base, pf_cw);
+        return table_sum<8, CW, 32>(t_base, pf_cw);
+    }
+
+    // The screening of node u's neighbours; SEEN and EST: which half of it this wave does.  What it needs of u's record is
+    // kept in the prefetch registers (nx_id: whose), the sums with it.
+    template <bool SEEN, bool EST>
+    __device__ __forceinline__ void fetch_screen(u32 u) {
+        if (u == nx_id) return;
+        nx_id = u;
+        if constexpr (SEEN) pf_id = load_id(u);
+        if constexpr (EST) { load_edges(u, pf_a, pf_c, pf_cw); pf_summed = false; }
+    }
+    __device__ __forceinline__ void sum_codes() {
+        if (!pf_summed) pf_sum = code_sum();
+        pf_summed = true;
+    }
+    template <bool SEEN, bool EST>
+    __device__ __forceinline__ void screen_node(u32 u, float Du, bool looked_up, bool unseen) {
+        fetch_screen<SEEN, EST>(u);
+        if constexpr (SEEN) {
+            if (!looked_up) unseen = find_unseen();
+            scr_id = pf_id;
+            team[TM_ID + lane] = unseen ? pf_id : PAG_EMPTY;
+        }
+        if constexpr (EST) {
+            sum_codes();
+            team[TM_EST + lane] = __float_as_uint(__builtin_fmaf(-2.0f * pf_a, pf_sum, Du + pf_c));
+        }
+    }
+
+    // One wave of the workgroup: queries until the batch is drained.  Each role is compiled by itself, so that the
+    // registers hold what that role needs.
+    enum Role { LISTS, SEEN, ESTIMATES, SCREEN, ROWS };       // SCREEN: SEEN and ESTIMATES in one wave
+    template <Role ROLE>
+    __device__ __forceinline__ void run_team() {
+        constexpr bool KEEPS_SEEN = ROLE == SEEN || ROLE == SCREEN, ESTIMATE = ROLE == ESTIMATES || ROLE == SCREEN;
+        for (;;) {
+            if constexpr (ROLE == LISTS) {
+                u32 qi = 0;
+                if (lane == 0) qi = atomicAdd(A.qcounter, 1u);
+                qi = uniform(qi);
+                if (qi >= A.nq) qi = PAG_EMPTY;
+                else if (A.order) qi = A.order[qi];
+                if (lane == 0) { team[TM_QUERY] = qi; team[TM_COUNT] = 0u; }
+            }
+            team_barrier();
+            const u32 qi = uniform(team[TM_QUERY]);
+            if (qi == PAG_EMPTY) break;
+            begin_query(qi);
+            reset_lists();
+            team_barrier();
+            if constexpr (ROLE == LISTS) s_queries++;
+            // ---- b entry nodes ----
+            const u32 ne = A.n_entry < A.b ? A.n_entry : A.b;
+            for (u32 base = 0; base < ne; base += 64) {
+                const u32 id = entry_node(base, ne);
+                const bool pass = id != PAG_EMPTY;
+                const u64 mask = __ballot(pass);
+                if (mask == 0ull) continue;
+                if constexpr (ROLE == ROWS) team_rows(id, mask);
+                else team_barrier();
+                if constexpr (KEEPS_SEEN) mark_seen(id, (u32)__popcll(mask), pass);
+                team_barrier();
+                if constexpr (ROLE == LISTS)
+                    merge(id, mask, (u32)__popcll(mask), pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
+                team_barrier();
+            }
+            if constexpr (ROLE == LISTS) {
+                if (nW != 0) s_rounds++;
+                post_next(qi);
+                clear_counts();
+            }
+            if (KEEPS_SEEN && lane == 0) team[TM_SCREENED] = PAG_EMPTY;
+            team_barrier();
+            // ---- hops ----
+            bool owed = false;                         // wave 0: a merge whose ring pushes are outstanding
+            Merge M;
+            for (;;) {
+                PAG_MARK(0);
+                const u32 u = uniform(team[TM_NODE]);
+                if (u == PAG_EMPTY) break;
+                const u32 du = uniform(team[TM_NODE_DIST]);
+                const u64 far = ((u64)uniform(team[TM_FAR_HI]) << 32) | uniform(team[TM_FAR_LO]);
+                const u32 second = uniform(team[TM_SECOND]), second_d = uniform(team[TM_SECOND_DIST]);
+                // TM_SCREENED stays as it is until all waves have read it: it is written again after the rows
+                if (uniform(team[TM_SCREENED]) != u) {
+                    if constexpr (KEEPS_SEEN || ESTIMATE) screen_node<KEEPS_SEEN, ESTIMATE>(u, __uint_as_float(du), false, false);
+                    team_barrier();
+                }
+                const u32 id = team[TM_ID + lane];
+                const float est = __uint_as_float(team[TM_EST + lane]);
+                bool pass = passes(id != PAG_EMPTY, est, threshold(far));
+                if (A.flags & PAG_SEARCH_DISTINCT) { const bool first = first_of_id(id, pass); pass = pass && first; }
+                const u64 mask = __ballot(pass);
+                const u32 np = (u32)__popcll(mask);
+                PAG_MARK(2);
+                bool unseen = false;                   // of the neighbours of `second`
+                if constexpr (ROLE == ROWS) {
+                    team_rows(id, mask);
+                } else {
+                    if constexpr (KEEPS_SEEN) {
+                        if (A.pes != nullptr) screen_pes(scr_id, est, ((u64)du << 32) | ((u64)u << 1));
+                    }
+                    if constexpr (KEEPS_SEEN || ESTIMATE) {
+                        if (second != PAG_EMPTY) fetch_screen<KEEPS_SEEN, ESTIMATE>(second);
+                    }
+                    team_barrier();
+                    if constexpr (ROLE == LISTS) {
+                        if (owed) merge_rings(M);
+                    }
+                    if constexpr (KEEPS_SEEN) {
+                        s_tests += (u32)__popcll(__ballot(id != PAG_EMPTY));
+                        s_passes += np;
+                        if (np) mark_seen(id, np, pass);
+                        if (second != PAG_EMPTY) unseen = find_unseen();
+                    }
+                    if constexpr (ESTIMATE) {
+                        if (second != PAG_EMPTY) sum_codes();
+                    }
+                }
+                PAG_MARK(1);
+                team_barrier();
+                PAG_MARK(3);
+                if constexpr (ROLE == LISTS) {
+                    s_exact += np;
+                    if constexpr (BIG) {
+                        owed = false;
+                        if (np) merge_unsorted(id, mask, np, pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
+                        post_next(qi);
+                    } else {
+                        owed = np != 0;
+                        if (np) merge_w(M, mask, np, pass);
+                        const u64 next = pop();
+                        if (next != PAG_KEY_INVALID) {
+                            post(next, farthest(), peek());
+                        } else {
+                            if (owed) merge_rings(M);
+                            owed = false;
+                            post_next(qi);
+                        }
+                    }
+                }
+                if constexpr (KEEPS_SEEN || ESTIMATE) {
+                    const u64 first = *team_min();     // of the passers; PAG_KEY_INVALID: none
+                    const u64 next2 = second != PAG_EMPTY ? ((u64)second_d << 32) | ((u64)second << 1) : PAG_KEY_INVALID;
+                    const bool passer = __ballot(first < far && first < next2) != 0ull;
+                    const u64 next = passer ? first : next2;
+                    const u32 node = uniform(next != PAG_KEY_INVALID ? (u32)next >> 1 : PAG_EMPTY);
+                    if (KEEPS_SEEN && lane == 0) team[TM_SCREENED] = node;
+                    if (node != PAG_EMPTY) screen_node<KEEPS_SEEN, ESTIMATE>(node, __uint_as_float((u32)(next >> 32)), !passer, unseen);
+                }
+                PAG_MARK(4);
+                team_barrier();
+                if constexpr (ROLE == LISTS) clear_counts();
+            }
+            if constexpr (ROLE == LISTS || KEEPS_SEEN) write_results(qi);
+            if constexpr (KEEPS_SEEN) {
+                if (n_spill) __threadfence();        // its bit-sets have landed before others clear
+                if (lane == 0) team[TM_SPILLED] = n_spill ? 1u : 0u;
+            }
+            team_barrier();
+            if (uniform(team[TM_SPILLED])) clear_bitmap();
         }
     }
 
@@ -1074,7 +1638,32 @@ __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
     w.flush_stats();
 }
 
+// The same with several waves per query, for batches that would leave the GPU mostly idle.
+template <int NQ, int NW, int VM>
+__attribute__((amdgpu_waves_per_eu(NQ <= 6 && NW <= 2 ? 4 : 2, 8)))
+__global__ void __launch_bounds__(64 * pag_team_max(NW)) k_search_team(const SearchArgs A) {
+    extern __shared__ __align__(64) unsigned char smem[];
+    Wave<NQ, NW, VM, PAG_MAX_CW, true> w(A, smem, (int)(threadIdx.x & 63), (int)uniform(threadIdx.x >> 6), (int)(blockDim.x >> 6));
+    typedef decltype(w) Wv;
+    if (w.wave == 0) {
+        w.template run_team<Wv::LISTS>();
+        w.flush_stats();
+    } else if (w.wave == 1) {
+        if (w.split()) w.template run_team<Wv::SEEN>();
+        else w.template run_team<Wv::SCREEN>();
+        w.flush_stats();
+    } else if (w.wave == 2 && w.split()) {
+        w.template run_team<Wv::ESTIMATES>();
+    } else {
+        w.template run_team<Wv::ROWS>();
+    }
+}
+
 }  // namespace pagk
+
+// Which ways of reading the store occur with NQ chunks per lane: 16-bit rows are read in 8-byte chunks where their number
+// of 256-element chunk rows is odd, else in 16-byte chunks of 512 elements, of which 3,072 elements need six.
+constexpr bool pag_search_reached(int nq, int vm) { return vm == 0 || (vm == 1 ? nq <= 6 : nq != 2 && nq != 4); }
 
 // One translation unit per (NQ, CW) defines the selector below: the kernels for every number of
 // W / R_L entries per lane (working sets of up to 64, 128, 256, 512, 1024 nodes) and the three ways of reading the store.
@@ -1092,5 +1681,27 @@ typedef void (*pag_search_fn)(const SearchArgs);
         }                                                                                             \
     }                                                                                                 \
     pag_search_fn pag_search_fn_nq##NQ##_cw##CW(int nw, int vm) {                                     \
-        return vm == 0 ? pag_search_by_nw<0>(nw) : (vm == 1 ? pag_search_by_nw<1>(nw) : pag_search_by_nw<2>(nw)); \
+        if (vm == 0) return pag_search_by_nw<0>(nw);                                                  \
+        if constexpr (pag_search_reached(NQ, 1)) { if (vm == 1) return pag_search_by_nw<1>(nw); }     \
+        if constexpr (pag_search_reached(NQ, 2)) { if (vm == 2) return pag_search_by_nw<2>(nw); }     \
+        return nullptr;                                                                               \
+    }
+// the same for the kernels with several waves per query (one translation unit per NQ)
+#define PAG_SEARCH_TEAM_INSTANCES(NQ)                                                                 \
+    template <int VM>                                                                                 \
+    static pag_search_fn pag_search_by_nw(int nw) {                                                   \
+        switch (nw) {                                                                                 \
+            case 1: return (pag_search_fn)pagk::k_search_team<NQ, 1, VM>;                             \
+            case 2: return (pag_search_fn)pagk::k_search_team<NQ, 2, VM>;                             \
+            case 4: return (pag_search_fn)pagk::k_search_team<NQ, 4, VM>;                             \
+            case 8: return (pag_search_fn)pagk::k_search_team<NQ, 8, VM>;                             \
+            case 16: return (pag_search_fn)pagk::k_search_team<NQ, 16, VM>;                           \
+            default: return nullptr;                                                                  \
+        }                                                                                             \
+    }                                                                                                 \
+    pag_search_fn pag_search_team_fn_nq##NQ(int nw, int vm) {                                         \
+        if (vm == 0) return pag_search_by_nw<0>(nw);                                                  \
+        if constexpr (pag_search_reached(NQ, 1)) { if (vm == 1) return pag_search_by_nw<1>(nw); }     \
+        if constexpr (pag_search_reached(NQ, 2)) { if (vm == 2) return pag_search_by_nw<2>(nw); }     \
+        return nullptr;                                                                               \
     }
