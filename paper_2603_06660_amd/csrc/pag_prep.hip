@@ -16,84 +16,136 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------------
 // Rotation: OUT[i][j] = fl32( sum_k X[i][k] * R[j][k] ),  X [rows x d], R [d x d] row-major.
-// The one dense contraction of the path: fp64 MFMA (v_mfma_f64_16x16x4), 64 x 64 output tile
-// per workgroup of 4 waves, each wave a 32 x 32 sub-tile (2 x 2 MFMA tiles), K staged through
-// LDS in steps of 32 as doubles.  Rows of the LDS tiles are padded to 36 doubles (72 dwords,
-// = 8 mod 64 banks) so that the 16 rows x 4 k-columns read by one MFMA operand fetch spread
-// over all banks.
+// The one dense contraction of the path: fp64 MFMA (v_mfma_f64_16x16x4).  A workgroup of four waves computes
+// 16 NT x 16 NT outputs; the waves share out the k range in chunks of 16 and add their partial sums through LDS at the end.
+// An operand wants row (lane % 16) and k (lane / 16) from each lane; which four k's make up one MFMA does not
+// matter as long as both operands agree, so a lane reads 16 consecutive bytes of its row and feeds their four elements to
+// four MFMAs: operands go from memory to registers without LDS or barriers, and the next chunk's are on their way while
+// one is multiplied.
+// Large batches are bound by the matrix cores (0.6 of the fp64 rate of a large product), small ones by the length of the
+// k loop, which the four waves cut to a quarter.
 // ---------------------------------------------------------------------------------------
-constexpr int BM = 64, BN = 64, KT = 32, LDT = 36;
-
+template <int NT>
 __global__ void __launch_bounds__(256) k_rotate(const float* __restrict__ X, u64 rows, u32 d,
                                                 const float* __restrict__ R, float* __restrict__ OUT) {
-    __shared__ double As[BM][LDT];
-    __shared__ double Bs[BN][LDT];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int wm = w >> 1, wn = w & 1;
-    const u64 m0 = (u64)blockIdx.y * BM;
-    const u32 n0 = blockIdx.x * BN;
-    double4_t acc[2][2];
+    __shared__ double part[2][NT * NT * 4 * 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const u64 m0 = (u64)blockIdx.y * (16 * NT);
+    const u32 n0 = blockIdx.x * (16 * NT);
+    const u32 k_lane = 4u * ((u32)lane >> 4);
+    const float* xp[NT];
+    const float* rp[NT];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NT; ++i) {
+        const u64 row = m0 + 16 * i + (lane & 15);
+        xp[i] = X + (row < rows ? row : rows - 1) * d;      // rows and columns past the end are computed and dropped
+    }
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (double4_t){0.0, 0.0, 0.0, 0.0};
-
-    for (u32 k0 = 0; k0 < d; k0 += KT) {
+    for (int j = 0; j < NT; ++j) {
+        const u32 col = n0 + 16 * j + (lane & 15);
+        rp[j] = R + (u64)(col < d ? col : d - 1) * d;
+    }
+    double4_t acc[NT][NT];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int idx = t + 256 * i, row = idx >> 3, k4 = (idx & 7) * 4;
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), bb = a;
-            if (m0 + row < rows && k0 + k4 < d) a = *(const float4*)(X + (m0 + row) * d + k0 + k4);
-            if (n0 + row < d && k0 + k4 < d) bb = *(const float4*)(R + (u64)(n0 + row) * d + k0 + k4);
-            As[row][k4 + 0] = (double)a.x; As[row][k4 + 1] = (double)a.y;
-            As[row][k4 + 2] = (double)a.z; As[row][k4 + 3] = (double)a.w;
-            Bs[row][k4 + 0] = (double)bb.x; Bs[row][k4 + 1] = (double)bb.y;
-            Bs[row][k4 + 2] = (double)bb.z; Bs[row][k4 + 3] = (double)bb.w;
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = (double4_t){0.0, 0.0, 0.0, 0.0};
+    float4 a[NT], b[NT];
+    auto load = [&](u32 k0) {
+        const u32 k = k0 + k_lane;                           // d is a multiple of four: 16 bytes lie inside or outside
+        const bool in = k < d;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) a[i] = in ? *(const float4*)(xp[i] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[j] = in ? *(const float4*)(rp[j] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    load(16u * w);
+    for (u32 k0 = 16u * w; k0 < d; k0 += 64) {
+        float4 ca[NT], cb[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) ca[i] = a[i];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) cb[j] = b[j];
+        if (k0 + 64 < d) load(k0 + 64);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            double av[NT], bv[NT];
+#pragma unroll
+            for (int i = 0; i < NT; ++i) av[i] = (double)(e == 0 ? ca[i].x : e == 1 ? ca[i].y : e == 2 ? ca[i].z : ca[i].w);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) bv[j] = (double)(e == 0 ? cb[j].x : e == 1 ? cb[j].y : e == 2 ? cb[j].z : cb[j].w);
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
+        }
+    }
+    // waves 2, 3 -> 0, 1, then 1 -> 0
+#pragma unroll
+    for (int step = 2; step > 0; step >>= 1) {
+        if (w >= step && w < 2 * step) {
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) part[w - step][((i * NT + j) * 4 + r) * 64 + lane] = acc[i][j][r];
         }
         __syncthreads();
+        if (w < step) {
 #pragma unroll
-        for (int kk = 0; kk < KT; kk += 4) {
-            const int r = lane & 15, kq = kk + (lane >> 4);
-            const double a0 = As[wm * 32 + r][kq], a1 = As[wm * 32 + 16 + r][kq];
-            const double b0 = Bs[wn * 32 + r][kq], b1 = Bs[wn * 32 + 16 + r][kq];
-            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[i][j][r] += part[w][((i * NT + j) * 4 + r) * 64 + lane];
         }
         __syncthreads();
     }
+    if (w != 0) return;
     // accumulator layout of the 16x16 f64 tile: register r of lane l holds row l/16 + 4*r, column l%16
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const u64 row = m0 + wm * 32 + i * 16 + (lane >> 4) + 4 * r;
-                const u32 col = n0 + wn * 32 + j * 16 + (lane & 15);
+                const u64 row = m0 + i * 16 + (lane >> 4) + 4 * r;
+                const u32 col = n0 + j * 16 + (lane & 15);
                 if (row < rows && col < d) OUT[row * d + col] = (float)acc[i][j][r];
             }
 }
 
 // tables[row][l][j] = fl32( sum_k r_jl[k] * q_l[k] ), k ascending; rows l >= P are zero padding.
+// A thread keeps one reference vector r_jl in registers and takes `per` rows with it: the codebook, whose vectors lie
+// side by side in a wave, is read once per workgroup and not once per query (10,000 x 32 tables of 32-element subspaces:
+// 318 us when every thread fetched its vector for one product).  DS: elements held at a time.
+template <u32 DS>
 __global__ void __launch_bounds__(256) k_tables(const float* __restrict__ qrot, u64 rows, u32 d, u32 P,
-                                                u32 Ppad, u32 dsub, const float* __restrict__ cb,
+                                                u32 Ppad, u32 dsub, const float* __restrict__ cb, u32 per,
                                                 float* __restrict__ tables) {
-    const u64 gid = (u64)blockIdx.x * 256 + threadIdx.x;
-    const u64 per_row = (u64)Ppad * PAG_NCODE;
-    if (gid >= rows * per_row) return;
-    const u64 row = gid / per_row;
-    const u32 lj = (u32)(gid % per_row), l = lj / PAG_NCODE;
-    float out = 0.f;
-    if (l < P) {
-        const float* r = cb + (u64)lj * dsub;
-        const float* q = qrot + row * d + (u64)l * dsub;
+    const u32 lj = blockIdx.x * 256 + threadIdx.x, l = lj / PAG_NCODE;      // Ppad * 16 is a multiple of 256
+    const u64 row0 = (u64)blockIdx.y * per, row1 = row0 + per < rows ? row0 + per : rows;
+    const bool real = l < P;
+    const float* r = cb + (u64)(real ? lj : 0u) * dsub;
+    float rv[DS];
+#pragma unroll
+    for (u32 k = 0; k < DS; ++k) rv[k] = k < dsub ? r[k] : 0.f;
+    for (u64 row = row0; row < row1; ++row) {
+        const float* q = qrot + row * d + (u64)(real ? l : 0u) * dsub;
         double acc = 0.0;
-        for (u32 k = 0; k < dsub; ++k) acc = __builtin_fma((double)r[k], (double)q[k], acc);
-        out = (float)acc;
+        if (dsub <= DS) {
+            float qv[DS];
+#pragma unroll
+            for (u32 k = 0; k < DS; ++k) qv[k] = k < dsub ? q[k] : 0.f;
+#pragma unroll
+            for (u32 k = 0; k < DS; ++k)
+                if (k < dsub) acc = __builtin_fma((double)rv[k], (double)qv[k], acc);
+        } else {
+            for (u32 k = 0; k < dsub; ++k) acc = __builtin_fma((double)r[k], (double)q[k], acc);
+        }
+        tables[row * Ppad * PAG_NCODE + lj] = real ? (float)acc : 0.f;
     }
-    tables[gid] = out;
 }
 
 // out = x / ||x||, one wave per row; norm from an fp64 sum of squares.
@@ -324,18 +376,28 @@ int pag_order_queries(pag_index* ix, const float* qrot, u64 nq, const u32** orde
     return PAG_OK;
 }
 
-int pag_launch_rotate(hipStream_t s, const float* X, u64 rows, u32 d, const float* rot, float* out) {
-    if (rows == 0) return PAG_OK;
-    const u64 by = (rows + BM - 1) / BM;
+template <int NT>
+static void launch_rotate(hipStream_t s, const float* X, u64 rows, u32 d, const float* rot, float* out) {
+    const u64 by = (rows + 16 * NT - 1) / (16 * NT);
     // gridDim.y is limited to 65535: walk the rows in slabs
     const u64 slab = 65535ull;
     for (u64 y0 = 0; y0 < by; y0 += slab) {
         const u64 ny = by - y0 < slab ? by - y0 : slab;
-        const u64 r0 = y0 * BM;
-        const u64 nrows = rows - r0 < ny * BM ? rows - r0 : ny * BM;
-        dim3 grid((d + BN - 1) / BN, (unsigned)ny);
-        hipLaunchKernelGGL(k_rotate, grid, dim3(256), 0, s, X + r0 * d, nrows, d, rot, out + r0 * d);
+        const u64 r0 = y0 * 16 * NT;
+        const u64 nrows = rows - r0 < ny * 16 * NT ? rows - r0 : ny * 16 * NT;
+        dim3 grid((d + 16 * NT - 1) / (16 * NT), (unsigned)ny);
+        hipLaunchKernelGGL(k_rotate<NT>, grid, dim3(256), 0, s, X + r0 * d, nrows, d, rot, out + r0 * d);
     }
+}
+
+int pag_launch_rotate(hipStream_t s, const float* X, u64 rows, u32 d, const float* rot, float* out) {
+    if (rows == 0) return PAG_OK;
+    // 32 x 32 outputs per workgroup if that gives every CU (256) one, else 16 x 16.  Larger tiles read less from L2 but
+    // leave fewer waves to cover the loads (10,000 x 1024: 64 x 64 530 us, 32 x 32 440 us; staged through LDS 490 us).
+    // One row of 768 takes 6 us (45 us as a loop over LDS tiles), 250 rows of 3072 120 us (330 us).
+    const u64 blocks = ((rows + 31) / 32) * ((d + 31) / 32);
+    if (blocks >= 256) launch_rotate<2>(s, X, rows, d, rot, out);
+    else launch_rotate<1>(s, X, rows, d, rot, out);
     PAG_HIP(hipGetLastError());
     return PAG_OK;
 }
@@ -343,9 +405,19 @@ int pag_launch_rotate(hipStream_t s, const float* X, u64 rows, u32 d, const floa
 int pag_launch_tables(hipStream_t s, const float* qrot, u64 rows, const pag_layout& L, const float* cb,
                       float* tables) {
     if (rows == 0) return PAG_OK;
-    const u64 total = rows * L.Ppad * PAG_NCODE;
-    hipLaunchKernelGGL(k_tables, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, qrot, rows, L.d, L.P,
-                       L.Ppad, L.dsub, cb, tables);
+    // enough workgroups for eight on every CU before a thread takes a second row; at most 32 rows
+    const u32 bx = L.Ppad * PAG_NCODE / 256;
+    const u32 per = (u32)std::min<u64>(32, std::max<u64>(1, rows * bx / 2048));
+    const u64 slab = 65535ull * per;                         // gridDim.y is limited to 65535
+    for (u64 r0 = 0; r0 < rows; r0 += slab) {
+        const u64 n = rows - r0 < slab ? rows - r0 : slab;
+        const dim3 grid(bx, (unsigned)((n + per - 1) / per));
+        const float* q = qrot + r0 * L.d;
+        float* t = tables + r0 * L.Ppad * PAG_NCODE;
+        if (L.dsub <= 16) hipLaunchKernelGGL(k_tables<16>, grid, dim3(256), 0, s, q, n, L.d, L.P, L.Ppad, L.dsub, cb, per, t);
+        else if (L.dsub <= 32) hipLaunchKernelGGL(k_tables<32>, grid, dim3(256), 0, s, q, n, L.d, L.P, L.Ppad, L.dsub, cb, per, t);
+        else hipLaunchKernelGGL(k_tables<48>, grid, dim3(256), 0, s, q, n, L.d, L.P, L.Ppad, L.dsub, cb, per, t);
+    }
     PAG_HIP(hipGetLastError());
     return PAG_OK;
 }
