@@ -365,6 +365,24 @@ static int launch_prune(hipStream_t s, const pag_index* ix, const u32* nodes, u3
     return PAG_OK;
 }
 
+// distances between the vector staged in LDS and the next four of the neighbours in `mask` (ids in id_lane), which are
+// taken out of it; their rows are in flight together.  Lane s receives neighbour s's.
+__device__ __forceinline__ void neighbour_distances(const pag_vecs& V, u32 d, const float* s, u32 id_lane, u64& mask, float& out) {
+    u32 w[4];
+    int at[4];
+    float dd[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        at[g] = mask ? __ffsll((long long)mask) - 1 : at[g > 0 ? g - 1 : 0];   // the last one again where there is none left
+        mask &= mask - 1;
+        w[g] = (u32)__builtin_amdgcn_readlane((int)id_lane, at[g]);
+    }
+    dist_lds4(V, d, s, w, dd);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        if ((int)threadIdx.x == at[g]) out = dd[g];
+}
+
 // ---- reverse edges, one wave per target (Sec. 2.1, N_in(v); Eq. 1) ----
 // Sorted pairs (target << 32 | dist bits, source).  The wave whose pair starts a target's segment
 // walks the segment.  For an incoming v at squared distance duv:
@@ -374,6 +392,8 @@ static int launch_prune(hipStream_t s, const pag_index* ix, const u32* nodes, u3
 // Pairs that come from the PES buffers H(v) (flag in bit 31 of the distance word) pass the same
 // Eq. 1 check but are only ever given a free slot.
 // Every slot that received a new neighbour is appended to `edges` for the inference-information pass.
+// Bound by the rows it fetches: they are asked for four at a time, those that can occlude v first, the others only where
+// a full list has to give one up.
 __global__ void __launch_bounds__(64) k_reverse(pag_vecs vec, uint8_t* __restrict__ recs,
                                                 float* __restrict__ e2, pag_layout L,
                                                 const u64* __restrict__ keys, const u32* __restrict__ vals,
@@ -402,20 +422,20 @@ __global__ void __launch_bounds__(64) k_reverse(pag_vecs vec, uint8_t* __restric
         if (v == u || __ballot(valid && id == v)) continue;
         // PES candidates are only added to available out-degree slots (Alg. 1, last loop)
         if (from_pes && __ballot((u32)lane < L.deg && id == PAG_EMPTY) == 0ull) continue;
+        __syncthreads();                                      // the last pair's reads of sv are done
         stage(vec, L.d, v, sv, lane);
         __syncthreads();
-        // lane s gets ||w_s - v||^2
-        float dwv = 0.f;
-        for (u64 mm = __ballot(valid); mm;) {
-            const int p = __ffsll((long long)mm) - 1;
-            mm &= mm - 1;
-            const u32 w = (u32)__builtin_amdgcn_readlane((int)id, p);
-            const float dd = dist_lds(vec, L.d, sv, w, lane);
-            if (lane == p) dwv = dd;
+        float dwv = 0.f;                                      // lane s: ||w_s - v||^2, as far as it is needed
+        // neighbours no farther from u than v is, until one occludes v (Eq. 1)
+        bool occluded = false;
+        for (u64 mm = __ballot(valid && we2 <= duv); mm && !occluded;) {
+            neighbour_distances(vec, L.d, sv, id, mm, dwv);
+            occluded = __ballot(valid && we2 <= duv && dwv <= duv && !((mm >> lane) & 1ull)) != 0ull;
         }
-        __syncthreads();
-        if (__ballot(valid && we2 <= duv && dwv <= duv)) continue;                 // Eq. 1: v is occluded
+        if (occluded) continue;
         const u64 freem = __ballot((u32)lane < L.deg && id == PAG_EMPTY);
+        if (!freem)                                           // the others, which v may occlude
+            for (u64 mm = __ballot(valid && we2 > duv); mm;) neighbour_distances(vec, L.d, sv, id, mm, dwv);
         int slot = -1;
         if (freem) {
             slot = __ffsll((long long)freem) - 1;
@@ -675,7 +695,8 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
     // the rows of a batch, gathered (its queries), and their tables
     if ((rc = ensure_floats(&ix->ws_qrot, &ix->ws_qrot_cap, max_batch * L.d))) return rc;
     if ((rc = ensure_floats(&ix->ws_tab, &ix->ws_tab_cap, max_batch * L.Ppad * PAG_NCODE))) return rc;
-    constexpr u32 kDensitySamples = 128, kDensityProbes = 2048;
+    // 32 waves share the probes of a sample: a wave waits for its rows, two of each kind at a time (with 8 waves: 358 us a batch)
+    constexpr u32 kDensitySamples = 128, kDensityProbes = 2048, kDensityWaves = 32;
     constexpr double kCrowdedRatio = 4.0;
     PAG_ALLOC(ws.density, kDensitySamples * 2 * 4);
     // one linking pass over `m` listed nodes: search, RobustPrune, reverse edges, inference information
@@ -739,7 +760,7 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
         if (m >= 64 && graph >= 64) {
             const u32 ns = kDensitySamples, np = (u32)std::min<u64>(std::min<u64>(m, graph), kDensityProbes);
             if ((rc = pag_launch_zero_u32(s, ws.density, 2 * ns))) return rc;
-            hipLaunchKernelGGL(k_batch_density, dim3(ns, 8), dim3(64), L.d * 4, s, pag_vecs_of(ix), ix->rec, ix->e2, L, ws.order, n_begin,
+            hipLaunchKernelGGL(k_batch_density, dim3(ns, kDensityWaves), dim3(64), L.d * 4, s, pag_vecs_of(ix), ix->rec, ix->e2, L, ws.order, n_begin,
                                done - m, (u32)m, ns, np, ws.density);
             PAG_HIP(hipGetLastError());
             u32 h[kDensitySamples * 2];
