@@ -625,8 +625,9 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
 //   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
 //     query 375 -> 242, 491 -> 271, 777 -> 414
 //   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
-//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455).  Working sets above 128
-//     nodes gain with the four waves that fit, too (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
+//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
+//     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
+//     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
 //   up to four per CU: 4 waves, if the rows come from HBM and not from the 256 MB cache: 1M x 768, efS 256, 1,000 queries
 //     1796 -> 1608 us, 200k x 1536, efS 768, 777 queries 5868 -> 5288.  Within the cache the instructions that a team
 //     adds cost more than the shorter wait saves (100k x 128, 800 queries: 534 -> 557)
@@ -637,7 +638,7 @@ static int plan_team(const pag_index* ix, u64 nq, u32 b, u32 ef, SearchArgs* a, 
     if (nq <= cus) {
         share = 1; most = 12; least = 4;
     } else if (nq <= 2 * cus) {
-        share = 2; most = 8; least = large_set ? 4 : 8;
+        share = 2; most = 8; least = b > 512 ? 4 : 8;
     } else if (nq <= 4 * cus && !large_set && ix->capacity * ix->L.d * pag_vec_elem(ix) >= (512ull << 20)) {
         share = 4; most = 4; least = 4;
     } else {

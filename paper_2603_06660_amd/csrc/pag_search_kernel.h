@@ -1182,6 +1182,7 @@ struct Wave {
     //           closest passer, if it enters W and is closer than W's closest unvisited member, else that member, whose
     //           neighbours are screened already; a passer's are screened now.  Only the threshold has to wait.
     // Where a round has ended in between the node is another one, and it is screened in a phase of its own.
+    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.6 with twelve; a trip to memory takes 0.55.
     enum : u32 {
         TM_QUERY = 0,                                  // query number, PAG_EMPTY: no more
         TM_NODE, TM_NODE_DIST, TM_FAR_LO, TM_FAR_HI,   // wave 0: the node to expand (PAG_EMPTY: the search is over), W's farthest
