@@ -621,6 +621,9 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
 
 // Batches that leave the GPU mostly idle with one wave per query get several (a team); `share` queries then share a CU.
 // Fills a->waves, the seen-set sizes, the LDS carve-up and the grid; a->waves stays 1 where one wave is the better plan.
+// A team takes longer to set up (its LDS, its entry nodes) than one wave: searches of 10 nodes lose with it (5,000 x 128,
+// whole call: 256 queries 105 -> 111 us, 512 queries 138 -> 182), at two queries per CU up to 32 nodes (227 -> 231); 20 and 64
+// nodes gain at one and two per CU (5,000 x 192, 300 queries, 20 nodes: 171 -> 156; 5,000 x 128, 512 queries, 64 nodes: 300 -> 272).
 // The lines, with kernel times of one wave -> a team (100,000 rows, efS 128, unless stated):
 //   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
 //     query 375 -> 242, 491 -> 271, 777 -> 414
@@ -628,18 +631,19 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
 //     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
 //     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
 //     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
-//   up to four per CU: 4 waves, if the rows come from HBM and not from the 256 MB cache: 1M x 768, efS 256, 1,000 queries
+//   up to four per CU: 4 waves, from 128 nodes on, if the rows come from HBM and not from the 256 MB cache: 1M x 768, efS 256, 1,000 queries
 //     1796 -> 1608 us, 200k x 1536, efS 768, 777 queries 5868 -> 5288.  Within the cache the instructions that a team
 //     adds cost more than the shorter wait saves (100k x 128, 800 queries: 534 -> 557)
 static int plan_team(const pag_index* ix, u64 nq, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
     const u64 cus = (u64)ix->num_cu;
     const bool large_set = b > PAG_LDS_RING_MAX_B;
+    const u32 length = std::max(ef, b);                             // nodes that a search expands, about
     u32 share, most, least;
-    if (nq <= cus) {
+    if (nq <= cus && length >= 16) {
         share = 1; most = 12; least = 4;
-    } else if (nq <= 2 * cus) {
+    } else if (nq > cus && nq <= 2 * cus && length >= 48) {
         share = 2; most = 8; least = b > 512 ? 4 : 8;
-    } else if (nq <= 4 * cus && !large_set && ix->capacity * ix->L.d * pag_vec_elem(ix) >= (512ull << 20)) {
+    } else if (nq > 2 * cus && nq <= 4 * cus && length >= 128 && !large_set && ix->capacity * ix->L.d * pag_vec_elem(ix) >= (512ull << 20)) {
         share = 4; most = 4; least = 4;
     } else {
         return PAG_OK;
