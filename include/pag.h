@@ -259,6 +259,12 @@ int pag_insertion_candidates(const pag_index* ix, const float* X, uint64_t m, ui
                              uint32_t* pes_count);
 
 /*
+ * Diagnostic: how pag_search would lay out a call of nq queries now.  *waves: wavefronts that work on one query
+ * (small batches get several); *resident: queries that the GPU works on at a time.  Nothing is launched.
+ */
+int pag_search_layout(const pag_index* ix, uint64_t nq, uint32_t K, uint32_t efS, uint32_t* waves, uint32_t* resident);
+
+/*
  * Diagnostic for the roofline (no step of the method): reads `rows` whole rows of the index's vector
  * store, in order (scattered = 0) or in a scattered permutation (scattered = 1), four rows in flight
  * per wavefront, and reports the achieved rate in GB/s.  This is what the exact-distance step of

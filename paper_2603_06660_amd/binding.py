@@ -23,7 +23,7 @@ EXPORTED_SYMBOLS = (
     "pag_build", "pag_search", "pag_search_static", "pag_insert", "pag_free", "pag_describe", "pag_export", "pag_import",
     "pag_get_counters", "pag_reset_counters", "pag_set_search_options", "pag_set_seen_capacity_log2",
     "pag_prepare_queries", "pag_exact_distances", "pag_screen", "pag_edge_info", "pag_insertion_candidates",
-    "pag_measure_row_reads",
+    "pag_search_layout", "pag_measure_row_reads",
     "pag_searcher_create", "pag_searcher_search", "pag_searcher_get_counters", "pag_searcher_free",
     "pag_last_error",
 )
@@ -289,6 +289,13 @@ class PagIndex:
         _check(load_library().pag_measure_row_reads(self._h, C.c_uint64(rows), C.c_int(int(scattered)),
                                                     C.byref(out)), "pag_measure_row_reads")
         return out.value
+
+    def search_layout(self, nq, K, efS):
+        """-> (wavefronts per query, queries resident at a time) that pag_search would use for nq queries now."""
+        waves, resident = C.c_uint32(0), C.c_uint32(0)
+        _check(load_library().pag_search_layout(self._h, C.c_uint64(nq), C.c_uint32(K), C.c_uint32(efS), C.byref(waves),
+                                                C.byref(resident)), "pag_search_layout")
+        return waves.value, resident.value
 
     def insertion_candidates(self, X, ef_construction):
         """pag_insertion_candidates for the raw vectors X (device): per vector R_L (ids, keys, count) and the PES

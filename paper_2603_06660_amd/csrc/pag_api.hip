@@ -801,6 +801,25 @@ extern "C" int pag_search(const pag_index* cix, const float* Q, uint64_t nq, uin
     return search_impl(ix, Q, nq, K, efS, ids, dists);
 }
 
+extern "C" int pag_search_layout(const pag_index* ix, uint64_t nq, uint32_t K, uint32_t efS, uint32_t* waves, uint32_t* resident) {
+    PAG_CHECK(ix && waves && resident, PAG_EINVAL, "null argument");
+    PAG_CHECK(nq >= 1 && nq < (1ull << 31), PAG_EINVAL, "nq must be in 1..2^31-1");
+    PAG_CHECK(K >= 1 && K <= ix->n, PAG_EINVAL, "K must be in 1..n");
+    PAG_CHECK(efS >= 1, PAG_EINVAL, "efS must be >= 1");
+    const u32 b = ix->search_b ? ix->search_b : std::max<u32>(10, K);
+    PAG_CHECK(b >= K, PAG_EINVAL, "search_b must be >= K");
+    PAG_CHECK(b <= PAG_MAX_B, PAG_EUNSUPPORTED, "working sets above 1024 nodes (K > 1024) are not built");
+    DeviceGuard g(ix->device);
+    SearchArgs a;
+    u32 lds = 0;
+    int grid = 0;
+    int rc;
+    if ((rc = search_plan(ix, nq, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    *waves = a.waves;
+    *resident = (u32)std::min<u64>(nq, (u64)grid);
+    return PAG_OK;
+}
+
 // ---------------------------------------------------------------------------------------------
 // pag_search_static: pag_search for callers that cannot allocate.  Everything the search needs beyond the index, the
 // queries and the outputs -- rotated queries, projection tables, normalised copies (COS) and the per-wave seen-set

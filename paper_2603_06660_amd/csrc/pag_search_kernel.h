@@ -263,6 +263,10 @@ struct Wave {
     static constexpr int TAILS = NQ >= 5 ? 2 : 1;
     u32 tail_idx[TAILS];
     u32 tail_mask[TAILS];
+    // Where the third wave on a SIMD leaves no register for a row waiting unmasked (see pag_search_occupancy) the values
+    // past the end are replaced right after the request: 16-bit rows of 2304 at 8,000 queries 0.95 of that with 40 dwords
+    // spilled, of 2816 0.7 with 85
+    static constexpr bool MASK_EARLY = !TEAM && (VM == 2 ? NQ == 10 || (NQ == 12 && CW < 8) : VM == 0 && NQ == 8 && NW == 2);
     // adjacency record requested ahead of time for the node that will be expanded next
     u32 nx_id;                      // whose record pf_* holds (PAG_EMPTY: none)
     u32 pf_id, pf_cw[CW];
@@ -402,7 +406,7 @@ struct Wave {
     // Branch-free row load: only the last TAILS chunks can run past the row; there the lane re-reads
     // chunk 0 (in bounds), so no load ever sits inside a branch and the loads of several rows stay in
     // flight together.  The values read past the end are replaced by zeros where they are used
-    // (lane_partial): doing it here would wait for the row right after asking for it.
+    // (lane_partial): doing it here waits for the row right after asking for it.
     __device__ __forceinline__ void load_vec(Chunk (&v)[NQ], u32 id) const {
         const Chunk* p = (const Chunk*)((const char*)A.vec + (u64)id * A.d * (HALF ? 2 : 4));
 #pragma unroll
@@ -410,16 +414,17 @@ struct Wave {
 #pragma unroll
         for (int t = 0; t < TAILS; ++t) {
             v[NQ - TAILS + t] = p[tail_idx[t]];
+            if constexpr (MASK_EARLY) v[NQ - TAILS + t] = masked(v[NQ - TAILS + t], tail_mask[t]);
         }
     }
 
-    __device__ __forceinline__ Chunk inside_row(Chunk x, int c) const {
-        if (c >= NQ - TAILS) {
-            const u32 m = tail_mask[c - (NQ - TAILS)];
-            x.x &= m; x.y &= m;
-            if constexpr (VM != 2) { x.z &= m; x.w &= m; }
-        }
+    __device__ __forceinline__ static Chunk masked(Chunk x, u32 m) {
+        x.x &= m; x.y &= m;
+        if constexpr (VM != 2) { x.z &= m; x.w &= m; }
         return x;
+    }
+    __device__ __forceinline__ Chunk inside_row(Chunk x, int c) const {
+        return !MASK_EARLY && c >= NQ - TAILS ? masked(x, tail_mask[c - (NQ - TAILS)]) : x;
     }
 
     // sum over this lane's elements of fl32(q - x)^2, accumulated in fp64
@@ -1616,14 +1621,28 @@ struct Wave {
     }
 };
 
+// Waves per SIMD that the registers have to leave room for.
+// Short rows: four (five where a row takes one chunk of fp32 or 8-byte chunks), at up to 21 dwords of spill (up to 56 with
+// 16-byte chunks of 16-bit rows).  Working sets above 128 nodes hold W in 4 NW registers per lane: three up to 512 nodes, two
+// for 1024 (a third wave there spills W and costs 50 %).
+// Long rows: left to itself the compiler keeps the two rows in flight in as many registers as it likes and gives up a wave for
+// them; with the line stated it spills at most 24 dwords.  Kernel times with and without, 1,030 to 8,000 queries: 3072-d at
+// K 200 5.16 -> 3.53 ms, 2560-d at K 400 1.4-1.5 times as fast, 16-bit rows of 1280 1.0-1.47 times, of 2816 at K 400 1.2-1.6.
+constexpr int pag_search_occupancy(int nq, int nw, int vm, int cw) {
+    if (nq <= 4) {
+        if (nw > 2) return nw >= 16 ? 2 : 3;
+        return nq > 3 ? 1 : (vm == 2 || (nq == 1 && vm == 0)) ? 5 : 4;
+    }
+    if (nw > 2) return nw >= 16 || (nw == 8 && nq == 12 && vm == 0) ? 1 : 2;
+    if (vm == 2) return nq == 8 || (nq == 12 && cw == 8) ? 2 : 3;      // two rows to a buffer at eight chunks
+    return vm == 0 && (nq == 6 || (nq == 8 && nw == 2)) ? 3 : 2;
+}
+
 // Persistent waves: every wave pulls query numbers from one counter until the batch is drained,
 // so long and short searches balance themselves; the loop ends for every wave once the counter
 // passes nq.
 template <int NQ, int NW, int VM, int CW>
-// Short rows leave room for four waves per SIMD (128 VGPRs, a few dwords of spill); longer rows
-// keep their registers for loads in flight.  Working sets above 128 nodes hold W in 4 NW registers per lane:
-// three waves per SIMD up to 512 nodes, two for 1024 (measured: a third wave there spills W and costs 50 %).
-__attribute__((amdgpu_waves_per_eu(VM == 2 && NQ <= 3 && NW <= 2 ? 5 : (NQ <= 3 && NW <= 2 ? 4 : (NQ <= 4 && NW > 2 ? (NW >= 16 ? 2 : 3) : 1)), 8)))
+__attribute__((amdgpu_waves_per_eu(pag_search_occupancy(NQ, NW, VM, CW), 8)))
 __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
     extern __shared__ __align__(64) unsigned char smem[];   // the table sits first: see table_sum
     const int lane = threadIdx.x;
