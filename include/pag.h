@@ -260,7 +260,8 @@ int pag_insertion_candidates(const pag_index* ix, const float* X, uint64_t m, ui
 
 /*
  * Diagnostic: how pag_search would lay out a call of nq queries now.  *waves: wavefronts that work on one query
- * (small batches get several); *resident: queries that the GPU works on at a time.  Nothing is launched.
+ * (small batches get several, unless other calls of this process keep the GPU busy); *resident: queries that the GPU
+ * works on at a time.  Nothing is launched.
  */
 int pag_search_layout(const pag_index* ix, uint64_t nq, uint32_t K, uint32_t efS, uint32_t* waves, uint32_t* resident);
 

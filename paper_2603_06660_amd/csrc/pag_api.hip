@@ -1,6 +1,7 @@
 // C ABI of the PAG library: argument checking, index life cycle, import / export, and the
 // host side of pag_search (Alg. 2) -- everything that computes runs in the kernels.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdlib>
@@ -11,6 +12,7 @@
 #include <vector>
 
 #include "pag_internal.h"
+#include "pag_plan.h"
 
 static thread_local std::string g_last_error;
 void pag_set_error(const std::string& msg) { g_last_error = msg; }
@@ -619,66 +621,27 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
     if (ix->seen_log2) *hlog = ix->seen_log2;
 }
 
-// Batches that leave the GPU mostly idle with one wave per query get several (a team); `share` queries then share a CU.
-// Fills a->waves, the seen-set sizes, the LDS carve-up and the grid; a->waves stays 1 where one wave is the better plan.
-// A team takes longer to set up (its LDS, its entry nodes) than one wave: searches of 10 nodes lose with it (5,000 x 128,
-// whole call: 256 queries 105 -> 111 us, 512 queries 138 -> 182), at two queries per CU up to 32 nodes (227 -> 231); 20 and 64
-// nodes gain at one and two per CU (5,000 x 192, 300 queries, 20 nodes: 171 -> 156; 5,000 x 128, 512 queries, 64 nodes: 300 -> 272).
-// The lines, with kernel times of one wave -> a team (100,000 rows, efS 128, unless stated):
-//   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
-//     query 375 -> 242, 491 -> 271, 777 -> 414
-//   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
-//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
-//     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
-//     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
-//   up to four per CU: 4 waves, from 128 nodes on, if the rows come from HBM and not from the 256 MB cache: 1M x 768, efS 256, 1,000 queries
-//     1796 -> 1608 us, 200k x 1536, efS 768, 777 queries 5868 -> 5288.  Within the cache the instructions that a team
-//     adds cost more than the shorter wait saves (100k x 128, 800 queries: 534 -> 557)
-static int plan_team(const pag_index* ix, u64 nq, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
-    const u64 cus = (u64)ix->num_cu;
-    const bool large_set = b > PAG_LDS_RING_MAX_B;
-    const u32 length = std::max(ef, b);                             // nodes that a search expands, about
-    u32 share, most, least;
-    if (nq <= cus && length >= 16) {
-        share = 1; most = 12; least = 4;
-    } else if (nq > cus && nq <= 2 * cus && length >= 48) {
-        share = 2; most = 8; least = b > 512 ? 4 : 8;
-    } else if (nq > 2 * cus && nq <= 4 * cus && length >= 128 && !large_set && ix->capacity * ix->L.d * pag_vec_elem(ix) >= (512ull << 20)) {
-        share = 4; most = 4; least = 4;
-    } else {
-        return PAG_OK;
-    }
-    most = std::min<u32>(most, (u32)pag_team_max(b <= 512 ? 8 : 16));
-    const u32 room = ix->lds_per_cu / share - 512;
+// Fills a->waves, the seen-set sizes, the LDS carve-up and the grid if the search is one for teams; a->waves stays 1 if not.
+static int plan_team(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
+    pag_team_request r;
+    r.nq = nq; r.others = others; r.store_bytes = ix->capacity * ix->L.d * pag_vec_elem(ix);
+    r.b = b; r.ef = ef; r.num_cu = (u32)ix->num_cu; r.lds_per_cu = ix->lds_per_cu;
+    r.hlog = a->hlog; r.blog = a->blog; r.seen_fixed = ix->seen_log2; r.most_waves = (u32)pag_team_max(b <= 512 ? 8 : 16);
     SearchArgs t = *a;
-    t.waves = most;
-    // The seen set: an exact hash of everything the search is expected to compute, if the LDS holds it half full;
-    // otherwise the bitmap behind a Bloom filter of 16 bits per node, as far as the LDS goes.
-    const u64 expected = b + 8ull * std::max(ef, b);
-    u32 lg = 9;
-    while ((1ull << lg) < 2 * expected && lg < 16) ++lg;
-    auto fits = [&](u32 hlog, u32 blog) { SearchArgs u = t; return (u32)pag_search_lds_bytes(ix->L, b, hlog, blog, &u) <= room; };
-    if (!ix->seen_log2 && (1ull << lg) >= 2 * expected && fits(lg, 0)) {
-        t.hlog = lg; t.blog = 0;
-    } else if (t.blog) {
-        while (t.blog < 20 && (1ull << t.blog) < 16 * expected && fits(t.hlog, t.blog + 1)) ++t.blog;
-    }
-    if (!fits(t.hlog, t.blog)) return PAG_OK;
-    const u32 need = (u32)pag_search_lds_bytes(ix->L, b, t.hlog, t.blog, &t);
-    // as many waves as leave every query resident
-    for (; t.waves >= least; --t.waves) {
-        int rc, g = 0;
-        if ((rc = pag_search_max_grid(ix, b, t.waves, need, &g))) return rc;
-        if ((u64)g < nq) continue;
-        *a = t; *lds = need; *grid = (int)nq;
-        return PAG_OK;
-    }
+    t.waves = 2;                                                    // any team: its words are part of the carve-up
+    pag_team_plan p;
+    const int rc = pag_plan_team(r, [&](u32 hlog, u32 blog) { return (u32)pag_search_lds_bytes(ix->L, b, hlog, blog, &t); },
+                                 [&](u32 waves, u32 bytes, int* n) { return pag_search_max_grid(ix, b, waves, bytes, n); }, &p);
+    if (rc || p.waves == 1) return rc;
+    a->waves = p.waves; a->hlog = p.hlog; a->blog = p.blog;
+    *lds = (u32)pag_search_lds_bytes(ix->L, b, p.hlog, p.blog, a);
+    *grid = (int)nq;
     return PAG_OK;
 }
 
 // Plans a search: fills the part of SearchArgs that depends only on the index and (b, ef), the LDS carve-up and the
 // largest useful grid.  Allocates nothing.
-static int search_plan(const pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+static int search_plan(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
     const pag_layout& L = ix->L;
     std::memset((void*)a, 0, sizeof(*a));
     a->vec = ix->vec; a->rec = ix->rec; a->entry = ix->entry;
@@ -693,7 +656,7 @@ static int search_plan(const pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, 
     // per-wave spill bitmaps of the seen set: one bit per node, rounded to 16 bytes
     a->bitmap_words = ((u64)ix->capacity + 127) / 128 * 4;
     a->waves = 1;
-    int rc = plan_team(ix, nq, b, ef, a, lds, grid);
+    int rc = plan_team(ix, nq, others, b, ef, a, lds, grid);
     if (rc || a->waves > 1) return rc;
     *lds = (u32)pag_search_lds_bytes(L, b, a->hlog, a->blog, a);
     if (*lds > 65536) { pag_set_error("search: working set, tables and seen set need more than 64 KB of LDS per wave"); return PAG_EUNSUPPORTED; }
@@ -728,8 +691,8 @@ static int search_plan(const pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, 
 }
 
 // The plan plus the workspaces it needs (grown on demand); shared with indexing.
-int pag_search_common(pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
-    int rc = search_plan(ix, nq, b, ef, n_limit, a, lds, grid);
+int pag_search_common(pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+    int rc = search_plan(ix, nq, others, b, ef, n_limit, a, lds, grid);
     if (rc) return rc;
     const u64 need = (u64)*grid * a->bitmap_words;
     if (ix->ws_bitmap_cap < need) {
@@ -744,6 +707,30 @@ int pag_search_common(pag_index* ix, u64 nq, u32 b, u32 ef, u64 n_limit, SearchA
     }
     return PAG_OK;
 }
+
+// The calls of this process that are under way on each GPU and the queries they search: the plan of the next call depends on
+// how full the GPU is (see pag_plan_team), its results do not.  Left out are
+//   batches that fill the GPU: another call does not run beside them but between them, and then has the GPU for itself
+//     (200k x 768, one query at efS 64 / 64 queries at efS 256 beside batches of 10,000: median 0.5 / 2.1 ms with teams, 1.5-2.1 /
+//     8.6-8.9 with one wave per query);
+//   the vectors that pag_insert searches for: a searcher that overlaps an insertion answers sooner with teams (20,000 vectors
+//     into 200k x 768, efS 256, median of 1 / 64 / 256 / 512 queries: 0.8 / 0.9 / 0.95 / 1.2 ms, with one wave per query 1.4 /
+//     1.65 / 1.8 / 1.9; the insertion takes no longer).
+struct GpuLoad { std::atomic<u64> calls, queries; };
+static GpuLoad g_load[kMaxDevices];
+
+static u64 queries_beside(int device) { return pag_queries_beside(g_load[device].calls.load(), g_load[device].queries.load()); }
+
+struct UnderWay {
+    GpuLoad& load;
+    const u64 nq;
+    UnderWay(int device, u64 n, int grid) : load(g_load[device]), nq(n <= (u64)grid ? n : 0) {
+        if (nq) { load.calls.fetch_add(1); load.queries.fetch_add(nq); }
+    }
+    ~UnderWay() { if (nq) { load.queries.fetch_sub(nq); load.calls.fetch_sub(1); } }
+    UnderWay(const UnderWay&) = delete;
+    UnderWay& operator=(const UnderWay&) = delete;
+};
 
 // The search of one batch with the workspaces, counters, events and stream of `ix` (an index, or a
 // searcher's view of one).
@@ -765,7 +752,8 @@ static int search_impl(pag_index* ix, const float* Q, uint64_t nq, uint32_t K, u
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = pag_search_common(ix, nq, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = pag_search_common(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
+    const UnderWay under_way(ix->device, nq, grid);
     if (nq > (u64)grid) {
         // several rounds of waves: as many waves as make the rounds equally full (10,000 queries on 4,096 waves: 3,334),
         // instead of a last round that leaves most of the GPU idle
@@ -814,7 +802,7 @@ extern "C" int pag_search_layout(const pag_index* ix, uint64_t nq, uint32_t K, u
     u32 lds = 0;
     int grid = 0;
     int rc;
-    if ((rc = search_plan(ix, nq, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = search_plan(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
     *waves = a.waves;
     *resident = (u32)std::min<u64>(nq, (u64)grid);
     return PAG_OK;
@@ -852,7 +840,8 @@ extern "C" int pag_search_static(const pag_index* cix, const float* Q, uint64_t 
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = search_plan(ix, nq, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = search_plan(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
+    const UnderWay under_way(ix->device, nq, grid);
     // bitmap part: as many per-wave bitmaps as fit behind the query part; fewer waves than the GPU could hold
     // make the search slower, not different
     const u64 room = (u64)PAG_STATIC_SCRATCH_BYTES - off_bitmap;

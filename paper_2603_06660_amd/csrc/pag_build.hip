@@ -587,7 +587,7 @@ static int search_candidates(pag_index* ix, BuildWs& ws, const float* qrot, u64 
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = pag_search_common(ix, m, b, ix->efC, n_limit, &a, &lds, &grid))) return rc;
+    if ((rc = pag_search_common(ix, m, 0, b, ix->efC, n_limit, &a, &lds, &grid))) return rc;
     a.qrot = qrot; a.tables = ix->ws_tab; a.nq = (u32)m; a.K = b;
     a.flags &= ~(u32)PAG_FLAG_NO_PRT;          // indexing always runs with the projection test on
     a.cand = ws.cand; a.cand_cnt = ws.cand_cnt; a.cand_cap = cand_cap;

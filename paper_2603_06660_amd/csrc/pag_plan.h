@@ -1,0 +1,92 @@
+// Which plan a search gets: arithmetic on sizes, without HIP, so that it can be checked on a CPU.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+struct pag_team_request {
+    uint64_t nq;             // queries of the call
+    uint64_t others;         // queries of other calls that the GPU searches beside them, see pag_queries_beside
+    uint64_t store_bytes;    // of the vectors
+    uint32_t b, ef;
+    uint32_t num_cu, lds_per_cu;
+    uint32_t hlog, blog;     // the seen set of the one-wave search
+    uint32_t seen_fixed;     // its size is the caller's choice
+    uint32_t most_waves;     // that the kernel is built for
+};
+
+struct pag_team_plan {
+    uint32_t waves;          // 1: no team
+    uint32_t hlog, blog;     // of the team's seen set
+    uint32_t lds;            // bytes
+};
+
+// Of `calls` other calls under way with `queries` queries in all, how many are searched side by side with a new one: HIP gives a
+// process four hardware queues, what is beyond waits.  (Eight searchers with 64 queries each, 200k x 768, efS 256: 247,000
+// queries/s when all seven others count, 276,000 when three do.)
+inline uint64_t pag_queries_beside(uint64_t calls, uint64_t queries) { return calls <= 3 ? queries : queries * 3 / calls; }
+
+// Batches that leave the GPU mostly idle with one wave per query get several (a team); `share` queries then share a CU.
+// `waves` stays 1 where one wave is the better plan.
+//   lds_bytes(hlog, blog): LDS of a team with that seen set; resident(waves, lds, &n): error code, teams that the GPU holds at a time
+//
+// What decides is not the call alone but the queries under way on the GPU: a team takes a large part of a CU, and teams of
+// several calls would wait for each other where smaller teams or single waves run side by side.  Four searchers with 256 queries
+// each (200k x 768, efS 256): 302,000 queries/s when every call plans as if it were alone, 482,000 with one wave per query,
+// 661,000 with what the sum asks for; with 1,000 queries each 706,000, 1,158,000 and 1,186,000, with 16 each 73,000, 39,000 and 73,000.
+//
+// A team takes longer to set up (its LDS, its entry nodes) than one wave: searches of 10 nodes lose with it (5,000 x 128,
+// whole call: 256 queries 105 -> 111 us, 512 queries 138 -> 182), at two queries per CU up to 32 nodes (227 -> 231); 20 and 64
+// nodes gain at one and two per CU (5,000 x 192, 300 queries, 20 nodes: 171 -> 156; 5,000 x 128, 512 queries, 64 nodes: 300 -> 272).
+// The lines, with kernel times of one wave -> a team (100,000 rows, efS 128, unless stated):
+//   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
+//     query 375 -> 242, 491 -> 271, 777 -> 414
+//   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
+//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
+//     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
+//     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
+//   up to four per CU: 4 waves, from 128 nodes on, if the rows come from HBM and not from the 256 MB cache: 1M x 768, efS 256, 1,000 queries
+//     1796 -> 1608 us, 200k x 1536, efS 768, 777 queries 5868 -> 5288.  Within the cache the instructions that a team
+//     adds cost more than the shorter wait saves (100k x 128, 800 queries: 534 -> 557)
+template <class Lds, class Resident>
+int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
+    const uint64_t cus = r.num_cu, load = r.nq + r.others;
+    const bool large_set = r.b > 128;
+    const uint32_t length = std::max(r.ef, r.b);                    // nodes that a search expands, about
+    uint32_t share, most, least;
+    p->waves = 1;
+    if (load <= cus && length >= 16) {
+        share = 1; most = 12; least = 4;
+    } else if (load > cus && load <= 2 * cus && length >= 48) {
+        share = 2; most = 8; least = r.b > 512 ? 4 : 8;
+    } else if (load > 2 * cus && load <= 4 * cus && length >= 128 && !large_set && r.store_bytes >= (512ull << 20)) {
+        share = 4; most = 4; least = 4;
+    } else {
+        return 0;
+    }
+    most = std::min(most, r.most_waves);
+    const uint32_t room = r.lds_per_cu / share - 512;
+    // The seen set: an exact hash of everything the search is expected to compute, if the LDS holds it half full;
+    // otherwise the bitmap behind a Bloom filter of 16 bits per node, as far as the LDS goes.
+    uint32_t hlog = r.hlog, blog = r.blog;
+    const uint64_t expected = r.b + 8ull * length;
+    uint32_t lg = 9;
+    while ((1ull << lg) < 2 * expected && lg < 16) ++lg;
+    if (!r.seen_fixed && (1ull << lg) >= 2 * expected && lds_bytes(lg, 0u) <= room) {
+        hlog = lg; blog = 0;
+    } else if (blog) {
+        while (blog < 20 && (1ull << blog) < 16 * expected && lds_bytes(hlog, blog + 1) <= room) ++blog;
+    }
+    const uint32_t lds = lds_bytes(hlog, blog);
+    if (lds > room) return 0;
+    // as many waves as leave every query resident
+    for (uint32_t waves = most; waves >= least; --waves) {
+        int rc, n = 0;
+        if ((rc = resident(waves, lds, &n))) return rc;
+        if ((uint64_t)n < load) continue;
+        p->waves = waves; p->hlog = hlog; p->blog = blog; p->lds = lds;
+        return 0;
+    }
+    return 0;
+}

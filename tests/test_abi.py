@@ -79,6 +79,7 @@ def test_argument_errors_need_no_gpu(lib):
     assert lib.pag_searcher_free(None) == 0
     assert lib.pag_search_static(None, None, C.c_uint64(1), C.c_uint32(1), C.c_uint32(1), None, None) == -1
     assert b"null" in lib.pag_last_error()
+    assert lib.pag_search_layout(None, C.c_uint64(1), C.c_uint32(1), C.c_uint32(1), None, None) == -1
     assert lib.pag_insertion_candidates(None, None, C.c_uint64(1), None, None, None, None, None, None) == -1
 
 

@@ -22,3 +22,37 @@ def test_resident_queries_of_large_batches(d, P, half, K, efS, per_cu):
     ix.close()
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     assert waves == 1 and resident >= per_cu * cus, (waves, resident / cus)
+
+
+def test_waves_follow_what_the_gpu_is_searching():
+    """A single query gets a team while nothing else is searched, one wave while a large batch is, and a team beside a batch
+    that fills the GPU (it has its turn between two of them)."""
+    import threading
+    import torch
+    from paper_2603_06660_amd import PagIndex
+    rng = np.random.default_rng(5)
+    rows = lambda n: torch.from_numpy(rng.standard_normal((n, 128), dtype=np.float32)).cuda()
+    ix = PagIndex.build(rows(4000), metric="l2", max_degree=32, num_subspaces=16, ef_construction=60, seed=2)
+    other = PagIndex.build(rows(500), metric="l2", max_degree=16, num_subspaces=16, ef_construction=30, seed=2)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    q = rows(12 * cus)
+    many = q.repeat(10, 1)
+    one = [x.clone() for x in other.search(q[:1].contiguous(), 10, 200)]
+    assert ix.search_layout(q.shape[0], 10, 20000)[1] == q.shape[0] and ix.search_layout(many.shape[0], 10, 20000)[1] < many.shape[0]
+    s = other.searcher()
+    for batch, efS, want in ((q, 20000, 1), (many, 3000, 12)):
+        assert other.search_layout(1, 10, 200)[0] == 12
+        started = threading.Event()
+        busy = threading.Thread(target=lambda: (started.set(), ix.search(batch, 10, efS)))
+        seen, got = [], []
+        busy.start()
+        started.wait()
+        while busy.is_alive():                              # nothing in here waits for the stream of the batch
+            seen.append(other.search_layout(1, 10, 200)[0])
+            got.append(s.search(q[:1], 10, 200))
+        busy.join()
+        torch.cuda.synchronize()
+        assert want in seen and (want == 1 or set(seen) == {12}), seen
+        assert all(torch.equal(i, one[0]) and torch.equal(d, one[1]) for i, d in got)       # the same answer either way
+    assert other.search_layout(1, 10, 200)[0] > 1
+    s.close(); other.close(); ix.close()

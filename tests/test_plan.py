@@ -1,0 +1,65 @@
+"""The rules that choose a search's plan, compiled for the CPU: they see sizes only, and an occupancy that the test makes up."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "pag_plan.h"
+// arguments: nq others store_bytes b ef waves_per_cu; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
+// or: calls queries, for pag_queries_beside
+int main(int n, char** v) {
+    if (n == 3) { std::printf("0 %llu\n", (unsigned long long)pag_queries_beside(strtoull(v[1], 0, 10), strtoull(v[2], 0, 10))); return 0; }
+    pag_team_request r = {};
+    r.nq = strtoull(v[1], 0, 10); r.others = strtoull(v[2], 0, 10); r.store_bytes = strtoull(v[3], 0, 10);
+    r.b = atoi(v[4]); r.ef = atoi(v[5]);
+    const uint32_t per_cu = atoi(v[6]);
+    r.num_cu = 256; r.lds_per_cu = 163840; r.most_waves = 12;
+    r.hlog = 9; r.blog = r.b + 8 * std::max(r.ef, r.b) > 1024 ? 15 : 0;
+    pag_team_plan p;
+    auto lds = [&](uint32_t h, uint32_t bl) { return 6144u + (4u << h) + (bl ? (1u << bl) / 8 : 0u); };
+    auto resident = [&](uint32_t w, uint32_t bytes, int* n) { *n = (int)(256 * std::min(per_cu / w, 163840 / bytes)); return 0; };
+    const int rc = pag_plan_team(r, lds, resident, &p);
+    std::printf("%d %u\n", rc, p.waves);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def waves(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2603_06660_amd", "csrc"),
+                           str(d / "plan.cpp"), "-o", str(d / "plan")])
+
+    def beside(calls, queries):
+        return int(subprocess.check_output([str(d / "plan"), str(calls), str(queries)], text=True).split()[1])
+
+    def run(nq, others=0, store=1 << 30, b=10, ef=256, per_cu=16):
+        rc, w = subprocess.check_output([str(d / "plan")] + [str(x) for x in (nq, others, store, b, ef, per_cu)], text=True).split()
+        assert rc == "0"
+        return int(w)
+    run.beside = beside
+    return run
+
+
+@pytest.mark.parametrize("nq,others,want", [(1, 0, 12), (256, 0, 12), (257, 0, 8), (512, 0, 8), (513, 0, 4), (1024, 0, 4), (1025, 0, 1)])
+def test_waves_of_a_call_alone(waves, nq, others, want):
+    assert waves(nq, others) == want
+
+
+# what another call searches meanwhile counts like queries of this one: the sum decides
+@pytest.mark.parametrize("nq,others,want", [(64, 192, 12), (64, 193, 8), (256, 256, 8), (256, 768, 4), (256, 769, 1), (1, 1024, 1),
+                                            (512, 1536, 1), (1, 10000, 1)])
+def test_waves_beside_other_calls(waves, nq, others, want):
+    assert waves(nq, others) == want
+    assert waves(nq, others, store=1 << 20) == (want if nq + others <= 512 else 1)       # short wait for rows: four waves do not pay
+
+
+@pytest.mark.parametrize("calls,queries,want", [(0, 0, 0), (1, 64, 64), (3, 1000, 1000), (7, 448, 192), (7, 1792, 768), (15, 3 * 2 ** 31, 3 * 2 ** 31 // 5)])
+def test_calls_beyond_the_hardware_queues_wait(waves, calls, queries, want):
+    assert waves.beside(calls, queries) == want
