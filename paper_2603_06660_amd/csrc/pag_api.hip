@@ -622,9 +622,9 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
 }
 
 // Fills a->waves, the seen-set sizes, the LDS carve-up and the grid if the search is one for teams; a->waves stays 1 if not.
-static int plan_team(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
+static int plan_team(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
     pag_team_request r;
-    r.nq = nq; r.others = others; r.store_bytes = ix->capacity * ix->L.d * pag_vec_elem(ix);
+    r.nq = nq; r.others = others; r.store_bytes = nodes * ix->L.d * pag_vec_elem(ix); r.half = ix->vec_half;
     r.b = b; r.ef = ef; r.num_cu = (u32)ix->num_cu; r.lds_per_cu = ix->lds_per_cu;
     r.hlog = a->hlog; r.blog = a->blog; r.seen_fixed = ix->seen_log2; r.most_waves = (u32)pag_team_max(b <= 512 ? 8 : 16);
     SearchArgs t = *a;
@@ -641,7 +641,8 @@ static int plan_team(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, Sea
 
 // Plans a search: fills the part of SearchArgs that depends only on the index and (b, ef), the LDS carve-up and the
 // largest useful grid.  Allocates nothing.
-static int search_plan(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+// `nodes` of the graph can be reached, ids from n_limit on are not part of it.
+static int search_plan(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
     const pag_layout& L = ix->L;
     std::memset((void*)a, 0, sizeof(*a));
     a->vec = ix->vec; a->rec = ix->rec; a->entry = ix->entry;
@@ -656,7 +657,7 @@ static int search_plan(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u
     // per-wave spill bitmaps of the seen set: one bit per node, rounded to 16 bytes
     a->bitmap_words = ((u64)ix->capacity + 127) / 128 * 4;
     a->waves = 1;
-    int rc = plan_team(ix, nq, others, b, ef, a, lds, grid);
+    int rc = plan_team(ix, nq, others, nodes, b, ef, a, lds, grid);
     if (rc || a->waves > 1) return rc;
     *lds = (u32)pag_search_lds_bytes(L, b, a->hlog, a->blog, a);
     if (*lds > 65536) { pag_set_error("search: working set, tables and seen set need more than 64 KB of LDS per wave"); return PAG_EUNSUPPORTED; }
@@ -691,8 +692,8 @@ static int search_plan(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u
 }
 
 // The plan plus the workspaces it needs (grown on demand); shared with indexing.
-int pag_search_common(pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
-    int rc = search_plan(ix, nq, others, b, ef, n_limit, a, lds, grid);
+int pag_search_common(pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+    int rc = search_plan(ix, nq, others, nodes, b, ef, n_limit, a, lds, grid);
     if (rc) return rc;
     const u64 need = (u64)*grid * a->bitmap_words;
     if (ix->ws_bitmap_cap < need) {
@@ -752,7 +753,7 @@ static int search_impl(pag_index* ix, const float* Q, uint64_t nq, uint32_t K, u
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = pag_search_common(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = pag_search_common(ix, nq, queries_beside(ix->device), ix->n, b, efS, ix->n, &a, &lds, &grid))) return rc;
     const UnderWay under_way(ix->device, nq, grid);
     if (nq > (u64)grid) {
         // several rounds of waves: as many waves as make the rounds equally full (10,000 queries on 4,096 waves: 3,334),
@@ -802,7 +803,7 @@ extern "C" int pag_search_layout(const pag_index* ix, uint64_t nq, uint32_t K, u
     u32 lds = 0;
     int grid = 0;
     int rc;
-    if ((rc = search_plan(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = search_plan(ix, nq, queries_beside(ix->device), ix->n, b, efS, ix->n, &a, &lds, &grid))) return rc;
     *waves = a.waves;
     *resident = (u32)std::min<u64>(nq, (u64)grid);
     return PAG_OK;
@@ -840,7 +841,7 @@ extern "C" int pag_search_static(const pag_index* cix, const float* Q, uint64_t 
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = search_plan(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = search_plan(ix, nq, queries_beside(ix->device), ix->n, b, efS, ix->n, &a, &lds, &grid))) return rc;
     const UnderWay under_way(ix->device, nq, grid);
     // bitmap part: as many per-wave bitmaps as fit behind the query part; fewer waves than the GPU could hold
     // make the search slower, not different

@@ -8,7 +8,8 @@
 struct pag_team_request {
     uint64_t nq;             // queries of the call
     uint64_t others;         // queries of other calls that the GPU searches beside them, see pag_queries_beside
-    uint64_t store_bytes;    // of the vectors
+    uint64_t store_bytes;    // of the vectors that the search can reach
+    uint32_t half;           // they are 16-bit floats
     uint32_t b, ef;
     uint32_t num_cu, lds_per_cu;
     uint32_t hlog, blog;     // the seen set of the one-wave search
@@ -46,9 +47,13 @@ inline uint64_t pag_queries_beside(uint64_t calls, uint64_t queries) { return ca
 //     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
 //     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
 //     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
-//   up to four per CU: 4 waves, from 128 nodes on, if the rows come from HBM and not from the 256 MB cache: 1M x 768, efS 256, 1,000 queries
-//     1796 -> 1608 us, 200k x 1536, efS 768, 777 queries 5868 -> 5288.  Within the cache the instructions that a team
-//     adds cost more than the shorter wait saves (100k x 128, 800 queries: 534 -> 557)
+//   up to four per CU: 4 waves, for searches of 128 nodes or more and working sets of up to 128.  Searches of 256 nodes with working
+//     sets of up to 64 gain with up to four per CU wherever their rows come from (1,000 queries, efS 256: 50k x 768 1244 -> 1171 us,
+//     1M x 128 1127 -> 983; 30k x 1536 1606 -> 1588 at least).  Shorter ones and larger working sets gain less and lose
+//     beyond 2.5 per CU (efS 128, 520 / 777 / 1,000 queries, one wave : team: 80k x 768 1.07 / 0.98 / 0.89, 300k x 128 1.07 / 0.96 /
+//     0.90; K 100, efS 256: 50k x 768 1.10 / 1.00 / 0.96), 3.75 if the rows come from HBM and not from the 256 MB cache (200k
+//     x 768 1.14 / 1.02 / 0.95, 2M x 128 1.12 / 1.06 / 1.02; with 400 MB of rows the two are even), four if they are 16-bit
+//     besides (600k x 768 1.22 / 1.13 / 1.05)
 template <class Lds, class Resident>
 int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
     const uint64_t cus = r.num_cu, load = r.nq + r.others;
@@ -60,7 +65,10 @@ int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& residen
         share = 1; most = 12; least = 4;
     } else if (load > cus && load <= 2 * cus && length >= 48) {
         share = 2; most = 8; least = r.b > 512 ? 4 : 8;
-    } else if (load > 2 * cus && load <= 4 * cus && length >= 128 && !large_set && r.store_bytes >= (512ull << 20)) {
+    } else if (load > 2 * cus && length >= 128 && !large_set) {
+        const bool from_hbm = r.store_bytes >= (512ull << 20);
+        const uint64_t quarters = (length >= 256 && r.b <= 64) || (from_hbm && r.half) ? 16 : from_hbm ? 15 : 10;
+        if (4 * load > quarters * cus) return 0;
         share = 4; most = 4; least = 4;
     } else {
         return 0;

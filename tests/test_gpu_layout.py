@@ -24,6 +24,20 @@ def test_resident_queries_of_large_batches(d, P, half, K, efS, per_cu):
     assert waves == 1 and resident >= per_cu * cus, (waves, resident / cus)
 
 
+def test_reserved_room_does_not_change_the_plan():
+    """Rows that an index has room for are not rows that a search reads."""
+    import torch
+    from paper_2603_06660_amd import PagIndex
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    d, layouts = 768, []
+    base = torch.from_numpy(np.random.default_rng(d).standard_normal((500, d), dtype=np.float32)).cuda()
+    for capacity in (0, (512 << 20) // (4 * d) + 1):
+        ix = PagIndex.build(base, metric="l2", max_degree=16, num_subspaces=32, ef_construction=20, capacity=capacity)
+        layouts.append([ix.search_layout(nq, K, 128) for nq in (1, cus, 2 * cus, 5 * cus // 2, 3 * cus, 4 * cus) for K in (10, 100)])
+        ix.close()
+    assert layouts[0] == layouts[1] and layouts[0][8][0] == 1       # 3 to a CU, efS 128, rows in the cache
+
+
 def test_waves_follow_what_the_gpu_is_searching():
     """A single query gets a team while nothing else is searched, one wave while a large batch is, and a team beside a batch
     that fills the GPU (it has its turn between two of them)."""

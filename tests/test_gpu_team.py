@@ -77,17 +77,18 @@ def test_team_equals_one_wave(n, d, P, deg, metric, half, K, efS):
     ix.close()
 
 
-def test_team_of_four_over_a_large_store():
-    """More queries than two per CU get teams of four only where the store exceeds the caches: the capacity says so."""
+def test_team_of_four():
+    """More queries than two per CU."""
     import torch
     from paper_2603_06660_amd import PagIndex
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     d = 768
     ix = PagIndex.build(torch.from_numpy(_rows(4000, d, 5, "ip")).cuda(), metric="ip", max_degree=32, num_subspaces=32,
-                        ef_construction=60, capacity=(512 << 20) // (4 * d) + 1, seed=3)
+                        ef_construction=60, seed=3)
     q = _rows(700, d, 6, "ip")
-    for K, efS in ((10, 128), (100, 400)):
-        _compare(ix, q, K, efS, (2 * cus + 1, 3 * cus, 4 * cus))
+    for K, efS, sizes in ((10, 128, (2 * cus + 1, 5 * cus // 2)), (64, 400, (2 * cus + 1, 3 * cus, 4 * cus)), (100, 400, (5 * cus // 2,))):
+        assert all(ix.search_layout(nq, K, efS)[0] == 4 for nq in sizes)
+        _compare(ix, q, K, efS, sizes)
     ix.close()
 
 

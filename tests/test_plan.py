@@ -10,14 +10,14 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "pag_plan.h"
-// arguments: nq others store_bytes b ef waves_per_cu; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
+// arguments: nq others store_bytes half b ef waves_per_cu; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
 // or: calls queries, for pag_queries_beside
 int main(int n, char** v) {
     if (n == 3) { std::printf("0 %llu\n", (unsigned long long)pag_queries_beside(strtoull(v[1], 0, 10), strtoull(v[2], 0, 10))); return 0; }
     pag_team_request r = {};
     r.nq = strtoull(v[1], 0, 10); r.others = strtoull(v[2], 0, 10); r.store_bytes = strtoull(v[3], 0, 10);
-    r.b = atoi(v[4]); r.ef = atoi(v[5]);
-    const uint32_t per_cu = atoi(v[6]);
+    r.half = atoi(v[4]); r.b = atoi(v[5]); r.ef = atoi(v[6]);
+    const uint32_t per_cu = atoi(v[7]);
     r.num_cu = 256; r.lds_per_cu = 163840; r.most_waves = 12;
     r.hlog = 9; r.blog = r.b + 8 * std::max(r.ef, r.b) > 1024 ? 15 : 0;
     pag_team_plan p;
@@ -39,8 +39,8 @@ def waves(tmp_path_factory):
     def beside(calls, queries):
         return int(subprocess.check_output([str(d / "plan"), str(calls), str(queries)], text=True).split()[1])
 
-    def run(nq, others=0, store=1 << 30, b=10, ef=256, per_cu=16):
-        rc, w = subprocess.check_output([str(d / "plan")] + [str(x) for x in (nq, others, store, b, ef, per_cu)], text=True).split()
+    def run(nq, others=0, store=1 << 30, half=0, b=10, ef=256, per_cu=16):
+        rc, w = subprocess.check_output([str(d / "plan")] + [str(x) for x in (nq, others, store, half, b, ef, per_cu)], text=True).split()
         assert rc == "0"
         return int(w)
     run.beside = beside
@@ -57,7 +57,17 @@ def test_waves_of_a_call_alone(waves, nq, others, want):
                                             (512, 1536, 1), (1, 10000, 1)])
 def test_waves_beside_other_calls(waves, nq, others, want):
     assert waves(nq, others) == want
-    assert waves(nq, others, store=1 << 20) == (want if nq + others <= 512 else 1)       # short wait for rows: four waves do not pay
+
+
+# more than two queries to a CU: how far four waves pay depends on the search's length, its working set and where the rows lie
+@pytest.mark.parametrize("most,store,half,b,ef", [(1024, 1 << 20, 0, 10, 256), (1024, 1 << 20, 0, 64, 100000), (640, 1 << 20, 0, 10, 255),
+                                                  (640, 1 << 20, 1, 10, 128), (640, 1 << 20, 0, 65, 256), (640, (1 << 29) - 1, 0, 128, 1000),
+                                                  (960, 1 << 29, 0, 10, 128), (960, 1 << 29, 0, 128, 1000), (1024, 1 << 29, 1, 100, 128),
+                                                  (512, 1 << 30, 1, 10, 127), (512, 1 << 30, 1, 513, 1000)])
+def test_four_waves(waves, most, store, half, b, ef):
+    kw = dict(store=store, half=half, b=b, ef=ef)
+    assert waves(513, **kw) == (4 if most > 512 else 1)
+    assert waves(most, **kw) == (4 if most > 512 else 8) and waves(most + 1, **kw) == 1
 
 
 @pytest.mark.parametrize("calls,queries,want", [(0, 0, 0), (1, 64, 64), (3, 1000, 1000), (7, 448, 192), (7, 1792, 768), (15, 3 * 2 ** 31, 3 * 2 ** 31 // 5)])
