@@ -5,6 +5,10 @@
 
 #include <algorithm>
 
+// How many queries the GPU holds, from the workgroups of `waves` waves that the occupancy query grants a CU.  A single wave is
+// launched whatever the answer, a team only if it fits.
+inline int pag_resident(int per_cu, int num_cu, uint32_t waves) { return std::max(per_cu, waves == 1 ? 1 : 0) * num_cu; }
+
 struct pag_team_request {
     uint64_t nq;             // queries of the call
     uint64_t others;         // queries of other calls that the GPU searches beside them, see pag_queries_beside

@@ -1,6 +1,7 @@
 // Launch logic of the search kernel: picks the instantiation for (d, b), sizes the per-wave LDS
 // carve-up and the persistent grid.
 #include "pag_internal.h"
+#include "pag_plan.h"
 
 typedef void (*pag_search_fn)(const SearchArgs);   // selectors: one per (row chunks per lane, code dwords)
 #define PAG_DECLARE(NQ)                                                                                  \
@@ -76,8 +77,7 @@ int pag_search_max_grid(const pag_index* ix, u32 b, u32 waves, u32 lds_bytes, in
     if (!fn) { pag_set_error("search: dimension above 3072 is not built"); return PAG_EUNSUPPORTED; }
     int per_cu = 0;
     PAG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)fn, (int)(64 * waves), lds_bytes));
-    if (per_cu < 1) per_cu = 1;
-    *grid = per_cu * ix->num_cu;
+    *grid = pag_resident(per_cu, ix->num_cu, waves);
     return PAG_OK;
 }
 

@@ -11,9 +11,10 @@ PROGRAM = r"""
 #include <cstdlib>
 #include "pag_plan.h"
 // arguments: nq others store_bytes half b ef waves_per_cu; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
-// or: calls queries, for pag_queries_beside
+// or: calls queries, for pag_queries_beside; or one number, for pag_resident: of a single wave, of a team
 int main(int n, char** v) {
     if (n == 3) { std::printf("0 %llu\n", (unsigned long long)pag_queries_beside(strtoull(v[1], 0, 10), strtoull(v[2], 0, 10))); return 0; }
+    if (n == 2) { std::printf("%d %d\n", pag_resident(atoi(v[1]), 256, 1), pag_resident(atoi(v[1]), 256, 4)); return 0; }
     pag_team_request r = {};
     r.nq = strtoull(v[1], 0, 10); r.others = strtoull(v[2], 0, 10); r.store_bytes = strtoull(v[3], 0, 10);
     r.half = atoi(v[4]); r.b = atoi(v[5]); r.ef = atoi(v[6]);
@@ -22,7 +23,7 @@ int main(int n, char** v) {
     r.hlog = 9; r.blog = r.b + 8 * std::max(r.ef, r.b) > 1024 ? 15 : 0;
     pag_team_plan p;
     auto lds = [&](uint32_t h, uint32_t bl) { return 6144u + (4u << h) + (bl ? (1u << bl) / 8 : 0u); };
-    auto resident = [&](uint32_t w, uint32_t bytes, int* n) { *n = (int)(256 * std::min(per_cu / w, 163840 / bytes)); return 0; };
+    auto resident = [&](uint32_t w, uint32_t bytes, int* n) { *n = pag_resident((int)std::min(per_cu / w, 163840 / bytes), 256, w); return 0; };
     const int rc = pag_plan_team(r, lds, resident, &p);
     std::printf("%d %u\n", rc, p.waves);
 }
@@ -44,6 +45,7 @@ def waves(tmp_path_factory):
         assert rc == "0"
         return int(w)
     run.beside = beside
+    run.resident = lambda per_cu: [int(x) for x in subprocess.check_output([str(d / "plan"), str(per_cu)], text=True).split()]
     return run
 
 
@@ -73,3 +75,13 @@ def test_four_waves(waves, most, store, half, b, ef):
 @pytest.mark.parametrize("calls,queries,want", [(0, 0, 0), (1, 64, 64), (3, 1000, 1000), (7, 448, 192), (7, 1792, 768), (15, 3 * 2 ** 31, 3 * 2 ** 31 // 5)])
 def test_calls_beyond_the_hardware_queues_wait(waves, calls, queries, want):
     assert waves.beside(calls, queries) == want
+
+
+# per_cu: waves that the registers of the made-up kernel leave room for on a CU
+@pytest.mark.parametrize("nq,per_cu,want", [(1, 12, 12), (1, 11, 11), (256, 4, 4), (256, 3, 1), (1, 0, 1), (512, 15, 1)])
+def test_a_team_that_does_not_fit_is_not_planned(waves, nq, per_cu, want):
+    assert waves(nq, per_cu=per_cu) == want
+
+
+def test_a_single_wave_is_always_resident(waves):
+    assert waves.resident(0) == [256, 0] and waves.resident(-1) == [256, 0] and waves.resident(3) == [768, 768]
