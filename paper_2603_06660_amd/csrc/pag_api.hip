@@ -683,11 +683,6 @@ static int search_plan(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b
             }
         }
     }
-    // With the GPU full from beginning to end, more rows in flight only make the waves evict each other's from the
-    // memory-side cache.  1M x 768, 10,000 queries, efS 1408: 51.5 -> 50.65 ms with paced requests; 200k x 1536, 8,000
-    // queries, efS 400: 19.3 -> 19.1.  Batches of one round of waves and short searches lose instead (1M x 768, 2,048
-    // queries: 13.0 -> 13.5 ms; 200k x 1024, 10,000 queries, efS 128: 4.92 -> 4.97).
-    if (nq > (u64)*grid && ef >= 256) a->flags |= PAG_SEARCH_PACED;
     return PAG_OK;
 }
 
@@ -755,12 +750,14 @@ static int search_impl(pag_index* ix, const float* Q, uint64_t nq, uint32_t K, u
     int grid = 0;
     if ((rc = pag_search_common(ix, nq, queries_beside(ix->device), ix->n, b, efS, ix->n, &a, &lds, &grid))) return rc;
     const UnderWay under_way(ix->device, nq, grid);
-    if (nq > (u64)grid) {
+    const u64 room = (u64)grid;
+    if (nq > room) {
         // several rounds of waves: as many waves as make the rounds equally full (10,000 queries on 4,096 waves: 3,334),
         // instead of a last round that leaves most of the GPU idle
         const u64 rounds = (nq + (u64)grid - 1) / (u64)grid;
         grid = (int)((nq + rounds - 1) / rounds);
     }
+    if (pag_paced(L.d, ix->vec_half != 0, b, efS, nq, (u64)grid, room)) a.flags |= PAG_SEARCH_PACED;
     a.qrot = ix->ws_qrot; a.tables = ix->ws_tab;
     a.nq = (u32)nq; a.K = K;
     a.out_ids = (long long*)ids; a.out_dists = dists;
@@ -849,7 +846,9 @@ extern "C" int pag_search_static(const pag_index* cix, const float* Q, uint64_t 
     const u64 fit = room / (a.bitmap_words * 4);
     PAG_CHECK(fit >= 64, PAG_EUNSUPPORTED,
               "pag_search_static: the index capacity is too large for the static seen-set bitmaps (4,194,304 vectors at most); use pag_search");
+    const u64 gpu_room = (u64)grid;
     if ((u64)grid > fit) grid = (int)fit;
+    if (pag_paced(L.d, ix->vec_half != 0, b, efS, nq, (u64)grid, gpu_room)) a.flags |= PAG_SEARCH_PACED;
     if ((u64)grid > nq) grid = (int)nq;
     unsigned char* base = nullptr;
     if ((rc = scratch_of(ix->device, &base))) return rc;

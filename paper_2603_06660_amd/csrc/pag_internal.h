@@ -22,7 +22,7 @@ typedef uint32_t u32;
 #define PAG_MAX_CW 8        // code dwords per neighbour: up to 64 subspaces
 #define PAG_TEAM_WORDS 512  // LDS words that a team shares
 #define PAG_SEARCH_DISTINCT (1u << 30)  // SearchArgs.flags, internal: a hop drops an id that an earlier slot of the record also lists
-#define PAG_SEARCH_PACED (1u << 29)     // SearchArgs.flags, internal: a wave asks for rows only when those before have arrived
+#define PAG_SEARCH_PACED (1u << 29)     // SearchArgs.flags, internal: a wave asks for rows only when those before have arrived (see pag_paced)
 #define PAG_STATIC_SCRATCH_BYTES (48u << 20)   // the device array behind pag_search_static, per GPU
 #define PAG_STATIC_QUERY_FLOATS (4ull << 20)    // of which at most 16 MB hold rotated queries, tables and normalised copies
 

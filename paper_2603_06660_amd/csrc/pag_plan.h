@@ -102,3 +102,14 @@ int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& residen
     }
     return 0;
 }
+
+// Whether a wave of the one-wave search waits for the rows it has asked for before it asks for the next ones.  With the GPU full
+// from beginning to end, more long rows in flight only make the waves evict each other's from the memory-side cache.  `room`:
+// waves the GPU holds, `waves`: that are launched.  Kernel time without : with, over batches of 4,200 to 10,000 queries and searches
+// of 300 to 1,408 nodes: 1M and 60k x 768 1.00 to 1.02 with at least 3/4 of the waves, 0.99 below; 400k x 1024 1.00 to 1.02, 60k and
+// 200k x 1536 0.99 to 1.03, 100k x 3072 0.99 to 1.01.  It loses with shorter rows (1M x 128 0.94 to 1.0, 700k x 384 0.97 to 0.99,
+// 400k x 640 0.97 to 1.01), 16-bit ones (1M x 768 0.97 to 1.0), larger working sets (1M x 768, K 100: 0.96 to 1.0) and batches of
+// one round (0.95 to 1.0).
+inline bool pag_paced(uint32_t d, bool half, uint32_t b, uint32_t ef, uint64_t nq, uint64_t waves, uint64_t room) {
+    return !half && d >= 768 && b <= 64 && ef >= 256 && nq > room && (d >= 1024 ? 2 * waves >= room : 4 * waves >= 3 * room);
+}

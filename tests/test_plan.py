@@ -11,10 +11,12 @@ PROGRAM = r"""
 #include <cstdlib>
 #include "pag_plan.h"
 // arguments: nq others store_bytes half b ef waves_per_cu; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
-// or: calls queries, for pag_queries_beside; or one number, for pag_resident: of a single wave, of a team
+// or: calls queries, for pag_queries_beside; or one number, for pag_resident: of a single wave, of a team;
+// or d half b ef nq waves room and a word, for pag_paced
 int main(int n, char** v) {
     if (n == 3) { std::printf("0 %llu\n", (unsigned long long)pag_queries_beside(strtoull(v[1], 0, 10), strtoull(v[2], 0, 10))); return 0; }
     if (n == 2) { std::printf("%d %d\n", pag_resident(atoi(v[1]), 256, 1), pag_resident(atoi(v[1]), 256, 4)); return 0; }
+    if (n == 9) { std::printf("%d\n", (int)pag_paced(atoi(v[1]), atoi(v[2]) != 0, atoi(v[3]), atoi(v[4]), atoi(v[5]), atoi(v[6]), atoi(v[7]))); return 0; }
     pag_team_request r = {};
     r.nq = strtoull(v[1], 0, 10); r.others = strtoull(v[2], 0, 10); r.store_bytes = strtoull(v[3], 0, 10);
     r.half = atoi(v[4]); r.b = atoi(v[5]); r.ef = atoi(v[6]);
@@ -45,6 +47,7 @@ def waves(tmp_path_factory):
         assert rc == "0"
         return int(w)
     run.beside = beside
+    run.paced = lambda *a: bool(int(subprocess.check_output([str(d / "plan")] + [str(int(x)) for x in a] + ["paced"], text=True)))
     run.resident = lambda per_cu: [int(x) for x in subprocess.check_output([str(d / "plan"), str(per_cu)], text=True).split()]
     return run
 
@@ -85,3 +88,16 @@ def test_a_team_that_does_not_fit_is_not_planned(waves, nq, per_cu, want):
 
 def test_a_single_wave_is_always_resident(waves):
     assert waves.resident(0) == [256, 0] and waves.resident(-1) == [256, 0] and waves.resident(3) == [768, 768]
+
+
+# d, 16-bit, b, efS, queries, waves launched, waves that the GPU holds
+@pytest.mark.parametrize("want,args", [(True, (768, False, 10, 1408, 10000, 3334, 4096)), (True, (768, False, 64, 256, 4097, 3072, 4096)),
+                                       (True, (1024, False, 10, 256, 3100, 1550, 3072)), (False, (768, False, 10, 1408, 4200, 2100, 4096)),
+                                       (False, (768, False, 10, 1408, 4096, 4096, 4096)), (False, (768, False, 10, 255, 10000, 3334, 4096)),
+                                       (False, (768, False, 65, 1408, 10000, 3334, 4096)), (False, (764, False, 10, 1408, 10000, 3334, 4096)),
+                                       (False, (768, True, 10, 1408, 10000, 3334, 4096)), (False, (768, False, 10, 1408, 10000, 64, 4096)),
+                                       (False, (1536, False, 10, 1408, 10000, 64, 3072))])
+def test_pacing(waves, want, args):
+    """Long fp32 rows, small working sets, long searches, and a GPU that stays full: a batch of which the scratch array of the
+    allocation-free entry point holds few waves does not keep it so."""
+    assert waves.paced(*args) == want
