@@ -8,11 +8,11 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <thread>
 #include <vector>
 
 #include "pag_internal.h"
 #include "pag_plan.h"
+#include "pag_random.h"
 
 static thread_local std::string g_last_error;
 void pag_set_error(const std::string& msg) { g_last_error = msg; }
@@ -23,76 +23,15 @@ extern "C" const char* pag_last_error(void) { return g_last_error.c_str(); }
         if (!(cond)) { pag_set_error(msg); return (code); } \
     } while (0)
 
-// ---------------------------------------------------------------------------------------------
-// Random structures of the method, drawn on the host once per index (Sec. 3.1; Alg. 1):
-// the orthogonal transform Q from the Haar measure (Gaussian matrix, Gram-Schmidt with
-// re-orthogonalisation) and, per subspace, independently rotated cross-polytopes.
-// Counter-based generator: SplitMix64 on (seed, stream, counter) + Box-Muller.
-// ---------------------------------------------------------------------------------------------
 namespace {
 
-struct Rng {
-    uint64_t state;
-    explicit Rng(uint64_t seed, uint64_t stream) : state(seed * 0x9E3779B97F4A7C15ull + stream * 0xD1B54A32D192ED03ull + 0x2545F4914F6CDD1Dull) {}
-    uint64_t next() {
-        uint64_t z = (state += 0x9E3779B97F4A7C15ull);
-        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-        return z ^ (z >> 31);
-    }
-    double uniform() { return ((double)(next() >> 11) + 0.5) * (1.0 / 9007199254740992.0); }
-    double normal() {
-        const double u1 = uniform(), u2 = uniform();
-        return std::sqrt(-2.0 * std::log(u1)) * std::cos(6.283185307179586476925 * u2);
-    }
-};
-
-// Fills g with normals, two draws each, in order.  The generator's state advances by a constant per draw, so several
-// threads can start where their part of g begins.
-void draw_normals(const Rng& first, std::vector<double>& g) {
-    const size_t threads = g.size() < (1u << 16) ? 1 : std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
-    auto part = [&](size_t lo, size_t hi) {
-        Rng rng = first;
-        rng.state += 2ull * lo * 0x9E3779B97F4A7C15ull;
-        for (size_t i = lo; i < hi; ++i) g[i] = rng.normal();
-    };
-    struct Threads {
-        std::vector<std::thread> all;
-        ~Threads() { for (auto& t : all) t.join(); }
-    } started;
-    started.all.reserve(threads);
-    for (size_t t = 1; t < threads; ++t) started.all.emplace_back(part, g.size() * t / threads, g.size() * (t + 1) / threads);
-    part(0, g.size() / threads);
-}
-
-// Orthonormalise the columns of the dim x dim Gaussian matrix g (column-major) in place:
-// classical Gram-Schmidt with one re-orthogonalisation pass.
-void orthonormalise(std::vector<double>& g, uint32_t dim) {
-    std::vector<double> proj(dim);
-    for (uint32_t j = 0; j < dim; ++j) {
-        double* aj = &g[(size_t)j * dim];
-        for (int pass = 0; pass < 2 && j > 0; ++pass) {
-            for (uint32_t i = 0; i < j; ++i) {
-                const double* qi = &g[(size_t)i * dim];
-                double s = 0.0;
-                for (uint32_t k = 0; k < dim; ++k) s += qi[k] * aj[k];
-                proj[i] = s;
-            }
-            for (uint32_t i = 0; i < j; ++i) {
-                const double* qi = &g[(size_t)i * dim];
-                const double p = proj[i];
-                for (uint32_t k = 0; k < dim; ++k) aj[k] -= p * qi[k];
-            }
-        }
-        double nrm = 0.0;
-        for (uint32_t k = 0; k < dim; ++k) nrm += aj[k] * aj[k];
-        nrm = std::sqrt(nrm);
-        for (uint32_t k = 0; k < dim; ++k) aj[k] /= nrm;
-    }
-}
+using pag_random::Rng;
+using pag_random::draw_normals;
+using pag_random::orthonormalise;
 
 // Q into `out` (dev).  Small transforms are orthogonalised on the host: below d = 192 that takes less than the GPU's
-// 5 d launches.  `rot` keeps the host's copy alive until the stream has been synchronised.
+// 5 d launches.  So are those whose workspace (16 d^2 bytes) the GPU has no room for, to the same bits.  `rot` keeps the host's
+// copy alive until the stream has been synchronised.
 int make_transform(hipStream_t stream, uint32_t d, uint64_t seed, bool permutation, float* out, std::vector<float>& rot) {
     Rng rng(seed, 1);
     if (permutation) {
@@ -105,7 +44,11 @@ int make_transform(hipStream_t stream, uint32_t d, uint64_t seed, bool permutati
     } else {
         std::vector<double> g((size_t)d * d);
         draw_normals(rng, g);
-        if (d >= 192) return pag_orthonormalise(stream, g.data(), d, out);
+        if (d >= 192) {
+            const int rc = pag_orthonormalise(stream, g.data(), d, out);
+            if (rc != PAG_ENOMEM) return rc;
+            (void)hipGetLastError();                    // the failed allocation is dealt with
+        }
         orthonormalise(g, d);
         rot.resize((size_t)d * d);
         // orthonormal columns are as good as rows: rot[j][k] = column j, element k

@@ -64,3 +64,39 @@ def test_transform_bits(d):
     differ = got != want
     assert differ.mean() <= 1e-4, differ.mean()
     assert np.abs(got - want).max() <= 2.0 ** -23
+
+
+@pytest.mark.gpu
+def test_build_without_room_for_the_workspace():
+    """The orthogonalisation's workspace (16 d^2 bytes) does not fit the memory that is left, the index does: the host
+    orthogonalises instead, to the same bits."""
+    import torch
+    from paper_2603_06660_amd import PagIndex
+    d = 2560
+    base = torch.from_numpy(np.random.default_rng(d).standard_normal((64, d), dtype=np.float32)).cuda()
+
+    def rotation():
+        ix = PagIndex.build(base, metric="l2", max_degree=8, num_subspaces=16, ef_construction=20, seed=7)
+        r = ix.export()["rotation"]
+        ix.close()
+        return r
+
+    want = rotation()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    filler = []
+    try:
+        for block in (1 << 30, 48 << 20):                   # until there is less than 48 MB in one piece
+            while True:
+                try:
+                    filler.append(torch.empty(block, dtype=torch.uint8, device="cuda"))
+                except torch.OutOfMemoryError:
+                    break
+        filler.pop()                                        # 48 to 96 MB are left
+        torch.cuda.empty_cache()
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(16 * d * d, dtype=torch.uint8, device="cuda")
+        assert np.array_equal(rotation(), want)
+    finally:
+        filler.clear()
+        torch.cuda.empty_cache()
