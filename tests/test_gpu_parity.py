@@ -3,6 +3,9 @@
 Bars (stated by the benchmark spec): result ids equal on >= 99.9 % of (query, rank) slots, distances within
 1e-5 relative, recall@K within 0.002; integer / index work (codes) bit-exact.  Because both sides
 take every decision in the same precision, the observed agreement is normally 100 %.
+
+Batches of a few hundred queries are searched by several waves per query; tests/test_gpu_one_wave.py holds the search of large
+batches, one wave per query, against the oracle on the same index.
 """
 import numpy as np
 import pytest
@@ -48,8 +51,8 @@ def _assert_search_parity(gix, oix, q, K, efS, gt=None, b=0):
 
 def _check_tests_counter(gix, q, K, efS, gc, oc, search_b=0):
     """`tests` counts the neighbours the projection test was evaluated for.  Short searches (exact LDS seen
-    set) evaluate it for unseen neighbours only, like the oracle.  Long searches consult the second level of
-    the seen set only for neighbours that pass, so their count also holds the seen neighbours that the first
+    set) evaluate it for unseen neighbours only, like the oracle.  Long searches of large batches consult the second
+    level of the seen set only for neighbours that pass, so their count also holds the seen neighbours that the first
     level did not recognise and that failed the test: at most one per exact distance computed and expanded
     node (a seen node is met again through one of its in-edges).  In counting mode
     (PAG_FLAG_EXACT_TEST_COUNT) the second level is consulted first and the count is the oracle's."""
