@@ -567,7 +567,7 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
 // Fills a->waves, the seen-set sizes, the LDS carve-up and the grid if the search is one for teams; a->waves stays 1 if not.
 static int plan_team(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
     pag_team_request r;
-    r.nq = nq; r.others = others; r.store_bytes = nodes * ix->L.d * pag_vec_elem(ix); r.half = ix->vec_half;
+    r.nq = nq; r.others = others; r.store_bytes = nodes * ix->L.d * pag_vec_elem(ix); r.half = ix->vec_half; r.d = ix->L.d;
     r.b = b; r.ef = ef; r.num_cu = (u32)ix->num_cu; r.lds_per_cu = ix->lds_per_cu;
     r.hlog = a->hlog; r.blog = a->blog; r.seen_fixed = ix->seen_log2; r.most_waves = (u32)pag_team_max(b <= 512 ? 8 : 16);
     SearchArgs t = *a;

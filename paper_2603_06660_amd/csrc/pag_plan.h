@@ -13,7 +13,7 @@ struct pag_team_request {
     uint64_t nq;             // queries of the call
     uint64_t others;         // queries of other calls that the GPU searches beside them, see pag_queries_beside
     uint64_t store_bytes;    // of the vectors that the search can reach
-    uint32_t half;           // they are 16-bit floats
+    uint32_t half, d;        // they are 16-bit floats; values to a row
     uint32_t b, ef;
     uint32_t num_cu, lds_per_cu;
     uint32_t hlog, blog;     // the seen set of the one-wave search
@@ -57,7 +57,7 @@ inline uint64_t pag_queries_beside(uint64_t calls, uint64_t queries) { return ca
 //     beyond 2.5 per CU (efS 128, 520 / 777 / 1,000 queries, one wave : team: 80k x 768 1.07 / 0.98 / 0.89, 300k x 128 1.07 / 0.96 /
 //     0.90; K 100, efS 256: 50k x 768 1.10 / 1.00 / 0.96), 3.75 if the rows come from HBM and not from the 256 MB cache (200k
 //     x 768 1.14 / 1.02 / 0.95, 2M x 128 1.12 / 1.06 / 1.02; with 400 MB of rows the two are even), four if they are 16-bit
-//     besides (600k x 768 1.22 / 1.13 / 1.05)
+//     besides (600k x 768 1.22 / 1.13 / 1.05).  16-bit rows of 2560 and more leave the team's kernel short of registers: 0.75 to 0.95
 template <class Lds, class Resident>
 int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
     const uint64_t cus = r.num_cu, load = r.nq + r.others;
@@ -69,7 +69,7 @@ int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& residen
         share = 1; most = 12; least = 4;
     } else if (load > cus && load <= 2 * cus && length >= 48) {
         share = 2; most = 8; least = r.b > 512 ? 4 : 8;
-    } else if (load > 2 * cus && length >= 128 && !large_set) {
+    } else if (load > 2 * cus && length >= 128 && !large_set && !(r.half && r.d >= 2560)) {
         const bool from_hbm = r.store_bytes >= (512ull << 20);
         const uint64_t quarters = (length >= 256 && r.b <= 64) || (from_hbm && r.half) ? 16 : from_hbm ? 15 : 10;
         if (4 * load > quarters * cus) return 0;

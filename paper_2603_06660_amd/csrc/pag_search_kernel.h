@@ -1664,8 +1664,11 @@ __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
 }
 
 // The same with several waves per query, for batches that would leave the GPU mostly idle.
+// Registers: 128 a lane, four waves per SIMD, where the rows in flight and the query allow it (at most 51 dwords of spill, with six
+// chunks a row), else the 168 that twelve waves leave (16-bit rows of 2560 and 3072 spill 98 dwords either way, and with
+// 128 registers every wave feels it: one query per CU 1.17 times as fast as one wave, 1.35 with 168, two per CU 0.85).
 template <int NQ, int NW, int VM>
-__attribute__((amdgpu_waves_per_eu(NQ <= 6 && NW <= 2 ? 4 : 2, 8)))
+__attribute__((amdgpu_waves_per_eu(NW <= 2 && (NQ <= 4 || (NQ == 6 && VM != 1)) ? 4 : 2, 8)))
 __global__ void __launch_bounds__(64 * pag_team_max(NW)) k_search_team(const SearchArgs A) {
     extern __shared__ __align__(64) unsigned char smem[];
     Wave<NQ, NW, VM, PAG_MAX_CW, true> w(A, smem, (int)(threadIdx.x & 63), (int)uniform(threadIdx.x >> 6), (int)(blockDim.x >> 6));

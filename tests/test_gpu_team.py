@@ -72,6 +72,7 @@ CASES = [
     (2000, 2048, 64, 33, "ip", False, 300, 900, 12, 1),
     (1500, 2304, 64, 32, "ip", True, 20, 100, 12, 1),
     (1500, 3072, 64, 32, "ip", False, 10, 128, 12, 1),
+    (1500, 3072, 64, 32, "ip", True, 10, 200, 12, 1),
     (3000, 96, 8, 32, "l2", False, 600, 1200, 8, 4),
     (3000, 768, 32, 32, "ip", False, 1000, 3000, 8, 4),
 ]

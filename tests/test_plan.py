@@ -10,17 +10,18 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "pag_plan.h"
-// arguments: nq others store_bytes half b ef waves_per_cu; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
+// arguments: nq others store_bytes half b ef waves_per_cu d; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
 // or: calls queries, for pag_queries_beside; or one number, for pag_resident: of a single wave, of a team;
-// or d half b ef nq waves room and a word, for pag_paced
+// or d half b ef nq waves room and two more, for pag_paced
 int main(int n, char** v) {
     if (n == 3) { std::printf("0 %llu\n", (unsigned long long)pag_queries_beside(strtoull(v[1], 0, 10), strtoull(v[2], 0, 10))); return 0; }
     if (n == 2) { std::printf("%d %d\n", pag_resident(atoi(v[1]), 256, 1), pag_resident(atoi(v[1]), 256, 4)); return 0; }
-    if (n == 9) { std::printf("%d\n", (int)pag_paced(atoi(v[1]), atoi(v[2]) != 0, atoi(v[3]), atoi(v[4]), atoi(v[5]), atoi(v[6]), atoi(v[7]))); return 0; }
+    if (n == 10) { std::printf("%d\n", (int)pag_paced(atoi(v[1]), atoi(v[2]) != 0, atoi(v[3]), atoi(v[4]), atoi(v[5]), atoi(v[6]), atoi(v[7]))); return 0; }
     pag_team_request r = {};
     r.nq = strtoull(v[1], 0, 10); r.others = strtoull(v[2], 0, 10); r.store_bytes = strtoull(v[3], 0, 10);
     r.half = atoi(v[4]); r.b = atoi(v[5]); r.ef = atoi(v[6]);
     const uint32_t per_cu = atoi(v[7]);
+    r.d = atoi(v[8]);
     r.num_cu = 256; r.lds_per_cu = 163840; r.most_waves = 12;
     r.hlog = 9; r.blog = r.b + 8 * std::max(r.ef, r.b) > 1024 ? 15 : 0;
     pag_team_plan p;
@@ -42,12 +43,12 @@ def waves(tmp_path_factory):
     def beside(calls, queries):
         return int(subprocess.check_output([str(d / "plan"), str(calls), str(queries)], text=True).split()[1])
 
-    def run(nq, others=0, store=1 << 30, half=0, b=10, ef=256, per_cu=16):
-        rc, w = subprocess.check_output([str(d / "plan")] + [str(x) for x in (nq, others, store, half, b, ef, per_cu)], text=True).split()
+    def run(nq, others=0, store=1 << 30, half=0, b=10, ef=256, per_cu=16, d_=768):
+        rc, w = subprocess.check_output([str(d / "plan")] + [str(x) for x in (nq, others, store, half, b, ef, per_cu, d_)], text=True).split()
         assert rc == "0"
         return int(w)
     run.beside = beside
-    run.paced = lambda *a: bool(int(subprocess.check_output([str(d / "plan")] + [str(int(x)) for x in a] + ["paced"], text=True)))
+    run.paced = lambda *a: bool(int(subprocess.check_output([str(d / "plan")] + [str(int(x)) for x in a] + ["paced", ""], text=True)))
     run.resident = lambda per_cu: [int(x) for x in subprocess.check_output([str(d / "plan"), str(per_cu)], text=True).split()]
     return run
 
@@ -73,6 +74,7 @@ def test_four_waves(waves, most, store, half, b, ef):
     kw = dict(store=store, half=half, b=b, ef=ef)
     assert waves(513, **kw) == (4 if most > 512 else 1)
     assert waves(most, **kw) == (4 if most > 512 else 8) and waves(most + 1, **kw) == 1
+    assert waves(513, d_=2560, **kw) == (4 if most > 512 and not half else 1)      # long 16-bit rows: too few registers
 
 
 @pytest.mark.parametrize("calls,queries,want", [(0, 0, 0), (1, 64, 64), (3, 1000, 1000), (7, 448, 192), (7, 1792, 768), (15, 3 * 2 ** 31, 3 * 2 ** 31 // 5)])
