@@ -1,7 +1,8 @@
-// PRT-TFB best-first search (Alg. 2, Sec. 3.3): one wavefront owns one query from the
-// entry nodes to the final top-K.  Included by the instantiation units pag_search_nq*_cw*.hip.
+// PRT-TFB best-first search (Alg. 2, Sec. 3.3).  In k_search one wavefront owns one query from the entry nodes to the final
+// top-K; in k_search_team the waves of a workgroup share a query (see run_team; pag_plan.h has the rule).  Included by the
+// instantiation units pag_search_nq*_cw*.hip and pag_search_team_nq*.hip.
 //
-// Wave-level data placement (64 lanes):
+// Wave-level data placement (64 lanes; a team's wave 0 holds W, R_L and the rings, its wave 1 keeps the seen set):
 //   query        registers, NQ float4 per lane (element chunk c*64+lane)
 //   W            registers, NW slots per lane (b <= 64 NW).  Up to 128 nodes (NW <= 2): sorted ascending by key, rank r
 //                in slot r/64 of lane r%64.  Above (NW >= 4): unsorted, entry i in slot i/64 of lane i%64; the node to
@@ -39,10 +40,10 @@ __device__ __forceinline__ u64 rdlane64(u64 v, int l) {
     u32 lo = rdlane((u32)v, l), hi = rdlane((u32)(v >> 32), l);
     return ((u64)hi << 32) | lo;
 }
-// The workgroup is a single wavefront and its LDS operations execute in program order, so all that
-// cross-lane LDS traffic needs is that the compiler keeps the accesses in place and that the LDS
-// queue has drained.  Unlike __syncthreads() this does not wait for global loads in flight
-// (prefetched records, seen-set words), which is the point.
+// Orders the LDS accesses of one wavefront: its LDS operations execute in program order, so all that traffic between its lanes
+// needs is that the compiler keeps the accesses in place and that the LDS queue has drained.  Unlike __syncthreads() this does
+// not wait for global loads in flight (prefetched records, seen-set words), which is the point.  Between the waves of a team
+// stands team_barrier.
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
@@ -1187,7 +1188,9 @@ struct Wave {
     //           closest passer, if it enters W and is closer than W's closest unvisited member, else that member, whose
     //           neighbours are screened already; a passer's are screened now.  Only the threshold has to wait.
     // Where a round has ended in between the node is another one, and it is screened in a phase of its own.
-    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.6 with twelve; a trip to memory takes 0.55.
+    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.6 with twelve (5,850 clocks: a row wave 1,120 to the requests,
+    // 1,760 for rows, distances and ranks, 590 for the slowest of them, 2,380 for wave 0: 840 merge, 370 post, 440 round
+    // ends, 290 + 160 the rest, 280 at barriers); a trip to memory takes 0.55 us.
     enum : u32 {
         TM_QUERY = 0,                                  // query number, PAG_EMPTY: no more
         TM_NODE, TM_NODE_DIST, TM_FAR_LO, TM_FAR_HI,   // wave 0: the node to expand (PAG_EMPTY: the search is over), W's farthest
