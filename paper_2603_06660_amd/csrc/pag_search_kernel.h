@@ -1532,13 +1532,8 @@ struct Wave {
                 }
                 const u32 id = team[TM_ID + lane];
                 const float est = __uint_as_float(team[TM_EST + lane]);
-                bool cand = id != PAG_EMPTY;
-                bool pass = passes(cand, est, threshold(far));
-                if (A.flags & PAG_SEARCH_DISTINCT) {
-                    const bool first = first_of_id(id, pass);
-                    pass = pass && first;
-                    cand = cand && first;
-                }
+                bool pass = passes(id != PAG_EMPTY, est, threshold(far));
+                if (A.flags & PAG_SEARCH_DISTINCT) { const bool first = first_of_id(id, pass); pass = pass && first; }
                 const u64 mask = __ballot(pass);
                 const u32 np = (u32)__popcll(mask);
                 PAG_MARK(2);
@@ -1557,7 +1552,7 @@ struct Wave {
                         if (owed) merge_rings(M);
                     }
                     if constexpr (KEEPS_SEEN) {
-                        s_tests += (u32)__popcll(__ballot(cand));
+                        s_tests += (u32)__popcll(__ballot(id != PAG_EMPTY));
                         s_passes += np;
                         if (np) mark_seen(id, np, pass);
                         if (second != PAG_EMPTY) unseen = find_unseen();
