@@ -126,7 +126,9 @@ typedef struct {
     uint64_t tests;              /* neighbours the projection test was evaluated for: the unseen ones; in long
                                     searches of large batches also already-seen ones that only the second
                                     level of the seen set would have recognised (it is consulted for passing
-                                    neighbours only), unless PAG_FLAG_EXACT_TEST_COUNT is set */
+                                    neighbours only), unless PAG_FLAG_EXACT_TEST_COUNT is set.  A searcher beside an
+                                    insertion can meet a record that lists a neighbour twice, and small batches then
+                                    count it twice */
     uint64_t passes;             /* of those, how many passed (gamma = passes / tests) */
     uint64_t exact;              /* exact distances computed, entry nodes included */
     uint64_t rounds;             /* TFB rounds */
