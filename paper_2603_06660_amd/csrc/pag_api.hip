@@ -633,7 +633,8 @@ static int search_plan(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b
 int pag_search_common(pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
     int rc = search_plan(ix, nq, others, nodes, b, ef, n_limit, a, lds, grid);
     if (rc) return rc;
-    const u64 need = (u64)*grid * a->bitmap_words;
+    // no more workgroups are launched than there are queries, whichever plan they get
+    const u64 groups = std::min<u64>(nq, (u64)*grid), need = groups * a->bitmap_words;
     if (ix->ws_bitmap_cap < need) {
         // a fresh buffer starts dirty: clear it once; every wave leaves its slice clean afterwards
         if ((rc = ensure_ws(&ix->ws_bitmap, &ix->ws_bitmap_cap, need))) return rc;
@@ -641,7 +642,7 @@ int pag_search_common(pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 e
     }
     a->bitmap = ix->ws_bitmap;
     if (b > PAG_LDS_RING_MAX_B) {
-        if ((rc = ensure_ws(&ix->ws_rings, &ix->ws_rings_cap, (u64)*grid * 3 * (u64)(a->ring_mask + 1)))) return rc;
+        if ((rc = ensure_ws(&ix->ws_rings, &ix->ws_rings_cap, groups * 3 * (u64)(a->ring_mask + 1)))) return rc;
         a->rings = ix->ws_rings;
     }
     return PAG_OK;

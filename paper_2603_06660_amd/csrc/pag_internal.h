@@ -130,7 +130,7 @@ struct SearchArgs {
     u32 off_hash, off_bloom, off_sa, off_sb, off_rf, off_rt, off_team;   // LDS offsets (bytes)
     u32 waves;               // waves per query; above 1 the kernel for teams runs
     u32 ring_mask;           // rings live in power-of-two buffers of >= b slots; only the last b pushes are valid
-    u64* rings;              // [grid * 3 * (ring_mask + 1)] per-wave R_F, R_T and R_L when b > PAG_LDS_RING_MAX_B, else unused
+    u64* rings;              // [min(grid, nq) * 3 * (ring_mask + 1)] per-wave R_F, R_T and R_L when b > PAG_LDS_RING_MAX_B, else unused
     long long* out_ids;      // [nq * K]       (search mode)
     float* out_dists;        // [nq * K]
     float out_scale;         // 1 for L2, 0.5 for IP / COS
@@ -141,7 +141,7 @@ struct SearchArgs {
     const u32* order;        // [nq] the order in which the waves take the queries (null: as numbered)
     u32* qcounter;
     u64* counters;
-    u32* bitmap;             // [grid * bitmap_words]
+    u32* bitmap;             // [min(grid, nq) * bitmap_words]
     u64 bitmap_words;
 };
 

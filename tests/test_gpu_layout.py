@@ -38,6 +38,35 @@ def test_reserved_room_does_not_change_the_plan():
     assert layouts[0] == layouts[1] and layouts[0][8][0] == 1       # 3 to a CU, efS 128, rows in the cache
 
 
+def test_workspaces_are_sized_by_the_batch():
+    """A small batch takes the seen-set bitmaps of its own queries, not of all that the GPU could hold at a time, also where it
+    gets one wave per query (as it does beside other calls), and its answers stay right when the next batches are larger."""
+    import torch
+    from paper_2603_06660_amd import PagIndex
+    d, capacity = 16, 1 << 20
+    rng = np.random.default_rng(3)
+    rows = lambda n: torch.from_numpy(rng.standard_normal((n, d), dtype=np.float32)).cuda()
+    kw = dict(metric="l2", max_degree=8, num_subspaces=4, ef_construction=20)
+    base = rows(2000)
+    ix, small = PagIndex.build(base, capacity=capacity, **kw), PagIndex.build(base, **kw)
+    q = rows(3000)
+    ix.search(q[:8], 1, 10)                                             # everything but the bitmaps' growth
+    assert ix.search_layout(100, 1, 10) == (1, 100)
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    ix.search(q[:100], 1, 10)
+    torch.cuda.synchronize()
+    assert free0 - torch.cuda.mem_get_info()[0] <= 100 * capacity // 8 + (16 << 20)
+    s = ix.searcher()
+    for nq, K, efS in ((100, 1, 10), (300, 10, 900), (3000, 10, 900), (50, 10, 900), (40, 300, 400), (2000, 300, 400)):
+        want = small.search(q[:nq], K, efS)
+        for search in (ix.search, s.search):
+            got = search(q[:nq], K, efS)
+            torch.cuda.synchronize()
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (nq, K, efS)
+    s.close(); ix.close(); small.close()
+
+
 def test_waves_follow_what_the_gpu_is_searching():
     """A single query gets a team while nothing else is searched, one wave while a large batch is, and a team beside a batch
     that fills the GPU (it has its turn between two of them)."""
