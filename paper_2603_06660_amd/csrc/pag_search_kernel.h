@@ -1631,6 +1631,7 @@ struct Wave {
 // Long rows: left to itself the compiler keeps the two rows in flight in as many registers as it likes and gives up a wave for
 // them; with the line stated it spills at most 24 dwords.  Kernel times with and without, 1,030 to 8,000 queries: 3072-d at
 // K 200 5.16 -> 3.53 ms, 2560-d at K 400 1.4-1.5 times as fast, 16-bit rows of 1280 1.0-1.47 times, of 2816 at K 400 1.2-1.6.
+// Up to one wave per SIMD it costs fp32 rows of 3072 5 % (900 queries, efS 512: 4.48 -> 4.73 ms; masked early 4.94).
 constexpr int pag_search_occupancy(int nq, int nw, int vm, int cw) {
     if (nq <= 4) {
         if (nw > 2) return nw >= 16 ? 2 : 3;
