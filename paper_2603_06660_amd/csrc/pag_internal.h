@@ -20,7 +20,7 @@ typedef uint32_t u32;
 #define PAG_LDS_RING_MAX_B 128  // larger working sets keep R_F / R_T in HBM (the kernel's NW > 2 instantiations)
 #define PAG_MAX_DEG 64      // one neighbour per lane
 #define PAG_MAX_CW 8        // code dwords per neighbour: up to 64 subspaces
-#define PAG_TEAM_WORDS 512  // LDS words that a team shares
+#define PAG_TEAM_WORDS 320  // LDS words that a team shares
 #define PAG_SEARCH_DISTINCT (1u << 30)  // SearchArgs.flags, internal: a hop drops an id that an earlier slot of the record also lists
 #define PAG_SEARCH_PACED (1u << 29)     // SearchArgs.flags, internal: a wave asks for rows only when those before have arrived (see pag_paced)
 #define PAG_STATIC_SCRATCH_BYTES (48u << 20)   // the device array behind pag_search_static, per GPU

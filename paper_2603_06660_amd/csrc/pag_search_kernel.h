@@ -46,6 +46,11 @@ __device__ __forceinline__ u64 rdlane64(u64 v, int l) {
 // stands team_barrier.
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// the value that lane l holds, in every lane
+__device__ __forceinline__ double lane_value(double x, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
 __device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
 
 __device__ __forceinline__ u32 hash_slot(u32 id, u32 hlog) { return (id * 2654435761u) >> (32 - hlog); }
@@ -83,20 +88,25 @@ __device__ __forceinline__ void bloom_set(u32* B, u32 blog, u32 id) {
     atomicOr(&B[h2 >> 5], 1u << (h2 & 31));
 }
 
+// The rank of this lane's key among the n <= 64 of lanes 0 .. n - 1 (the other lanes: the largest key): broadcast four at a
+// time, their comparisons do not wait for each other, nor for LDS.
+__device__ __forceinline__ u32 rank_among(u64 k, u32 n) {
+    u32 r = 0;
+    for (u32 j = 0; j < n; j += 4) {
+        u64 o[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) o[g] = rdlane64(k, (int)j + g);     // beyond n: the largest key, smaller than none
+#pragma unroll
+        for (int g = 0; g < 4; ++g) r += (o[g] < k) ? 1u : 0u;
+    }
+    return r;
+}
+
 // dst[rank] = src[i], rank = number of smaller keys; keys are distinct.  Quadratic: for short lists.
-// Up to 64 keys sit in one register and are broadcast from there, four at a time: their comparisons do not wait for each
-// other, nor for LDS.
 __device__ __forceinline__ void rank_sort(const u64* src, u64* dst, u32 n, int lane) {
     if (n <= 64) {
         const u64 k = (u32)lane < n ? src[lane] : PAG_KEY_INVALID;
-        u32 r = 0;
-        for (u32 j = 0; j < n; j += 4) {
-            u64 o[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) o[g] = rdlane64(k, (int)j + g);     // beyond n: the largest key, smaller than none
-#pragma unroll
-            for (int g = 0; g < 4; ++g) r += (o[g] < k) ? 1u : 0u;
-        }
+        const u32 r = rank_among(k, n);
         if ((u32)lane < n) dst[r] = k;
         return;
     }
@@ -252,6 +262,8 @@ struct Wave {
     u64 W[NW];
     u64 RL[NW > 2 ? 1 : NW];        // unused for large working sets: their R_L is SA[0, nRL)
     u32 nW, nRL;
+    u64 done[NW > 2 ? 1 : NW];      // TEAM, wave 0: W of the last round, if it has yet to enter R_L, ...
+    u32 n_done;                     // ... how many keys that are
     u32 cntF, hdF, cntT, hdT;       // rings: valid entries (<= b) and total pushes; slot = push number & ring mask
     u32 n_hash, n_spill;
     u32 n_cand;                     // indexing mode: entries of R_L written so far
@@ -571,34 +583,20 @@ struct Wave {
 #pragma unroll
         for (int s = 0; s < NW; ++s) R.cntW[s] = 0;
         u32 cP = 0, cPW = 0;
-        // MU passers at a time: their broadcasts and counts do not depend on each other (a missing one counts as larger
-        // than everything)
-        constexpr int MU = TEAM ? 4 : 1;    // one wave per query: others fill the gaps
         for (u64 m = mask; m;) {
-            u64 k[MU];
-            int p[MU];
+            const int p = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            const u64 k = rdlane64(R.pk, p);
+            u32 c = 0;
 #pragma unroll
-            for (int g = 0; g < MU; ++g) {
-                p[g] = m ? __ffsll((long long)m) - 1 : -1;
-                k[g] = m ? rdlane64(R.pk, p[g]) : PAG_KEY_INVALID;
-                m &= m - 1;
+            for (int s = 0; s < NW; ++s) {
+                // keys are distinct, so one comparison tells both sides (an empty slot counts as larger)
+                const bool lt = W[s] < k;
+                c += (u32)__popcll(__ballot(lt));
+                R.cntW[s] += lt ? 0u : 1u;
             }
-            u32 c[MU];
-#pragma unroll
-            for (int g = 0; g < MU; ++g) {
-                c[g] = 0;
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    // keys are distinct, so one comparison tells both sides (an empty slot counts as larger)
-                    const bool lt = W[s] < k[g];
-                    c[g] += (u32)__popcll(__ballot(lt));
-                    R.cntW[s] += lt ? 0u : 1u;
-                }
-                cP += (k[g] < R.pk) ? 1u : 0u;
-            }
-#pragma unroll
-            for (int g = 0; g < MU; ++g)
-                if (lane == p[g]) cPW = c[g];
+            cP += (k < R.pk) ? 1u : 0u;
+            if (lane == p) cPW = c;
         }
         R.cP = cP;
         R.rP = cP + cPW;
@@ -656,7 +654,7 @@ struct Wave {
         } else {
             Ranks R;
             rank(R, id_lane, mask, pass, dist);
-            if constexpr (!TEAM) request_next(R.cntW, pass, R.cP, R.rP, id_lane);
+            request_next(R.cntW, pass, R.cP, R.rP, id_lane);
             settle(R, np, pass);
         }
     }
@@ -819,7 +817,7 @@ struct Wave {
         for (int s = 0; s < NW; ++s) W[s] = PAG_KEY_INVALID;
 #pragma unroll
         for (int s = 0; s < (BIG ? 1 : NW); ++s) RL[s] = PAG_KEY_INVALID;
-        nW = nRL = 0;
+        nW = nRL = n_done = 0;
         cntF = hdF = cntT = hdT = 0;
         n_hash = n_spill = 0;
         Hk = PAG_KEY_INVALID;
@@ -955,14 +953,16 @@ struct Wave {
     // searches that overlap an insertion: a record read between two states of a reverse-edge pass may
     // list one node in two slots; the first slot stands, the merge needs distinct keys
     __device__ __forceinline__ bool first_of_id(u32 id, bool pass) const {
-        bool first = true;
-        for (u64 m = __ballot(pass); m;) {
+        const u64 all = __ballot(pass);
+        u64 again = 0;
+        for (u64 m = all; m;) {
             const int p = __ffsll((long long)m) - 1;
             m &= m - 1;
-            const u64 same = __ballot(lane > p && id == rdlane(id, p));
-            if (same) { m &= ~same; if ((same >> lane) & 1ull) first = false; }
+            const u64 same = __ballot(id == rdlane(id, p)) & m;      // slots behind p only are left in m
+            m &= ~same;
+            again |= same;
         }
-        return first;
+        return !((again >> lane) & 1ull);
     }
 
     // ---- round end (Alg. 2): W -> R_L, clear W; merge + sort rings; refill W; rest -> R_T ----
@@ -994,6 +994,11 @@ struct Wave {
                 const u32 idx = s * 64 + lane;
                 if (idx < nRL) SA[idx] = x[s];
             }
+        } else if constexpr (TEAM) {
+            // kept until the others are busy with rows (see keep_best)
+#pragma unroll
+            for (int s = 0; s < NW; ++s) done[s] = W[s];
+            n_done = nW;
         } else {
 #pragma unroll
             for (int s = 0; s < NW; ++s) {
@@ -1055,6 +1060,24 @@ struct Wave {
             }
             cntT = rest; hdT = rest;
             cntF = 0; hdF = 0;
+        } else if (cntF + cntT <= 64) {
+            // in registers: one key a lane
+            const u32 n = cntF + cntT;
+            u64 x = PAG_KEY_INVALID;
+            if ((u32)lane < cntF) x = RF[(hdF - cntF + lane) & A.ring_mask];
+            else if ((u32)lane < n) x = RT[(hdT - cntT + (lane - cntF)) & A.ring_mask];
+            const u32 r = rank_among(x, n);
+            if ((u32)lane < n) SA[r] = x;
+            lds_sync();
+            if ((u32)lane < n) x = SA[lane];
+            nW = n < b ? n : b;
+            W[0] = (u32)lane < nW ? x : PAG_KEY_INVALID;
+#pragma unroll
+            for (int s = 1; s < NW; ++s) W[s] = PAG_KEY_INVALID;
+            if ((u32)lane >= nW && (u32)lane < n) RT[n - 1 - lane] = x;      // the rest, worst first
+            cntT = hdT = n - nW;
+            cntF = 0; hdF = 0;
+            lds_sync();
         } else {
             for (u32 i = lane; i < cntF; i += 64) SA[i] = RF[(hdF - cntF + i) & A.ring_mask];
             for (u32 i = lane; i < cntT; i += 64) SA[cntF + i] = RT[(hdT - cntT + i) & A.ring_mask];
@@ -1180,32 +1203,32 @@ struct Wave {
     // wave 0 keeps W and the rings, wave 1 the seen set, wave 2 (wave 1 too, in teams of less than six) computes the
     // estimates, and the other waves fetch the rows.  A hop has two phases between barriers:
     //   rows    every wave reads the node's neighbours, their estimates and the threshold from LDS and derives the
-    //           passers, whose rows are fetched all at once.  Meanwhile wave 0 finishes the last merge, wave 1 enters the
-    //           passers into the seen set, and the neighbours of W's closest unvisited member are screened ahead.  A
-    //           barrier inside the phase, while the rows are on their way, makes W's keys available to all: each wave
-    //           ranks its passers' keys against them as they are computed;
-    //   lists   wave 0 rebuilds W from the ranks and pops the next node.  Which node that will be is known before: the
-    //           closest passer, if it enters W and is closer than W's closest unvisited member, else that member, whose
-    //           neighbours are screened already; a passer's are screened now.  Only the threshold has to wait.
-    // Where a round has ended in between the node is another one, and it is screened in a phase of its own.
-    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.6 with twelve (5,850 clocks: a row wave 1,120 to the requests,
-    // 1,760 for rows, distances and ranks, 590 for the slowest of them, 2,380 for wave 0: 840 merge, 370 post, 440 round
-    // ends, 290 + 160 the rest, 280 at barriers); a trip to memory takes 0.55 us.
+    //           passers, whose rows are fetched all at once, their records behind them.  Meanwhile wave 0 does what the last
+    //           hop left it (ring pushes, a finished round's entry into R_L), wave 1 enters the passers into the seen set, and the
+    //           neighbours of W's closest unvisited member are screened ahead;
+    //   lists   wave 0 enters the passers that are closer than W's farthest member and pops the next node.  Which node that will
+    //           be is known before: the closest passer, if it enters W and is closer than W's closest unvisited member (half of
+    //           the hops at b = 10), else that member, whose neighbours are screened already; a passer's are screened now.
+    //           Only the threshold has to wait.
+    // Where a round has ended in between (every eleventh hop at b = 10) the node is another one, and it is screened in a phase
+    // of its own.
+    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.2 with twelve (5,000 clocks: rows 2,800, of which a trip to
+    // memory is 1,200, wave 0's lists 1,400, the rest posting, reading what is posted, barriers).  While every row wave also
+    // ranked its passers against W for a merge by scatter through LDS, and a record was first asked for when its node was
+    // expanded, it was 2.6.
     enum : u32 {
         TM_QUERY = 0,                                  // query number, PAG_EMPTY: no more
-        TM_NODE, TM_NODE_DIST, TM_FAR_LO, TM_FAR_HI,   // wave 0: the node to expand (PAG_EMPTY: the search is over), W's farthest
-        TM_SECOND, TM_SECOND_DIST,                     // wave 0: W's closest unvisited member after that (PAG_EMPTY: none)
-        TM_COUNT,                                      // wave 0: members of W, whose keys lie in SA
-        TM_SCREENED,                                   // wave 1: the node whose neighbours are screened
         TM_SPILLED,                                    // wave 1: the search has used its bitmap
-        TM_MIN = 16,                                   // u64: the smallest key of the hop's passers
+        // four words wave 0: the node to expand (PAG_EMPTY: the search is over) and its distance, W's farthest
+        TM_NODE = 4, TM_NODE_DIST, TM_FAR_LO, TM_FAR_HI,
+        // two words wave 0: W's closest unvisited member after that (PAG_EMPTY: none); wave 1: the node whose neighbours are screened
+        TM_SECOND = 8, TM_SECOND_DIST, TM_SCREENED,
+        TM_MIN = 16,                                   // u64 per hop parity: the smallest key of the hop's passers
         TM_ID = 64,                                    // wave 1, per neighbour slot: id (PAG_EMPTY: not an unseen node)
         TM_EST = 128,                                  // wave 2, per neighbour slot: estimate
-        TM_KEY = 192,                                  // u64: keys of the hop's passers, in slot order
-        TM_BEFORE = 320,                               // per passer: members of W that are closer
-        TM_CLOSER = 384                                // per member of W (NW <= 2): passers that are closer
+        TM_KEY = 192                                   // u64: keys of the hop's passers, in slot order
     };
-    static_assert(TM_CLOSER + 128 <= PAG_TEAM_WORDS, "team words");
+    static_assert(TM_KEY + 128 <= PAG_TEAM_WORDS, "team words");
 
     // raw barrier: unlike __syncthreads() it leaves global loads in flight
     __device__ __forceinline__ void team_barrier() const {
@@ -1219,57 +1242,50 @@ struct Wave {
 
     __device__ __forceinline__ u32 team_index(u64 mask) const { return (u32)__popcll(mask & ((1ull << lane) - 1)); }
     __device__ __forceinline__ u64* team_keys() const { return (u64*)(team + TM_KEY); }
-    __device__ __forceinline__ u64* team_min() const { return (u64*)(team + TM_MIN); }
+    __device__ __forceinline__ u64* team_min(u32 hop) const { return (u64*)(team + TM_MIN) + (hop & 1u); }
 
-    // This wave's share of the rows of the lanes in `mask`, TR of them in flight at a time, and the inner barrier of the
-    // rows phase.  The rows of a wave are reduced together: one row alone is a chain of dependent instructions.
+    // This wave's share of the rows of the lanes in `mask`, TR of them in flight at a time.  The rows of a wave are reduced
+    // together: one row alone is a chain of dependent instructions.
     static constexpr int TR = NQ * (int)sizeof(Chunk) <= 48 ? 4 : (NQ * (int)sizeof(Chunk) <= 96 ? 2 : 1);
 
-    // keys of G rows (those with i < r exist), and their ranks against W's keys w
+    // keys of G rows (those with i < r exist)
     template <int G>
-    __device__ __forceinline__ void team_reduce(const Chunk (&v)[TR][NQ], const u32 (&id)[TR], const u64 (&w)[NW > 2 ? 1 : NW], u32 at, u32 step, u32 r) const {
+    __device__ __forceinline__ void team_reduce(const Chunk (&v)[TR][NQ], const u32 (&id)[TR], u32 at, u32 step, u32 r, u32 hop) const {
         double acc[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) acc[g] = lane_partial(v[g]);
         const double tot = fold_sum<G>(acc);                // lanes g * 64 / G ...: the total of row g
-        u32 my_id = id[0], before = 0;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const u32 bits = __float_as_uint((float)fold_total<G>(tot, g));
-            if (g > 0 && lane >= g * (64 / G)) my_id = id[g];
-            if constexpr (!BIG) {
-                if ((u32)g < r) {
-                    const u64 key = ((u64)bits << 32) | ((u64)id[g] << 1);
-                    u32 c = 0;
-#pragma unroll
-                    for (int s = 0; s < NW; ++s) {
-                        const bool lt = w[s] < key;
-                        c += (u32)__popcll(__ballot(lt));
-                        if (!lt) atomicAdd(&team[TM_CLOSER + s * 64 + lane], 1u);
-                    }
-                    if (lane >= g * (64 / G)) before = c;
-                }
-            }
-        }
         const u32 g = (u32)lane / (64 / G);
+        u32 my_id = id[0];
+#pragma unroll
+        for (u32 i = 1; i < G; ++i) {
+            u32 other = id[i];
+            asm volatile("" : "+s"(other));                 // or the compiler indexes the ids in scratch
+            my_id = g == i ? other : my_id;
+        }
         if ((u32)lane % (64 / G) == 0 && g < r) {
-            const u64 key = ((u64)__float_as_uint((float)tot) << 32) | ((u64)my_id << 1);
+            const u32 bits = __float_as_uint((float)tot);       // a NaN of either sign: the largest distance
+            const u64 key = ((u64)(bits < 0x7FC00000u ? bits : 0x7FC00000u) << 32) | ((u64)my_id << 1);
             team_keys()[at + g * step] = key;
-            team[TM_BEFORE + at + g * step] = before;
-            atomicMin((unsigned long long*)team_min(), (unsigned long long)key);
+            atomicMin((unsigned long long*)team_min(hop), (unsigned long long)key);
         }
     }
 
-    __device__ __forceinline__ void team_rows(u32 id_lane, u64 mask) const {
+    // Half of the nodes that are expanded are passers of the hop before: the row's record is asked for behind it, one lane per
+    // 128-byte line, so that the caches have it when the node is screened (teams of six and more: smaller ones fill the GPU, and
+    // then the traffic costs more; without a branch, which would wait for it).  Returns something of it, to be waited for later.
+    __device__ __forceinline__ u32 team_rows(u32 id_lane, u64 mask, u32 hop) const {
         const u32 first = split() ? 3u : 2u;                // the first wave that fetches rows
         const u32 n = (u32)__popcll(mask), step = (u32)nwaves - first;
         const u32 mine = ((mask >> lane) & 1ull) ? team_index(mask) : PAG_EMPTY;
-        u32 at = (u32)wave - first;
-        u64 w[NW > 2 ? 1 : NW];
-        bool joined = false;
-        do {
+        const bool ahead = split();
+        const u32 line = ahead && (u32)lane * 128u < A.rec_bytes ? (u32)lane * 128u : 0u;
+        const u64 stride = ahead ? A.rec_bytes : (u64)A.d * (HALF ? 2 : 4);
+        const char* store = ahead ? (const char*)A.rec : (const char*)A.vec;
+        u32 touched = 0;
+        for (u32 at = (u32)wave - first; at < n; at += TR * step) {
             Chunk v[TR][NQ];
-            u32 id[TR], r = 0;
+            u32 id[TR], word[TR], r = 0;
 #pragma unroll
             for (int g = 0; g < TR; ++g) {
                 id[g] = 0;
@@ -1279,20 +1295,15 @@ struct Wave {
                     ++r;
                 }
             }
-            if (!joined) {
-                team_barrier();
-                joined = true;
-                if constexpr (!BIG) {
-                    const u32 count = uniform(team[TM_COUNT]);
 #pragma unroll
-                    for (int s = 0; s < NW; ++s) w[s] = (u32)(s * 64 + lane) < count ? SA[s * 64 + lane] : PAG_KEY_INVALID;
-                }
-            }
-            if (TR >= 4 && r > 2) { if constexpr (TR >= 4) team_reduce<4>(v, id, w, at, step, r); }
-            else if (TR >= 2 && r > 1) { if constexpr (TR >= 2) team_reduce<2>(v, id, w, at, step, r); }
-            else if (r) team_reduce<1>(v, id, w, at, step, r);
-            at += TR * step;
-        } while (at < n);
+            for (int g = 0; g < TR; ++g) word[g] = *(const u32*)(store + (u64)((u32)g < r ? id[g] : id[0]) * stride + line);
+            if (TR >= 4 && r > 2) { if constexpr (TR >= 4) team_reduce<4>(v, id, at, step, r, hop); }
+            else if (TR >= 2 && r > 1) { if constexpr (TR >= 2) team_reduce<2>(v, id, at, step, r, hop); }
+            else team_reduce<1>(v, id, at, step, r, hop);
+#pragma unroll
+            for (int g = 0; g < TR; ++g) touched |= word[g];
+        }
+        return touched;
     }
 
     // key of W's closest unvisited member, which stays unvisited
@@ -1315,12 +1326,35 @@ struct Wave {
     // wave 0: what the other waves need to know of W
     __device__ __forceinline__ void post(u64 node, u64 far, u64 second) const {
         if (lane == 0) {
-            team[TM_NODE] = node != PAG_KEY_INVALID ? (u32)node >> 1 : PAG_EMPTY;
-            team[TM_NODE_DIST] = (u32)(node >> 32);
-            team[TM_FAR_LO] = (u32)far; team[TM_FAR_HI] = (u32)(far >> 32);
-            team[TM_SECOND] = second != PAG_KEY_INVALID ? (u32)second >> 1 : PAG_EMPTY;
-            team[TM_SECOND_DIST] = (u32)(second >> 32);
-            team[TM_COUNT] = nW;
+            const u32 n = node != PAG_KEY_INVALID ? (u32)node >> 1 : PAG_EMPTY, s = second != PAG_KEY_INVALID ? (u32)second >> 1 : PAG_EMPTY;
+            *(uint4*)(team + TM_NODE) = make_uint4(n, (u32)(node >> 32), (u32)far, (u32)(far >> 32));
+            *(uint2*)(team + TM_SECOND) = make_uint2(s, (u32)(second >> 32));
+        }
+    }
+
+    // wave 0: R_L <- the best K of R_L and the W of the last round
+    __device__ __forceinline__ void keep_best() {
+        if constexpr (!BIG) {
+            if (n_done == 0) return;
+            double w[NW];
+            u64 kth = PAG_KEY_INVALID;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                w[s] = __longlong_as_double((long long)((u32)(s * 64 + lane) < nRL ? RL[s] : BEHIND_ALL));
+                if (nRL == A.K && (int)((A.K - 1) >> 6) == s) kth = rdlane64(RL[s], (int)((A.K - 1) & 63u));
+            }
+            u32 n = 0;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const u32 enter = (u32)__popcll(__ballot((u32)(s * 64 + lane) < n_done && done[s] < kth));      // done is sorted
+                const double d = __longlong_as_double((long long)done[s]);
+                for (u32 i = 0; i < enter; ++i) insert(w, lane_value(d, (int)i));
+                n += enter;
+            }
+            nRL = nRL + n < A.K ? nRL + n : A.K;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) RL[s] = (u32)(s * 64 + lane) < nRL ? (u64)__double_as_longlong(w[s]) : PAG_KEY_INVALID;
+            n_done = 0;
         }
     }
 
@@ -1330,97 +1364,84 @@ struct Wave {
         while (round < A.Rmax && nW != 0) {
             ukey = pop();
             if (ukey != PAG_KEY_INVALID) break;
+            keep_best();
             end_round(qi);
             round++;
             if (round < A.Rmax && nW != 0) s_rounds++;
-            if constexpr (!BIG) {
-#pragma unroll
-                for (int s = 0; s < NW; ++s)
-                    if ((u32)(s * 64 + lane) < nW) SA[s * 64 + lane] = W[s];
-            }
         }
         post(ukey, farthest(), ukey != PAG_KEY_INVALID ? peek() : PAG_KEY_INVALID);
     }
 
-    // wave 0, sorted W: a merge whose ranks against W are known (see team_rows), in two parts: W itself, ...
+    // wave 0, sorted W: the hop's np passers, whose keys lie in LDS, in two parts: W itself, ...
+    // A passer takes its place by one comparison of every member, and those behind it step to the next lane (470 clocks a hop; by
+    // ranks and a scatter through LDS 840, with the counting in the row waves besides).  The keys are
+    // compared as doubles, whose order is theirs (the distance word of a key is at most that of a NaN, 0x7FC00000, see
+    // team_reduce: no key is a NaN or an infinity as a double), in one instruction each.
     struct Merge {
-        u64 oldW[NW], pk;
-        u32 closer[NW], cP, rP, nW, n_ins, np;
-        bool pass;
+        u64 oldW[NW], pk, far;
+        u32 nW, np;
     };
-    __device__ __forceinline__ void merge_w(Merge& M, u64 mask, u32 np, bool pass) {
-        const u32 b = A.b, mine = team_index(mask);
-        M.np = np; M.pass = pass; M.nW = nW;
-        // all of LDS that is needed, asked for at once (lanes without a passer read what is not theirs)
-        const u32 x = (u32)lane >> 3, y = (u32)lane & 7u, at = mine & 63u;
-        const u64 pk = team_keys()[at], kx = team_keys()[x], ky = team_keys()[y];
-        const u32 before = team[TM_BEFORE + at];
+    static constexpr u64 BEHIND_ALL = 0x7FEFFFFFFFFFFFFFull;       // the largest double
+    template <bool FIRST>
+    __device__ __forceinline__ static double from_below(double x, double first) {      // lane l: x of lane l - 1; lane 0: first, or 0
+        constexpr int WAVE_SHR1 = 0x138;
+        const int lo = __builtin_amdgcn_update_dpp(FIRST ? __double2loint(first) : 0, __double2loint(x), WAVE_SHR1, 0xF, 0xF, !FIRST);
+        const int hi = __builtin_amdgcn_update_dpp(FIRST ? __double2hiint(first) : 0, __double2hiint(x), WAVE_SHR1, 0xF, 0xF, !FIRST);
+        return __hiloint2double(hi, lo);
+    }
+    __device__ __forceinline__ static void insert(double (&w)[NW], double k) {
+        double below[NW];
+        below[0] = from_below<false>(w[0], 0.0);
 #pragma unroll
-        for (int s = 0; s < NW; ++s) M.closer[s] = team[TM_CLOSER + s * 64 + lane];
+        for (int s = 1; s < NW; ++s) below[s] = from_below<true>(w[s], lane_value(w[s - 1], 63));
 #pragma unroll
-        for (int s = 0; s < NW; ++s) M.oldW[s] = W[s];
-        M.pk = pk;
-        // ranks among the passers: lane 8 x + y compares passers x and y of two groups of eight
-        u32 cP = (u32)__popcll((__ballot(x < np && y < np && kx < ky) >> (mine & 7u)) & 0x0101010101010101ull);
-        if (np > 8) {
-            cP = 0;
-            for (u32 i = 0; i < np; i += 8) {
-                const u64 a = i + x < np ? team_keys()[i + x] : PAG_KEY_INVALID;
-                for (u32 j = 0; j < np; j += 8) {
-                    const u64 lt = __ballot(a < (j + y < np ? team_keys()[j + y] : PAG_KEY_INVALID));
-                    if ((mine & ~7u) == j) cP += (u32)__popcll((lt >> (mine & 7u)) & 0x0101010101010101ull);
-                }
-            }
-        }
-        M.cP = cP; M.rP = cP + before;
-        M.n_ins = (u32)__popcll(__ballot(pass && M.rP < b));
+        for (int s = 0; s < NW; ++s) w[s] = fmin(w[s], fmax(below[s], k));
+    }
+    __device__ __forceinline__ void merge_w(Merge& M, u32 np) {
+        M.pk = (u32)lane < np ? team_keys()[lane] : PAG_KEY_INVALID;
+        M.np = np; M.nW = nW;
+        double w[NW];
 #pragma unroll
         for (int s = 0; s < NW; ++s) {
-            const u32 idx = s * 64 + lane, r = idx + M.closer[s];
-            if (idx < nW && r < b) SA[r] = W[s];
+            M.oldW[s] = W[s];
+            w[s] = __longlong_as_double((long long)((u32)(s * 64 + lane) < nW ? W[s] : BEHIND_ALL));
         }
-        if (pass && M.rP < b) SA[M.rP] = M.pk;
-        nW = nW + np < b ? nW + np : b;
-        lds_sync();
+        const double pk = __longlong_as_double((long long)M.pk);
+        const u64 far0 = farthest();
+        for (u64 m = __ballot((u32)lane < np && M.pk < far0); m; m &= m - 1) insert(w, lane_value(pk, __ffsll((long long)m) - 1));
+        nW = nW + np < A.b ? nW + np : A.b;
 #pragma unroll
-        for (int s = 0; s < NW; ++s) W[s] = (u32)(s * 64 + lane) < nW ? SA[s * 64 + lane] : PAG_KEY_INVALID;
+        for (int s = 0; s < NW; ++s) W[s] = (u32)(s * 64 + lane) < nW ? (u64)__double_as_longlong(w[s]) : PAG_KEY_INVALID;
+        M.far = farthest();
     }
-    // ... and what it pushes to the rings
+    // ... and what it pushes to the rings: displaced members to R_T (largest first), passers that do not fit to R_F (smallest first)
     __device__ __forceinline__ void merge_rings(const Merge& M) {
         const u32 b = A.b;
-        const u32 n_f = M.np - M.n_ins;                            // false positives -> R_F
-        const u32 n_ej = M.nW + M.n_ins - nW;                      // displaced members -> R_T
+        const u64 fails = __ballot((u32)lane < M.np && M.pk > M.far);
+        const u32 n_f = (u32)__popcll(fails);
+        const u32 n_ej = M.nW + (M.np - n_f) - (M.nW + M.np < b ? M.nW + M.np : b);
         if (n_ej) {
 #pragma unroll
             for (int s = 0; s < NW; ++s) {
                 const u32 idx = s * 64 + lane;
-                if (idx < M.nW && idx + M.closer[s] >= b) RT[(hdT + (M.nW - 1 - idx)) & A.ring_mask] = M.oldW[s];   // largest first
+                if (idx < M.nW && M.oldW[s] > M.far) RT[(hdT + (M.nW - 1 - idx)) & A.ring_mask] = M.oldW[s];
             }
             if (cntT + n_ej > b) s_rt += cntT + n_ej - b;
             cntT = cntT + n_ej < b ? cntT + n_ej : b;
             hdT += n_ej;
         }
         if (n_f) {
-            if (M.pass && M.rP >= b) {
-                const u32 oi = M.cP - M.n_ins;                      // smallest first
-                if (oi + b >= n_f) RF[(hdF + oi) & A.ring_mask] = M.pk;  // older ones would be overwritten anyway
-            }
+            u32 oi = 0;
+            for (u64 m = fails; m; m &= m - 1) oi += rdlane64(M.pk, __ffsll((long long)m) - 1) < M.pk ? 1u : 0u;
+            if (((fails >> lane) & 1ull) && oi + b >= n_f) RF[(hdF + oi) & A.ring_mask] = M.pk;  // older ones would be overwritten anyway
             if (cntF + n_f > b) s_rf += cntF + n_f - b;
             cntF = cntF + n_f < b ? cntF + n_f : b;
             hdF += n_f;
         }
     }
 
-    // wave 0: the words that a hop's keys are counted in
-    __device__ __forceinline__ void clear_counts() const {
-#pragma unroll
-        for (int s = 0; s < (BIG ? 0 : NW); ++s) team[TM_CLOSER + s * 64 + lane] = 0u;
-        if (lane == 0) *team_min() = PAG_KEY_INVALID;
-    }
-
-    // which of a node's neighbours (in pf_id) are unseen
-    __device__ __forceinline__ bool find_unseen() const {
-        const u32 id = pf_id;
+    // which of a node's neighbours are unseen
+    __device__ __forceinline__ bool find_unseen(u32 id) const {
         bool cand = id != PAG_EMPTY && id < A.n_limit;
         u32 word = 0;
         if (A.blog != 0) {
@@ -1436,16 +1457,17 @@ struct Wave {
         return cand && !((word >> (id & 31)) & 1u);
     }
 
-    // sum_l T[l][code_l] of a node's neighbours (in pf_cw)
-    __device__ __forceinline__ float code_sum() const {
+    // sum_l T[l][code_l] of a node's neighbours
+    __device__ __forceinline__ float code_sum(const u32 (&cwv)[CW]) const {
         if (A.flags & PAG_FLAG_NO_PRT) return 0.f;
-        if (A.cw == 2) return table_sum<2>(t_base, pf_cw);
-        if (A.cw == 4) return table_sum<4, CW, 32>(t_base, pf_cw);
-        return table_sum<8, CW, 32>(t_base, pf_cw);
+        if (A.cw == 2) return table_sum<2>(t_base, cwv);
+        if (A.cw == 4) return table_sum<4, CW, 32>(t_base, cwv);
+        return table_sum<8, CW, 32>(t_base, cwv);
     }
 
-    // The screening of node u's neighbours; SEEN and EST: which half of it this wave does.  What it needs of u's record is
-    // kept in the prefetch registers (nx_id: whose), the sums with it.
+    // The screening of a node's neighbours; SEEN and EST: which half of it this wave does.  What it needs of the record of
+    // W's closest unvisited member is kept in the prefetch registers (nx_id: whose), the sums with it: that member is often
+    // expanded some hops later.
     template <bool SEEN, bool EST>
     __device__ __forceinline__ void fetch_screen(u32 u) {
         if (u == nx_id) return;
@@ -1454,21 +1476,28 @@ struct Wave {
         if constexpr (EST) { load_edges(u, pf_a, pf_c, pf_cw); pf_summed = false; }
     }
     __device__ __forceinline__ void sum_codes() {
-        if (!pf_summed) pf_sum = code_sum();
+        if (!pf_summed) pf_sum = code_sum(pf_cw);
         pf_summed = true;
     }
+    __device__ __forceinline__ void put_unseen(u32 id, bool unseen) {
+        scr_id = id;
+        team[TM_ID + lane] = unseen ? id : PAG_EMPTY;
+    }
+    __device__ __forceinline__ void put_estimate(float Du, float ea, float ec, float sum) {
+        team[TM_EST + lane] = __float_as_uint(__builtin_fmaf(-2.0f * ea, sum, Du + ec));
+    }
+    // ... of a node whose record is not at hand
     template <bool SEEN, bool EST>
-    __device__ __forceinline__ void screen_node(u32 u, float Du, bool looked_up, bool unseen) {
-        fetch_screen<SEEN, EST>(u);
-        if constexpr (SEEN) {
-            if (!looked_up) unseen = find_unseen();
-            scr_id = pf_id;
-            team[TM_ID + lane] = unseen ? pf_id : PAG_EMPTY;
-        }
+    __device__ __forceinline__ void screen_node(u32 u, float Du) {
+        u32 id = PAG_EMPTY;
+        float ea, ec;
+        u32 cwv[CW];
+        if constexpr (SEEN) id = load_id(u);
         if constexpr (EST) {
-            sum_codes();
-            team[TM_EST + lane] = __float_as_uint(__builtin_fmaf(-2.0f * pf_a, pf_sum, Du + pf_c));
+            load_edges(u, ea, ec, cwv);
+            put_estimate(Du, ea, ec, code_sum(cwv));
         }
+        if constexpr (SEEN) put_unseen(id, find_unseen(id));
     }
 
     // One wave of the workgroup: queries until the batch is drained.  Each role is compiled by itself, so that the
@@ -1484,7 +1513,7 @@ struct Wave {
                 qi = uniform(qi);
                 if (qi >= A.nq) qi = PAG_EMPTY;
                 else if (A.order) qi = A.order[qi];
-                if (lane == 0) { team[TM_QUERY] = qi; team[TM_COUNT] = 0u; }
+                if (lane == 0) team[TM_QUERY] = qi;
             }
             team_barrier();
             const u32 qi = uniform(team[TM_QUERY]);
@@ -1500,46 +1529,61 @@ struct Wave {
                 const bool pass = id != PAG_EMPTY;
                 const u64 mask = __ballot(pass);
                 if (mask == 0ull) continue;
-                if constexpr (ROLE == ROWS) team_rows(id, mask);
-                else team_barrier();
-                if constexpr (KEEPS_SEEN) mark_seen(id, (u32)__popcll(mask), pass);
+                const u32 np = (u32)__popcll(mask);
+                if constexpr (ROLE == ROWS) (void)team_rows(id, mask, 0u);
+                if constexpr (KEEPS_SEEN) mark_seen(id, np, pass);
                 team_barrier();
-                if constexpr (ROLE == LISTS)
-                    merge(id, mask, (u32)__popcll(mask), pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
+                if constexpr (ROLE == LISTS) {
+                    s_exact += np;
+                    if constexpr (BIG) {
+                        merge_unsorted(id, mask, np, pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
+                    } else {
+                        Merge M;
+                        merge_w(M, np);                // no more than b in all: nothing for the rings
+                    }
+                }
                 team_barrier();
             }
             if constexpr (ROLE == LISTS) {
                 if (nW != 0) s_rounds++;
                 post_next(qi);
-                clear_counts();
+                if (lane == 0) *team_min(0) = *team_min(1) = PAG_KEY_INVALID;
             }
             if (KEEPS_SEEN && lane == 0) team[TM_SCREENED] = PAG_EMPTY;
             team_barrier();
             // ---- hops ----
             bool owed = false;                         // wave 0: a merge whose ring pushes are outstanding
             Merge M;
-            for (;;) {
+            for (u32 hop = 0;; ++hop) {
                 PAG_MARK(0);
-                const u32 u = uniform(team[TM_NODE]);
+                // all that wave 0 and the screening have left, asked for at once
+                const uint4 posted = *(const uint4*)(team + TM_NODE), more = *(const uint4*)(team + TM_SECOND);
+                u32 id = team[TM_ID + lane];
+                float est = __uint_as_float(team[TM_EST + lane]);
+                const u32 u = uniform(posted.x), du = uniform(posted.y);
                 if (u == PAG_EMPTY) break;
-                const u32 du = uniform(team[TM_NODE_DIST]);
-                const u64 far = ((u64)uniform(team[TM_FAR_HI]) << 32) | uniform(team[TM_FAR_LO]);
-                const u32 second = uniform(team[TM_SECOND]), second_d = uniform(team[TM_SECOND_DIST]);
+                const u64 far = ((u64)uniform(posted.w) << 32) | uniform(posted.z);
+                const u32 second = uniform(more.x), second_d = uniform(more.y);
                 // TM_SCREENED stays as it is until all waves have read it: it is written again after the rows
-                if (uniform(team[TM_SCREENED]) != u) {
-                    if constexpr (KEEPS_SEEN || ESTIMATE) screen_node<KEEPS_SEEN, ESTIMATE>(u, __uint_as_float(du), false, false);
+                if (uniform(more.z) != u) {
+                    if constexpr (KEEPS_SEEN || ESTIMATE) screen_node<KEEPS_SEEN, ESTIMATE>(u, __uint_as_float(du));
                     team_barrier();
+                    id = team[TM_ID + lane];
+                    est = __uint_as_float(team[TM_EST + lane]);
                 }
-                const u32 id = team[TM_ID + lane];
-                const float est = __uint_as_float(team[TM_EST + lane]);
                 bool pass = passes(id != PAG_EMPTY, est, threshold(far));
                 if (A.flags & PAG_SEARCH_DISTINCT) { const bool first = first_of_id(id, pass); pass = pass && first; }
                 const u64 mask = __ballot(pass);
                 const u32 np = (u32)__popcll(mask);
                 PAG_MARK(2);
                 bool unseen = false;                   // of the neighbours of `second`
+                u32 touched = 0;
                 if constexpr (ROLE == ROWS) {
-                    team_rows(id, mask);
+                    touched = team_rows(id, mask, hop);
+                } else if constexpr (ROLE == LISTS) {
+                    if (lane == 0) *team_min(hop + 1) = PAG_KEY_INVALID;   // last read before the barrier that began this hop
+                    if (owed) merge_rings(M);
+                    keep_best();
                 } else {
                     if constexpr (KEEPS_SEEN) {
                         if (A.pes != nullptr) screen_pes(scr_id, est, ((u64)du << 32) | ((u64)u << 1));
@@ -1547,15 +1591,11 @@ struct Wave {
                     if constexpr (KEEPS_SEEN || ESTIMATE) {
                         if (second != PAG_EMPTY) fetch_screen<KEEPS_SEEN, ESTIMATE>(second);
                     }
-                    team_barrier();
-                    if constexpr (ROLE == LISTS) {
-                        if (owed) merge_rings(M);
-                    }
                     if constexpr (KEEPS_SEEN) {
                         s_tests += (u32)__popcll(__ballot(id != PAG_EMPTY));
                         s_passes += np;
                         if (np) mark_seen(id, np, pass);
-                        if (second != PAG_EMPTY) unseen = find_unseen();
+                        if (second != PAG_EMPTY) unseen = find_unseen(pf_id);
                     }
                     if constexpr (ESTIMATE) {
                         if (second != PAG_EMPTY) sum_codes();
@@ -1564,6 +1604,7 @@ struct Wave {
                 PAG_MARK(1);
                 team_barrier();
                 PAG_MARK(3);
+                if constexpr (ROLE == ROWS) asm volatile("" :: "v"(touched));
                 if constexpr (ROLE == LISTS) {
                     s_exact += np;
                     if constexpr (BIG) {
@@ -1572,10 +1613,10 @@ struct Wave {
                         post_next(qi);
                     } else {
                         owed = np != 0;
-                        if (np) merge_w(M, mask, np, pass);
+                        if (np) merge_w(M, np);
                         const u64 next = pop();
                         if (next != PAG_KEY_INVALID) {
-                            post(next, farthest(), peek());
+                            post(next, owed ? M.far : farthest(), peek());
                         } else {
                             if (owed) merge_rings(M);
                             owed = false;
@@ -1584,18 +1625,24 @@ struct Wave {
                     }
                 }
                 if constexpr (KEEPS_SEEN || ESTIMATE) {
-                    const u64 first = *team_min();     // of the passers; PAG_KEY_INVALID: none
+                    const u64 first = *team_min(hop);  // of the passers; PAG_KEY_INVALID: none
                     const u64 next2 = second != PAG_EMPTY ? ((u64)second_d << 32) | ((u64)second << 1) : PAG_KEY_INVALID;
                     const bool passer = __ballot(first < far && first < next2) != 0ull;
                     const u64 next = passer ? first : next2;
                     const u32 node = uniform(next != PAG_KEY_INVALID ? (u32)next >> 1 : PAG_EMPTY);
                     if (KEEPS_SEEN && lane == 0) team[TM_SCREENED] = node;
-                    if (node != PAG_EMPTY) screen_node<KEEPS_SEEN, ESTIMATE>(node, __uint_as_float((u32)(next >> 32)), !passer, unseen);
+                    const float Du = __uint_as_float((u32)(next >> 32));
+                    if (passer) {
+                        screen_node<KEEPS_SEEN, ESTIMATE>(node, Du);
+                    } else if (node != PAG_EMPTY) {
+                        if constexpr (KEEPS_SEEN) put_unseen(pf_id, unseen);
+                        if constexpr (ESTIMATE) put_estimate(Du, pf_a, pf_c, pf_sum);
+                    }
                 }
                 PAG_MARK(4);
                 team_barrier();
-                if constexpr (ROLE == LISTS) clear_counts();
             }
+            if constexpr (ROLE == LISTS) keep_best();
             if constexpr (ROLE == LISTS || KEEPS_SEEN) write_results(qi);
             if constexpr (KEEPS_SEEN) {
                 if (n_spill) __threadfence();        // its bit-sets have landed before others clear
