@@ -191,8 +191,8 @@ int alloc_index(pag_index* ix) {
     if ((rc = dev_alloc(&ix->cb, (u64)ix->L.P * PAG_NCODE * ix->L.dsub))) return rc;
     if ((rc = dev_alloc(&ix->entry, 1024))) return rc;
     if ((rc = dev_alloc(&ix->d_qcounter, 4))) return rc;
-    if ((rc = dev_alloc(&ix->d_counters, CTR_COUNT))) return rc;
-    PAG_HIP(hipMemsetAsync(ix->d_counters, 0, CTR_COUNT * sizeof(u64), ix->stream));
+    if ((rc = dev_alloc(&ix->d_counters, PAG_CTR_COPIES * CTR_LINE))) return rc;
+    PAG_HIP(hipMemsetAsync(ix->d_counters, 0, PAG_CTR_COPIES * CTR_LINE * sizeof(u64), ix->stream));
     for (auto& e : ix->ev) PAG_HIP(hipEventCreate(&e));
     // pag_search_static must find its workspace without loading or allocating anything: look it up now
     unsigned char* static_ws = nullptr;
@@ -485,9 +485,11 @@ extern "C" int pag_get_counters(const pag_index* ix, pag_counters* out) {
     PAG_CHECK(ix && out, PAG_EINVAL, "null argument");
     PAG_CHECK(out->struct_size == sizeof(pag_counters), PAG_EINVAL, "pag_counters.struct_size does not match this library");
     DeviceGuard g(ix->device);
-    u64 h[CTR_COUNT];
+    u64 copies[PAG_CTR_COPIES][CTR_LINE], h[CTR_COUNT] = {};
     PAG_HIP(hipStreamSynchronize(ix->stream));
-    PAG_HIP(hipMemcpy(h, ix->d_counters, sizeof h, hipMemcpyDeviceToHost));
+    PAG_HIP(hipMemcpy(copies, ix->d_counters, sizeof copies, hipMemcpyDeviceToHost));
+    for (const auto& line : copies)
+        for (int i = 0; i < CTR_COUNT; ++i) h[i] += line[i];
     out->adj_record_bytes = ix->L.rec_bytes;
     out->queries = h[CTR_QUERIES]; out->hops = h[CTR_HOPS]; out->tests = h[CTR_TESTS]; out->passes = h[CTR_PASSES];
     out->exact = h[CTR_EXACT]; out->rounds = h[CTR_ROUNDS]; out->rf_overflow = h[CTR_RF_OVER];
@@ -504,7 +506,7 @@ extern "C" int pag_get_counters(const pag_index* ix, pag_counters* out) {
 extern "C" int pag_reset_counters(pag_index* ix) {
     PAG_CHECK(ix, PAG_EINVAL, "null argument");
     DeviceGuard g(ix->device);
-    int rc = pag_launch_zero_u32(ix->stream, (u32*)ix->d_counters, CTR_COUNT * 2);
+    int rc = pag_launch_zero_u32(ix->stream, (u32*)ix->d_counters, PAG_CTR_COPIES * CTR_LINE * 2);
     if (rc) return rc;
     PAG_HIP(hipStreamSynchronize(ix->stream));
     return PAG_OK;
@@ -713,7 +715,6 @@ static int search_impl(pag_index* ix, const float* Q, uint64_t nq, uint32_t K, u
     if ((rc = prepare(ix, Q, nq, ix->ws_qrot, ix->ws_tab))) return rc;
     // more queries than resident waves: those that run side by side are chosen to be neighbours
     if (!(ix->flags & PAG_FLAG_KEEP_QUERY_ORDER) && nq > (u64)grid && (rc = pag_order_queries(ix, ix->ws_qrot, nq, &a.order))) return rc;
-    if ((rc = pag_launch_zero_u32(ix->stream, ix->d_qcounter, 1))) return rc;
     PAG_HIP(hipEventRecord(ix->ev[1], ix->stream));
     if ((rc = pag_launch_search(ix, a, lds, &grid))) return rc;
     PAG_HIP(hipEventRecord(ix->ev[2], ix->stream));
@@ -806,7 +807,6 @@ extern "C" int pag_search_static(const pag_index* cix, const float* Q, uint64_t 
     // the array keeps whatever the last call left there, possibly under another layout: the bitmaps start clean
     if ((rc = pag_launch_zero_u32(ix->stream, a.bitmap, (u64)grid * a.bitmap_words))) return rc;
     if ((rc = prepare_into(ix, Q, nq, (float*)(base + off_norm), (float*)(base + off_qrot), (float*)(base + off_tab)))) return rc;
-    if ((rc = pag_launch_zero_u32(ix->stream, ix->d_qcounter, 1))) return rc;
     PAG_HIP(hipEventRecord(ix->ev[1], ix->stream));
     if ((rc = pag_launch_search(ix, a, lds, &grid))) return rc;
     PAG_HIP(hipEventRecord(ix->ev[2], ix->stream));
@@ -854,8 +854,8 @@ extern "C" int pag_searcher_create(const pag_index* ix, void* stream, pag_search
     for (auto& e : v.ev) e = nullptr;
     v.last_search_ms = v.last_prepare_ms = v.last_build_ms = 0.0;
     int rc;
-    if ((rc = dev_alloc(&v.d_qcounter, 4)) || (rc = dev_alloc(&v.d_counters, CTR_COUNT))) { searcher_release(s); return rc; }
-    hipError_t e = hipMemsetAsync(v.d_counters, 0, CTR_COUNT * sizeof(u64), v.stream);
+    if ((rc = dev_alloc(&v.d_qcounter, 4)) || (rc = dev_alloc(&v.d_counters, PAG_CTR_COPIES * CTR_LINE))) { searcher_release(s); return rc; }
+    hipError_t e = hipMemsetAsync(v.d_counters, 0, PAG_CTR_COPIES * CTR_LINE * sizeof(u64), v.stream);
     for (auto& ev : v.ev) if (e == hipSuccess) e = hipEventCreate(&ev);
     if (e == hipSuccess) e = hipStreamSynchronize(v.stream);
     if (e != hipSuccess) { searcher_release(s); pag_set_error(std::string("pag_searcher_create: ") + hipGetErrorString(e)); return PAG_EHIP; }

@@ -40,11 +40,17 @@ void pag_set_error(const std::string& msg);
         }                                                                                    \
     } while (0)
 
-// Device-side statistics, summed with atomics by every wave when it retires.
+// Device-side statistics, summed with atomics by every wave when it retires.  They are kept PAG_CTR_COPIES times, a 128-byte line
+// each, and a workgroup adds to the copy of its number: atomics on one address are done one after the other, 14 ns each across the
+// GPU, and 1,000 queries with nine counters of two waves each spent a third of a short search on them (10,000 x 128, 1,000 queries,
+// efS 64: 360 -> 290 us).
 enum {
     CTR_QUERIES = 0, CTR_HOPS, CTR_TESTS, CTR_PASSES, CTR_EXACT, CTR_ROUNDS, CTR_RF_OVER,
-    CTR_RT_OVER, CTR_SPILLS, CTR_PHASE0, CTR_PHASE1, CTR_PHASE2, CTR_PHASE3, CTR_PHASE4, CTR_PHASE5, CTR_COUNT
+    CTR_RT_OVER, CTR_SPILLS, CTR_PHASE0, CTR_PHASE1, CTR_PHASE2, CTR_PHASE3, CTR_PHASE4, CTR_PHASE5, CTR_COUNT, CTR_LINE = 16
 };
+
+constexpr u32 PAG_CTR_COPIES = 256;
+static_assert((int)CTR_COUNT <= (int)CTR_LINE, "counters of a line");
 
 // Adjacency record of node u (one burst of whole 128-byte lines):
 //   [ids deg x u32][a deg x f32][c deg x f32][pad to 16 B][codes deg x (cw dwords)]   padded to 128 bytes
@@ -107,7 +113,7 @@ struct pag_index {
     u64* ws_rings;   u64 ws_rings_cap;    // u64 keys: per-wave R_F / R_T / R_L of large working sets
     u32* ws_order;   u64 ws_order_cap;    // u32 words: workspace of pag_order_queries
     u32* d_qcounter;                      // persistent-wave work counter
-    u64* d_counters;                      // CTR_COUNT
+    u64* d_counters;                      // [PAG_CTR_COPIES][CTR_LINE]
     hipEvent_t ev[4];
     int num_cu;
     u32 lds_per_cu;                       // bytes
@@ -139,7 +145,7 @@ struct SearchArgs {
     u32 cand_cap;
     u64* pes;                // [nq * deg] indexing mode: PES buffer H(v), ascending keys, PAG_KEY_INVALID = empty; null = off
     const u32* order;        // [nq] the order in which the waves take the queries (null: as numbered)
-    u32* qcounter;
+    u32* qcounter;           // queries taken beyond the first of each workgroup, which is the workgroup's number; untouched if that is all
     u64* counters;
     u32* bitmap;             // [min(grid, nq) * bitmap_words]
     u64 bitmap_words;

@@ -87,6 +87,10 @@ int pag_launch_search(const pag_index* ix, const SearchArgs& a, u32 lds_bytes, i
     int grid = *grid_io;
     if ((u64)grid > a.nq) grid = (int)a.nq;
     if (grid < 1) return PAG_OK;
+    if ((u64)grid < a.nq) {
+        const int rc = pag_launch_zero_u32(ix->stream, a.qcounter, 1);
+        if (rc) return rc;
+    }
     SearchArgs args = a;
     void* kargs[] = { (void*)&args };
     PAG_HIP(hipLaunchKernel((const void*)fn, dim3(grid), dim3(64 * a.waves), kargs, lds_bytes, ix->stream));

@@ -1506,11 +1506,9 @@ struct Wave {
     template <Role ROLE>
     __device__ __forceinline__ void run_team() {
         constexpr bool KEEPS_SEEN = ROLE == SEEN || ROLE == SCREEN, ESTIMATE = ROLE == ESTIMATES || ROLE == SCREEN;
-        for (;;) {
+        for (u32 take = 0;; ++take) {
             if constexpr (ROLE == LISTS) {
-                u32 qi = 0;
-                if (lane == 0) qi = atomicAdd(A.qcounter, 1u);
-                qi = uniform(qi);
+                u32 qi = take == 0 ? blockIdx.x : next_query();
                 if (qi >= A.nq) qi = PAG_EMPTY;
                 else if (A.order) qi = A.order[qi];
                 if (lane == 0) team[TM_QUERY] = qi;
@@ -1653,21 +1651,29 @@ struct Wave {
         }
     }
 
+    // the query after this workgroup's last one (A.nq and above: there is none)
+    __device__ __forceinline__ u32 next_query() const {
+        if (gridDim.x >= A.nq) return A.nq;
+        u32 qi = 0;
+        if (lane == 0) qi = gridDim.x + atomicAdd(A.qcounter, 1u);
+        return uniform(qi);
+    }
+
     __device__ __forceinline__ void flush_stats() {
-        if (lane == 0) {
-            atomicAdd(&A.counters[CTR_QUERIES], (u64)s_queries);
-            atomicAdd(&A.counters[CTR_HOPS], (u64)s_hops);
-            atomicAdd(&A.counters[CTR_TESTS], (u64)s_tests);
-            atomicAdd(&A.counters[CTR_PASSES], (u64)s_passes);
-            atomicAdd(&A.counters[CTR_EXACT], (u64)s_exact);
-            atomicAdd(&A.counters[CTR_ROUNDS], (u64)s_rounds);
-            atomicAdd(&A.counters[CTR_RF_OVER], (u64)s_rf);
-            atomicAdd(&A.counters[CTR_RT_OVER], (u64)s_rt);
-            atomicAdd(&A.counters[CTR_SPILLS], (u64)s_spill);
+        u64* line = A.counters + (u64)(blockIdx.x % PAG_CTR_COPIES) * CTR_LINE;
+        // one counter a lane
+        u32 v = 0;
+        auto put = [&](int counter, u32 x) {
+            asm volatile("" : "+v"(x));          // or the compiler indexes the members in scratch, and with them all of this object
+            v = lane == counter ? x : v;
+        };
+        put(CTR_QUERIES, s_queries); put(CTR_HOPS, s_hops); put(CTR_TESTS, s_tests); put(CTR_PASSES, s_passes); put(CTR_EXACT, s_exact);
+        put(CTR_ROUNDS, s_rounds); put(CTR_RF_OVER, s_rf); put(CTR_RT_OVER, s_rt); put(CTR_SPILLS, s_spill);
+        if (lane <= CTR_SPILLS && v) atomicAdd(&line[lane], (u64)v);
 #ifdef PAG_PHASE_TIMERS
-            for (int i = 0; i < 6; ++i) atomicAdd(&A.counters[CTR_PHASE0 + i], s_phase[i]);
+        if (lane == 0)
+            for (int i = 0; i < 6; ++i) atomicAdd(&line[CTR_PHASE0 + i], s_phase[i]);
 #endif
-        }
     }
 };
 
@@ -1689,23 +1695,15 @@ constexpr int pag_search_occupancy(int nq, int nw, int vm, int cw) {
     return vm == 0 && (nq == 6 || (nq == 8 && nw == 2)) ? 3 : 2;
 }
 
-// Persistent waves: every wave pulls query numbers from one counter until the batch is drained,
-// so long and short searches balance themselves; the loop ends for every wave once the counter
-// passes nq.
+// Persistent waves: every wave begins with the query of its own number and pulls further ones from one counter until the batch
+// is drained, so long and short searches balance themselves; the loop ends for every wave once the counter passes nq.
 template <int NQ, int NW, int VM, int CW>
 __attribute__((amdgpu_waves_per_eu(pag_search_occupancy(NQ, NW, VM, CW), 8)))
 __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
     extern __shared__ __align__(64) unsigned char smem[];   // the table sits first: see table_sum
     const int lane = threadIdx.x;
     Wave<NQ, NW, VM, CW> w(A, smem, lane);
-    for (;;) {
-        u32 qi = 0;
-        if (lane == 0) qi = atomicAdd(A.qcounter, 1u);
-        qi = uniform(qi);
-        if (qi >= A.nq) break;
-        if (A.order) qi = A.order[qi];
-        w.run_query(qi);
-    }
+    for (u32 qi = blockIdx.x; qi < A.nq; qi = w.next_query()) w.run_query(A.order ? A.order[qi] : qi);
     w.flush_stats();
 }
 
