@@ -575,8 +575,10 @@ static int plan_team(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, 
     SearchArgs t = *a;
     t.waves = 2;                                                    // any team: its words are part of the carve-up
     pag_team_plan p;
-    const int rc = pag_plan_team(r, [&](u32 hlog, u32 blog) { return (u32)pag_search_lds_bytes(ix->L, b, hlog, blog, &t); },
-                                 [&](u32 waves, u32 bytes, int* n) { return pag_search_max_grid(ix, b, waves, bytes, n); }, &p);
+    auto lds_bytes = [&](u32 hlog, u32 blog) { return (u32)pag_search_lds_bytes(ix->L, b, hlog, blog, &t); };
+    auto resident = [&](u32 waves, u32 bytes, int* n) { return pag_search_max_grid(ix, b, waves, bytes, n); };
+    int rc = pag_plan_team(r, lds_bytes, resident, &p);
+    if (!rc && p.waves == 1) rc = pag_plan_four(r, nodes, lds_bytes, resident, &p);
     if (rc || p.waves == 1) return rc;
     a->waves = p.waves; a->hlog = p.hlog; a->blog = p.blog;
     *lds = (u32)pag_search_lds_bytes(ix->L, b, p.hlog, p.blog, a);

@@ -32,52 +32,12 @@ struct pag_team_plan {
 // queries/s when all seven others count, 276,000 when three do.)
 inline uint64_t pag_queries_beside(uint64_t calls, uint64_t queries) { return calls <= 3 ? queries : queries * 3 / calls; }
 
-// Batches that leave the GPU mostly idle with one wave per query get several (a team); `share` queries then share a CU.
-// `waves` stays 1 where one wave is the better plan.
-//   lds_bytes(hlog, blog): LDS of a team with that seen set; resident(waves, lds, &n): error code, teams that the GPU holds at a time
-//
-// What decides is not the call alone but the queries under way on the GPU: a team takes a large part of a CU, and teams of
-// several calls would wait for each other where smaller teams or single waves run side by side.  Four searchers with 256 queries
-// each (200k x 768, efS 256): 302,000 queries/s when every call plans as if it were alone, 482,000 with one wave per query,
-// 661,000 with what the sum asks for; with 1,000 queries each 706,000, 1,158,000 and 1,186,000, with 16 each 73,000, 39,000 and 73,000.
-//
-// A team takes longer to set up (its LDS, its entry nodes) than one wave: searches of 10 nodes lose with it (5,000 x 128,
-// whole call: 256 queries 105 -> 111 us, 512 queries 138 -> 182), at two queries per CU up to 32 nodes (227 -> 231); 20 and 64
-// nodes gain at one and two per CU (5,000 x 192, 300 queries, 20 nodes: 171 -> 156; 5,000 x 128, 512 queries, 64 nodes: 300 -> 272).
-// The lines, with kernel times of one wave -> a team (100,000 rows, efS 128, unless stated):
-//   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
-//     query 375 -> 242, 491 -> 271, 777 -> 414
-//   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
-//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
-//     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
-//     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
-//   up to four per CU: 4 waves, for searches of 128 nodes or more and working sets of up to 128.  Searches of 256 nodes with working
-//     sets of up to 64 gain with up to four per CU wherever their rows come from (1,000 queries, efS 256: 50k x 768 1244 -> 1171 us,
-//     1M x 128 1127 -> 983; 30k x 1536 1606 -> 1588 at least).  Shorter ones and larger working sets gain less and lose
-//     beyond 2.5 per CU (efS 128, 520 / 777 / 1,000 queries, one wave : team: 80k x 768 1.07 / 0.98 / 0.89, 300k x 128 1.07 / 0.96 /
-//     0.90; K 100, efS 256: 50k x 768 1.10 / 1.00 / 0.96), 3.75 if the rows come from HBM and not from the 256 MB cache (200k
-//     x 768 1.14 / 1.02 / 0.95, 2M x 128 1.12 / 1.06 / 1.02; with 400 MB of rows the two are even), four if they are 16-bit
-//     besides (600k x 768 1.22 / 1.13 / 1.05).  16-bit rows of 2560 and more leave the team's kernel short of registers: 0.75 to 0.95
+// A team of `most` to `least` waves, as many as leave every query resident where `share` queries share a CU; `waves` stays as it is if
+// there is no such team.
 template <class Lds, class Resident>
-int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
-    const uint64_t cus = r.num_cu, load = r.nq + r.others;
-    const bool large_set = r.b > 128;
+int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint32_t least, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
+    const uint64_t load = r.nq + r.others;
     const uint32_t length = std::max(r.ef, r.b);                    // nodes that a search expands, about
-    uint32_t share, most, least;
-    p->waves = 1;
-    if (load <= cus && length >= 16) {
-        share = 1; most = 12; least = 4;
-    } else if (load > cus && load <= 2 * cus && length >= 48) {
-        share = 2; most = 8; least = r.b > 512 ? 4 : 8;
-    } else if (load > 2 * cus && length >= 128 && !large_set && !(r.half && r.d >= 2560)) {
-        const bool from_hbm = r.store_bytes >= (512ull << 20);
-        const uint64_t quarters = (length >= 256 && r.b <= 64) || (from_hbm && r.half) ? 16 : from_hbm ? 15 : 10;
-        if (4 * load > quarters * cus) return 0;
-        share = 4; most = 4; least = 4;
-    } else {
-        return 0;
-    }
-    most = std::min(most, r.most_waves);
     const uint32_t room = r.lds_per_cu / share - 512;
     // The seen set: an exact hash of everything the search is expected to compute, if the LDS holds it half full;
     // otherwise the bitmap behind a Bloom filter of 16 bits per node, as far as the LDS goes.
@@ -101,6 +61,69 @@ int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& residen
         return 0;
     }
     return 0;
+}
+
+// Batches that leave the GPU mostly idle with one wave per query get several (a team); `share` queries then share a CU.
+// `waves` stays 1 where one wave is the better plan.
+//   lds_bytes(hlog, blog): LDS of a team with that seen set; resident(waves, lds, &n): error code, teams that the GPU holds at a time
+//
+// What decides is not the call alone but the queries under way on the GPU: a team takes a large part of a CU, and teams of
+// several calls would wait for each other where smaller teams or single waves run side by side.  Four searchers with 256 queries
+// each (200k x 768, efS 256): 302,000 queries/s when every call plans as if it were alone, 482,000 with one wave per query,
+// 661,000 with what the sum asks for; with 1,000 queries each 706,000, 1,158,000 and 1,186,000, with 16 each 73,000, 39,000 and 73,000.
+//
+// The shortest searches keep one wave (kernel times of 10 nodes, 5,000 x 128, 256 queries: 76 -> 43 us with a team, of which a call's host
+// part leaves little); from 16 nodes with up to one query per CU and 24 with up to two they get teams (5,000 x 128, 16 nodes, 256 queries
+// 112 -> 71 us; 24 nodes, 512 queries 142 -> 92; 50k x 768 259 -> 191).
+// The lines, with kernel times of one wave -> a team (100,000 rows, efS 128, unless stated) as they were when the lines were drawn:
+//   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
+//     query 375 -> 242, 491 -> 271, 777 -> 414
+//   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
+//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
+//     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
+//     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
+//   up to four per CU: 4 waves, for searches of 128 nodes or more and working sets of up to 128.  Searches of 256 nodes with working
+//     sets of up to 64 gain with up to four per CU wherever their rows come from (1,000 queries, efS 256: 50k x 768 1244 -> 1171 us,
+//     1M x 128 1127 -> 983; 30k x 1536 1606 -> 1588 at least).  Shorter ones and larger working sets gain less and lose
+//     beyond 2.5 per CU (efS 128, 520 / 777 / 1,000 queries, one wave : team: 80k x 768 1.07 / 0.98 / 0.89, 300k x 128 1.07 / 0.96 /
+//     0.90; K 100, efS 256: 50k x 768 1.10 / 1.00 / 0.96), 3.75 if the rows come from HBM and not from the 256 MB cache (200k
+//     x 768 1.14 / 1.02 / 0.95, 2M x 128 1.12 / 1.06 / 1.02; with 400 MB of rows the two are even), four if they are 16-bit
+//     besides (600k x 768 1.22 / 1.13 / 1.05).  16-bit rows of 2560 and more leave the team's kernel short of registers: 0.75 to 0.95
+template <class Lds, class Resident>
+int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
+    const uint64_t cus = r.num_cu, load = r.nq + r.others;
+    const bool large_set = r.b > 128;
+    const uint32_t length = std::max(r.ef, r.b);                    // nodes that a search expands, about
+    uint32_t share, most, least;
+    p->waves = 1;
+    if (load <= cus && length >= 16) {
+        share = 1; most = 12; least = 4;
+    } else if (load > cus && load <= 2 * cus && length >= 24) {
+        share = 2; most = 8; least = r.b > 512 ? 4 : 8;
+    } else if (load > 2 * cus && length >= 128 && !large_set && !(r.half && r.d >= 2560)) {
+        const bool from_hbm = r.store_bytes >= (512ull << 20);
+        const uint64_t quarters = (length >= 256 && r.b <= 64) || (from_hbm && r.half) ? 16 : from_hbm ? 15 : 10;
+        if (4 * load > quarters * cus) return 0;
+        share = 4; most = 4; least = 4;
+    } else {
+        return 0;
+    }
+    return pag_fit_team(r, share, std::min(most, r.most_waves), least, lds_bytes, resident, p);
+}
+
+// What pag_plan_team leaves to one wave although no more than four queries come to a CU: teams of four, where the registers of their
+// kernel let every query be resident.  (The lines above date from when every wave of a team began and ended with atomics on the same few
+// addresses, 0.35 us a query in all.)  Kernel times of one wave -> four, 777 and 1,000 queries: 10k x 128 at efS 32 / 64 / 128
+// 192 -> 140, 280 -> 211, 478 -> 350 us; 50k x 768 289 -> 203, 446 -> 303, 698 -> 505, K 100 1080 -> 825; 1M x 128 at efS 64 360 -> 260,
+// K 100 1105 -> 785; 30k x 1536 at efS 64 497 -> 382; 16-bit 30k x 768 at efS 64 412 -> 299, K 150 1796 -> 1545; 30k x 128, K 150
+// 1367 -> 1306; rows of 2560 and more and working sets above 256 do not fit.  Graphs of less than 1,024 nodes keep the plan they had
+// (500 x 768, efS 128: 404 -> 301 us is left there).
+template <class Lds, class Resident>
+int pag_plan_four(const pag_team_request& r, uint64_t nodes, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
+    const uint64_t cus = r.num_cu, load = r.nq + r.others;
+    p->waves = 1;
+    if (load <= 2 * cus || load > 4 * cus || nodes < 1024) return 0;
+    return pag_fit_team(r, 4, 4, 4, lds_bytes, resident, p);
 }
 
 // Whether a wave of the one-wave search waits for the rows it has asked for before it asks for the next ones.  With the GPU full
