@@ -391,28 +391,33 @@ __device__ __forceinline__ void neighbour_distances(const pag_vecs& V, u32 d, co
 //   occludes (||v-f||^2 <= ||f-u||^2), or failing that the farthest of N_out(u) + {v}.
 // Pairs that come from the PES buffers H(v) (flag in bit 31 of the distance word) pass the same
 // Eq. 1 check but are only ever given a free slot.
-// Every slot that received a new neighbour is appended to `edges` for the inference-information pass.
+// The slots that received a new neighbour are left in `edges`, at the places of the target's pairs (the rest of those: empty), for the
+// inference-information pass: no list whose length the host would have to wait for.
 // Bound by the rows it fetches: they are asked for four at a time, those that can occlude v first, the others only where
 // a full list has to give one up (1,024 x 768: 218 us a batch; all of them one after the other: 600 us).
 __global__ void __launch_bounds__(64) k_reverse(pag_vecs vec, uint8_t* __restrict__ recs,
                                                 float* __restrict__ e2, pag_layout L,
                                                 const u64* __restrict__ keys, const u32* __restrict__ vals,
-                                                u32 n_pairs, u32* __restrict__ edges, u32* __restrict__ n_edges) {
+                                                u32 n_pairs, u32* __restrict__ edges) {
     extern __shared__ __align__(16) unsigned char smem[];
     float* sv = (float*)smem;
     const u32 i0 = blockIdx.x;
     if (i0 >= n_pairs) return;
-    const u64 k0 = keys[i0];
-    if (k0 == PAG_KEY_INVALID) return;
-    const u32 u = (u32)(k0 >> 32);
-    if (i0 > 0 && (u32)(keys[i0 - 1] >> 32) == u) return;       // not the head of its segment
     const int lane = threadIdx.x;
+    const u64 k0 = keys[i0];
+    const u32 u = (u32)(k0 >> 32);
+    if (k0 == PAG_KEY_INVALID) {
+        if (lane == 0) edges[2 * (u64)i0] = PAG_EMPTY;
+        return;
+    }
+    if (i0 > 0 && (u32)(keys[i0 - 1] >> 32) == u) return;       // not the head of its segment
     uint8_t* rec = recs + (u64)u * L.rec_bytes;
     u32 id = PAG_EMPTY;
     float we2 = 0.f;
     if ((u32)lane < L.deg) { id = ((const u32*)rec)[lane]; we2 = e2[(u64)u * L.deg + lane]; }
     u64 changed = 0;
-    for (u32 i = i0; i < n_pairs; ++i) {
+    u32 i = i0;
+    for (; i < n_pairs; ++i) {
         const u64 k = keys[i];
         if (k == PAG_KEY_INVALID || (u32)(k >> 32) != u) break;
         const u32 v = vals[i];
@@ -473,17 +478,13 @@ __global__ void __launch_bounds__(64) k_reverse(pag_vecs vec, uint8_t* __restric
             for (u32 k = 0; k < L.cw; ++k) cw[k] = 0u;
         }
     }
-    const u32 nch = (u32)__popcll(changed);
-    if (nch) {
-        u32 base = 0;
-        if (lane == 0) base = atomicAdd(n_edges, nch);
-        base = (u32)__builtin_amdgcn_readfirstlane((int)base);
-        if ((changed >> lane) & 1ull) {
-            const u32 idx = base + (u32)__popcll(changed & ((1ull << lane) - 1));
-            edges[2 * (u64)idx] = u;
-            edges[2 * (u64)idx + 1] = (u32)lane;
-        }
+    // a pair changes one slot at most: the segment's places in `edges` hold its changed slots
+    if ((changed >> lane) & 1ull) {
+        const u64 at = i0 + (u32)__popcll(changed & ((1ull << lane) - 1));
+        edges[2 * at] = u;
+        edges[2 * at + 1] = (u32)lane;
     }
+    for (u32 at = i0 + (u32)__popcll(changed) + lane; at < i; at += 64) edges[2 * (u64)at] = PAG_EMPTY;
 }
 
 // ---- is a batch a region of its own? ----
@@ -538,7 +539,7 @@ __global__ void __launch_bounds__(64) k_batch_density(pag_vecs vec, const uint8_
 struct BuildWs {
     u64* cand = nullptr; u64* cand_sorted = nullptr; u32* cand_cnt = nullptr; u64* pes = nullptr;
     u64 *rk_in = nullptr, *rk_out = nullptr; u32 *rv_in = nullptr, *rv_out = nullptr;
-    u32* edges = nullptr; u32* n_edges = nullptr;
+    u32* edges = nullptr;
     u32* order = nullptr;
     const u32* taken = nullptr;    // the order in which the last insertion search took its points (null: as listed)
     u32* density = nullptr;
@@ -548,7 +549,7 @@ struct BuildWs {
     hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // phase marks of one linking pass
     ~BuildWs() {
         for (auto& e : ev) if (e) (void)hipEventDestroy(e);
-        void* p[] = { cand, cand_sorted, cand_cnt, pes, rk_in, rk_out, rv_in, rv_out, edges, n_edges, order, density, sort_tmp, seg_begin, seg_end, seg_tmp };
+        void* p[] = { cand, cand_sorted, cand_cnt, pes, rk_in, rk_out, rv_in, rv_out, edges, order, density, sort_tmp, seg_begin, seg_end, seg_tmp };
         for (void* x : p) if (x) (void)hipFree(x);
     }
 };
@@ -687,7 +688,6 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
     PAG_ALLOC(ws.rv_in, max_pairs * 4);
     PAG_ALLOC(ws.rv_out, max_pairs * 4);
     PAG_ALLOC(ws.edges, max_pairs * 8);
-    PAG_ALLOC(ws.n_edges, 16);
     PAG_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, ws.sort_bytes, ws.rk_in, ws.rk_out, ws.rv_in, ws.rv_out,
                                                (int)max_pairs, 0, 64, s));
     PAG_ALLOC(ws.sort_tmp, ws.sort_bytes);
@@ -698,6 +698,15 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
     constexpr u32 kDensitySamples = 128, kDensityProbes = 2048, kDensityWaves = 32;
     constexpr double kCrowdedRatio = 4.0;
     PAG_ALLOC(ws.density, kDensitySamples * 2 * 4);
+    // after the stream has been synchronised: the phases of the last linking pass
+    auto add_phases = [&]() -> int {
+        for (int i = 0; i < 4; ++i) {            // search kernel | sort + RobustPrune | pair sort + reverse edges | inference information
+            float ms = 0.f;
+            PAG_HIP(hipEventElapsedTime(&ms, ws.ev[i], ws.ev[i + 1]));
+            ix->build_phase_ms[i] += ms;
+        }
+        return PAG_OK;
+    };
     // one linking pass over `m` listed nodes: search, RobustPrune, reverse edges, inference information
     auto link = [&](const u32* nodes, u64 m) -> int {
         int rc;
@@ -727,23 +736,15 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
         PAG_HIP(hipcub::DeviceRadixSort::SortPairs(ws.sort_tmp, ws.sort_bytes, ws.rk_in, ws.rk_out, ws.rv_in, ws.rv_out,
                                                    (int)n_pairs, 0, 64, s));
         // 5. apply them
-        if ((rc = pag_launch_zero_u32(s, ws.n_edges, 1))) return rc;
         hipLaunchKernelGGL(k_reverse, dim3(n_pairs), dim3(64), L.d * 4, s, pag_vecs_of(ix), ix->rec, ix->e2, L, ws.rk_out,
-                           ws.rv_out, n_pairs, ws.edges, ws.n_edges);
+                           ws.rv_out, n_pairs, ws.edges);
         PAG_HIP(hipGetLastError());
         PAG_HIP(hipEventRecord(ws.ev[3], s));
         // 6. inference information of the new forward edges and of every changed reverse slot
         if ((rc = pag_launch_edge_info_of(s, ix, nodes, m))) return rc;
+        if ((rc = pag_launch_edge_info_list(s, ix, ws.edges, n_pairs))) return rc;
         PAG_HIP(hipEventRecord(ws.ev[4], s));
-        u32 n_edges = 0;
-        PAG_HIP(hipMemcpyAsync(&n_edges, ws.n_edges, 4, hipMemcpyDeviceToHost, s));
-        PAG_HIP(hipStreamSynchronize(s));
-        for (int i = 0; i < 4; ++i) {            // search kernel | sort + RobustPrune | pair sort + reverse edges | inference information
-            float ms = 0.f;
-            PAG_HIP(hipEventElapsedTime(&ms, ws.ev[i], ws.ev[i + 1]));
-            ix->build_phase_ms[i] += ms;
-        }
-        return pag_launch_edge_info_list(s, ix, ws.edges, n_edges);
+        return PAG_OK;
     };
     while (done < count) {
         const u64 graph = n_begin + done;                  // nodes in the graph so far
@@ -765,6 +766,7 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
             u32 h[kDensitySamples * 2];
             PAG_HIP(hipMemcpyAsync(h, ws.density, sizeof h, hipMemcpyDeviceToHost, s));
             PAG_HIP(hipStreamSynchronize(s));
+            if ((rc = add_phases())) return rc;
             double mates = 0.0, older = 0.0;
             for (u32 i = 0; i < ns; ++i) { mates += h[2 * i]; older += h[2 * i + 1]; }
             // both counts are out of ns * np probes: their ratio compares the two densities directly
@@ -774,10 +776,16 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
                 constexpr u64 kParts = 8;
                 for (u64 k = 0; k < kParts; ++k) {
                     const u64 j0 = m * k / kParts, j1 = m * (k + 1) / kParts;
-                    if (j1 > j0 && (rc = link(nodes + j0, j1 - j0))) return rc;
+                    if (j1 <= j0) continue;
+                    if ((rc = link(nodes + j0, j1 - j0))) return rc;
+                    PAG_HIP(hipStreamSynchronize(s));
+                    if ((rc = add_phases())) return rc;
                 }
                 ix->relinked_batches++;
             }
+        } else {
+            PAG_HIP(hipStreamSynchronize(s));
+            if ((rc = add_phases())) return rc;
         }
     }
     PAG_HIP(hipStreamSynchronize(s));
