@@ -192,6 +192,38 @@ struct PruneRows {
     }
 };
 
+// N_out(v), lane s holding its s-th neighbour and that one's distance bits, into v's record, and its pairs
+__device__ __forceinline__ void put_pruned(uint8_t* __restrict__ recs, const pag_layout& L, u32 v, u32 vi, u32 m, const u32* kept, u32 nk, u32 my_id,
+                                           u32 my_key, int lane, const u64* __restrict__ pes, float* __restrict__ e2, u64* __restrict__ rev_keys,
+                                           u32* __restrict__ rev_vals) {
+    u32* ids = (u32*)(recs + (u64)v * L.rec_bytes);
+    if ((u32)lane < L.deg) {
+        ids[lane] = my_id;
+        // ||w - v||^2 as the search computed it: what the reverse-edge step reads should v be a target in the same batch
+        e2[(u64)v * L.deg + lane] = my_id == PAG_EMPTY ? 0.f : __uint_as_float(my_key);
+        const u64 o = (u64)vi * L.deg + lane;
+        rev_keys[o] = my_id == PAG_EMPTY ? PAG_KEY_INVALID : (((u64)my_id << 32) | my_key);
+        rev_vals[o] = v;
+        if (pes) {
+            // PES candidates u -> v (Alg. 1, H(v)): pairs flagged in bit 31 of the distance word (a
+            // non-negative float never sets it), so that they sort behind the ordinary reverse edges
+            // of the same target and are only granted free slots.  Nodes already chosen as
+            // out-neighbours of v have their ordinary pair.
+            const u64 hk = pes[(u64)vi * L.deg + lane];
+            u64 pk = PAG_KEY_INVALID;
+            if (hk != PAG_KEY_INVALID) {
+                const u32 u = (u32)(hk & 0xFFFFFFFFull) >> 1;
+                bool dup = u == v;
+                for (u32 s = 0; s < nk; ++s) dup = dup || kept[s] == u;
+                if (!dup) pk = ((u64)u << 32) | 0x80000000ull | (hk >> 32);
+            }
+            const u64 o2 = (u64)m * L.deg + o;
+            rev_keys[o2] = pk;
+            rev_vals[o2] = v;
+        }
+    }
+}
+
 template <int NQ, int C, int G, int NB>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 4)))
 k_prune(pag_vecs vec, uint8_t* __restrict__ recs, pag_layout L, const u32* __restrict__ nodes, u32 m,
@@ -320,31 +352,121 @@ k_prune(pag_vecs vec, uint8_t* __restrict__ recs, pag_layout L, const u32* __res
         if (done) break;
     }
     __syncthreads();
-    u32* ids = (u32*)(recs + (u64)v * L.rec_bytes);
-    if ((u32)lane < L.deg) {
-        ids[lane] = my_id;
-        // ||w - v||^2 as the search computed it: what the reverse-edge step reads should v be a target in the same batch
-        e2[(u64)v * L.deg + lane] = my_id == PAG_EMPTY ? 0.f : __uint_as_float(my_key);
-        const u64 o = (u64)vi * L.deg + lane;
-        rev_keys[o] = my_id == PAG_EMPTY ? PAG_KEY_INVALID : (((u64)my_id << 32) | my_key);
-        rev_vals[o] = v;
-        if (pes) {
-            // PES candidates u -> v (Alg. 1, H(v)): pairs flagged in bit 31 of the distance word (a
-            // non-negative float never sets it), so that they sort behind the ordinary reverse edges
-            // of the same target and are only granted free slots.  Nodes already chosen as
-            // out-neighbours of v have their ordinary pair.
-            const u64 hk = pes[(u64)vi * L.deg + lane];
-            u64 pk = PAG_KEY_INVALID;
-            if (hk != PAG_KEY_INVALID) {
-                const u32 u = (u32)(hk & 0xFFFFFFFFull) >> 1;
-                bool dup = u == v;
-                for (u32 s = 0; s < nk; ++s) dup = dup || kept[s] == u;
-                if (!dup) pk = ((u64)u << 32) | 0x80000000ull | (hk >> 32);
-            }
-            const u64 o2 = (u64)m * L.deg + o;
-            rev_keys[o2] = pk;
-            rev_vals[o2] = v;
+    put_pruned(recs, L, v, vi, m, kept, nk, my_id, my_key, lane, pes, e2, rev_keys, rev_vals);
+}
+
+// The same with four waves per node, for batches that leave the GPU mostly idle with one: each wave tests two candidates of eight
+// against the rows kept so far, which the waves share in LDS (J of them, and one place more); the step's survivors are then
+// kept in list order, each written by its wave and met by the survivors behind it.  One wave spends 5 us on a step of two, 1.7 of it
+// in arithmetic alone; what bounds four is that arithmetic (1,024 nodes of 768-d, 200 candidates each: 519 -> 250 us).
+template <int NQ>
+__global__ void __launch_bounds__(256) k_prune_team(pag_vecs vec, uint8_t* __restrict__ recs, pag_layout L, const u32* __restrict__ nodes, u32 m,
+            const u64* __restrict__ cand_sorted, const u32* __restrict__ cand_cnt, u32 cand_cap, u32 efC, u32 J,
+            const u64* __restrict__ pes, float* __restrict__ e2, u64* __restrict__ rev_keys, u32* __restrict__ rev_vals,
+            const u32* __restrict__ taken) {
+    constexpr int C = 2, G = 2, WAVES = 4;
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (blockIdx.x >= m) return;
+    const u32 vi = taken ? taken[blockIdx.x] : blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = (int)(threadIdx.x >> 6);
+    u32* kept = (u32*)(smem + (size_t)(J + 1) * NQ * 1024);  // [64]
+    u32* kept_key = kept + 64;                               // [64]
+    u32* alive = kept_key + 64;                              // [2][WAVES]: which of a wave's candidates survive
+    const PruneRows<NQ, C, G> P{vec, L.d / 4, lane, (float4*)smem};
+    const u64* sorted = cand_sorted + (u64)vi * cand_cap;
+    const u32 v = nodes[vi];
+    u32 nc = cand_cnt[vi];
+    if (nc > cand_cap) nc = cand_cap;
+    if (nc > efC) nc = efC;
+    u32 nk = 0;
+
+    auto fetch = [&](u32 ci, u64 (&key)[C], float4 (&rows)[C][NQ]) {       // candidates ci, ci + 1 (the last one again where there is none)
+#pragma unroll
+        for (int i = 0; i < C; ++i) key[i] = sorted[ci + i < nc ? ci + i : nc - 1];
+#pragma unroll
+        for (int i = 0; i < C; ++i) P.load_row((u32)__builtin_amdgcn_readfirstlane((int)(u32)key[i]) >> 1, rows[i]);
+    };
+    // one step: WAVES * C candidates from ci0 on
+    auto decide = [&](u32 ci0, u32 parity, const u64 (&key)[C], const float4 (&rows)[C][NQ]) {
+        const u32 ci = ci0 + (u32)wave * C;
+        float dv[C], dd[C];
+        bool occ[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            dv[i] = __uint_as_float((u32)(key[i] >> 32));
+            occ[i] = !(ci + i < nc) || (u32)(key[i] & 0xFFFFFFFFull) >> 1 == v;
         }
+        const u32 in_lds = nk < J ? nk : J;
+        for (u32 j = 0; j < in_lds && !(occ[0] && occ[1]); ++j) {
+            P.to_lds_row(rows, j, dd);
+#pragma unroll
+            for (int i = 0; i < C; ++i) occ[i] = occ[i] || dd[i] <= dv[i];
+        }
+        for (u32 s0 = J; s0 < nk && !(occ[0] && occ[1]); s0 += G) {
+            u32 sid[G];
+            float dm[C][G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) sid[g] = kept[s0 + g < nk ? s0 + g : nk - 1];
+            P.to_memory_rows(rows, sid, dm);
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+#pragma unroll
+                for (int g = 0; g < G; ++g) occ[i] = occ[i] || dm[i][g] <= dv[i];
+        }
+        u32* words = alive + parity * WAVES;
+        if (lane == 0) words[wave] = (occ[0] ? 0u : 1u) | (occ[1] ? 0u : 2u);
+        __syncthreads();
+        u32 left = words[0] | words[1] << 2 | words[2] << 4 | words[3] << 6;     // in list order
+        left = (u32)__builtin_amdgcn_readfirstlane((int)left);
+        while (left && nk < L.deg) {
+            const u32 first = (u32)__builtin_ctz(left);
+            left &= left - 1;
+            const u32 place = nk < J ? nk : J;
+            if (first / C == (u32)wave) {
+#pragma unroll
+                for (int i = 0; i < C; ++i)
+                    if (first % C == (u32)i) {
+                        if (lane == 0) { kept[nk] = (u32)(key[i] & 0xFFFFFFFFull) >> 1; kept_key[nk] = (u32)(key[i] >> 32); }
+                        float4* kr = P.K + (size_t)place * (NQ * 64);
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) kr[lane + 64 * q] = rows[i][q];
+                    }
+            }
+            nk++;
+            __syncthreads();
+            if (!left || nk == L.deg) break;
+            const u32 mine = (left >> (C * wave)) & 3u;
+            if (mine) {
+                P.to_lds_row(rows, place, dd);
+                const u32 gone = (dd[0] <= dv[0] ? 1u : 0u) | (dd[1] <= dv[1] ? 2u : 0u);
+                if (lane == 0) words[wave] = mine & ~gone;
+            } else if (lane == 0) {
+                words[wave] = 0u;
+            }
+            __syncthreads();
+            left = words[0] | words[1] << 2 | words[2] << 4 | words[3] << 6;
+            left = (u32)__builtin_amdgcn_readfirstlane((int)left);
+        }
+    };
+
+    u64 key[2][C];
+    float4 row[2][C][NQ];
+    constexpr u32 STEP = WAVES * C;
+    if (nc) {
+        fetch((u32)wave * C, key[0], row[0]);
+        fetch(STEP + (u32)wave * C, key[1], row[1]);
+    }
+    for (u32 ci = 0; ci < nc && nk < L.deg; ci += 2 * STEP) {
+        decide(ci, 0u, key[0], row[0]);
+        if (ci + STEP >= nc || nk == L.deg) break;
+        fetch(ci + 2 * STEP + (u32)wave * C, key[0], row[0]);
+        decide(ci + STEP, 1u, key[1], row[1]);
+        fetch(ci + 3 * STEP + (u32)wave * C, key[1], row[1]);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const u32 my_id = (u32)lane < nk ? kept[lane] : PAG_EMPTY, my_key = (u32)lane < nk ? kept_key[lane] : 0u;
+        put_pruned(recs, L, v, vi, m, kept, nk, my_id, my_key, lane, pes, e2, rev_keys, rev_vals);
     }
 }
 
@@ -352,6 +474,24 @@ template <int NQ>
 static int launch_prune(hipStream_t s, const pag_index* ix, const u32* nodes, u32 m, const u64* cand_sorted,
                         const u32* cand_cnt, u32 cand_cap, const u64* pes, u64* rev_keys, u32* rev_vals, const u32* taken) {
     const pag_layout& L = ix->L;
+    // Four waves per node in small batches: prune phase of a build of 24,000, one wave -> four, batches of 256 / 1,024 / 2,048:
+    // 128-d 17.6 -> 8.5, 5.3 -> 2.9, 3.6 -> 2.5 ms, 768-d 46 -> 20, 14.5 -> 7.8, 10.0 -> 6.8, 1536-d 96 -> 43, 30 -> 19, 21 -> 17, 3072-d
+    // 135 -> 61 at 256, 74 -> 53 at 512, 41 -> 46 at 1,024.  Large batches fetch their rows from HBM, and then the waves that one-wave
+    // groups leave room for matter more: 200,000 x 1536 in batches of 4,096 163 -> 178 ms, 16,384 127 -> 157 (300,000 x 768: 106 -> 90, 82 -> 77).
+    const u32 cus = (u32)ix->num_cu;
+    if (m <= (NQ <= 4 ? 8u : NQ <= 8 ? 4u : 2u) * cus) {
+        // as many kept rows as the LDS holds with the nodes that share a CU
+        const u32 share = std::min<u32>((m + cus - 1) / cus, 4u), fixed = (64 + 64 + 8) * 4;
+        const u32 room = std::min<u32>(65536u, ix->lds_per_cu / share - 512u);
+        const u32 fit = (room - fixed) / (NQ * 1024u);
+        if (fit >= 2) {
+            const u32 J = std::min<u32>(fit - 1, L.deg);
+            hipLaunchKernelGGL((k_prune_team<NQ>), dim3(m), dim3(256), (J + 1) * NQ * 1024u + fixed, s, pag_vecs_of(ix), ix->rec, L, nodes, m, cand_sorted,
+                               cand_cnt, cand_cap, ix->efC, J, pes, ix->e2, rev_keys, rev_vals, taken);
+            PAG_HIP(hipGetLastError());
+            return PAG_OK;
+        }
+    }
     // kept rows held in LDS (slots of NQ KB): four, more while they fit 16 KB, fewer beyond 36 KB.  Measured on
     // 1M x 768 / 1024 / 1536 and 250k x 3072: 16 / 16 / 24 / 36 KB are the fastest; larger sets lose more waves than
     // they save reads.
