@@ -1223,7 +1223,6 @@ struct Wave {
         TM_NODE = 4, TM_NODE_DIST, TM_FAR_LO, TM_FAR_HI,
         // two words wave 0: W's closest unvisited member after that (PAG_EMPTY: none); wave 1: the node whose neighbours are screened
         TM_SECOND = 8, TM_SECOND_DIST, TM_SCREENED,
-        TM_MIN = 16,                                   // u64 per hop parity: the smallest key of the hop's passers
         TM_ID = 64,                                    // wave 1, per neighbour slot: id (PAG_EMPTY: not an unseen node)
         TM_EST = 128,                                  // wave 2, per neighbour slot: estimate
         TM_KEY = 192                                   // u64: keys of the hop's passers, in slot order
@@ -1242,7 +1241,19 @@ struct Wave {
 
     __device__ __forceinline__ u32 team_index(u64 mask) const { return (u32)__popcll(mask & ((1ull << lane) - 1)); }
     __device__ __forceinline__ u64* team_keys() const { return (u64*)(team + TM_KEY); }
-    __device__ __forceinline__ u64* team_min(u32 hop) const { return (u64*)(team + TM_MIN) + (hop & 1u); }
+
+    // the smallest key of the hop's np passers; PAG_KEY_INVALID: there are none
+    __device__ __forceinline__ u64 closest_passer(u32 np) const {
+        if (np == 0) return PAG_KEY_INVALID;
+        const u64 k = (u32)lane < np ? team_keys()[lane] : PAG_KEY_INVALID;
+        const u32 hi = (u32)(k >> 32);
+        if (np <= 16) {
+            const u32 mh = row0_extreme_u32<false>(hi);
+            return ((u64)mh << 32) | row0_extreme_u32<false>(hi == mh ? (u32)k : 0xFFFFFFFFu);
+        }
+        const u32 mh = wave_extreme_u32<false>(hi);
+        return ((u64)mh << 32) | wave_extreme_u32<false>(hi == mh ? (u32)k : 0xFFFFFFFFu);
+    }
 
     // This wave's share of the rows of the lanes in `mask`, TR of them in flight at a time.  The rows of a wave are reduced
     // together: one row alone is a chain of dependent instructions.
@@ -1250,7 +1261,7 @@ struct Wave {
 
     // keys of G rows (those with i < r exist)
     template <int G>
-    __device__ __forceinline__ void team_reduce(const Chunk (&v)[TR][NQ], const u32 (&id)[TR], u32 at, u32 step, u32 r, u32 hop) const {
+    __device__ __forceinline__ void team_reduce(const Chunk (&v)[TR][NQ], const u32 (&id)[TR], u32 at, u32 step, u32 r) const {
         double acc[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) acc[g] = lane_partial(v[g]);
@@ -1265,43 +1276,40 @@ struct Wave {
         }
         if ((u32)lane % (64 / G) == 0 && g < r) {
             const u32 bits = __float_as_uint((float)tot);       // a NaN of either sign: the largest distance
-            const u64 key = ((u64)(bits < 0x7FC00000u ? bits : 0x7FC00000u) << 32) | ((u64)my_id << 1);
-            team_keys()[at + g * step] = key;
-            atomicMin((unsigned long long*)team_min(hop), (unsigned long long)key);
+            team_keys()[at + g * step] = ((u64)(bits < 0x7FC00000u ? bits : 0x7FC00000u) << 32) | ((u64)my_id << 1);
         }
     }
 
-    // Half of the nodes that are expanded are passers of the hop before: the row's record is asked for behind it, one lane per
+    // Half of the nodes that are expanded are passers of the hop before: AHEAD asks for a row's record behind it, one lane per
     // 128-byte line, so that the caches have it when the node is screened (teams of six and more: smaller ones fill the GPU, and
-    // then the traffic costs more; without a branch, which would wait for it).  Returns something of it, to be waited for later.
-    __device__ __forceinline__ u32 team_rows(u32 id_lane, u64 mask, u32 hop) const {
-        const u32 first = split() ? 3u : 2u;                // the first wave that fetches rows
+    // then the traffic costs more).  Returns something of it, to be waited for later.
+    template <bool AHEAD>
+    __device__ __forceinline__ u32 team_rows(u32 id_lane, u64 mask) const {
+        const u32 first = AHEAD ? 3u : 2u;                  // the first wave that fetches rows
         const u32 n = (u32)__popcll(mask), step = (u32)nwaves - first;
         const u32 mine = ((mask >> lane) & 1ull) ? team_index(mask) : PAG_EMPTY;
-        const bool ahead = split();
-        const u32 line = ahead && (u32)lane * 128u < A.rec_bytes ? (u32)lane * 128u : 0u;
-        const u64 stride = ahead ? A.rec_bytes : (u64)A.d * (HALF ? 2 : 4);
-        const char* store = ahead ? (const char*)A.rec : (const char*)A.vec;
+        const u32 line = (u32)lane * 128u < A.rec_bytes ? (u32)lane * 128u : 0u;
         u32 touched = 0;
         for (u32 at = (u32)wave - first; at < n; at += TR * step) {
             Chunk v[TR][NQ];
             u32 id[TR], word[TR], r = 0;
 #pragma unroll
             for (int g = 0; g < TR; ++g) {
-                id[g] = 0;
+                id[g] = 0; word[g] = 0;
                 if (at + (u32)g * step < n) {
                     id[g] = rdlane(id_lane, __ffsll((long long)__ballot(mine == at + (u32)g * step)) - 1);
                     load_vec(v[g], id[g]);
+                    if constexpr (AHEAD) word[g] = *(const u32*)(A.rec + (u64)id[g] * A.rec_bytes + line);
                     ++r;
                 }
             }
+            if (TR >= 4 && r > 2) { if constexpr (TR >= 4) team_reduce<4>(v, id, at, step, r); }
+            else if (TR >= 2 && r > 1) { if constexpr (TR >= 2) team_reduce<2>(v, id, at, step, r); }
+            else team_reduce<1>(v, id, at, step, r);
+            if constexpr (AHEAD) {
 #pragma unroll
-            for (int g = 0; g < TR; ++g) word[g] = *(const u32*)(store + (u64)((u32)g < r ? id[g] : id[0]) * stride + line);
-            if (TR >= 4 && r > 2) { if constexpr (TR >= 4) team_reduce<4>(v, id, at, step, r, hop); }
-            else if (TR >= 2 && r > 1) { if constexpr (TR >= 2) team_reduce<2>(v, id, at, step, r, hop); }
-            else team_reduce<1>(v, id, at, step, r, hop);
-#pragma unroll
-            for (int g = 0; g < TR; ++g) touched |= word[g];
+                for (int g = 0; g < TR; ++g) touched |= word[g];
+            }
         }
         return touched;
     }
@@ -1502,10 +1510,11 @@ struct Wave {
 
     // One wave of the workgroup: queries until the batch is drained.  Each role is compiled by itself, so that the
     // registers hold what that role needs.
-    enum Role { LISTS, SEEN, ESTIMATES, SCREEN, ROWS };       // SCREEN: SEEN and ESTIMATES in one wave
+    enum Role { LISTS, SEEN, ESTIMATES, SCREEN, ROWS, ROWS_AHEAD };       // SCREEN: SEEN and ESTIMATES in one wave; ROWS_AHEAD: see team_rows
     template <Role ROLE>
     __device__ __forceinline__ void run_team() {
         constexpr bool KEEPS_SEEN = ROLE == SEEN || ROLE == SCREEN, ESTIMATE = ROLE == ESTIMATES || ROLE == SCREEN;
+        constexpr bool AHEAD = ROLE == ROWS_AHEAD, FETCH = ROLE == ROWS || AHEAD;
         for (u32 take = 0;; ++take) {
             if constexpr (ROLE == LISTS) {
                 u32 qi = take == 0 ? blockIdx.x : next_query();
@@ -1528,7 +1537,7 @@ struct Wave {
                 const u64 mask = __ballot(pass);
                 if (mask == 0ull) continue;
                 const u32 np = (u32)__popcll(mask);
-                if constexpr (ROLE == ROWS) (void)team_rows(id, mask, 0u);
+                if constexpr (FETCH) (void)team_rows<AHEAD>(id, mask);
                 if constexpr (KEEPS_SEEN) mark_seen(id, np, pass);
                 team_barrier();
                 if constexpr (ROLE == LISTS) {
@@ -1545,19 +1554,19 @@ struct Wave {
             if constexpr (ROLE == LISTS) {
                 if (nW != 0) s_rounds++;
                 post_next(qi);
-                if (lane == 0) *team_min(0) = *team_min(1) = PAG_KEY_INVALID;
             }
             if (KEEPS_SEEN && lane == 0) team[TM_SCREENED] = PAG_EMPTY;
             team_barrier();
             // ---- hops ----
             bool owed = false;                         // wave 0: a merge whose ring pushes are outstanding
             Merge M;
-            for (u32 hop = 0;; ++hop) {
+            for (;;) {
                 PAG_MARK(0);
                 // all that wave 0 and the screening have left, asked for at once
-                const uint4 posted = *(const uint4*)(team + TM_NODE), more = *(const uint4*)(team + TM_SECOND);
+                uint4 posted = *(const uint4*)(team + TM_NODE), more = *(const uint4*)(team + TM_SECOND);
                 u32 id = team[TM_ID + lane];
                 float est = __uint_as_float(team[TM_EST + lane]);
+                asm volatile("" : "+v"(posted.x), "+v"(posted.y), "+v"(posted.z), "+v"(posted.w), "+v"(more.x), "+v"(more.y), "+v"(more.z), "+v"(id), "+v"(est));
                 const u32 u = uniform(posted.x), du = uniform(posted.y);
                 if (u == PAG_EMPTY) break;
                 const u64 far = ((u64)uniform(posted.w) << 32) | uniform(posted.z);
@@ -1576,10 +1585,9 @@ struct Wave {
                 PAG_MARK(2);
                 bool unseen = false;                   // of the neighbours of `second`
                 u32 touched = 0;
-                if constexpr (ROLE == ROWS) {
-                    touched = team_rows(id, mask, hop);
+                if constexpr (FETCH) {
+                    touched = team_rows<AHEAD>(id, mask);
                 } else if constexpr (ROLE == LISTS) {
-                    if (lane == 0) *team_min(hop + 1) = PAG_KEY_INVALID;   // last read before the barrier that began this hop
                     if (owed) merge_rings(M);
                     keep_best();
                 } else {
@@ -1602,7 +1610,7 @@ struct Wave {
                 PAG_MARK(1);
                 team_barrier();
                 PAG_MARK(3);
-                if constexpr (ROLE == ROWS) asm volatile("" :: "v"(touched));
+                if constexpr (AHEAD) asm volatile("" :: "v"(touched));
                 if constexpr (ROLE == LISTS) {
                     s_exact += np;
                     if constexpr (BIG) {
@@ -1623,9 +1631,9 @@ struct Wave {
                     }
                 }
                 if constexpr (KEEPS_SEEN || ESTIMATE) {
-                    const u64 first = *team_min(hop);  // of the passers; PAG_KEY_INVALID: none
+                    const u64 first = closest_passer(np);
                     const u64 next2 = second != PAG_EMPTY ? ((u64)second_d << 32) | ((u64)second << 1) : PAG_KEY_INVALID;
-                    const bool passer = __ballot(first < far && first < next2) != 0ull;
+                    const bool passer = first < far && first < next2;
                     const u64 next = passer ? first : next2;
                     const u32 node = uniform(next != PAG_KEY_INVALID ? (u32)next >> 1 : PAG_EMPTY);
                     if (KEEPS_SEEN && lane == 0) team[TM_SCREENED] = node;
@@ -1727,7 +1735,8 @@ __global__ void __launch_bounds__(64 * pag_team_max(NW)) k_search_team(const Sea
     } else if (w.wave == 2 && w.split()) {
         w.template run_team<Wv::ESTIMATES>();
     } else {
-        w.template run_team<Wv::ROWS>();
+        if (w.split()) w.template run_team<Wv::ROWS_AHEAD>();
+        else w.template run_team<Wv::ROWS>();
     }
 }
 

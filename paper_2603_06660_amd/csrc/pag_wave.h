@@ -9,8 +9,9 @@ namespace pagk {
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double x) {
     int lo = __double2loint(x), hi = __double2hiint(x);
-    lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xF, 0xF, false);
+    // every lane has a source in the patterns used; bound_ctrl spares the register that would stand in for one
+    lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xF, 0xF, true);
+    hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
 
@@ -81,7 +82,7 @@ __device__ __forceinline__ u32 pick32(u32 a, u32 b) {
 
 template <int CTRL>
 __device__ __forceinline__ u32 dpp_move_u32(u32 x) {
-    return (u32)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
+    return (u32)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
 }
 
 template <bool MAX>
