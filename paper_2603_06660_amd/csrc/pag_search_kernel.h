@@ -1200,8 +1200,8 @@ struct Wave {
     // ---- several waves on one query (TEAM) ----
     // With few queries the GPU waits for one hop after the other, and a single wave adds up the hop's trips to memory
     // (record, rows two at a time, next record) and all of its bookkeeping, at one instruction per 4 to 10 clocks.  Here
-    // wave 0 keeps W and the rings, wave 1 the seen set, wave 2 (wave 1 too, in teams of less than six) computes the
-    // estimates, and the other waves fetch the rows.  A hop has two phases between barriers:
+    // wave 0 keeps W and the rings, wave 1 the seen set, wave 2 computes the estimates (in teams of less than six wave 1 those
+    // that have time, and wave 2 fetches rows besides), and the other waves fetch the rows.  A hop has two phases between barriers:
     //   rows    every wave reads the node's neighbours, their estimates and the threshold from LDS and derives the
     //           passers, whose rows are fetched all at once, their records behind them.  Meanwhile wave 0 does what the last
     //           hop left it (ring pushes, a finished round's entry into R_L), wave 1 enters the passers into the seen set, and the
@@ -1515,6 +1515,9 @@ struct Wave {
     __device__ __forceinline__ void run_team() {
         constexpr bool KEEPS_SEEN = ROLE == SEEN || ROLE == SCREEN, ESTIMATE = ROLE == ESTIMATES || ROLE == SCREEN;
         constexpr bool AHEAD = ROLE == ROWS_AHEAD, FETCH = ROLE == ROWS || AHEAD;
+        // a node whose estimates are not at hand gets them from wave 2, in small teams too: its rows are done then
+        constexpr bool MAY_ESTIMATE = ROLE == ESTIMATES || ROLE == ROWS;
+        const bool estimates = ROLE == ESTIMATES || (ROLE == ROWS && wave == 2);
         for (u32 take = 0;; ++take) {
             if constexpr (ROLE == LISTS) {
                 u32 qi = take == 0 ? blockIdx.x : next_query();
@@ -1573,7 +1576,8 @@ struct Wave {
                 const u32 second = uniform(more.x), second_d = uniform(more.y);
                 // TM_SCREENED stays as it is until all waves have read it: it is written again after the rows
                 if (uniform(more.z) != u) {
-                    if constexpr (KEEPS_SEEN || ESTIMATE) screen_node<KEEPS_SEEN, ESTIMATE>(u, __uint_as_float(du));
+                    if constexpr (KEEPS_SEEN) screen_node<true, false>(u, __uint_as_float(du));
+                    if constexpr (MAY_ESTIMATE) { if (estimates) screen_node<false, true>(u, __uint_as_float(du)); }
                     team_barrier();
                     id = team[TM_ID + lane];
                     est = __uint_as_float(team[TM_EST + lane]);
@@ -1630,7 +1634,7 @@ struct Wave {
                         }
                     }
                 }
-                if constexpr (KEEPS_SEEN || ESTIMATE) {
+                if ((KEEPS_SEEN || ESTIMATE) || (MAY_ESTIMATE && estimates)) {
                     const u64 first = closest_passer(np);
                     const u64 next2 = second != PAG_EMPTY ? ((u64)second_d << 32) | ((u64)second << 1) : PAG_KEY_INVALID;
                     const bool passer = first < far && first < next2;
@@ -1639,7 +1643,8 @@ struct Wave {
                     if (KEEPS_SEEN && lane == 0) team[TM_SCREENED] = node;
                     const float Du = __uint_as_float((u32)(next >> 32));
                     if (passer) {
-                        screen_node<KEEPS_SEEN, ESTIMATE>(node, Du);
+                        if constexpr (KEEPS_SEEN) screen_node<true, false>(node, Du);
+                        if constexpr (MAY_ESTIMATE) screen_node<false, true>(node, Du);
                     } else if (node != PAG_EMPTY) {
                         if constexpr (KEEPS_SEEN) put_unseen(pf_id, unseen);
                         if constexpr (ESTIMATE) put_estimate(Du, pf_a, pf_c, pf_sum);
