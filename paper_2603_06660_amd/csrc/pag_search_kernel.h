@@ -268,6 +268,7 @@ struct Wave {
     u32 n_hash, n_spill;
     u32 n_cand;                     // indexing mode: entries of R_L written so far
     u32 round;                      // TEAM, wave 0: rounds finished
+    u32 posted_node;                // TEAM, wave 0: the node to expand next
     u32 scr_id;                     // TEAM, wave 1: the neighbours last screened
     float pf_sum; bool pf_summed;   // TEAM: the code sums of the record in pf_*, once they are computed
     // The last TAILS chunk rows of the NQ may lie partly or wholly beyond the end of a row (the host
@@ -1200,8 +1201,8 @@ struct Wave {
     // ---- several waves on one query (TEAM) ----
     // With few queries the GPU waits for one hop after the other, and a single wave adds up the hop's trips to memory
     // (record, rows two at a time, next record) and all of its bookkeeping, at one instruction per 4 to 10 clocks.  Here
-    // wave 0 keeps W and the rings, wave 1 the seen set, wave 2 computes the estimates (in teams of less than six wave 1 those
-    // that have time, and wave 2 fetches rows besides), and the other waves fetch the rows.  A hop has two phases between barriers:
+    // wave 0 keeps W and the rings, wave 1 the seen set, wave 2 computes the estimates, and the other waves fetch the rows; in teams of
+    // less than six wave 0 computes those estimates that have time, and wave 2 fetches rows besides.  A hop has two phases between barriers:
     //   rows    every wave reads the node's neighbours, their estimates and the threshold from LDS and derives the
     //           passers, whose rows are fetched all at once, their records behind them.  Meanwhile wave 0 does what the last
     //           hop left it (ring pushes, a finished round's entry into R_L), wave 1 enters the passers into the seen set, and the
@@ -1271,7 +1272,7 @@ struct Wave {
 #pragma unroll
         for (u32 i = 1; i < G; ++i) {
             u32 other = id[i];
-            asm volatile("" : "+s"(other));                 // or the compiler indexes the ids in scratch
+            asm volatile("" : "+v"(other));                 // or the compiler indexes the ids in scratch
             my_id = g == i ? other : my_id;
         }
         if ((u32)lane % (64 / G) == 0 && g < r) {
@@ -1332,9 +1333,10 @@ struct Wave {
     }
 
     // wave 0: what the other waves need to know of W
-    __device__ __forceinline__ void post(u64 node, u64 far, u64 second) const {
+    __device__ __forceinline__ void post(u64 node, u64 far, u64 second) {
+        const u32 n = posted_node = node != PAG_KEY_INVALID ? (u32)node >> 1 : PAG_EMPTY;
         if (lane == 0) {
-            const u32 n = node != PAG_KEY_INVALID ? (u32)node >> 1 : PAG_EMPTY, s = second != PAG_KEY_INVALID ? (u32)second >> 1 : PAG_EMPTY;
+            const u32 s = second != PAG_KEY_INVALID ? (u32)second >> 1 : PAG_EMPTY;
             *(uint4*)(team + TM_NODE) = make_uint4(n, (u32)(node >> 32), (u32)far, (u32)(far >> 32));
             *(uint2*)(team + TM_SECOND) = make_uint2(s, (u32)(second >> 32));
         }
@@ -1510,16 +1512,18 @@ struct Wave {
 
     // One wave of the workgroup: queries until the batch is drained.  Each role is compiled by itself, so that the
     // registers hold what that role needs.
-    enum Role { LISTS, SEEN, ESTIMATES, SCREEN, ROWS, ROWS_AHEAD };       // SCREEN: SEEN and ESTIMATES in one wave; ROWS_AHEAD: see team_rows
+    enum Role { LISTS, SEEN, ESTIMATES, ROWS_AHEAD, LISTS_FEW, ROWS };       // teams of six and more: the first four; smaller ones: LISTS_FEW, SEEN, ROWS
     template <Role ROLE>
     __device__ __forceinline__ void run_team() {
-        constexpr bool KEEPS_SEEN = ROLE == SEEN || ROLE == SCREEN, ESTIMATE = ROLE == ESTIMATES || ROLE == SCREEN;
+        constexpr bool KEEPS_LISTS = ROLE == LISTS || ROLE == LISTS_FEW, KEEPS_SEEN = ROLE == SEEN;
         constexpr bool AHEAD = ROLE == ROWS_AHEAD, FETCH = ROLE == ROWS || AHEAD;
-        // a node whose estimates are not at hand gets them from wave 2, in small teams too: its rows are done then
+        // the estimates of the neighbours of W's closest unvisited member, computed ahead: wave 2, in small teams wave 0
+        constexpr bool ESTIMATE = ROLE == ESTIMATES || ROLE == LISTS_FEW;
+        // those of a node whose record is not at hand: wave 2, in small teams too, whose rows are done then
         constexpr bool MAY_ESTIMATE = ROLE == ESTIMATES || ROLE == ROWS;
         const bool estimates = ROLE == ESTIMATES || (ROLE == ROWS && wave == 2);
         for (u32 take = 0;; ++take) {
-            if constexpr (ROLE == LISTS) {
+            if constexpr (KEEPS_LISTS) {
                 u32 qi = take == 0 ? blockIdx.x : next_query();
                 if (qi >= A.nq) qi = PAG_EMPTY;
                 else if (A.order) qi = A.order[qi];
@@ -1531,7 +1535,7 @@ struct Wave {
             begin_query(qi);
             reset_lists();
             team_barrier();
-            if constexpr (ROLE == LISTS) s_queries++;
+            if constexpr (KEEPS_LISTS) s_queries++;
             // ---- b entry nodes ----
             const u32 ne = A.n_entry < A.b ? A.n_entry : A.b;
             for (u32 base = 0; base < ne; base += 64) {
@@ -1543,7 +1547,7 @@ struct Wave {
                 if constexpr (FETCH) (void)team_rows<AHEAD>(id, mask);
                 if constexpr (KEEPS_SEEN) mark_seen(id, np, pass);
                 team_barrier();
-                if constexpr (ROLE == LISTS) {
+                if constexpr (KEEPS_LISTS) {
                     s_exact += np;
                     if constexpr (BIG) {
                         merge_unsorted(id, mask, np, pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
@@ -1554,7 +1558,7 @@ struct Wave {
                 }
                 team_barrier();
             }
-            if constexpr (ROLE == LISTS) {
+            if constexpr (KEEPS_LISTS) {
                 if (nW != 0) s_rounds++;
                 post_next(qi);
             }
@@ -1589,33 +1593,31 @@ struct Wave {
                 PAG_MARK(2);
                 bool unseen = false;                   // of the neighbours of `second`
                 u32 touched = 0;
-                if constexpr (FETCH) {
-                    touched = team_rows<AHEAD>(id, mask);
-                } else if constexpr (ROLE == LISTS) {
+                if constexpr (KEEPS_SEEN) {
+                    if (A.pes != nullptr) screen_pes(scr_id, est, ((u64)du << 32) | ((u64)u << 1));
+                }
+                if constexpr (KEEPS_SEEN || ESTIMATE) {
+                    if (second != PAG_EMPTY) fetch_screen<KEEPS_SEEN, ESTIMATE>(second);
+                }
+                if constexpr (FETCH) touched = team_rows<AHEAD>(id, mask);
+                if constexpr (KEEPS_SEEN) {
+                    s_tests += (u32)__popcll(__ballot(id != PAG_EMPTY));
+                    s_passes += np;
+                    if (np) mark_seen(id, np, pass);
+                    if (second != PAG_EMPTY) unseen = find_unseen(pf_id);
+                }
+                if constexpr (KEEPS_LISTS) {
                     if (owed) merge_rings(M);
                     keep_best();
-                } else {
-                    if constexpr (KEEPS_SEEN) {
-                        if (A.pes != nullptr) screen_pes(scr_id, est, ((u64)du << 32) | ((u64)u << 1));
-                    }
-                    if constexpr (KEEPS_SEEN || ESTIMATE) {
-                        if (second != PAG_EMPTY) fetch_screen<KEEPS_SEEN, ESTIMATE>(second);
-                    }
-                    if constexpr (KEEPS_SEEN) {
-                        s_tests += (u32)__popcll(__ballot(id != PAG_EMPTY));
-                        s_passes += np;
-                        if (np) mark_seen(id, np, pass);
-                        if (second != PAG_EMPTY) unseen = find_unseen(pf_id);
-                    }
-                    if constexpr (ESTIMATE) {
-                        if (second != PAG_EMPTY) sum_codes();
-                    }
+                }
+                if constexpr (ESTIMATE) {
+                    if (second != PAG_EMPTY) sum_codes();
                 }
                 PAG_MARK(1);
                 team_barrier();
                 PAG_MARK(3);
                 if constexpr (AHEAD) asm volatile("" :: "v"(touched));
-                if constexpr (ROLE == LISTS) {
+                if constexpr (KEEPS_LISTS) {
                     s_exact += np;
                     if constexpr (BIG) {
                         owed = false;
@@ -1634,7 +1636,7 @@ struct Wave {
                         }
                     }
                 }
-                if ((KEEPS_SEEN || ESTIMATE) || (MAY_ESTIMATE && estimates)) {
+                if (KEEPS_SEEN || (MAY_ESTIMATE && estimates)) {
                     const u64 first = closest_passer(np);
                     const u64 next2 = second != PAG_EMPTY ? ((u64)second_d << 32) | ((u64)second << 1) : PAG_KEY_INVALID;
                     const bool passer = first < far && first < next2;
@@ -1647,14 +1649,17 @@ struct Wave {
                         if constexpr (MAY_ESTIMATE) screen_node<false, true>(node, Du);
                     } else if (node != PAG_EMPTY) {
                         if constexpr (KEEPS_SEEN) put_unseen(pf_id, unseen);
-                        if constexpr (ESTIMATE) put_estimate(Du, pf_a, pf_c, pf_sum);
+                        if constexpr (ROLE == ESTIMATES) put_estimate(Du, pf_a, pf_c, pf_sum);
                     }
+                }
+                if constexpr (ROLE == LISTS_FEW) {
+                    if (second != PAG_EMPTY && posted_node == second) put_estimate(__uint_as_float(second_d), pf_a, pf_c, pf_sum);
                 }
                 PAG_MARK(4);
                 team_barrier();
             }
-            if constexpr (ROLE == LISTS) keep_best();
-            if constexpr (ROLE == LISTS || KEEPS_SEEN) write_results(qi);
+            if constexpr (KEEPS_LISTS) keep_best();
+            if constexpr (KEEPS_LISTS || KEEPS_SEEN) write_results(qi);
             if constexpr (KEEPS_SEEN) {
                 if (n_spill) __threadfence();        // its bit-sets have landed before others clear
                 if (lane == 0) team[TM_SPILLED] = n_spill ? 1u : 0u;
@@ -1731,17 +1736,17 @@ __global__ void __launch_bounds__(64 * pag_team_max(NW)) k_search_team(const Sea
     Wave<NQ, NW, VM, PAG_MAX_CW, true> w(A, smem, (int)(threadIdx.x & 63), (int)uniform(threadIdx.x >> 6), (int)(blockDim.x >> 6));
     typedef decltype(w) Wv;
     if (w.wave == 0) {
-        w.template run_team<Wv::LISTS>();
+        if (w.split()) w.template run_team<Wv::LISTS>();
+        else w.template run_team<Wv::LISTS_FEW>();
         w.flush_stats();
     } else if (w.wave == 1) {
-        if (w.split()) w.template run_team<Wv::SEEN>();
-        else w.template run_team<Wv::SCREEN>();
+        w.template run_team<Wv::SEEN>();
         w.flush_stats();
-    } else if (w.wave == 2 && w.split()) {
-        w.template run_team<Wv::ESTIMATES>();
+    } else if (w.split()) {
+        if (w.wave == 2) w.template run_team<Wv::ESTIMATES>();
+        else w.template run_team<Wv::ROWS_AHEAD>();
     } else {
-        if (w.split()) w.template run_team<Wv::ROWS_AHEAD>();
-        else w.template run_team<Wv::ROWS>();
+        w.template run_team<Wv::ROWS>();
     }
 }
 
