@@ -658,7 +658,7 @@ int pag_search_common(pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 e
 //     (200k x 768, one query at efS 64 / 64 queries at efS 256 beside batches of 10,000: median 0.5 / 2.1 ms with teams, 1.5-2.1 /
 //     8.6-8.9 with one wave per query);
 //   the vectors that pag_insert searches for: a searcher that overlaps an insertion answers sooner with teams (20,000 vectors
-//     into 200k x 768, efS 256, median of 1 / 64 / 256 / 512 queries: 0.8 / 0.9 / 0.95 / 1.2 ms, with one wave per query 1.4 /
+//     into 200k x 768, efS 256, median of 1 / 64 / 256 / 512 queries: 0.64 / 0.70 / 0.75 / 0.90 ms, with one wave per query 1.4 /
 //     1.65 / 1.8 / 1.9; the insertion takes no longer).
 struct GpuLoad { std::atomic<u64> calls, queries; };
 static GpuLoad g_load[kMaxDevices];

@@ -145,6 +145,7 @@ struct SearchArgs {
     u32 cand_cap;
     u64* pes;                // [nq * deg] indexing mode: PES buffer H(v), ascending keys, PAG_KEY_INVALID = empty; null = off
     const u32* order;        // [nq] the order in which the waves take the queries (null: as numbered)
+    u32 grid;                // workgroups that are launched
     u32* qcounter;           // queries taken beyond the first of each workgroup, which is the workgroup's number; untouched if that is all
     u64* counters;
     u32* bitmap;             // [min(grid, nq) * bitmap_words]

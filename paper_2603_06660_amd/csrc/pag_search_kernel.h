@@ -1061,7 +1061,7 @@ struct Wave {
             }
             cntT = rest; hdT = rest;
             cntF = 0; hdF = 0;
-        } else if (cntF + cntT <= 64) {
+        } else if (TEAM && cntF + cntT <= 64) {
             // in registers: one key a lane
             const u32 n = cntF + cntT;
             u64 x = PAG_KEY_INVALID;
@@ -1671,9 +1671,9 @@ struct Wave {
 
     // the query after this workgroup's last one (A.nq and above: there is none)
     __device__ __forceinline__ u32 next_query() const {
-        if (gridDim.x >= A.nq) return A.nq;
+        if (A.grid >= A.nq) return A.nq;
         u32 qi = 0;
-        if (lane == 0) qi = gridDim.x + atomicAdd(A.qcounter, 1u);
+        if (lane == 0) qi = A.grid + atomicAdd(A.qcounter, 1u);
         return uniform(qi);
     }
 
