@@ -145,8 +145,8 @@ struct SearchArgs {
     u32 cand_cap;
     u64* pes;                // [nq * deg] indexing mode: PES buffer H(v), ascending keys, PAG_KEY_INVALID = empty; null = off
     const u32* order;        // [nq] the order in which the waves take the queries (null: as numbered)
-    u32 grid;                // workgroups that are launched
-    u32* qcounter;           // queries taken beyond the first of each workgroup, which is the workgroup's number; untouched if that is all
+    u32 numbered;            // queries that go to the workgroup of their number (see pag_numbered): every workgroup has one, or none has
+    u32* qcounter;           // of the queries beyond those, how many have been taken; untouched if there are none
     u64* counters;
     u32* bitmap;             // [min(grid, nq) * bitmap_words]
     u64 bitmap_words;

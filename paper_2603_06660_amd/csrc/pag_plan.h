@@ -126,6 +126,20 @@ int pag_plan_four(const pag_team_request& r, uint64_t nodes, Lds&& lds_bytes, Re
     return pag_fit_team(r, 4, 4, 4, lds_bytes, resident, p);
 }
 
+// How many workgroups with that LDS a CU really holds.  It is handed out in pieces of 1,280 bytes, which the occupancy query does not
+// know: workgroups that only wait, with 11,904 bytes each, run twelve at a time and not thirteen, with 6,144 25 and not 26 (every size
+// from 5 to 40 KB).
+inline uint32_t pag_lds_room(uint32_t bytes, uint32_t lds_per_cu) { return lds_per_cu / std::max(1280u, (bytes + 1279) / 1280 * 1280); }
+
+// How many of a batch's queries go to the workgroup of their number instead of being taken from a counter, of `groups` workgroups that
+// are launched and `sure` that have room at a time.  The counter costs 14 ns a query, done one after the other at the start of a
+// batch (4,000 queries of 100,000 x 768, efS 10, all resident: 515 us with it, 459 without).  But a workgroup that finds no place before another one
+// ends keeps the query of its number until then, and where the others go on to the rest of the batch that is its end (search phase of
+// 200,000 rows built with efC 200 / 100, 13 workgroups of 768-d and 11 of 128-d a CU launched, 12 and 10 held, by number -> by counter: 768-d
+// 150 -> 144 / 83 -> 75 ms, 128-d efC 100 59 -> 54; 6,600 queries of 100,000 x 768, K 100, efS 300: 6.34 -> 5.99 ms).  A batch
+// without a rest has no such end: a workgroup is done with its one query, and the next has its place.
+inline uint64_t pag_numbered(uint64_t nq, uint64_t groups, uint64_t sure) { return groups >= nq || groups <= sure ? groups : 0; }
+
 // Whether a wave of the one-wave search waits for the rows it has asked for before it asks for the next ones.  With the GPU full
 // from beginning to end, more long rows in flight only make the waves evict each other's from the memory-side cache.  `room`:
 // waves the GPU holds, `waves`: that are launched.  Kernel time without : with, over batches of 4,200 to 10,000 queries and searches

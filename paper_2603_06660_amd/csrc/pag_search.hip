@@ -92,7 +92,7 @@ int pag_launch_search(const pag_index* ix, const SearchArgs& a, u32 lds_bytes, i
         if (rc) return rc;
     }
     SearchArgs args = a;
-    args.grid = (u32)grid;
+    args.numbered = (u32)pag_numbered(a.nq, (u64)grid, (u64)pag_lds_room(lds_bytes, ix->lds_per_cu) * (u64)ix->num_cu);
     void* kargs[] = { (void*)&args };
     PAG_HIP(hipLaunchKernel((const void*)fn, dim3(grid), dim3(64 * a.waves), kargs, lds_bytes, ix->stream));
     *grid_io = grid;

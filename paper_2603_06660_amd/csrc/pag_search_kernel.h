@@ -1524,7 +1524,7 @@ struct Wave {
         const bool estimates = ROLE == ESTIMATES || (ROLE == ROWS && wave == 2);
         for (u32 take = 0;; ++take) {
             if constexpr (KEEPS_LISTS) {
-                u32 qi = take == 0 ? blockIdx.x : next_query();
+                u32 qi = take == 0 && A.numbered ? blockIdx.x : next_query();
                 if (qi >= A.nq) qi = PAG_EMPTY;
                 else if (A.order) qi = A.order[qi];
                 if (lane == 0) team[TM_QUERY] = qi;
@@ -1669,11 +1669,11 @@ struct Wave {
         }
     }
 
-    // the query after this workgroup's last one (A.nq and above: there is none)
+    // the next query that no workgroup has (A.nq and above: there is none)
     __device__ __forceinline__ u32 next_query() const {
-        if (A.grid >= A.nq) return A.nq;
+        if (A.numbered >= A.nq) return A.nq;
         u32 qi = 0;
-        if (lane == 0) qi = A.grid + atomicAdd(A.qcounter, 1u);
+        if (lane == 0) qi = A.numbered + atomicAdd(A.qcounter, 1u);
         return uniform(qi);
     }
 
@@ -1713,15 +1713,15 @@ constexpr int pag_search_occupancy(int nq, int nw, int vm, int cw) {
     return vm == 0 && (nq == 6 || (nq == 8 && nw == 2)) ? 3 : 2;
 }
 
-// Persistent waves: every wave begins with the query of its own number and pulls further ones from one counter until the batch
-// is drained, so long and short searches balance themselves; the loop ends for every wave once the counter passes nq.
+// Persistent waves: every wave begins with the query of its own number, if all are resident at once, and pulls further ones from one
+// counter until the batch is drained, so long and short searches balance themselves; the loop ends for every wave once the counter passes nq.
 template <int NQ, int NW, int VM, int CW>
 __attribute__((amdgpu_waves_per_eu(pag_search_occupancy(NQ, NW, VM, CW), 8)))
 __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
     extern __shared__ __align__(64) unsigned char smem[];   // the table sits first: see table_sum
     const int lane = threadIdx.x;
     Wave<NQ, NW, VM, CW> w(A, smem, lane);
-    for (u32 qi = blockIdx.x; qi < A.nq; qi = w.next_query()) w.run_query(A.order ? A.order[qi] : qi);
+    for (u32 qi = A.numbered ? blockIdx.x : w.next_query(); qi < A.nq; qi = w.next_query()) w.run_query(A.order ? A.order[qi] : qi);
     w.flush_stats();
 }
 
