@@ -567,18 +567,15 @@ static void seen_sizes_for(const pag_index* ix, u32 ef, u32 b, u32* hlog, u32* b
 }
 
 // Fills a->waves, the seen-set sizes, the LDS carve-up and the grid if the search is one for teams; a->waves stays 1 if not.
-static int plan_team(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
+static int plan_team(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, SearchArgs* a, u32* lds, int* grid) {
     pag_team_request r;
-    r.nq = nq; r.others = others; r.store_bytes = nodes * ix->L.d * pag_vec_elem(ix); r.half = ix->vec_half; r.d = ix->L.d;
-    r.b = b; r.ef = ef; r.num_cu = (u32)ix->num_cu; r.lds_per_cu = ix->lds_per_cu;
+    r.nq = nq; r.others = others; r.b = b; r.ef = ef; r.num_cu = (u32)ix->num_cu; r.lds_per_cu = ix->lds_per_cu;
     r.hlog = a->hlog; r.blog = a->blog; r.seen_fixed = ix->seen_log2; r.most_waves = (u32)pag_team_max(b <= 512 ? 8 : 16);
     SearchArgs t = *a;
     t.waves = 2;                                                    // any team: its words are part of the carve-up
     pag_team_plan p;
-    auto lds_bytes = [&](u32 hlog, u32 blog) { return (u32)pag_search_lds_bytes(ix->L, b, hlog, blog, &t); };
-    auto resident = [&](u32 waves, u32 bytes, int* n) { return pag_search_max_grid(ix, b, waves, bytes, n); };
-    int rc = pag_plan_team(r, lds_bytes, resident, &p);
-    if (!rc && p.waves == 1) rc = pag_plan_four(r, nodes, lds_bytes, resident, &p);
+    const int rc = pag_plan_team(r, [&](u32 hlog, u32 blog) { return (u32)pag_search_lds_bytes(ix->L, b, hlog, blog, &t); },
+                                 [&](u32 waves, u32 bytes, int* n) { return pag_search_max_grid(ix, b, waves, bytes, n); }, &p);
     if (rc || p.waves == 1) return rc;
     a->waves = p.waves; a->hlog = p.hlog; a->blog = p.blog;
     *lds = (u32)pag_search_lds_bytes(ix->L, b, p.hlog, p.blog, a);
@@ -588,8 +585,8 @@ static int plan_team(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, 
 
 // Plans a search: fills the part of SearchArgs that depends only on the index and (b, ef), the LDS carve-up and the
 // largest useful grid.  Allocates nothing.
-// `nodes` of the graph can be reached, ids from n_limit on are not part of it.
-static int search_plan(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+// Ids from n_limit on are not part of the graph.
+static int search_plan(const pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
     const pag_layout& L = ix->L;
     std::memset((void*)a, 0, sizeof(*a));
     a->vec = ix->vec; a->rec = ix->rec; a->entry = ix->entry;
@@ -604,7 +601,7 @@ static int search_plan(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b
     // per-wave spill bitmaps of the seen set: one bit per node, rounded to 16 bytes
     a->bitmap_words = ((u64)ix->capacity + 127) / 128 * 4;
     a->waves = 1;
-    int rc = plan_team(ix, nq, others, nodes, b, ef, a, lds, grid);
+    int rc = plan_team(ix, nq, others, b, ef, a, lds, grid);
     if (rc || a->waves > 1) return rc;
     *lds = (u32)pag_search_lds_bytes(L, b, a->hlog, a->blog, a);
     if (*lds > 65536) { pag_set_error("search: working set, tables and seen set need more than 64 KB of LDS per wave"); return PAG_EUNSUPPORTED; }
@@ -634,8 +631,8 @@ static int search_plan(const pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b
 }
 
 // The plan plus the workspaces it needs (grown on demand); shared with indexing.
-int pag_search_common(pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
-    int rc = search_plan(ix, nq, others, nodes, b, ef, n_limit, a, lds, grid);
+int pag_search_common(pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid) {
+    int rc = search_plan(ix, nq, others, b, ef, n_limit, a, lds, grid);
     if (rc) return rc;
     // no more workgroups are launched than there are queries, whichever plan they get
     const u64 groups = std::min<u64>(nq, (u64)*grid), need = groups * a->bitmap_words;
@@ -696,7 +693,7 @@ static int search_impl(pag_index* ix, const float* Q, uint64_t nq, uint32_t K, u
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = pag_search_common(ix, nq, queries_beside(ix->device), ix->n, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = pag_search_common(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
     const UnderWay under_way(ix->device, nq, grid);
     const u64 room = (u64)grid;
     if (nq > room) {
@@ -747,7 +744,7 @@ extern "C" int pag_search_layout(const pag_index* ix, uint64_t nq, uint32_t K, u
     u32 lds = 0;
     int grid = 0;
     int rc;
-    if ((rc = search_plan(ix, nq, queries_beside(ix->device), ix->n, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = search_plan(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
     *waves = a.waves;
     *resident = (u32)std::min<u64>(nq, (u64)grid);
     return PAG_OK;
@@ -785,7 +782,7 @@ extern "C" int pag_search_static(const pag_index* cix, const float* Q, uint64_t 
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = search_plan(ix, nq, queries_beside(ix->device), ix->n, b, efS, ix->n, &a, &lds, &grid))) return rc;
+    if ((rc = search_plan(ix, nq, queries_beside(ix->device), b, efS, ix->n, &a, &lds, &grid))) return rc;
     const UnderWay under_way(ix->device, nq, grid);
     // bitmap part: as many per-wave bitmaps as fit behind the query part; fewer waves than the GPU could hold
     // make the search slower, not different

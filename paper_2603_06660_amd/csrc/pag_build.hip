@@ -717,10 +717,10 @@ static int alloc_candidate_ws(BuildWs& ws, u64 max_batch, u32 cand_cap, u32 deg,
     return PAG_OK;
 }
 
-// The search of Alg. 1 for m points (rotated rows `qrot`) over the nodes below n_limit, `nodes` of which are linked: tables, the PRT-TFB search in
+// The search of Alg. 1 for m points (rotated rows `qrot`) over the nodes below n_limit: tables, the PRT-TFB search in
 // indexing mode (ef = efC, b = min(efC, 100), every round's W collected, PES screening into ws.pes), then every
 // point's candidates sorted by (dist, id) -- bits 1..63 of the keys, the visited flag aside -- into ws.cand_sorted.
-static int search_candidates(pag_index* ix, BuildWs& ws, const float* qrot, u64 m, u32 b, u32 cand_cap, u64 n_limit, u64 nodes) {
+static int search_candidates(pag_index* ix, BuildWs& ws, const float* qrot, u64 m, u32 b, u32 cand_cap, u64 n_limit) {
     const pag_layout& L = ix->L;
     hipStream_t s = ix->stream;
     int rc;
@@ -728,7 +728,7 @@ static int search_candidates(pag_index* ix, BuildWs& ws, const float* qrot, u64 
     SearchArgs a;
     u32 lds = 0;
     int grid = 0;
-    if ((rc = pag_search_common(ix, m, 0, nodes, b, ix->efC, n_limit, &a, &lds, &grid))) return rc;
+    if ((rc = pag_search_common(ix, m, 0, b, ix->efC, n_limit, &a, &lds, &grid))) return rc;
     a.qrot = qrot; a.tables = ix->ws_tab; a.nq = (u32)m; a.K = b;
     a.flags &= ~(u32)PAG_FLAG_NO_PRT;          // indexing always runs with the projection test on
     a.cand = ws.cand; a.cand_cnt = ws.cand_cnt; a.cand_cap = cand_cap;
@@ -855,7 +855,7 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
         PAG_HIP(hipGetLastError());
         // 2. + 3. PRT-TFB search of the graph built so far, candidates sorted.  Nodes that are not inserted yet have
         //    empty records and no in-edges, and the entry list holds inserted nodes only, so they cannot be reached.
-        if ((rc = search_candidates(ix, ws, ix->ws_qrot, m, b, cand_cap, n_end, n_begin + done))) return rc;
+        if ((rc = search_candidates(ix, ws, ix->ws_qrot, m, b, cand_cap, n_end))) return rc;
         //    RobustPrune -> N_out(v), reverse pairs
         {
 #define PRUNE_ARGS s, ix, nodes, (u32)m, ws.cand_sorted, ws.cand_cnt, cand_cap, ws.pes, ws.rk_in, ws.rv_in, ws.taken
@@ -980,7 +980,7 @@ extern "C" int pag_insertion_candidates(const pag_index* cix, const float* X, ui
                 if ((rc = pag_launch_convert(s, ix->ws_qrot, 0, half_rows, 1, cm * L.d))) return rc;
                 if ((rc = pag_launch_convert(s, half_rows, 1, ix->ws_qrot, 0, cm * L.d))) return rc;
             }
-            if ((rc = search_candidates(ix, ws, ix->ws_qrot, cm, b, cand_cap, ix->n, ix->n))) return rc;
+            if ((rc = search_candidates(ix, ws, ix->ws_qrot, cm, b, cand_cap, ix->n))) return rc;
             PAG_HIP(hipMemcpyAsync(keys.data(), ws.cand_sorted, cm * cand_cap * 8, hipMemcpyDeviceToHost, s));
             PAG_HIP(hipMemcpyAsync(cnt.data(), ws.cand_cnt, cm * 4, hipMemcpyDeviceToHost, s));
             if (use_pes) PAG_HIP(hipMemcpyAsync(hk.data(), ws.pes, cm * L.deg * 8, hipMemcpyDeviceToHost, s));

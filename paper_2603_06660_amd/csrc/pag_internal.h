@@ -177,8 +177,8 @@ int pag_launch_hop_traffic(hipStream_t s, const pag_index* ix, u64 hops, u32* bi
 int pag_launch_edge_info_list(hipStream_t s, const pag_index* ix, const u32* edge_list, u64 n_edges);
 int pag_launch_edge_info_of(hipStream_t s, const pag_index* ix, const u32* nodes, u64 m);   // every slot of m listed nodes (device ids)
 
-// others: queries that other calls are searching meanwhile; nodes: in the graph so far
-int pag_search_common(pag_index* ix, u64 nq, u64 others, u64 nodes, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid);
+// others: queries that other calls are searching meanwhile
+int pag_search_common(pag_index* ix, u64 nq, u64 others, u32 b, u32 ef, u64 n_limit, SearchArgs* a, u32* lds, int* grid);
 inline pag_vecs pag_vecs_of(const pag_index* ix) { return pag_vecs{ ix->vec, ix->L.d, ix->vec_half }; }
 inline size_t pag_vec_elem(const pag_index* ix) { return ix->vec_half ? 2 : 4; }
 int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end);   // batch-synchronous insertion of nodes [n_begin, n_end)

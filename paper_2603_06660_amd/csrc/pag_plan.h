@@ -12,8 +12,6 @@ inline int pag_resident(int per_cu, int num_cu, uint32_t waves) { return std::ma
 struct pag_team_request {
     uint64_t nq;             // queries of the call
     uint64_t others;         // queries of other calls that the GPU searches beside them, see pag_queries_beside
-    uint64_t store_bytes;    // of the vectors that the search can reach
-    uint32_t half, d;        // they are 16-bit floats; values to a row
     uint32_t b, ef;
     uint32_t num_cu, lds_per_cu;
     uint32_t hlog, blog;     // the seen set of the one-wave search
@@ -82,17 +80,15 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
 //     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
 //     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
 //     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
-//   up to four per CU: 4 waves, for searches of 128 nodes or more and working sets of up to 128.  Searches of 256 nodes with working
-//     sets of up to 64 gain with up to four per CU wherever their rows come from (1,000 queries, efS 256: 50k x 768 1244 -> 1171 us,
-//     1M x 128 1127 -> 983; 30k x 1536 1606 -> 1588 at least).  Shorter ones and larger working sets gain less and lose
-//     beyond 2.5 per CU (efS 128, 520 / 777 / 1,000 queries, one wave : team: 80k x 768 1.07 / 0.98 / 0.89, 300k x 128 1.07 / 0.96 /
-//     0.90; K 100, efS 256: 50k x 768 1.10 / 1.00 / 0.96), 3.75 if the rows come from HBM and not from the 256 MB cache (200k
-//     x 768 1.14 / 1.02 / 0.95, 2M x 128 1.12 / 1.06 / 1.02; with 400 MB of rows the two are even), four if they are 16-bit
-//     besides (600k x 768 1.22 / 1.13 / 1.05).  16-bit rows of 2560 and more leave the team's kernel short of registers: 0.75 to 0.95
+//   up to four per CU: 4 waves, where the registers of the kernel let every query be resident (all four of short rows and working sets
+//     of up to 128 nodes, three of long rows and of up to 512, none above).  Whole calls with one wave -> four: 777 and 1,000 queries of
+//     5k x 32 / 128 at efS 10 91 -> 72, 102 -> 74 us, 50k x 768 at efS 10 / 24 247 -> 178, 345 -> 307, 16-bit 244 -> 180, 380 -> 318, 20k x
+//     1536 345 -> 280, 471 -> 386; 768 queries of 50k x 768 at efS 128 / 512 755 -> 485, 2523 -> 1563, K 300 3431 -> 2736, of 12k x 3072
+//     at efS 16 / 512 670 -> 642, 3729 -> 3568, K 400 5897 -> 5144, 16-bit 669 -> 593, 3718 -> 3017, 5917 -> 5126.  Small graphs, 1,000 queries: 120 x 128
+//     at efS 10 / 64 68 -> 58, 166 -> 137, K 100 182 either way; 500 x 768 at efS 10 / 128 146 -> 122, 480 -> 340
 template <class Lds, class Resident>
 int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
     const uint64_t cus = r.num_cu, load = r.nq + r.others;
-    const bool large_set = r.b > 128;
     const uint32_t length = std::max(r.ef, r.b);                    // nodes that a search expands, about
     uint32_t share, most, least;
     p->waves = 1;
@@ -100,30 +96,12 @@ int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& residen
         share = 1; most = 12; least = 4;
     } else if (load > cus && load <= 2 * cus && length >= 24) {
         share = 2; most = 8; least = r.b > 512 ? 4 : 8;
-    } else if (load > 2 * cus && length >= 128 && !large_set && !(r.half && r.d >= 2560)) {
-        const bool from_hbm = r.store_bytes >= (512ull << 20);
-        const uint64_t quarters = (length >= 256 && r.b <= 64) || (from_hbm && r.half) ? 16 : from_hbm ? 15 : 10;
-        if (4 * load > quarters * cus) return 0;
+    } else if (load > 2 * cus && load <= 4 * cus) {
         share = 4; most = 4; least = 4;
     } else {
         return 0;
     }
     return pag_fit_team(r, share, std::min(most, r.most_waves), least, lds_bytes, resident, p);
-}
-
-// What pag_plan_team leaves to one wave although no more than four queries come to a CU: teams of four, where the registers of their
-// kernel let every query be resident.  (The lines above date from when every wave of a team began and ended with atomics on the same few
-// addresses, 0.35 us a query in all.)  Kernel times of one wave -> four, 777 and 1,000 queries: 10k x 128 at efS 32 / 64 / 128
-// 192 -> 140, 280 -> 211, 478 -> 350 us; 50k x 768 289 -> 203, 446 -> 303, 698 -> 505, K 100 1080 -> 825; 1M x 128 at efS 64 360 -> 260,
-// K 100 1105 -> 785; 30k x 1536 at efS 64 497 -> 382; 16-bit 30k x 768 at efS 64 412 -> 299, K 150 1796 -> 1545; 30k x 128, K 150
-// 1367 -> 1306; rows of 2560 and more and working sets above 256 do not fit.  Graphs of less than 1,024 nodes keep the plan they had
-// (500 x 768, efS 128: 404 -> 301 us is left there).
-template <class Lds, class Resident>
-int pag_plan_four(const pag_team_request& r, uint64_t nodes, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
-    const uint64_t cus = r.num_cu, load = r.nq + r.others;
-    p->waves = 1;
-    if (load <= 2 * cus || load > 4 * cus || nodes < 1024) return 0;
-    return pag_fit_team(r, 4, 4, 4, lds_bytes, resident, p);
 }
 
 // How many workgroups with that LDS a CU really holds.  It is handed out in pieces of 1,280 bytes, which the occupancy query does not

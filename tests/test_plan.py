@@ -10,7 +10,7 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "pag_plan.h"
-// arguments: nq others store_bytes half b ef waves_per_cu d; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
+// arguments: nq others b ef waves_per_cu; a CU holds that many waves of the kernel, 160 KB of LDS; 256 CUs
 // or: calls queries, for pag_queries_beside; or one number, for pag_resident: of a single wave, of a team;
 // or d half b ef nq waves room and two more, for pag_paced
 int main(int n, char** v) {
@@ -18,10 +18,8 @@ int main(int n, char** v) {
     if (n == 2) { std::printf("%d %d\n", pag_resident(atoi(v[1]), 256, 1), pag_resident(atoi(v[1]), 256, 4)); return 0; }
     if (n == 10) { std::printf("%d\n", (int)pag_paced(atoi(v[1]), atoi(v[2]) != 0, atoi(v[3]), atoi(v[4]), atoi(v[5]), atoi(v[6]), atoi(v[7]))); return 0; }
     pag_team_request r = {};
-    r.nq = strtoull(v[1], 0, 10); r.others = strtoull(v[2], 0, 10); r.store_bytes = strtoull(v[3], 0, 10);
-    r.half = atoi(v[4]); r.b = atoi(v[5]); r.ef = atoi(v[6]);
-    const uint32_t per_cu = atoi(v[7]);
-    r.d = atoi(v[8]);
+    r.nq = strtoull(v[1], 0, 10); r.others = strtoull(v[2], 0, 10); r.b = atoi(v[3]); r.ef = atoi(v[4]);
+    const uint32_t per_cu = atoi(v[5]);
     r.num_cu = 256; r.lds_per_cu = 163840; r.most_waves = 12;
     r.hlog = 9; r.blog = r.b + 8 * std::max(r.ef, r.b) > 1024 ? 15 : 0;
     pag_team_plan p;
@@ -43,8 +41,8 @@ def waves(tmp_path_factory):
     def beside(calls, queries):
         return int(subprocess.check_output([str(d / "plan"), str(calls), str(queries)], text=True).split()[1])
 
-    def run(nq, others=0, store=1 << 30, half=0, b=10, ef=256, per_cu=16, d_=768):
-        rc, w = subprocess.check_output([str(d / "plan")] + [str(x) for x in (nq, others, store, half, b, ef, per_cu, d_)], text=True).split()
+    def run(nq, others=0, b=10, ef=256, per_cu=16):
+        rc, w = subprocess.check_output([str(d / "plan")] + [str(x) for x in (nq, others, b, ef, per_cu)], text=True).split()
         assert rc == "0"
         return int(w)
     run.beside = beside
@@ -65,16 +63,12 @@ def test_waves_beside_other_calls(waves, nq, others, want):
     assert waves(nq, others) == want
 
 
-# more than two queries to a CU: how far four waves pay depends on the search's length, its working set and where the rows lie
-@pytest.mark.parametrize("most,store,half,b,ef", [(1024, 1 << 20, 0, 10, 256), (1024, 1 << 20, 0, 64, 100000), (640, 1 << 20, 0, 10, 255),
-                                                  (640, 1 << 20, 1, 10, 128), (640, 1 << 20, 0, 65, 256), (640, (1 << 29) - 1, 0, 128, 1000),
-                                                  (960, 1 << 29, 0, 10, 128), (960, 1 << 29, 0, 128, 1000), (1024, 1 << 29, 1, 100, 128),
-                                                  (512, 1 << 30, 1, 10, 127), (512, 1 << 30, 1, 513, 1000)])
-def test_four_waves(waves, most, store, half, b, ef):
-    kw = dict(store=store, half=half, b=b, ef=ef)
-    assert waves(513, **kw) == (4 if most > 512 else 1)
-    assert waves(most, **kw) == (4 if most > 512 else 8) and waves(most + 1, **kw) == 1
-    assert waves(513, d_=2560, **kw) == (4 if most > 512 and not half else 1)      # long 16-bit rows: too few registers
+# more than two queries to a CU: four waves for searches of any length and working sets of any size, as long as all queries are resident
+@pytest.mark.parametrize("b,ef", [(10, 1), (10, 127), (10, 100000), (64, 256), (128, 1000), (256, 300)])
+def test_four_waves(waves, b, ef):
+    assert [waves(nq, b=b, ef=ef) for nq in (513, 1024, 1025)] == [4, 4, 1]
+    assert [waves(nq, b=b, ef=ef, per_cu=15) for nq in (513, 768, 769, 1024)] == [4, 4, 1, 1]
+    assert waves(513, b=b, ef=ef, per_cu=11) == 1
 
 
 @pytest.mark.parametrize("calls,queries,want", [(0, 0, 0), (1, 64, 64), (3, 1000, 1000), (7, 448, 192), (7, 1792, 768), (15, 3 * 2 ** 31, 3 * 2 ** 31 // 5)])
