@@ -92,7 +92,8 @@ int pag_launch_search(const pag_index* ix, const SearchArgs& a, u32 lds_bytes, i
         if (rc) return rc;
     }
     SearchArgs args = a;
-    args.numbered = (u32)pag_numbered(a.nq, (u64)grid, (u64)pag_lds_room(lds_bytes, ix->lds_per_cu) * (u64)ix->num_cu);
+    // teams are planned only where all of them are resident
+    args.numbered = a.waves > 1 ? (u32)grid : (u32)pag_numbered(a.nq, (u64)grid, (u64)pag_lds_room(lds_bytes, ix->lds_per_cu) * (u64)ix->num_cu);
     void* kargs[] = { (void*)&args };
     PAG_HIP(hipLaunchKernel((const void*)fn, dim3(grid), dim3(64 * a.waves), kargs, lds_bytes, ix->stream));
     *grid_io = grid;

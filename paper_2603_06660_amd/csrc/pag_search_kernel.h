@@ -1524,7 +1524,7 @@ struct Wave {
         const bool estimates = ROLE == ESTIMATES || (ROLE == ROWS && wave == 2);
         for (u32 take = 0;; ++take) {
             if constexpr (KEEPS_LISTS) {
-                u32 qi = take == 0 && A.numbered ? blockIdx.x : next_query();
+                u32 qi = take == 0 ? blockIdx.x : next_query();
                 if (qi >= A.nq) qi = PAG_EMPTY;
                 else if (A.order) qi = A.order[qi];
                 if (lane == 0) team[TM_QUERY] = qi;
