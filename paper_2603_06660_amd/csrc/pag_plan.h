@@ -70,9 +70,8 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
 // each (200k x 768, efS 256): 302,000 queries/s when every call plans as if it were alone, 482,000 with one wave per query,
 // 661,000 with what the sum asks for; with 1,000 queries each 706,000, 1,158,000 and 1,186,000, with 16 each 73,000, 39,000 and 73,000.
 //
-// The shortest searches keep one wave (kernel times of 10 nodes, 5,000 x 128, 256 queries: 76 -> 43 us with a team, of which a call's host
-// part leaves little); from 16 nodes with up to one query per CU and 24 with up to two they get teams (5,000 x 128, 16 nodes, 256 queries
-// 112 -> 71 us; 24 nodes, 512 queries 142 -> 92; 50k x 768 259 -> 191).
+// The shortest searches gain like all others (whole calls of 10 nodes with one wave -> a team; one query: 5k x 32 68 -> 48 us, 5k x 128
+// 88 -> 57, 50k x 768 91 -> 55, 12k x 3072 159 -> 99; 256 queries: 90 -> 60, 96 -> 63, 176 -> 98, 323 -> 234; 512: 91 -> 61, 97 -> 65, 199 -> 124).
 // The lines, with kernel times of one wave -> a team (100,000 rows, efS 128, unless stated) as they were when the lines were drawn:
 //   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
 //     query 375 -> 242, 491 -> 271, 777 -> 414
@@ -81,22 +80,21 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
 //     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
 //     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
 //   up to four per CU: 4 waves, where the registers of the kernel let every query be resident (all four of short rows and working sets
-//     of up to 128 nodes, three of long rows and of up to 512, none above).  Whole calls with one wave -> four: 777 and 1,000 queries of
+//     of up to 128 nodes, three of long rows and of up to 512, none above).  Whole calls with one wave -> four: 1,024 queries of
 //     5k x 32 / 128 at efS 10 91 -> 72, 102 -> 74 us, 50k x 768 at efS 10 / 24 247 -> 178, 345 -> 307, 16-bit 244 -> 180, 380 -> 318, 20k x
 //     1536 345 -> 280, 471 -> 386; 768 queries of 50k x 768 at efS 128 / 512 755 -> 485, 2523 -> 1563, K 300 3431 -> 2736, of 12k x 3072
-//     at efS 16 / 512 670 -> 642, 3729 -> 3568, K 400 5897 -> 5144, 16-bit 669 -> 593, 3718 -> 3017, 5917 -> 5126.  Small graphs, 1,000 queries: 120 x 128
+//     at efS 16 / 512 670 -> 642, 3729 -> 3568, K 400 5897 -> 5144, 16-bit 669 -> 593, 3718 -> 3017, 5917 -> 5126.  Small graphs, 1,024 queries: 120 x 128
 //     at efS 10 / 64 68 -> 58, 166 -> 137, K 100 182 either way; 500 x 768 at efS 10 / 128 146 -> 122, 480 -> 340
 template <class Lds, class Resident>
 int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
     const uint64_t cus = r.num_cu, load = r.nq + r.others;
-    const uint32_t length = std::max(r.ef, r.b);                    // nodes that a search expands, about
     uint32_t share, most, least;
     p->waves = 1;
-    if (load <= cus && length >= 16) {
+    if (load <= cus) {
         share = 1; most = 12; least = 4;
-    } else if (load > cus && load <= 2 * cus && length >= 24) {
+    } else if (load <= 2 * cus) {
         share = 2; most = 8; least = r.b > 512 ? 4 : 8;
-    } else if (load > 2 * cus && load <= 4 * cus) {
+    } else if (load <= 4 * cus) {
         share = 4; most = 4; least = 4;
     } else {
         return 0;

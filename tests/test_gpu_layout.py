@@ -40,7 +40,7 @@ def test_reserved_room_does_not_change_the_plan():
 
 def test_workspaces_are_sized_by_the_batch():
     """A small batch takes the seen-set bitmaps of its own queries, not of all that the GPU could hold at a time, also where it
-    gets one wave per query (as it does beside other calls), and its answers stay right when the next batches are larger."""
+    gets one wave per query, and its answers stay right when the next batches are larger."""
     import torch
     from paper_2603_06660_amd import PagIndex
     d, capacity = 16, 1 << 20
@@ -51,12 +51,14 @@ def test_workspaces_are_sized_by_the_batch():
     ix, small = PagIndex.build(base, capacity=capacity, **kw), PagIndex.build(base, **kw)
     q = rows(3000)
     ix.search(q[:8], 1, 10)                                             # everything but the bitmaps' growth
-    assert ix.search_layout(100, 1, 10) == (1, 100)
-    torch.cuda.synchronize()
-    free0 = torch.cuda.mem_get_info()[0]
-    ix.search(q[:100], 1, 10)
-    torch.cuda.synchronize()
-    assert free0 - torch.cuda.mem_get_info()[0] <= 100 * capacity // 8 + (16 << 20)
+    few = 4 * torch.cuda.get_device_properties(0).multi_processor_count + 1
+    for nq, waves in ((100, 12), (few, 1)):
+        assert ix.search_layout(nq, 1, 10) == (waves, nq)
+        torch.cuda.synchronize()
+        free0 = torch.cuda.mem_get_info()[0]
+        ix.search(q[:nq], 1, 10)
+        torch.cuda.synchronize()
+        assert free0 - torch.cuda.mem_get_info()[0] <= nq * capacity // 8 + (16 << 20)
     s = ix.searcher()
     for nq, K, efS in ((100, 1, 10), (300, 10, 900), (3000, 10, 900), (50, 10, 900), (40, 300, 400), (2000, 300, 400)):
         want = small.search(q[:nq], K, efS)

@@ -57,9 +57,9 @@ def _compare(ix, q, K, efS, sizes, search=None, waves=None, flags=0):
 
 # n, d, subspaces, degree, metric, half, K, efS: chunks of a row per lane 1 .. 12 with and without a tail, code words
 # 2 / 4 / 8, register slots of W 1 / 2 / 4 / 8 / 16, exact LDS hash and bitmap, degrees up to a full wave; then the waves per query
-# that up to one and up to two queries per CU get (one where two teams' registers do not fit a CU, or the search is short)
+# that up to one and up to two queries per CU get (one where two teams' registers do not fit a CU)
 CASES = [
-    (3000, 32, 8, 16, "l2", False, 1, 16, 12, 1),
+    (3000, 32, 8, 16, "l2", False, 1, 16, 12, 8),
     (3000, 128, 16, 32, "l2", False, 10, 64, 12, 8),
     (3000, 256, 16, 32, "ip", False, 10, 600, 12, 8),
     (2500, 260, 20, 24, "ip", False, 64, 300, 12, 8),
