@@ -30,10 +30,10 @@ struct pag_team_plan {
 // queries/s when all seven others count, 276,000 when three do.)
 inline uint64_t pag_queries_beside(uint64_t calls, uint64_t queries) { return calls <= 3 ? queries : queries * 3 / calls; }
 
-// A team of `most` to `least` waves, as many as leave every query resident where `share` queries share a CU; `waves` stays as it is if
-// there is no such team.
+// A team of `most` waves, or of as many less in steps of `step` as leave every query resident where `share` queries share a CU, but not of less
+// than four; `waves` stays as it is if there is no such team.
 template <class Lds, class Resident>
-int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint32_t least, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
+int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint32_t step, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
     const uint64_t load = r.nq + r.others;
     const uint32_t length = std::max(r.ef, r.b);                    // nodes that a search expands, about
     const uint32_t room = r.lds_per_cu / share - 512;
@@ -51,7 +51,7 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
     const uint32_t lds = lds_bytes(hlog, blog);
     if (lds > room) return 0;
     // as many waves as leave every query resident
-    for (uint32_t waves = most; waves >= least; --waves) {
+    for (uint32_t waves = most; waves >= 4; waves -= step) {
         int rc, n = 0;
         if ((rc = resident(waves, lds, &n))) return rc;
         if ((uint64_t)n < load) continue;
@@ -76,9 +76,11 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
 //   one query per CU: up to 12 waves.  128-d 474 -> 310 us, 768-d 650 -> 365, 3072-d 1068 -> 605 (256 queries); a single
 //     query 375 -> 242, 491 -> 271, 777 -> 414
 //   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
-//     1536-d 995 -> 747 (512 queries); with fewer waves longer rows lose (3072-d: 1138 -> 1455), and so
-//     do working sets of 129 to 512 nodes (30k x 768, K = 300, 400 queries: 4.6 -> 5.7 ms).  Above that, where the merges
-//     into W take most of a hop, four waves gain (1M x 768, K = 1000, 300 queries: 26.1 -> 21.6 ms)
+//     1536-d 995 -> 747 (512 queries).  Where they allow twelve, teams of four, of which three fit: two teams of six are granted but
+//     run one after the other.  Whole calls with one wave / six / four, 512 queries: 3072-d at efS 128 1183 / 1363 / 1051 us, at efS 512 3348 /
+//     4048 / 2930, K 200 2993 / 3974 / 2614, 16-bit 1267 / 1404 / 997, 3528 / 4105 / 2717, 3113 / 4472 / 2583; K 200 and 400 of 50k x 768 2227 / 2794 /
+//     1606, 4367 / 5271 / 3108, of 20k x 1536 2482 / 2994 / 1840, 4822 / 5682 / 3420.  Where they allow eight (working sets above 512), four, too:
+//     K 600 and 1000 of 50k x 768 6883 -> 5523, 10696 -> 8595
 //   up to four per CU: 4 waves, where the registers of the kernel let every query be resident (all four of short rows and working sets
 //     of up to 128 nodes, three of long rows and of up to 512, none above).  Whole calls with one wave -> four: 1,024 queries of
 //     5k x 32 / 128 at efS 10 91 -> 72, 102 -> 74 us, 50k x 768 at efS 10 / 24 247 -> 178, 345 -> 307, 16-bit 244 -> 180, 380 -> 318, 20k x
@@ -88,18 +90,18 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
 template <class Lds, class Resident>
 int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& resident, pag_team_plan* p) {
     const uint64_t cus = r.num_cu, load = r.nq + r.others;
-    uint32_t share, most, least;
+    uint32_t share, most, step;
     p->waves = 1;
     if (load <= cus) {
-        share = 1; most = 12; least = 4;
+        share = 1; most = 12; step = 1;
     } else if (load <= 2 * cus) {
-        share = 2; most = 8; least = r.b > 512 ? 4 : 8;
+        share = 2; most = 8; step = 4;
     } else if (load <= 4 * cus) {
-        share = 4; most = 4; least = 4;
+        share = 4; most = 4; step = 4;
     } else {
         return 0;
     }
-    return pag_fit_team(r, share, std::min(most, r.most_waves), least, lds_bytes, resident, p);
+    return pag_fit_team(r, share, std::min(most, r.most_waves), step, lds_bytes, resident, p);
 }
 
 // How many workgroups with that LDS a CU really holds.  It is handed out in pieces of 1,280 bytes, which the occupancy query does not

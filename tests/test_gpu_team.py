@@ -57,7 +57,7 @@ def _compare(ix, q, K, efS, sizes, search=None, waves=None, flags=0):
 
 # n, d, subspaces, degree, metric, half, K, efS: chunks of a row per lane 1 .. 12 with and without a tail, code words
 # 2 / 4 / 8, register slots of W 1 / 2 / 4 / 8 / 16, exact LDS hash and bitmap, degrees up to a full wave; then the waves per query
-# that up to one and up to two queries per CU get (one where two teams' registers do not fit a CU)
+# that up to one and up to two queries per CU get (four where the registers of two teams of eight do not fit a CU)
 CASES = [
     (3000, 32, 8, 16, "l2", False, 1, 16, 12, 8),
     (3000, 128, 16, 32, "l2", False, 10, 64, 12, 8),
@@ -69,10 +69,10 @@ CASES = [
     (2500, 1024, 32, 48, "ip", True, 129, 400, 12, 8),
     (2500, 1280, 40, 64, "ip", False, 10, 1500, 12, 8),
     (2000, 1536, 64, 48, "cos", False, 50, 768, 12, 8),
-    (2000, 2048, 64, 33, "ip", False, 300, 900, 12, 1),
-    (1500, 2304, 64, 32, "ip", True, 20, 100, 12, 1),
-    (1500, 3072, 64, 32, "ip", False, 10, 128, 12, 1),
-    (1500, 3072, 64, 32, "ip", True, 10, 200, 12, 1),
+    (2000, 2048, 64, 33, "ip", False, 300, 900, 12, 4),
+    (1500, 2304, 64, 32, "ip", True, 20, 100, 12, 4),
+    (1500, 3072, 64, 32, "ip", False, 10, 128, 12, 4),
+    (1500, 3072, 64, 32, "ip", True, 10, 200, 12, 4),
     (3000, 96, 8, 32, "l2", False, 600, 1200, 8, 4),
     (3000, 768, 32, 32, "ip", False, 1000, 3000, 8, 4),
 ]

@@ -77,7 +77,8 @@ def test_calls_beyond_the_hardware_queues_wait(waves, calls, queries, want):
 
 
 # per_cu: waves that the registers of the made-up kernel leave room for on a CU
-@pytest.mark.parametrize("nq,per_cu,want", [(1, 12, 12), (1, 11, 11), (256, 4, 4), (256, 3, 1), (1, 0, 1), (512, 15, 1)])
+@pytest.mark.parametrize("nq,per_cu,want", [(1, 12, 12), (1, 11, 11), (256, 4, 4), (256, 3, 1), (1, 0, 1), (512, 16, 8), (512, 15, 4), (512, 12, 4),
+                                              (512, 8, 4), (512, 7, 1)])
 def test_a_team_that_does_not_fit_is_not_planned(waves, nq, per_cu, want):
     assert waves(nq, per_cu=per_cu) == want
 
