@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "pag_internal.h"
+#include "pag_plan.h"
 #include "pag_wave.h"
 
 namespace {
@@ -355,7 +356,7 @@ k_prune(pag_vecs vec, uint8_t* __restrict__ recs, pag_layout L, const u32* __res
     put_pruned(recs, L, v, vi, m, kept, nk, my_id, my_key, lane, pes, e2, rev_keys, rev_vals);
 }
 
-// The same with four waves per node, for batches that leave the GPU mostly idle with one: each wave tests two candidates of eight
+// The same with four waves per node (see pag_prune_line): each wave tests two candidates of eight
 // against the rows kept so far, which the waves share in LDS (J of them, and one place more); the step's survivors are then
 // kept in list order, each written by its wave and met by the survivors behind it.  One wave spends 5 us on a step of two, 1.7 of it
 // in arithmetic alone; what bounds four is that arithmetic (1,024 nodes of 768-d, 200 candidates each: 519 -> 250 us).
@@ -474,33 +475,25 @@ template <int NQ>
 static int launch_prune(hipStream_t s, const pag_index* ix, const u32* nodes, u32 m, const u64* cand_sorted,
                         const u32* cand_cnt, u32 cand_cap, const u64* pes, u64* rev_keys, u32* rev_vals, const u32* taken) {
     const pag_layout& L = ix->L;
-    // Four waves per node in small batches: prune phase of a build of 24,000, one wave -> four, batches of 256 / 1,024 / 2,048:
-    // 128-d 17.6 -> 8.5, 5.3 -> 2.9, 3.6 -> 2.5 ms, 768-d 46 -> 20, 14.5 -> 7.8, 10.0 -> 6.8, 1536-d 96 -> 43, 30 -> 19, 21 -> 17, 3072-d
-    // 135 -> 61 at 256, 74 -> 53 at 512, 41 -> 46 at 1,024.  Large batches fetch their rows from HBM, and then the waves that one-wave
-    // groups leave room for matter more: 200,000 x 1536 in batches of 4,096 163 -> 178 ms, 16,384 127 -> 157 (300,000 x 768: 106 -> 90, 82 -> 77).
     const u32 cus = (u32)ix->num_cu;
-    if (m <= (NQ <= 4 ? 8u : NQ <= 8 ? 4u : 2u) * cus) {
+    if (m <= pag_prune_line(NQ, cus)) {
         // as many kept rows as the LDS holds with the nodes that share a CU
         const u32 share = std::min<u32>((m + cus - 1) / cus, 4u), fixed = (64 + 64 + 8) * 4;
         const u32 room = std::min<u32>(65536u, ix->lds_per_cu / share - 512u);
-        const u32 fit = (room - fixed) / (NQ * 1024u);
-        if (fit >= 2) {
-            const u32 J = std::min<u32>(fit - 1, L.deg);
-            hipLaunchKernelGGL((k_prune_team<NQ>), dim3(m), dim3(256), (J + 1) * NQ * 1024u + fixed, s, pag_vecs_of(ix), ix->rec, L, nodes, m, cand_sorted,
-                               cand_cnt, cand_cap, ix->efC, J, pes, ix->e2, rev_keys, rev_vals, taken);
-            PAG_HIP(hipGetLastError());
-            return PAG_OK;
-        }
+        const u32 J = std::min<u32>((room - fixed) / (NQ * 1024u) - 1, L.deg);       // two at least: twelve chunks, four nodes to a CU
+        hipLaunchKernelGGL((k_prune_team<NQ>), dim3(m), dim3(256), (J + 1) * NQ * 1024u + fixed, s, pag_vecs_of(ix), ix->rec, L, nodes, m, cand_sorted,
+                           cand_cnt, cand_cap, ix->efC, J, pes, ix->e2, rev_keys, rev_vals, taken);
+    } else if constexpr (pag_prune_line(NQ, 1) != PAG_ANY_BATCH) {
+        // kept rows held in LDS (slots of NQ KB): four, more while they fit 16 KB, fewer beyond 36 KB.  Measured on
+        // 1M x 768 / 1024 / 1536 and 250k x 3072: 16 / 16 / 24 / 36 KB are the fastest; larger sets lose more waves than
+        // they save reads.
+        u32 J = std::max<u32>(4u, 16u / NQ);
+        J = std::min<u32>(J, 36u / NQ);
+        J = std::min<u32>(J, L.deg);
+        const u32 lds = J * NQ * 1024u + L.deg * 4;
+        hipLaunchKernelGGL((k_prune<NQ, 2, 2, 2>), dim3(m), dim3(64), lds, s, pag_vecs_of(ix), ix->rec, L, nodes, m, cand_sorted,
+                           cand_cnt, cand_cap, ix->efC, J, pes, ix->e2, rev_keys, rev_vals, taken);
     }
-    // kept rows held in LDS (slots of NQ KB): four, more while they fit 16 KB, fewer beyond 36 KB.  Measured on
-    // 1M x 768 / 1024 / 1536 and 250k x 3072: 16 / 16 / 24 / 36 KB are the fastest; larger sets lose more waves than
-    // they save reads.
-    u32 J = std::max<u32>(4u, 16u / NQ);
-    J = std::min<u32>(J, 36u / NQ);
-    J = std::min<u32>(J, L.deg);
-    const u32 lds = J * NQ * 1024u + L.deg * 4;
-    hipLaunchKernelGGL((k_prune<NQ, 2, 2, 2>), dim3(m), dim3(64), lds, s, pag_vecs_of(ix), ix->rec, L, nodes, m, cand_sorted,
-                       cand_cnt, cand_cap, ix->efC, J, pes, ix->e2, rev_keys, rev_vals, taken);
     PAG_HIP(hipGetLastError());
     return PAG_OK;
 }

@@ -104,6 +104,23 @@ int pag_plan_team(const pag_team_request& r, Lds&& lds_bytes, Resident&& residen
     return pag_fit_team(r, share, std::min(most, r.most_waves), step, lds_bytes, resident, p);
 }
 
+// The largest batch of new nodes whose RobustPrune has four waves per node, for rows of `chunks` 16-byte chunks a lane (1, 2, 3, 4, 6, 8, 12).
+// Four waves finish a node sooner and keep more of its rows on the chip; one wave per node leaves the CU to more nodes, which counts
+// where their rows come from HBM and their candidates are few to a kept row.  Prune phase of whole builds, one wave -> four:
+//   up to 768-d any batch gains.  100,000 rows in batches of 2,048 / 16,384: 128-d 22.4 -> 17.4, 15.2 -> 13.6 ms, 768-d 34.9 -> 25.2, 22.1 ->
+//     19.1; 300,000 in 16,384: 256-d, degree 64 21.3 -> 18.3 (65,536: 18.6 -> 17.1), 512-d 45.8 -> 41.5, 768-d, degree 16 / 64 34.0 -> 30.2,
+//     74.9 -> 63.6; 1M in 16,384: 128-d 59.7 -> 56.7, 768-d 357 -> 341
+//   1024-d up to 32 nodes a CU.  300,000 rows, degree 48, batches of 4,096 / 8,192 / 16,384: 117 -> 97, 93 -> 86, 81 -> 80, degree 32
+//     73.9 -> 72.2 at 8,192, 66.2 -> 68.0 at 16,384; 1M, degree 48, in 16,384: 651 -> 687
+//   1280-d and 1536-d up to 8.  300,000 x 1280 in 2,048 / 4,096: 166 -> 147, 119 -> 130; 300,000 x 1536 326 -> 293, 234 -> 256 (16,384: 179 -> 225)
+//   2048-d any batch.  200,000 rows in 2,048 / 4,096 / 16,384: 164 -> 129, 127 -> 114, 106 -> 101
+//   longer ones up to 3.  100,000 x 2560 in 512 / 1,024: 287 -> 202, 154 -> 171; 200,000 x 3072 in 512 / 768: 588 -> 394, 413 -> 359;
+//     30,000 x 3072 in 768 / 1,024: 64 -> 59, 51 -> 57
+constexpr uint64_t PAG_ANY_BATCH = ~0ull;
+constexpr uint64_t pag_prune_line(uint32_t chunks, uint32_t num_cu) {
+    return chunks <= 3 || chunks == 8 ? PAG_ANY_BATCH : (uint64_t)num_cu * (chunks == 4 ? 32 : chunks == 6 ? 8 : 3);
+}
+
 // How many workgroups with that LDS a CU really holds.  It is handed out in pieces of 1,280 bytes, which the occupancy query does not
 // know: workgroups that only wait, with 11,904 bytes each, run twelve at a time and not thirteen, with 6,144 25 and not 26 (every size
 // from 5 to 40 KB).
