@@ -281,9 +281,10 @@ def test_small_and_extreme_shapes(orc, n, d, P, deg, efC, subbatch):
     (768, 32, 32, 100, "l2", True),      # the 16-bit vector store
 ])
 def test_every_row_length_class(orc, d, P, deg, efC, metric, half):
-    """Construction in the default batches at one row length per instantiation of the pruning kernel (16-byte
-    chunks per lane: 1, 2, 3, 4, 6, 8, 12), on isotropic data, where RobustPrune keeps more neighbours than the
-    kernel holds in LDS: both of its paths (kept rows in LDS, kept rows from memory) decide as the oracle does."""
+    """Construction in the default batches at one row length per instantiation of the pruning kernel with four waves per
+    node, which batches of this size get (16-byte chunks per lane: 1, 2, 3, 4, 6, 8, 12), on isotropic data, where RobustPrune
+    keeps many neighbours; with long rows more than the kernel holds in LDS.  tests/test_gpu_prune_waves.py has larger batches, the
+    kernel with one wave per node, and asserts which rows are held."""
     PagIndex = _gpu()
     from paper_2603_06660_amd import FLAG_FP16_VECTORS, FLAG_KEEP_ORDER
     n = 520
@@ -299,7 +300,7 @@ def test_every_row_length_class(orc, d, P, deg, efC, metric, half):
                      max_batch=min(n, 1024))
     _assert_same_index(ex, oix, "row length d=%d" % d)
     kept = (ex["adj"] != orc.EMPTY).sum(axis=1)
-    assert kept.max() > 16 or deg <= 16        # beyond the rows held in LDS at every length
+    assert kept.max() > 16 or deg <= 16
 
 
 def test_duplicated_vectors(orc):
