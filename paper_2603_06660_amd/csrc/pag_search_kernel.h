@@ -23,9 +23,10 @@
 //
 // One hop evaluates the projection test for all neighbours of u at once, lane s <-> neighbour
 // slot s, against the threshold read when u is popped; the hop's passers enter W as if they
-// were admitted one after another in ascending (dist, id) order, which a merge by ranks
-// reproduces exactly: the b smallest of W + passers stay, displaced W members go to R_T
-// (largest first), passers that do not fit go to R_F (smallest first).
+// were admitted one after another in ascending (dist, id) order: the b smallest of W + passers
+// stay, displaced W members go to R_T (largest first), passers that do not fit go to R_F
+// (smallest first).  One wave by itself merges a sorted W by ranks, a team's wave 0 inserts one
+// passer after another, a step of one lane each; an unsorted W takes them one replacement at a time.
 #pragma once
 
 #include "pag_internal.h"
@@ -1213,8 +1214,8 @@ struct Wave {
     //           Only the threshold has to wait.
     // Where a round has ended in between (every eleventh hop at b = 10) the node is another one, and it is screened in a phase
     // of its own.
-    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.2 with twelve (5,000 clocks: rows 2,800, of which a trip to
-    // memory is 1,200, wave 0's lists 1,400, the rest posting, reading what is posted, barriers).  While every row wave also
+    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.2 with twelve (4,900 clocks: rows 2,800, of which a trip to
+    // memory is 1,200, wave 0's lists 1,340, the rest reading what is posted, barriers).  While every row wave also
     // ranked its passers against W for a merge by scatter through LDS, and a record was first asked for when its node was
     // expanded, it was 2.6.
     enum : u32 {
@@ -1726,9 +1727,11 @@ __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
 }
 
 // The same with several waves per query, for batches that would leave the GPU mostly idle.
-// Registers: 128 a lane, four waves per SIMD, where the rows in flight and the query allow it (at most 51 dwords of spill, with six
-// chunks a row), else the 168 that twelve waves leave (16-bit rows of 2560 and 3072 spill 98 dwords either way, and with
-// 128 registers every wave feels it: one query per CU 1.17 times as fast as one wave, 1.35 with 168, two per CU 0.85).
+// Registers: 128 a lane, four waves per SIMD, where the rows in flight and the query allow it (up to 12 of them spilled; of 16-bit rows in
+// 16-byte chunks 91 with three and 34 with four chunks, in 8-byte chunks 89 with six, and still teams of eight and four are 1.1 to 1.5 times as
+// fast as one wave on 1280-d and 1536-d, 300 to 1,024 queries, where 168 registers would leave room for half as many), else the 168 that
+// twelve waves leave (16-bit rows of 2560 and 3072 spill 65 to 86 of those; with 128 every wave felt it: one query per CU 1.17 times as fast as
+// one wave, 1.35 with 168, two per CU 0.85).
 template <int NQ, int NW, int VM>
 __attribute__((amdgpu_waves_per_eu(NW <= 2 && (NQ <= 4 || (NQ == 6 && VM != 1)) ? 4 : 2, 8)))
 __global__ void __launch_bounds__(64 * pag_team_max(NW)) k_search_team(const SearchArgs A) {
