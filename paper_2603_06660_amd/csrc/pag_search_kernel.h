@@ -1257,28 +1257,49 @@ struct Wave {
         return ((u64)mh << 32) | wave_extreme_u32<false>(hi == mh ? (u32)k : 0xFFFFFFFFu);
     }
 
-    // This wave's share of the rows of the lanes in `mask`, TR of them in flight at a time.  The rows of a wave are reduced
+    // This wave's share of the rows of the lanes in `mask`, at most TR of them in flight at a time.  The rows of a wave are reduced
     // together: one row alone is a chain of dependent instructions.
     static constexpr int TR = NQ * (int)sizeof(Chunk) <= 48 ? 4 : (NQ * (int)sizeof(Chunk) <= 96 ? 2 : 1);
 
-    // keys of G rows (those with i < r exist)
-    template <int G>
-    __device__ __forceinline__ void team_reduce(const Chunk (&v)[TR][NQ], const u32 (&id)[TR], u32 at, u32 step, u32 r) const {
+    // R rows of this wave, those of passers at, at + step, ...: they are asked for in straight-line code.  With a request in a branch of its own
+    // the compiler waits for an earlier row before it: of four rows the third and the fourth came a trip to memory
+    // later (1,000 queries of 1M x 768 1.161 -> 1.122 ms, 250 x 3072 1.442 -> 1.366, 512 x 768 in 16 bits 1.379 -> 1.332).
+    template <int R, bool AHEAD>
+    __device__ __forceinline__ void rows_at(u32 id_lane, u32 mine, u32 at, u32 step, u32& touched) const {
+        constexpr int G = R == 3 ? 4 : R;
+        const u32 line = (u32)lane * 128u < A.rec_bytes ? (u32)lane * 128u : 0u;
+        Chunk v[R][NQ];
+        u32 id[R], word[R];
+#pragma unroll
+        for (int g = 0; g < R; ++g) id[g] = rdlane(id_lane, __ffsll((long long)__ballot(mine == at + (u32)g * step)) - 1);
+#pragma unroll
+        for (int g = 0; g < R; ++g) load_vec(v[g], id[g]);
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int g = 0; g < R; ++g) word[g] = *(const u32*)(A.rec + (u64)id[g] * A.rec_bytes + line);
+        }
+        __builtin_amdgcn_sched_barrier(0);
         double acc[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) acc[g] = lane_partial(v[g]);
+        for (int g = 0; g < G; ++g) acc[g] = 0.0;
+#pragma unroll
+        for (int g = 0; g < R; ++g) acc[g] = lane_partial(v[g]);
         const double tot = fold_sum<G>(acc);                // lanes g * 64 / G ...: the total of row g
         const u32 g = (u32)lane / (64 / G);
         u32 my_id = id[0];
 #pragma unroll
-        for (u32 i = 1; i < G; ++i) {
+        for (u32 i = 1; i < R; ++i) {
             u32 other = id[i];
             asm volatile("" : "+v"(other));                 // or the compiler indexes the ids in scratch
             my_id = g == i ? other : my_id;
         }
-        if ((u32)lane % (64 / G) == 0 && g < r) {
+        if ((u32)lane % (64 / G) == 0 && g < (u32)R) {
             const u32 bits = __float_as_uint((float)tot);       // a NaN of either sign: the largest distance
             team_keys()[at + g * step] = ((u64)(bits < 0x7FC00000u ? bits : 0x7FC00000u) << 32) | ((u64)my_id << 1);
+        }
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int g = 0; g < R; ++g) touched |= word[g];
         }
     }
 
@@ -1290,28 +1311,12 @@ struct Wave {
         const u32 first = AHEAD ? 3u : 2u;                  // the first wave that fetches rows
         const u32 n = (u32)__popcll(mask), step = (u32)nwaves - first;
         const u32 mine = ((mask >> lane) & 1ull) ? team_index(mask) : PAG_EMPTY;
-        const u32 line = (u32)lane * 128u < A.rec_bytes ? (u32)lane * 128u : 0u;
         u32 touched = 0;
         for (u32 at = (u32)wave - first; at < n; at += TR * step) {
-            Chunk v[TR][NQ];
-            u32 id[TR], word[TR], r = 0;
-#pragma unroll
-            for (int g = 0; g < TR; ++g) {
-                id[g] = 0; word[g] = 0;
-                if (at + (u32)g * step < n) {
-                    id[g] = rdlane(id_lane, __ffsll((long long)__ballot(mine == at + (u32)g * step)) - 1);
-                    load_vec(v[g], id[g]);
-                    if constexpr (AHEAD) word[g] = *(const u32*)(A.rec + (u64)id[g] * A.rec_bytes + line);
-                    ++r;
-                }
-            }
-            if (TR >= 4 && r > 2) { if constexpr (TR >= 4) team_reduce<4>(v, id, at, step, r); }
-            else if (TR >= 2 && r > 1) { if constexpr (TR >= 2) team_reduce<2>(v, id, at, step, r); }
-            else team_reduce<1>(v, id, at, step, r);
-            if constexpr (AHEAD) {
-#pragma unroll
-                for (int g = 0; g < TR; ++g) touched |= word[g];
-            }
+            if (TR < 2 || at + step >= n) rows_at<1, AHEAD>(id_lane, mine, at, step, touched);
+            else if (TR < 4 || at + 2 * step >= n) { if constexpr (TR >= 2) rows_at<2, AHEAD>(id_lane, mine, at, step, touched); }
+            else if (at + 3 * step >= n) { if constexpr (TR >= 4) rows_at<3, AHEAD>(id_lane, mine, at, step, touched); }
+            else if constexpr (TR >= 4) rows_at<4, AHEAD>(id_lane, mine, at, step, touched);
         }
         return touched;
     }
