@@ -56,25 +56,41 @@ __device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_rea
 
 __device__ __forceinline__ u32 hash_slot(u32 id, u32 hlog) { return (id * 2654435761u) >> (32 - hlog); }
 
-// The table is probed in buckets of four slots that fill from the front: one 16-byte read tells nearly all, where the longest run of
-// 32 lanes that probed slot by slot took several reads, one after the other (one query
-// of 1M x 768 185 -> 182 us, 37 queries 1,268 -> 1,233, 512 x 768 in 16 bits 1,332 -> 1,293).
+// BUCKETS (teams): the table is probed in buckets of four slots that fill from the front.  One 16-byte read tells nearly all, where the
+// longest run of 32 lanes that probe slot by slot takes several reads, one after the other (37 queries of 1M x 768 1,268 -> 1,233 us,
+// 512 x 768 in 16 bits 1,332 -> 1,293).  Single waves fill the GPU and wait for the LDS rather than for one read after the
+// other: there a read of one slot stays the better one.
+template <bool BUCKETS>
 __device__ __forceinline__ bool hash_contains(const u32* H, u32 hlog, u32 id) {
     const u32 mask = (1u << hlog) - 1;
-    u32 p = hash_slot(id, hlog) & ~3u;
-    for (;;) {
-        const uint4 v = *(const uint4*)(H + p);
-        if (v.x == id || v.y == id || v.z == id || v.w == id) return true;
-        if (v.w == PAG_EMPTY) return false;
-        p = (p + 4) & mask;
+    u32 p = hash_slot(id, hlog);
+    if constexpr (BUCKETS) {
+        p &= ~3u;
+        for (;;) {
+            const uint4 v = *(const uint4*)(H + p);
+            if (v.x == id || v.y == id || v.z == id || v.w == id) return true;
+            if (v.w == PAG_EMPTY) return false;
+            p = (p + 4) & mask;
+        }
+    } else {
+        for (;;) {
+            const u32 v = H[p];
+            if (v == id) return true;
+            if (v == PAG_EMPTY) return false;
+            p = (p + 1) & mask;
+        }
     }
 }
 
+template <bool BUCKETS>
 __device__ __forceinline__ void hash_insert(u32* H, u32 hlog, u32 id) {
     const u32 mask = (1u << hlog) - 1;
-    u32 p = hash_slot(id, hlog) & ~3u;
-    const uint4 v = *(const uint4*)(H + p);
-    p += v.x == PAG_EMPTY ? 0u : v.y == PAG_EMPTY ? 1u : v.z == PAG_EMPTY ? 2u : 3u;
+    u32 p = hash_slot(id, hlog);
+    if constexpr (BUCKETS) {
+        p &= ~3u;
+        const uint4 v = *(const uint4*)(H + p);
+        p += v.x == PAG_EMPTY ? 0u : v.y == PAG_EMPTY ? 1u : v.z == PAG_EMPTY ? 2u : 3u;
+    }
     for (;;) {
         const u32 old = atomicCAS(&H[p], PAG_EMPTY, id);
         if (old == PAG_EMPTY || old == id) return;
@@ -360,22 +376,23 @@ struct Wave {
         const u32 sl = (u32)lane < A.deg ? (u32)lane : 0u;
         ea = ((const float*)(rec + A.off_a))[sl];
         ec = ((const float*)(rec + A.off_c))[sl];
+        const u32* cp = (const u32*)(rec + A.off_codes) + sl * (u32)CW;    // 16-byte aligned section
         if constexpr (TEAM) {
             // Two 16-byte reads whatever the length of the codes, in straight-line code (8 bytes: of a pair of neighbours; the section is
             // 16-byte aligned and the record has room behind an odd last one).
             const bool pairs = A.cw == 2;
-            const uint8_t* cp = rec + A.off_codes + (pairs ? (sl >> 1) * 16u : sl * A.cw * 4u);
-            const uint4 t = *(const uint4*)cp, v = *(const uint4*)(cp + (A.cw == 8 ? 16u : 0u));
+            const uint8_t* tp = rec + A.off_codes + (pairs ? (sl >> 1) * 16u : sl * A.cw * 4u);
+            const uint4 t = *(const uint4*)tp, v = *(const uint4*)(tp + (A.cw == 8 ? 16u : 0u));
             const bool upper = pairs && (sl & 1u);
             cwv[0] = upper ? t.z : t.x; cwv[1] = upper ? t.w : t.y; cwv[2] = t.z; cwv[3] = t.w;
             cwv[4] = v.x; cwv[5] = v.y; cwv[6] = v.z; cwv[7] = v.w;
         } else if constexpr (CW == 2) {
-            const uint2 t = *(const uint2*)(rec + A.off_codes + sl * 8u);
+            const uint2 t = *(const uint2*)cp;
             cwv[0] = t.x; cwv[1] = t.y;
         } else {
 #pragma unroll
             for (int k = 0; k < CW; k += 4) {
-                const uint4 t = *(const uint4*)(rec + A.off_codes + sl * (CW * 4u) + k * 4);   // 16-byte aligned section
+                const uint4 t = *(const uint4*)(cp + k);
                 cwv[k] = t.x; cwv[k + 1] = t.y; cwv[k + 2] = t.z; cwv[k + 3] = t.w;
             }
         }
@@ -543,7 +560,7 @@ struct Wave {
             // short searches: exact open-addressing hash, kept at most half full; beyond that the bitmap
             const bool spill = (n_hash + np) > (1u << (A.hlog - 1));
             if (pass) {
-                if (!spill) hash_insert(H, A.hlog, id_lane);
+                if (!spill) hash_insert<TEAM>(H, A.hlog, id_lane);
                 else atomicOr(&bitmap[id_lane >> 5], 1u << (id_lane & 31));
             }
             if (spill) { n_spill += np; s_spill += np; } else n_hash += np;
@@ -902,7 +919,7 @@ struct Wave {
         // recent ids now; the Bloom filter and the bitmap only for the neighbours that pass the test
         // (a bitmap read costs more than the table sums of the seen neighbours it would spare).
         cand = in_graph;
-        if (cand) cand = A.blog != 0 ? H[hash_slot(id, A.hlog)] != id : !hash_contains(H, A.hlog, id);
+        if (cand) cand = A.blog != 0 ? H[hash_slot(id, A.hlog)] != id : !hash_contains<TEAM>(H, A.hlog, id);
         u32 bm_word = 0;
         if (A.blog == 0 && n_spill && cand)
             bm_word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1468,7 +1485,7 @@ struct Wave {
             if (cand && bloom_maybe(BL, A.blog, id))
                 word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
-            if (cand) cand = !hash_contains(H, A.hlog, id);
+            if (cand) cand = !hash_contains<TEAM>(H, A.hlog, id);
             if (n_spill && cand) word = __hip_atomic_load(&bitmap[id >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return cand && !((word >> (id & 31)) & 1u);
