@@ -4,8 +4,8 @@
 //
 // Wave-level data placement (64 lanes; a team's wave 0 holds W, R_L and the rings, its wave 1 keeps the seen set):
 //   query        registers, NQ float4 per lane (element chunk c*64+lane)
-//   W            registers, NW slots per lane (b <= 64 NW).  Up to 128 nodes (NW <= 2): sorted ascending by key, rank r
-//                in slot r/64 of lane r%64.  Above (NW >= 4): unsorted, entry i in slot i/64 of lane i%64; the node to
+//   W            registers, NW slots per lane (b <= 64 NW).  Up to 128 nodes (NW <= 2), and up to 512 in a team: sorted ascending
+//                by key, rank r in slot r/64 of lane r%64 (above 128 nodes the last slots are used).  Else: unsorted, entry i in slot i/64 of lane i%64; the node to
 //                expand and the farthest member are found by wave-wide minima / maxima, the farthest one is cached
 //   R_L          up to 128 nodes: registers, same placement (capacity K <= b); above: the front of a per-wave HBM buffer
 //   table T      LDS, float [Ppad][16]
@@ -274,10 +274,13 @@ struct Wave {
     // per query
     static constexpr int QV = NQ * EPC / 4;         // float4 registers holding the query
     static constexpr bool RINGS_IN_HBM = NW > 2;    // matches the host's LDS carve-up
-    static constexpr bool BIG = NW > 2;             // large working sets: W unsorted, see merge_unsorted
+    static constexpr bool BIG = NW > 2;             // large working sets
+    // W is kept sorted: up to 128 nodes, by a team up to 512; else see merge_unsorted
+    static constexpr bool SORTED = NW <= 2 || (TEAM && NW <= 8);
     u64 wmax;                       // BIG: key of W's farthest member, valid while nW == b
     u64 nx_key;                     // BIG: key of the node to expand next (PAG_KEY_INVALID: W has no unvisited node)
     bool nx_known;                  // BIG: nx_key is up to date
+    u32 open_slot;                  // BIG, TEAM: the slots before this one hold no unvisited member
     u64 GM, GU;                     // BIG: lane s < NW holds slot s's farthest member (0: slot empty) and its closest
                                     // unvisited member (PAG_KEY_INVALID: none); the other lanes hold 0 / PAG_KEY_INVALID
     float4 q[QV];
@@ -733,6 +736,19 @@ struct Wave {
         }
     }
 
+    // TEAM: W's closest unvisited member, and its slot in open_slot
+    __device__ __forceinline__ u64 closest_open() {
+        u64 k = PAG_KEY_INVALID;
+#pragma unroll
+        for (int s = 0; s < NW; ++s)
+            if ((u32)s >= open_slot && k == PAG_KEY_INVALID) {
+                const u64 m = __ballot(!(W[s] & 1ull));
+                open_slot = (u32)s;
+                if (m) k = rdlane64(W[s], __ffsll((long long)m) - 1);
+            }
+        return k;
+    }
+
     // finds the node that will be expanded next and requests its adjacency record
     __device__ __forceinline__ void look_ahead() {
         nx_key = over_slots<false>(GU);
@@ -834,7 +850,8 @@ struct Wave {
 
     __device__ __forceinline__ void reset_lists() {
 #pragma unroll
-        for (int s = 0; s < NW; ++s) W[s] = PAG_KEY_INVALID;
+        for (int s = 0; s < NW; ++s) W[s] = !(BIG && SORTED) ? PAG_KEY_INVALID : (u32)s < first_slot() ? BEFORE_ALL : BEHIND_ALL;
+        open_slot = 0;
 #pragma unroll
         for (int s = 0; s < (BIG ? 1 : NW); ++s) RL[s] = PAG_KEY_INVALID;
         nW = nRL = n_done = 0;
@@ -852,7 +869,11 @@ struct Wave {
     __device__ __forceinline__ u64 pop() {
         const u32 b = A.b;
         u64 ukey = PAG_KEY_INVALID;
-        if constexpr (BIG) {
+        if constexpr (BIG && SORTED) {
+            ukey = closest_open();
+            if (ukey == PAG_KEY_INVALID) return ukey;
+            at_slot((int)open_slot, [&](auto S_) { constexpr int S = decltype(S_)::value; if (W[S] == ukey) W[S] |= 1ull; });
+        } else if constexpr (BIG) {
             if (!nx_known) nx_key = over_slots<false>(GU);
             nx_known = false;
             if (nx_key == PAG_KEY_INVALID) return nx_key;
@@ -891,7 +912,9 @@ struct Wave {
     // key of W's farthest member; PAG_KEY_INVALID while W is not full
     __device__ __forceinline__ u64 farthest() const {
         if (nW != A.b) return PAG_KEY_INVALID;
-        if constexpr (BIG) {
+        if constexpr (BIG && SORTED) {
+            return rdlane64(W[NW - 1], (int)((A.b - 1) & 63u));
+        } else if constexpr (BIG) {
             return wmax;
         } else {
             const u32 wr = A.b - 1;
@@ -1003,7 +1026,7 @@ struct Wave {
 #pragma unroll
             for (int s = 0; s < NW; ++s) {
                 const u32 idx = s * 64 + lane;
-                x[s] = idx < nW ? W[s] : PAG_KEY_INVALID;
+                x[s] = (SORTED ? rank_at(s) : idx) < nW ? W[s] : PAG_KEY_INVALID;
                 x[NW + s] = idx < nRL ? SA[idx] : PAG_KEY_INVALID;
             }
             bitonic_registers<2 * NW>(x, lane);
@@ -1057,26 +1080,46 @@ struct Wave {
                 const u32 idx = s * 64 + lane;
                 W[s] = idx < nW ? x[s] : PAG_KEY_INVALID;
             }
-            // W is sorted now: a slot's farthest member is its last, its closest unvisited one the first unvisited
-            GM = 0ull; GU = PAG_KEY_INVALID;
+            // W is sorted now
+            if constexpr (!SORTED) {
+                // a slot's farthest member is its last, its closest unvisited one the first unvisited
+                GM = 0ull; GU = PAG_KEY_INVALID;
 #pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                const u32 first = s * 64;
-                if (nW > first) {
-                    const u32 cnt = nW - first < 64u ? nW - first : 64u;
-                    const u64 far = rdlane64(W[s], (int)cnt - 1);
-                    const u64 open = __ballot((u32)lane < cnt && !(W[s] & 1ull));
-                    const u64 near = open ? rdlane64(W[s], __ffsll((long long)open) - 1) : PAG_KEY_INVALID;
-                    if (lane == s) { GM = far; GU = near; }
+                for (int s = 0; s < NW; ++s) {
+                    const u32 first = s * 64;
+                    if (nW > first) {
+                        const u32 cnt = nW - first < 64u ? nW - first : 64u;
+                        const u64 far = rdlane64(W[s], (int)cnt - 1);
+                        const u64 open = __ballot((u32)lane < cnt && !(W[s] & 1ull));
+                        const u64 near = open ? rdlane64(W[s], __ffsll((long long)open) - 1) : PAG_KEY_INVALID;
+                        if (lane == s) { GM = far; GU = near; }
+                    }
                 }
+                wmax = nW == b ? over_slots<true>(GM) : 0ull;
+                nx_known = false;
             }
-            wmax = nW == b ? over_slots<true>(GM) : 0ull;
-            nx_known = false;
             const u32 rest = n - nW;                         // <= b; written worst first
 #pragma unroll
             for (int s = 0; s < 2 * NW; ++s) {
                 const u32 e = s * 64 + lane;
                 if (e >= nW && e < n) RT[n - 1 - e] = x[s];
+            }
+            if constexpr (SORTED) {
+                // to its slots, through the memory of R_F, which is empty now
+#pragma unroll
+                for (int s = 0; s < NW; ++s) {
+                    const u32 idx = s * 64 + lane;
+                    if (idx < b) RF[idx] = idx < nW ? x[s] : BEHIND_ALL;
+                }
+                __threadfence();
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < NW; ++s) {
+                    const u32 at = rank_at(s);
+                    const u64 k = __hip_atomic_load(&RF[at < b ? at : 0u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    W[s] = at < b ? k : (u32)s < first_slot() ? BEFORE_ALL : BEHIND_ALL;
+                }
+                open_slot = 0;
             }
             cntT = rest; hdT = rest;
             cntF = 0; hdF = 0;
@@ -1341,7 +1384,9 @@ struct Wave {
 
     // key of W's closest unvisited member, which stays unvisited
     __device__ __forceinline__ u64 peek() {
-        if constexpr (BIG) {
+        if constexpr (BIG && SORTED) {
+            return closest_open();
+        } else if constexpr (BIG) {
             if (!nx_known) nx_key = over_slots<false>(GU);
             nx_known = true;
             return nx_key;
@@ -1382,7 +1427,7 @@ struct Wave {
             for (int s = 0; s < NW; ++s) {
                 const u32 enter = (u32)__popcll(__ballot((u32)(s * 64 + lane) < n_done && done[s] < kth));      // done is sorted
                 const double d = __longlong_as_double((long long)done[s]);
-                for (u32 i = 0; i < enter; ++i) insert(w, lane_value(d, (int)i));
+                for (u32 i = 0; i < enter; ++i) (void)insert(w, lane_value(d, (int)i));
                 n += enter;
             }
             nRL = nRL + n < A.K ? nRL + n : A.K;
@@ -1407,15 +1452,25 @@ struct Wave {
     }
 
     // wave 0, sorted W: the hop's np passers, whose keys lie in LDS, in two parts: W itself, ...
+    // (Working sets of 129 to 512 nodes were unsorted here too.  A passer cost them a reduction over one slot, one over all
+    // slots and a search for the member that leaves, all one after the other; to step to the next lane is four slots at a time and needs no
+    // search.  1 to 512 queries of 50k x 768, K 150 / 200 / 300 / 500: 1.55, 1.5, 1.27 and 1.26 times as fast with twelve waves, 1.16 with
+    // four from K 300 on.  With sixteen slots the registers spill inside the hop: 300 queries, K 1000 17.9 ms unsorted, 19.2 sorted.)
     // A passer takes its place by one comparison of every member, and those behind it step to the next lane (470 clocks a hop; by
     // ranks and a scatter through LDS 840, with the counting in the row waves besides).  The keys are
     // compared as doubles, whose order is theirs (the distance word of a key is at most that of a NaN, 0x7FC00000, see
     // team_reduce: no key is a NaN or an infinity as a double), in one instruction each.
+    static constexpr int OW = NW < 2 ? NW : 2;          // the slots that lose members: a hop has 64 passers at most
     struct Merge {
-        u64 oldW[NW], pk, far;
+        u64 oldW[OW], pk, far;
         u32 nW, np;
     };
-    static constexpr u64 BEHIND_ALL = 0x7FEFFFFFFFFFFFFFull;       // the largest double
+    // Above 128 nodes rank r lies in slot first_slot() + r / 64, so that the farthest member of a full W is in the last slot; places
+    // without a member count as visited.
+    static constexpr u64 BEHIND_ALL = 0x7FEFFFFFFFFFFFFFull;       // a place behind the last member: the largest double
+    static constexpr u64 BEFORE_ALL = 0xBFF0000000000001ull;       // the places of slots before the first: below 0
+    __device__ __forceinline__ u32 first_slot() const { return BIG ? (u32)NW - (A.b + 63u) / 64u : 0u; }
+    __device__ __forceinline__ u32 rank_at(int s) const { return ((u32)s - first_slot()) * 64u + (u32)lane; }       // of slots before the first: huge
     template <bool FIRST>
     __device__ __forceinline__ static double from_below(double x, double first) {      // lane l: x of lane l - 1; lane 0: first, or 0
         constexpr int WAVE_SHR1 = 0x138;
@@ -1423,29 +1478,52 @@ struct Wave {
         const int hi = __builtin_amdgcn_update_dpp(FIRST ? __double2hiint(first) : 0, __double2hiint(x), WAVE_SHR1, 0xF, 0xF, !FIRST);
         return __hiloint2double(hi, lo);
     }
-    __device__ __forceinline__ static void insert(double (&w)[NW], double k) {
-        double below[NW];
-        below[0] = from_below<false>(w[0], 0.0);
+    // Four slots at a time where there are many, those before k's place left alone; returns the first slot that may have changed.
+    __device__ __forceinline__ static u32 insert(double (&w)[NW], double k) {
+        if constexpr (NW <= 2) {
+            double below[NW];
+            below[0] = from_below<false>(w[0], 0.0);
 #pragma unroll
-        for (int s = 1; s < NW; ++s) below[s] = from_below<true>(w[s], lane_value(w[s - 1], 63));
+            for (int s = 1; s < NW; ++s) below[s] = from_below<true>(w[s], lane_value(w[s - 1], 63));
 #pragma unroll
-        for (int s = 0; s < NW; ++s) w[s] = fmin(w[s], fmax(below[s], k));
+            for (int s = 0; s < NW; ++s) w[s] = fmin(w[s], fmax(below[s], k));
+            return 0;
+        } else {
+            constexpr int STEP = 4;
+            u32 slot = NW - STEP;
+            bool here = true;
+#pragma unroll
+            for (int g = NW - STEP; g >= 0; g -= STEP) {
+                if (g < NW - STEP) here = here && k < lane_value(w[g + STEP - 1], 63);
+                if (here) {
+#pragma unroll
+                    for (int s = g + STEP - 1; s >= g; --s) w[s] = fmin(w[s], fmax(from_below<true>(w[s], s > 0 ? lane_value(w[s > 0 ? s - 1 : 0], 63) : -1.0), k));
+                    slot = (u32)g;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            return slot;
+        }
     }
     __device__ __forceinline__ void merge_w(Merge& M, u32 np) {
         M.pk = (u32)lane < np ? team_keys()[lane] : PAG_KEY_INVALID;
         M.np = np; M.nW = nW;
         double w[NW];
 #pragma unroll
-        for (int s = 0; s < NW; ++s) {
-            M.oldW[s] = W[s];
-            w[s] = __longlong_as_double((long long)((u32)(s * 64 + lane) < nW ? W[s] : BEHIND_ALL));
-        }
+        for (int s = 0; s < OW; ++s) M.oldW[s] = W[NW - OW + s];
+#pragma unroll
+        for (int s = 0; s < NW; ++s)
+            w[s] = __longlong_as_double((long long)(BIG || (u32)(s * 64 + lane) < nW ? W[s] : BEHIND_ALL));
         const double pk = __longlong_as_double((long long)M.pk);
         const u64 far0 = farthest();
-        for (u64 m = __ballot((u32)lane < np && M.pk < far0); m; m &= m - 1) insert(w, lane_value(pk, __ffsll((long long)m) - 1));
+        for (u64 m = __ballot((u32)lane < np && M.pk < far0); m; m &= m - 1) {
+            const u32 slot = insert(w, lane_value(pk, __ffsll((long long)m) - 1));
+            if (BIG && slot < open_slot) open_slot = slot;
+        }
         nW = nW + np < A.b ? nW + np : A.b;
 #pragma unroll
-        for (int s = 0; s < NW; ++s) W[s] = (u32)(s * 64 + lane) < nW ? (u64)__double_as_longlong(w[s]) : PAG_KEY_INVALID;
+        for (int s = 0; s < NW; ++s) W[s] = BIG || (u32)(s * 64 + lane) < nW ? (u64)__double_as_longlong(w[s]) : PAG_KEY_INVALID;
+        if (BIG && (u32)lane > ((A.b - 1) & 63u)) W[NW - 1] = BEHIND_ALL;       // pushed out of a full W
         M.far = farthest();
     }
     // ... and what it pushes to the rings: displaced members to R_T (largest first), passers that do not fit to R_F (smallest first)
@@ -1456,8 +1534,8 @@ struct Wave {
         const u32 n_ej = M.nW + (M.np - n_f) - (M.nW + M.np < b ? M.nW + M.np : b);
         if (n_ej) {
 #pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                const u32 idx = s * 64 + lane;
+            for (int s = 0; s < OW; ++s) {
+                const u32 idx = rank_at(NW - OW + s);
                 if (idx < M.nW && M.oldW[s] > M.far) RT[(hdT + (M.nW - 1 - idx)) & A.ring_mask] = M.oldW[s];
             }
             if (cntT + n_ej > b) s_rt += cntT + n_ej - b;
@@ -1576,11 +1654,11 @@ struct Wave {
                 team_barrier();
                 if constexpr (KEEPS_LISTS) {
                     s_exact += np;
-                    if constexpr (BIG) {
-                        merge_unsorted(id, mask, np, pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
-                    } else {
+                    if constexpr (SORTED) {
                         Merge M;
                         merge_w(M, np);                // no more than b in all: nothing for the rings
+                    } else {
+                        merge_unsorted(id, mask, np, pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
                     }
                 }
                 team_barrier();
@@ -1646,11 +1724,7 @@ struct Wave {
                 if constexpr (AHEAD) asm volatile("" :: "v"(touched));
                 if constexpr (KEEPS_LISTS) {
                     s_exact += np;
-                    if constexpr (BIG) {
-                        owed = false;
-                        if (np) merge_unsorted(id, mask, np, pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
-                        post_next(qi);
-                    } else {
+                    if constexpr (SORTED) {
                         owed = np != 0;
                         if (np) merge_w(M, np);
                         const u64 next = pop();
@@ -1661,6 +1735,10 @@ struct Wave {
                             owed = false;
                             post_next(qi);
                         }
+                    } else {
+                        owed = false;
+                        if (np) merge_unsorted(id, mask, np, pass, __uint_as_float((u32)(team_keys()[pass ? team_index(mask) : 0u] >> 32)));
+                        post_next(qi);
                     }
                 }
                 if (KEEPS_SEEN || (MAY_ESTIMATE && estimates)) {
@@ -1753,13 +1831,13 @@ __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
 }
 
 // The same with several waves per query, for batches that would leave the GPU mostly idle.
-// Registers: 128 a lane, four waves per SIMD, where the rows in flight and the query allow it (up to 12 of them spilled; of 16-bit rows in
-// 16-byte chunks 91 with three and 34 with four chunks, in 8-byte chunks 89 with six, and still teams of eight and four are 1.1 to 1.5 times as
-// fast as one wave on 1280-d and 1536-d, 300 to 1,024 queries, where 168 registers would leave room for half as many), else the 168 that
-// twelve waves leave (16-bit rows of 2560 and 3072 spill 65 to 86 of those; with 128 every wave felt it: one query per CU 1.17 times as fast as
-// one wave, 1.35 with 168, two per CU 0.85).
+// Registers: 128 a lane, four waves per SIMD, where the rows in flight, the query and W allow it: working sets of up to 128 nodes with fp32
+// rows spill none of them, 16-bit ones up to 4, with six 8-byte chunks 22; 129 to 256 nodes 14 to 36, at their ends of rounds above all, and
+// 700 and 1,000 queries of 50k x 768, K 150, are 1.33 and 1.62 times as fast as with room for three teams.  Else the 168 that twelve waves
+// leave: none or 2 spilled, 16-bit rows in six 16-byte chunks 39, of 3072 42 (with 128 every wave felt it: one query per CU 1.17 times
+// as fast as one wave, 1.35 with 168, two per CU 0.85), working sets of 257 to 512 nodes 38 to 93.
 template <int NQ, int NW, int VM>
-__attribute__((amdgpu_waves_per_eu(NW <= 2 && (NQ <= 4 || (NQ == 6 && VM != 1)) ? 4 : 2, 8)))
+__attribute__((amdgpu_waves_per_eu(NW <= 4 && (NQ <= 4 || (NW <= 2 && NQ == 6 && VM != 1)) ? 4 : 2, 8)))
 __global__ void __launch_bounds__(64 * pag_team_max(NW)) k_search_team(const SearchArgs A) {
     extern __shared__ __align__(64) unsigned char smem[];
     Wave<NQ, NW, VM, PAG_MAX_CW, true> w(A, smem, (int)(threadIdx.x & 63), (int)uniform(threadIdx.x >> 6), (int)(blockDim.x >> 6));
