@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "pag_internal.h"
@@ -42,23 +43,51 @@ __device__ __forceinline__ float dist_lds(const pag_vecs& V, u32 d, const float*
     return (float)wave_sum(acc);
 }
 
-// squared distances between the vector staged in LDS and four rows at once (their loads are in
-// flight together); all lanes get all four results
+// What follows is bound by trips to memory, so a row's chunks are asked for together: CH of them (16 bytes a lane of fp32, 8 of 16-bit rows) for
+// four rows at once.  In a loop over single chunks a row of 768 took three trips (reverse edges of a batch of 1,024 x 768 214 us,
+// with the chunks together 174; density 51, 47).
+template <bool HALF> struct RawChunk { using type = float4; };
+template <> struct RawChunk<true> { using type = uint2; };
+template <bool HALF>
+__device__ __forceinline__ typename RawChunk<HALF>::type load_chunk(const pag_vecs& V, u64 row, u32 c) {
+    if constexpr (HALF) return *(const uint2*)((const __half*)V.base + row * V.d + 4 * (u64)c);
+    else return ((const float4*)((const float*)V.base + row * V.d))[c];
+}
+__device__ __forceinline__ float4 widened(const float4& x) { return x; }
+__device__ __forceinline__ float4 widened(const uint2& raw) {
+    const float2 a = __half22float2(*(const __half2*)&raw.x), b = __half22float2(*(const __half2*)&raw.y);
+    return make_float4(a.x, a.y, b.x, b.y);
+}
+
+// squared distances between the vector staged in LDS and four rows at once; all lanes get all four results
+template <int CH, bool HALF>
 __device__ __forceinline__ void dist_lds4(const pag_vecs& V, u32 d, const float* s, const u32 (&id)[4], float (&out)[4]) {
     const float4* q = (const float4*)s;
+    const u32 d4 = d / 4;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (u32 c = threadIdx.x; c < d / 4; c += 64) {
-        const float4 a = q[c];
-        float4 b[4];
+    for (u32 c0 = 0; c0 < d4; c0 += 64 * CH) {
+        typename RawChunk<HALF>::type b[CH][4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) b[g] = pag_vload4(V, id[g], c);
+        for (int t = 0; t < CH; ++t) {
+            const u32 c = c0 + 64 * t + threadIdx.x;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float dx = a.x - b[g].x, dy = a.y - b[g].y, dz = a.z - b[g].z, dw = a.w - b[g].w;
-            acc[g] = __builtin_fma((double)dx, (double)dx, acc[g]);
-            acc[g] = __builtin_fma((double)dy, (double)dy, acc[g]);
-            acc[g] = __builtin_fma((double)dz, (double)dz, acc[g]);
-            acc[g] = __builtin_fma((double)dw, (double)dw, acc[g]);
+            for (int g = 0; g < 4; ++g) b[t][g] = load_chunk<HALF>(V, id[g], c < d4 ? c : 0u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+            const u32 c = c0 + 64 * t + threadIdx.x;
+            const bool in = c < d4;
+            const float4 a = q[in ? c : 0u];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 w = widened(b[t][g]);
+                const float dx = in ? a.x - w.x : 0.f, dy = in ? a.y - w.y : 0.f, dz = in ? a.z - w.z : 0.f, dw = in ? a.w - w.w : 0.f;
+                acc[g] = __builtin_fma((double)dx, (double)dx, acc[g]);
+                acc[g] = __builtin_fma((double)dy, (double)dy, acc[g]);
+                acc[g] = __builtin_fma((double)dz, (double)dz, acc[g]);
+                acc[g] = __builtin_fma((double)dw, (double)dw, acc[g]);
+            }
         }
     }
     const double tot = pagk::fold_sum<4>(acc);
@@ -66,8 +95,36 @@ __device__ __forceinline__ void dist_lds4(const pag_vecs& V, u32 d, const float*
     for (int g = 0; g < 4; ++g) out[g] = (float)pagk::fold_total<4>(tot, g);
 }
 
+template <int CH, bool HALF>
 __device__ __forceinline__ void stage(const pag_vecs& V, u32 d, u32 id, float* s, int lane) {
-    for (u32 c = lane; c < d / 4; c += 64) ((float4*)s)[c] = pag_vload4(V, id, c);
+    const u32 d4 = d / 4;
+    for (u32 c0 = 0; c0 < d4; c0 += 64 * CH) {
+        typename RawChunk<HALF>::type x[CH];
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+            const u32 c = c0 + 64 * t + (u32)lane;
+            x[t] = load_chunk<HALF>(V, id, c < d4 ? c : 0u);
+        }
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+            const u32 c = c0 + 64 * t + (u32)lane;
+            if (c < d4) ((float4*)s)[c] = widened(x[t]);
+        }
+    }
+}
+
+// f(chunks, half): chunks of a row asked for together, as a compile-time constant: all of up to four, else two or more parts of three or four
+template <class F>
+void by_chunks(u32 d, u32 half, F&& f) {
+    const u32 nq = (d / 4 + 63) / 64, ch = nq <= 4 ? nq : nq <= 6 ? 3 : 4;
+    auto with = [&](auto h) {
+        if (ch == 1) f(std::integral_constant<int, 1>{}, h);
+        else if (ch == 2) f(std::integral_constant<int, 2>{}, h);
+        else if (ch == 3) f(std::integral_constant<int, 3>{}, h);
+        else f(std::integral_constant<int, 4>{}, h);
+    };
+    if (half) with(std::integral_constant<bool, true>{});
+    else with(std::integral_constant<bool, false>{});
 }
 
 // ---- initial nodes: each of the n_init listed nodes is linked to its nearest min(deg, n_init-1) peers ----
@@ -80,7 +137,7 @@ __global__ void __launch_bounds__(64) k_init_clique(pag_vecs vec, uint8_t* __res
     const u32 vi = blockIdx.x;
     const u32 v = nodes[vi];
     const int lane = threadIdx.x;
-    stage(vec, L.d, v, sv, lane);
+    for (u32 c = lane; c < L.d / 4; c += 64) ((float4*)sv)[c] = pag_vload4(vec, v, c);
     __syncthreads();
     for (u32 o = 0; o < n_init; ++o) {
         const u32 w = nodes[o];
@@ -500,6 +557,7 @@ static int launch_prune(hipStream_t s, const pag_index* ix, const u32* nodes, u3
 
 // distances between the vector staged in LDS and the next four of the neighbours in `mask` (ids in id_lane), which are
 // taken out of it; their rows are in flight together.  Lane s receives neighbour s's.
+template <int CH, bool HALF>
 __device__ __forceinline__ void neighbour_distances(const pag_vecs& V, u32 d, const float* s, u32 id_lane, u64& mask, float& out) {
     u32 w[4];
     int at[4];
@@ -510,7 +568,7 @@ __device__ __forceinline__ void neighbour_distances(const pag_vecs& V, u32 d, co
         mask &= mask - 1;
         w[g] = (u32)__builtin_amdgcn_readlane((int)id_lane, at[g]);
     }
-    dist_lds4(V, d, s, w, dd);
+    dist_lds4<CH, HALF>(V, d, s, w, dd);
 #pragma unroll
     for (int g = 0; g < 4; ++g)
         if ((int)threadIdx.x == at[g]) out = dd[g];
@@ -527,7 +585,8 @@ __device__ __forceinline__ void neighbour_distances(const pag_vecs& V, u32 d, co
 // The slots that received a new neighbour are left in `edges`, at the places of the target's pairs (the rest of those: empty), for the
 // inference-information pass: no list whose length the host would have to wait for.
 // Bound by the rows it fetches: they are asked for four at a time, those that can occlude v first, the others only where
-// a full list has to give one up (1,024 x 768: 218 us a batch; all of them one after the other: 600 us).
+// a full list has to give one up (1,024 x 768: 174 us a batch; all of them one after the other, a chunk at a time: 600 us).
+template <int CH, bool HALF>
 __global__ void __launch_bounds__(64) k_reverse(pag_vecs vec, uint8_t* __restrict__ recs,
                                                 float* __restrict__ e2, pag_layout L,
                                                 const u64* __restrict__ keys, const u32* __restrict__ vals,
@@ -561,19 +620,19 @@ __global__ void __launch_bounds__(64) k_reverse(pag_vecs vec, uint8_t* __restric
         // PES candidates are only added to available out-degree slots (Alg. 1, last loop)
         if (from_pes && __ballot((u32)lane < L.deg && id == PAG_EMPTY) == 0ull) continue;
         __syncthreads();                                      // the last pair's reads of sv are done
-        stage(vec, L.d, v, sv, lane);
+        stage<CH, HALF>(vec, L.d, v, sv, lane);
         __syncthreads();
         float dwv = 0.f;                                      // lane s: ||w_s - v||^2, as far as it is needed
         // neighbours no farther from u than v is, until one occludes v (Eq. 1)
         bool occluded = false;
         for (u64 mm = __ballot(valid && we2 <= duv); mm && !occluded;) {
-            neighbour_distances(vec, L.d, sv, id, mm, dwv);
+            neighbour_distances<CH, HALF>(vec, L.d, sv, id, mm, dwv);
             occluded = __ballot(valid && we2 <= duv && dwv <= duv && !((mm >> lane) & 1ull)) != 0ull;
         }
         if (occluded) continue;
         const u64 freem = __ballot((u32)lane < L.deg && id == PAG_EMPTY);
         if (!freem)                                           // the others, which v may occlude
-            for (u64 mm = __ballot(valid && we2 > duv); mm;) neighbour_distances(vec, L.d, sv, id, mm, dwv);
+            for (u64 mm = __ballot(valid && we2 > duv); mm;) neighbour_distances<CH, HALF>(vec, L.d, sv, id, mm, dwv);
         int slot = -1;
         if (freem) {
             slot = __ffsll((long long)freem) - 1;
@@ -629,6 +688,7 @@ __global__ void __launch_bounds__(64) k_reverse(pag_vecs vec, uint8_t* __restric
 // in eight parts taken one after the other.
 // order: the ids being inserted, in insertion order; the first `done` of them and all ids below n_begin are in the
 // graph already, the batch is order[done .. done + m).
+template <int CH, bool HALF>
 __global__ void __launch_bounds__(64) k_batch_density(pag_vecs vec, const uint8_t* __restrict__ recs, const float* __restrict__ e2,
                                                       pag_layout L, const u32* __restrict__ order, u64 n_begin, u64 done, u32 m,
                                                       u32 n_sample, u32 n_probe, u32* __restrict__ out) {
@@ -638,7 +698,7 @@ __global__ void __launch_bounds__(64) k_batch_density(pag_vecs vec, const uint8_
     const u32* nodes = order + done;
     const u64 graph = n_begin + done;
     const u32 x = nodes[(u64)blockIdx.x * m / n_sample];
-    stage(vec, L.d, x, sv, lane);
+    stage<CH, HALF>(vec, L.d, x, sv, lane);
     __syncthreads();
     float far = 0.f;
     if ((u32)lane < L.deg && ((const u32*)(recs + (u64)x * L.rec_bytes))[lane] != PAG_EMPTY) far = e2[(u64)x * L.deg + lane];
@@ -658,7 +718,7 @@ __global__ void __launch_bounds__(64) k_batch_density(pag_vecs vec, const uint8_
             const u64 t = (u64)jj * graph / n_probe;
             y[2 + g] = t < n_begin ? (u32)t : order[t - n_begin];
         }
-        dist_lds4(vec, L.d, sv, y, dd);
+        dist_lds4<CH, HALF>(vec, L.d, sv, y, dd);
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             const bool in = j + g < j1;
@@ -869,8 +929,10 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
         PAG_HIP(hipcub::DeviceRadixSort::SortPairs(ws.sort_tmp, ws.sort_bytes, ws.rk_in, ws.rk_out, ws.rv_in, ws.rv_out,
                                                    (int)n_pairs, 0, 64, s));
         // 5. apply them
-        hipLaunchKernelGGL(k_reverse, dim3(n_pairs), dim3(64), L.d * 4, s, pag_vecs_of(ix), ix->rec, ix->e2, L, ws.rk_out,
-                           ws.rv_out, n_pairs, ws.edges);
+        by_chunks(L.d, ix->vec_half, [&](auto ch, auto half) {
+            hipLaunchKernelGGL((k_reverse<decltype(ch)::value, decltype(half)::value>), dim3(n_pairs), dim3(64), L.d * 4, s, pag_vecs_of(ix), ix->rec,
+                               ix->e2, L, ws.rk_out, ws.rv_out, n_pairs, ws.edges);
+        });
         PAG_HIP(hipGetLastError());
         PAG_HIP(hipEventRecord(ws.ev[3], s));
         // 6. inference information of the new forward edges and of every changed reverse slot
@@ -893,8 +955,10 @@ int pag_build_range(pag_index* ix, u64 n_begin, u64 n_end) {
         if (m >= 64 && graph >= 64) {
             const u32 ns = kDensitySamples, np = (u32)std::min<u64>(std::min<u64>(m, graph), kDensityProbes);
             if ((rc = pag_launch_zero_u32(s, ws.density, 2 * ns))) return rc;
-            hipLaunchKernelGGL(k_batch_density, dim3(ns, kDensityWaves), dim3(64), L.d * 4, s, pag_vecs_of(ix), ix->rec, ix->e2, L, ws.order, n_begin,
-                               done - m, (u32)m, ns, np, ws.density);
+            by_chunks(L.d, ix->vec_half, [&](auto ch, auto half) {
+                hipLaunchKernelGGL((k_batch_density<decltype(ch)::value, decltype(half)::value>), dim3(ns, kDensityWaves), dim3(64), L.d * 4, s,
+                                   pag_vecs_of(ix), ix->rec, ix->e2, L, ws.order, n_begin, done - m, (u32)m, ns, np, ws.density);
+            });
             PAG_HIP(hipGetLastError());
             u32 h[kDensitySamples * 2];
             PAG_HIP(hipMemcpyAsync(h, ws.density, sizeof h, hipMemcpyDeviceToHost, s));
