@@ -82,7 +82,8 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
 //     1606, 4367 / 5271 / 3108, of 20k x 1536 2482 / 2994 / 1840, 4822 / 5682 / 3420.  Where they allow eight (working sets above 512), four, too:
 //     K 600 and 1000 of 50k x 768 6883 -> 5523, 10696 -> 8595
 //   up to four per CU: 4 waves, where the registers of the kernel let every query be resident (all four of short rows and working sets
-//     of up to 128 nodes, three of long rows and of up to 512, none above).  Whole calls with one wave -> four: 1,024 queries of
+//     of up to 256 nodes, three of long rows and of up to 512, none above).  Working sets of 129 to 256 nodes, 1,000 queries of 50k x 768,
+//     K 150 / 200: 1863 -> 1149, 4081 -> 2618 us; eight waves, 300 queries: 1246 (four) -> 790, 2672 -> 1762.  Whole calls with one wave -> four: 1,024 queries of
 //     5k x 32 / 128 at efS 10 91 -> 72, 102 -> 74 us, 50k x 768 at efS 10 / 24 247 -> 178, 345 -> 307, 16-bit 244 -> 180, 380 -> 318, 20k x
 //     1536 345 -> 280, 471 -> 386; 768 queries of 50k x 768 at efS 128 / 512 755 -> 485, 2523 -> 1563, K 300 3431 -> 2736, of 12k x 3072
 //     at efS 16 / 512 670 -> 642, 3729 -> 3568, K 400 5897 -> 5144, 16-bit 669 -> 593, 3718 -> 3017, 5917 -> 5126.  Small graphs, 1,024 queries: 120 x 128
