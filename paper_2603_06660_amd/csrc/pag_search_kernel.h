@@ -1459,7 +1459,7 @@ struct Wave {
     // A passer takes its place by one comparison of every member, and those behind it step to the next lane (470 clocks a hop; by
     // ranks and a scatter through LDS 840, with the counting in the row waves besides).  The keys are
     // compared as doubles, whose order is theirs (the distance word of a key is at most that of a NaN, 0x7FC00000, see
-    // team_reduce: no key is a NaN or an infinity as a double), in one instruction each.
+    // rows_at: no key is a NaN or an infinity as a double), in one instruction each.
     static constexpr int OW = NW < 2 ? NW : 2;          // the slots that lose members: a hop has 64 passers at most
     struct Merge {
         u64 oldW[OW], pk, far;
