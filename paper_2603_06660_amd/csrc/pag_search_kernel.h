@@ -380,9 +380,27 @@ struct Wave {
         ea = ((const float*)(rec + A.off_a))[sl];
         ec = ((const float*)(rec + A.off_c))[sl];
         const u32* cp = (const u32*)(rec + A.off_codes) + sl * (u32)CW;    // 16-byte aligned section
-        if constexpr (TEAM) {
+        if constexpr (TEAM && NQ == 1 && NW <= 2) {
+            // Short rows come from the caches, a hop waits for its estimates, and a read that the codes do not need delays them: each length has its own
+            // (50k rows of 32 to 256 values, 8- and 16-byte codes, 1 to 1,000 queries, K 10 and 100: 0.97 to 1.01 of the time with the two reads
+            // below, 0.99 on average; one query of 128-d, K 10, efS 512 813 -> 795 us, 1,000 queries with K 100 861 -> 851.  32-byte codes, 256-d: 0.97 to
+            // 1.02).  Above 128 nodes the two reads are as good or better here too (0.97 to 1.02, 1.00 on average).
+            // Every word is written on every path, else the arrays would not stay in registers.
+            const u32* tp = (const u32*)(rec + A.off_codes) + sl * A.cw;
+            uint4 t = make_uint4(0, 0, 0, 0), v = t;
+            if (A.cw == 2) {
+                const uint2 w = *(const uint2*)tp;
+                t.x = w.x; t.y = w.y;
+            } else {
+                t = *(const uint4*)tp;
+                if (A.cw == 8) v = *(const uint4*)(tp + 4);
+            }
+            cwv[0] = t.x; cwv[1] = t.y; cwv[2] = t.z; cwv[3] = t.w;
+            cwv[4] = v.x; cwv[5] = v.y; cwv[6] = v.z; cwv[7] = v.w;
+        } else if constexpr (TEAM) {
             // Two 16-byte reads whatever the length of the codes, in straight-line code (8 bytes: of a pair of neighbours; the section is
-            // 16-byte aligned and the record has room behind an odd last one).
+            // 16-byte aligned and the record has room behind an odd last one).  A read by length took 0.98 to 1.03 times
+            // the time with 32-byte codes and longer rows, one query of 1536-d, 2304-d and 3072-d 1.02 to 1.03; 0.98 to 1.01 with shorter codes.
             const bool pairs = A.cw == 2;
             const uint8_t* tp = rec + A.off_codes + (pairs ? (sl >> 1) * 16u : sl * A.cw * 4u);
             const uint4 t = *(const uint4*)tp, v = *(const uint4*)(tp + (A.cw == 8 ? 16u : 0u));
