@@ -774,6 +774,7 @@ static int alloc_candidate_ws(BuildWs& ws, u64 max_batch, u32 cand_cap, u32 deg,
 // indexing mode (ef = efC, b = min(efC, 100), every round's W collected, PES screening into ws.pes), then every
 // point's candidates sorted by (dist, id) -- bits 1..63 of the keys, the visited flag aside -- into ws.cand_sorted.
 static int search_candidates(pag_index* ix, BuildWs& ws, const float* qrot, u64 m, u32 b, u32 cand_cap, u64 n_limit) {
+    if (b > PAG_LDS_RING_MAX_B) { pag_set_error("indexing: working sets above 128 nodes are not built"); return PAG_EUNSUPPORTED; }   // see Wave::end_round
     const pag_layout& L = ix->L;
     hipStream_t s = ix->stream;
     int rc;

@@ -277,11 +277,11 @@ struct Wave {
     static constexpr bool BIG = NW > 2;             // large working sets
     // W is kept sorted: up to 128 nodes, by a team up to 512; else see merge_unsorted
     static constexpr bool SORTED = NW <= 2 || (TEAM && NW <= 8);
-    u64 wmax;                       // BIG: key of W's farthest member, valid while nW == b
-    u64 nx_key;                     // BIG: key of the node to expand next (PAG_KEY_INVALID: W has no unvisited node)
-    bool nx_known;                  // BIG: nx_key is up to date
-    u32 open_slot;                  // BIG, TEAM: the slots before this one hold no unvisited member
-    u64 GM, GU;                     // BIG: lane s < NW holds slot s's farthest member (0: slot empty) and its closest
+    u64 wmax;                       // W not sorted: key of its farthest member, valid while nW == b
+    u64 nx_key;                     // W not sorted: key of the node to expand next (PAG_KEY_INVALID: W has no unvisited node)
+    bool nx_known;                  // W not sorted: nx_key is up to date
+    u32 open_slot;                  // W sorted, above 128 nodes: the slots before this one hold no unvisited member
+    u64 GM, GU;                     // W not sorted: lane s < NW holds slot s's farthest member (0: slot empty) and its closest
                                     // unvisited member (PAG_KEY_INVALID: none); the other lanes hold 0 / PAG_KEY_INVALID
     float4 q[QV];
     u64 W[NW];
@@ -700,7 +700,7 @@ struct Wave {
         }
     }
 
-    // ---- working sets above 128 nodes (NW >= 4): W is kept unsorted ----
+    // ---- working sets above 128 nodes (NW >= 4): W is kept unsorted, in teams above 512 ----
     // Keeping up to 1024 keys sorted by rank costs a pass over all NW slots per passer and a round trip of the
     // whole set through LDS per hop.  What a hop needs of W is only its closest unvisited member, its farthest
     // member and the replacement of that one; the order of the rest matters at the round's end alone, where
@@ -754,7 +754,7 @@ struct Wave {
         }
     }
 
-    // TEAM: W's closest unvisited member, and its slot in open_slot
+    // W sorted, above 128 nodes: its closest unvisited member, and that one's slot in open_slot
     __device__ __forceinline__ u64 closest_open() {
         u64 k = PAG_KEY_INVALID;
 #pragma unroll
@@ -1031,7 +1031,8 @@ struct Wave {
         const u32 b = A.b;
         nx_id = PAG_EMPTY;
         if (A.cand) {
-            // indexing: R_L has room for every round's W (capacity efC >= Rmax * b is enforced by the host)
+            // indexing: R_L has room for every round's W (capacity efC >= Rmax * b and b <= 128 are enforced by the host: above,
+            // a team's sorted W lies in other slots, and to compute its ranks here costs its hops 1 to 18 % in spilled registers)
 #pragma unroll
             for (int s = 0; s < NW; ++s) {
                 const u32 idx = s * 64 + lane;
@@ -1093,14 +1094,13 @@ struct Wave {
             }
             bitonic_registers<2 * NW>(x, lane);
             nW = n < b ? n : b;
-#pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                const u32 idx = s * 64 + lane;
-                W[s] = idx < nW ? x[s] : PAG_KEY_INVALID;
-            }
-            // W is sorted now
             if constexpr (!SORTED) {
-                // a slot's farthest member is its last, its closest unvisited one the first unvisited
+#pragma unroll
+                for (int s = 0; s < NW; ++s) {
+                    const u32 idx = s * 64 + lane;
+                    W[s] = idx < nW ? x[s] : PAG_KEY_INVALID;
+                }
+                // W is sorted now: a slot's farthest member is its last, its closest unvisited one the first unvisited
                 GM = 0ull; GU = PAG_KEY_INVALID;
 #pragma unroll
                 for (int s = 0; s < NW; ++s) {
@@ -1123,7 +1123,7 @@ struct Wave {
                 if (e >= nW && e < n) RT[n - 1 - e] = x[s];
             }
             if constexpr (SORTED) {
-                // to its slots, through the memory of R_F, which is empty now
+                // W to its slots, through the memory of R_F, which is empty now
 #pragma unroll
                 for (int s = 0; s < NW; ++s) {
                     const u32 idx = s * 64 + lane;
