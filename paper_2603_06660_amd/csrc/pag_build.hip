@@ -45,7 +45,9 @@ __device__ __forceinline__ float dist_lds(const pag_vecs& V, u32 d, const float*
 
 // What follows is bound by trips to memory, so a row's chunks are asked for together: CH of them (16 bytes a lane of fp32, 8 of 16-bit rows) for
 // four rows at once.  In a loop over single chunks a row of 768 took three trips (reverse edges of a batch of 1,024 x 768 214 us,
-// with the chunks together 174; density 51, 47).
+// with the chunks together 174; density 51, 47.  Reverse phase of whole builds, a chunk at a time -> together, 50,000 x 384 8.4 -> 7.2 ms, 768 12.3 ->
+// 10.1, 30,000 x 1280 12.4 -> 10.3, 1792 15.9 -> 12.4, 2560 19.7 -> 15.5, 3072 24.9 -> 17.7; 16-bit rows 768 15.9 -> 9.3, 1280 17.8 -> 10.1,
+// 1792 23.9 -> 11.7, 2560 30.3 -> 14.5, 3072 40.2 -> 16.0; 20,000 x 2304 14.1 -> 10.3, 16-bit 22.2 -> 9.9).
 template <bool HALF> struct RawChunk { using type = float4; };
 template <> struct RawChunk<true> { using type = uint2; };
 template <bool HALF>
@@ -113,10 +115,17 @@ __device__ __forceinline__ void stage(const pag_vecs& V, u32 d, u32 id, float* s
     }
 }
 
-// f(chunks, half): chunks of a row asked for together, as a compile-time constant: all of up to four, else two or more parts of three or four
+// How many chunks of a row of nq are asked for together: all of up to four, else parts of three or four, whichever reads fewer past its end (nine
+// chunks in three parts of three, not twelve chunks in parts of four: reverse phase of 20,000 x 2304 11.8 -> 10.4 ms, x 2112 17.8 -> 15.3, 16-bit 11.8 -> 9.8
+// and 18.8 -> 15.5).
+constexpr u32 chunks_together(u32 nq) { return nq <= 4 ? nq : (nq + 2) / 3 * 3 < (nq + 3) / 4 * 4 ? 3 : 4; }
+static_assert(chunks_together(1) == 1 && chunks_together(4) == 4 && chunks_together(5) == 3 && chunks_together(6) == 3 && chunks_together(7) == 4 &&
+              chunks_together(9) == 3 && chunks_together(10) == 4 && chunks_together(12) == 4);
+
+// f(chunks, half): chunks of a row asked for together, as a compile-time constant
 template <class F>
 void by_chunks(u32 d, u32 half, F&& f) {
-    const u32 nq = (d / 4 + 63) / 64, ch = nq <= 4 ? nq : nq <= 6 ? 3 : 4;
+    const u32 ch = chunks_together((d / 4 + 63) / 64);
     auto with = [&](auto h) {
         if (ch == 1) f(std::integral_constant<int, 1>{}, h);
         else if (ch == 2) f(std::integral_constant<int, 2>{}, h);
