@@ -22,7 +22,8 @@ def index_and_queries():
     ix.close()
 
 
-@pytest.mark.parametrize("K,efS", [(1, 64), (10, 64), (64, 200), (100, 300)])     # one and two members of W per lane, at and below the slot's end
+# one and two members of W per lane, at and below the slot's end; above 128 nodes up to four and up to eight, with slots before the first and without
+@pytest.mark.parametrize("K,efS", [(1, 64), (10, 64), (64, 200), (100, 300), (129, 129), (200, 600), (256, 300), (257, 600), (512, 1200)])
 @pytest.mark.parametrize("kind", ["near", "odd"])
 def test_values(index_and_queries, kind, K, efS):
     import torch
