@@ -78,12 +78,16 @@ int pag_fit_team(const pag_team_request& r, uint32_t share, uint32_t most, uint3
 //   two per CU: 8 waves, where the registers of the kernel allow 16 on a CU.  128-d 508 -> 401 us, 768-d 704 -> 492,
 //     1536-d 995 -> 747 (512 queries).  Where they allow twelve, teams of four, of which three fit: two teams of six are granted but
 //     run one after the other.  Whole calls with one wave / six / four, 512 queries: 3072-d at efS 128 1183 / 1363 / 1051 us, at efS 512 3348 /
-//     4048 / 2930, K 200 2993 / 3974 / 2614, 16-bit 1267 / 1404 / 997, 3528 / 4105 / 2717, 3113 / 4472 / 2583; K 200 and 400 of 50k x 768 2227 / 2794 /
-//     1606, 4367 / 5271 / 3108, of 20k x 1536 2482 / 2994 / 1840, 4822 / 5682 / 3420.  Where they allow eight (working sets above 512), four, too:
+//     4048 / 2930, K 200 2993 / 3974 / 2614, 16-bit 1267 / 1404 / 997, 3528 / 4105 / 2717, 3113 / 4472 / 2583; K 400 of 50k x 768 4367 /
+//     5271 / 3108, K 200 and 400 of 20k x 1536 2482 / 2994 / 1840, 4822 / 5682 / 3420 (all with W unsorted above 128 nodes).  Working sets of 129 to 256
+//     nodes with rows of up to four chunks allow sixteen: four -> eight, W sorted, 512 queries of 50k x 128 / 768 / 1024, K 150, efS 600 1470 -> 1247,
+//     1644 -> 1440, 1858 -> 1565, K 200, efS 800 1875 -> 1588, 2067 -> 1813, 2329 -> 1955, 16-bit 768 and 30k x 2048 1.16 to 1.23 times as
+//     fast.  Where they allow eight (working sets above 512), four, too:
 //     K 600 and 1000 of 50k x 768 6883 -> 5523, 10696 -> 8595
 //   up to four per CU: 4 waves, where the registers of the kernel let every query be resident (all four of short rows and working sets
-//     of up to 256 nodes, three of long rows and of up to 512, none above).  Working sets of 129 to 256 nodes, 1,000 queries of 50k x 768,
-//     K 150 / 200: 1863 -> 1149, 4081 -> 2618 us; eight waves, 300 queries: 1246 (four) -> 790, 2672 -> 1762.  Whole calls with one wave -> four: 1,024 queries of
+//     of up to 256 nodes, three of long rows and of up to 512, none above).  Whole calls with one wave -> four, working sets of 129 to 256 nodes,
+//     1,000 queries, K 150, efS 600 / K 200, efS 800: 50k x 128 2414 -> 1817, 3141 -> 2287 us, 768 3170 -> 2106, 4110 -> 2621, 1024 3391 -> 2460, 4360 ->
+//     3034, 16-bit 768 3312 -> 2150, 4298 -> 2696, 30k x 2048 4957 -> 3173, 6292 -> 3930; smaller ones: 1,024 queries of
 //     5k x 32 / 128 at efS 10 91 -> 72, 102 -> 74 us, 50k x 768 at efS 10 / 24 247 -> 178, 345 -> 307, 16-bit 244 -> 180, 380 -> 318, 20k x
 //     1536 345 -> 280, 471 -> 386; 768 queries of 50k x 768 at efS 128 / 512 755 -> 485, 2523 -> 1563, K 300 3431 -> 2736, of 12k x 3072
 //     at efS 16 / 512 670 -> 642, 3729 -> 3568, K 400 5897 -> 5144, 16-bit 669 -> 593, 3718 -> 3017, 5917 -> 5126.  Small graphs, 1,024 queries: 120 x 128

@@ -1472,8 +1472,10 @@ struct Wave {
     // wave 0, sorted W: the hop's np passers, whose keys lie in LDS, in two parts: W itself, ...
     // (Working sets of 129 to 512 nodes were unsorted here too.  A passer cost them a reduction over one slot, one over all
     // slots and a search for the member that leaves, all one after the other; to step to the next lane is four slots at a time and needs no
-    // search.  1 to 512 queries of 50k x 768, K 150 / 200 / 300 / 500: 1.55, 1.5, 1.27 and 1.26 times as fast with twelve waves, 1.16 with
-    // four from K 300 on.  With sixteen slots the registers spill inside the hop: 300 queries, K 1000 17.9 ms unsorted, 19.2 sorted.)
+    // search.  Unsorted -> sorted, 50k x 768, one query / 256 / 512: K 150, efS 600 1778 -> 1170 us, 1832 -> 1226, 2134 -> 1448 (with the eight waves that the
+    // registers allow now); K 300, efS 1200 3437 -> 2867, 3518 -> 2916, 4225 -> 3790; K 500, efS 1500 4217 -> 3459, 4385 -> 3600, 5143 -> 4574.  Every length of
+    // rows and store that there is a kernel for, 128-d to 3072-d, K 150 to 256: 1.28 to 1.78 times as fast up to one query a CU, 1.15 to 1.68 up to two; K 300 to 500
+    // 1.17 to 1.50, 1.02 to 1.32.  With sixteen slots the registers spill inside the hop: 300 queries, K 1000 17.9 ms unsorted, 19.2 sorted.)
     // A passer takes its place by one comparison of every member, and those behind it step to the next lane (470 clocks a hop; by
     // ranks and a scatter through LDS 840, with the counting in the row waves besides).  The keys are
     // compared as doubles, whose order is theirs (the distance word of a key is at most that of a NaN, 0x7FC00000, see
@@ -1850,8 +1852,9 @@ __global__ void __launch_bounds__(64) k_search(const SearchArgs A) {
 
 // The same with several waves per query, for batches that would leave the GPU mostly idle.
 // Registers: 128 a lane, four waves per SIMD, where the rows in flight, the query and W allow it: working sets of up to 128 nodes with fp32
-// rows spill none of them, 16-bit ones up to 4, with six 8-byte chunks 22; 129 to 256 nodes 14 to 36, at their ends of rounds above all, and
-// 700 and 1,000 queries of 50k x 768, K 150, are 1.33 and 1.62 times as fast as with room for three teams.  Else the 168 that twelve waves
+// rows spill none of them, 16-bit ones up to 4, with six 8-byte chunks 22; 129 to 256 nodes 14 to 36, at their ends of rounds above all.
+// With 168 there, rows of 128-d to 1024-d and 16-bit ones to 2048, K 150 and 200: up to one query a CU 1.00 to 0.97 of the time, 700 queries 1.00 to
+// 0.92, but up to two a CU 1.12 to 1.23 of it (teams of four instead of eight), 1,000 queries 1.33 to 1.74 (one wave each).  Else the 168 that twelve waves
 // leave: none or 2 spilled, 16-bit rows in six 16-byte chunks 39, of 3072 42 (with 128 every wave felt it: one query per CU 1.17 times
 // as fast as one wave, 1.35 with 168, two per CU 0.85), working sets of 257 to 512 nodes 38 to 93.
 template <int NQ, int NW, int VM>
