@@ -1293,8 +1293,8 @@ struct Wave {
     //           Only the threshold has to wait.
     // Where a round has ended in between (every eleventh hop at b = 10) the node is another one, and it is screened in a phase
     // of its own.
-    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.2 with twelve (4,900 clocks: rows 2,800, of which a trip to
-    // memory is 1,200, wave 0's lists 1,340, the rest reading what is posted, barriers).  While every row wave also
+    // 37 queries, 1M x 768, efS 512: 5.85 us a hop with one wave, 2.2 with twelve (4,900 clocks: rows 2,600, of which a trip to
+    // memory is 1,200 and wave 1's seen set 1,700, wave 0's lists 1,400, the rest reading what is posted, barriers).  While every row wave also
     // ranked its passers against W for a merge by scatter through LDS, and a record was first asked for when its node was
     // expanded, it was 2.6.
     enum : u32 {
